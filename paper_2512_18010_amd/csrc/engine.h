@@ -23,35 +23,74 @@ constexpr int kMaxTermsPerPair = 9;
 // Component pairs per unit: the layout granule of packed weights and term
 // slots, and one pair of MFMA k-steps (4 pairs each) of the grid kernel.
 constexpr int kChunk = 8;
-// The grid kernel stages whole chunks of consecutive units that share a term
-// count npp: at most kMaxUnitsPerChunk units and kMaxChunkTerms terms.
+// Chunks: runs of consecutive units that share a term count npp, at most
+// kMaxUnitsPerChunk units and kMaxChunkTerms terms (reported by scff_query).
 constexpr int kMaxUnitsPerChunk = 4;
 constexpr int kMaxChunkTerms = kChunk * kMaxTermsPerPair;   // 72
-// The grid kernel may split a grid's chunk list into up to kMaxSplit ranges
+// Grid kernel: z rows (distinct 1D rows of the z axis) come in k-steps of
+// kZStep, sorted by their number of terms (at most kZTerms: the component
+// pairs of one primitive pair that share its z powers).
+constexpr int kZStep = 32;
+constexpr int kZTerms = 9;
+constexpr int kWPasses = 2;       // W items per lane whose loads go out a step ahead
+constexpr int kGridLds = 65536 - 16;   // LDS bytes of a workgroup (the batch kernel adds 16)
+constexpr int kWLine = 84;        // floats of W per line: 4 groups of 8 z rows, padded apart in the banks
+constexpr int kGridClasses = 8;   // kernel variants: column groups per tile x precision
+// Term counts of the k-steps, longest rows first: k-step k has the largest n
+// with k < kend[n], so a k-step's position in the term arrays is closed form.
+struct KSteps {
+    int kend[kZTerms + 1];   // [n]: k-steps of n or more terms (n >= 1)
+};
+__host__ __device__ inline int ksteps_terms(const KSteps& s, int k) {
+    int n = 0;
+    for (int i = 1; i <= kZTerms; ++i) n += k < s.kend[i];
+    return n;
+}
+__host__ __device__ inline int ksteps_first(const KSteps& s, int k) {   // terms per z row of the k-steps before k
+    int c = 0;
+    for (int i = 1; i <= kZTerms; ++i) c += k < s.kend[i] ? k : s.kend[i];
+    return c;
+}
+// Floats of the weights of one term index of a k-step: [group of 8 z rows][state][8 + 4]
+__host__ __device__ constexpr int grid_term_weights(int ns) { return 48 * ns; }
+// The grid kernel may split a grid's k-steps into up to kMaxSplit ranges
 // (one workgroup per tile and range, FP64 partial sums reduced afterwards)
 // when the grid has too few tiles to fill the device.
-constexpr int kMaxSplit = 8;
+constexpr int kMaxSplit = 32;
 // The pair-sum buffer G of the separable-integral and dipole paths holds
 // nv x ncomp pair sums followed by ns x ncomp x kSepParts slices of their
 // transition-weighted reduction.
 constexpr int kSepParts = 64;
 struct ChunkSplit {
     int n;                   // number of ranges (1 = no split)
-    int lo[kMaxSplit + 1];   // range j is chunks [lo[j], lo[j+1]); lo[0] = 0, lo[n] = n_chunks
+    int lo[kMaxSplit + 1];   // range j is k-steps [lo[j], lo[j+1]); lo[0] = 0, lo[n] = n_ksteps
+};
+// Tiling of an evaluation: columns (q_z values computed: the upper half of an
+// axis symmetric about 0), column groups of 16 per tile (cg) and in all (ncg,
+// padded to whole tiles), row and column tiles, lines per qx (padded to pairs),
+// terms of a k-step handled between two barriers, most line pairs a tile
+// touches, LDS bytes of a workgroup.
+struct GridShape {
+    int reflect, ncol, iz0, cg, ntc, ncg, ntl, nyp, tcm, np, lds;
 };
 // Everything the fused grid kernel needs for one evaluation (one request of
-// a batch): the 1D tables, the term slots and chunk list, the packed
-// weights, the grid and its tiling, the split of the chunk list and the
-// outputs.  Filled on the host; the batch kernel reads it from device memory.
+// a batch): the x / y tables, the z axis' operand blocks, the k-steps with
+// their terms and weights, the grid and its tiling, the split of the k-steps
+// and the outputs.  Filled on the host; the batch kernel reads it from device
+// memory.
 struct GridDesc {
-    const float2* V;          // 1D tables [rows][vstride]
-    int vstride, vrows;
-    const int4* terms;        // term slots (row ids)
-    const int4* chunks;       // chunk table (first unit, units, npp, first slot)
+    const float2* V;          // x table, then (from byte ybase) the y table
+    int nxr, nyr;             // their rows, the zero row included
+    uint32_t ybase;
+    const uint4* Bt;          // z axis, operand order
+    const int2* terms;        // (x row, y row)
+    const float* Tw;          // weights (grid_term_weights)
+    const double* sinv;       // per state: the power of two that undoes the scaling
     ChunkSplit sp;
-    const uint32_t* Tp;       // packed weights (FP32 bits or split-BF16 halves)
-    int3 n, ntiles;           // grid points and tiles per axis
+    int3 n;                   // grid points per axis
+    KSteps steps;
     int nx_eval, n_states;
+    int ntl, ntc, ncg, ncol, iz0, reflect, nyp, tcm, np;
     float2* f;                // outputs (NULL to skip), or
     float* f2;
     double2* partial;         // FP64 partial sums of a split (NULL: unsplit)
@@ -128,15 +167,15 @@ struct PrepInputs {
     double eps, spin;
 };
 
-// Device buffers of the precompute; rows/slots/cnpp/coff/chunks/tp32/tpbf are
-// what the evaluation kernels consume.  cnpp/coff are per unit (terms per
-// pair, first slot); chunks holds (first unit, units) per grid-kernel chunk.
+// Device buffers of the precompute.  What the grid kernel reads: rows, zslots,
+// zterms, zw and the state factors in small; the layout by component
+// pairs (made when another path first needs it): slots, tp32, vcp and, per
+// unit, cnpp (terms per pair) and coff (first slot).
 struct PrepWork {
     DeviceBuffer rows_all, rowsum, trow, tbound, wt, cpmn, tp64, bsum, part, small, nk, nv, vbase,
-        tmp, key, val, vinfo, tmp2, cnpp, csize, coff, tmp3, slots, tp32, tpbf, row_used, newid, tmp4,
-        rows, uhist, chunks,
+        tmp, key, val, vinfo, tmp2, cnpp, csize, coff, tmp3, slots, tp32, row_used, newid, tmp4,
+        rows, zslots, zterms, zw,
         vcp;   // per packed pair: its component pair (index of tp64), -1 for padding
-    std::vector<int> chunk_host;   // staging of the chunk table (kept until the next prep)
     // pinned host memory of the context (kPinnedBytes, or NULL if it could
     // not be allocated): small readbacks and the chunk table travel through
     // it by DMA; every use is complete before run_prep returns
@@ -144,10 +183,17 @@ struct PrepWork {
 };
 
 constexpr size_t kPinnedBytes = (size_t)4 << 20;
+// byte offsets in the precompute's small buffer
+constexpr size_t kSmallStats = 1024, kSmallSinv = 1280, kSmallKs = 1792, kSmallZhist = 2048;
 constexpr size_t kPinnedTables = 4096;   // byte offset of the chunk table / molecule upload
 
 struct PrepResult {
-    int n_vpairs = 0, n_units = 0, n_chunks = 0, n_rows = 0, state_blocks = 1;
+    int n_rows = 0, n_x = 0, n_y = 0;   // compacted rows: the zero row, n_x x rows, n_y y rows, the z rows
+    int n_ksteps = 0, state_blocks = 1;
+    KSteps ksteps{};
+    long long n_zterms = 0, n_zweights = 0;
+    // layout by component pairs (run_prep_stats)
+    int n_virtual = 0, n_vpairs = 0, n_units = 0, n_chunks = 0;
     long long n_slots = 0, pairs_kept = 0, terms_kept = 0;
 };
 
@@ -159,10 +205,16 @@ std::string build_basis(Basis& b, int n_atoms, const double* xyz, int n_shells,
 // ---- device precompute (prep.hip) ----
 hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStream_t st,
                     const std::function<hipError_t(DeviceBuffer&, size_t)>& alloc);
+hipError_t run_prep_stats(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStream_t st);
+hipError_t run_prep_pairs(const PrepInputs& in, PrepWork& w, const PrepResult& res, hipStream_t st,
+                          const std::function<hipError_t(DeviceBuffer&, size_t)>& alloc);
 
 // ---- static scratch (scratch.hip) ----
 // Bytes of the per-device scratch array of scff_eval_grid_noalloc.
+// kScratchBytes is the limit on a grid's tables; kScratchSlack covers z rows
+// padded to whole k-steps and column tiles when there are few of them.
 constexpr size_t kScratchBytes = (size_t)256 << 20;
+constexpr size_t kScratchSlack = (size_t)8 << 20;
 // Device address of this device's array (device current; resolved once).
 hipError_t scratch_address(int device, void** ptr);
 
@@ -263,21 +315,22 @@ size_t ctx_device_bytes(const scff_ctx* c);
 // captured into a graph.
 struct BatchEval {
     GridDesc desc;
-    int cls = 0;               // grid kernel variant
+    GridShape shape;
+    int cls = 0;               // grid kernel variant, < kGridClasses
     long long blocks = 0;      // tiles x splits of the evaluation
     int n_split = 1, nx_eval = 0;
     size_t nout = 0;           // output values (n_states x grid points)
 };
 int ctx_batch_reserve(scff_ctx* c, const scff_grid* g, int precision, bool want_f, bool want_f2, BatchEval* be);
-int ctx_batch_tables(scff_ctx* c, const scff_grid* g, hipStream_t st);
+int ctx_batch_tables(scff_ctx* c, const scff_grid* g, const BatchEval& be, hipStream_t st);
 int ctx_batch_finish(scff_ctx* c, const scff_grid* g, const BatchEval& be, float* host_f, float* host_f2,
                      hipStream_t st);
 // After the batch's stream has been synchronised: the context has no
 // asynchronous work pending.
 void ctx_batch_done(scff_ctx* c);
 // Grid kernel launchers (kernels.hip)
-int grid_wg_per_cu(int state_blocks, int precision);
-hipError_t launch_grid_batch(int cls, const GridDesc* descs, const int2* items, int n_items, int* counter, int wgs,
+int grid_wgs_per_cu(int cls, int lds);
+hipError_t launch_grid_batch(int cls, int lds, const GridDesc* descs, const int2* items, int n_items, int* counter, int wgs,
                              hipStream_t st);
 hipError_t launch_zero_counters(int* c, int n, hipStream_t st);
 int ctx_n_cu(const scff_ctx* c);

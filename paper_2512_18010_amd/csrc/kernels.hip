@@ -10,25 +10,20 @@
 // CartesianVector in monomial form (eq. Ccoefficients).
 //
 //  * vtable_kernel: the 1D tables V[row][n] for every grid value of each
-//    axis (O(rows x N) work, a precompute next to the O(R x N^3) bulk).  They
-//    are evaluated in FP64 (phase q*P with range reduction, Gaussian,
-//    polynomial) and rounded once to FP32: the polynomial can cancel, and
-//    FP32 evaluation would leave errors proportional to its bound rather
-//    than to its value.
-//  * grid_kernel: one workgroup per q-tile of 4 x 8 lines (qx,qy) x
-//    (4*QZL) values of qz.  Per chunk of 8-32 component pairs the tile's
-//    W = Vx*Vy (per line) and Vz (per qz) slices are staged in LDS; every
-//    lane then forms G for 2 lines x QZL qz values of one component pair on
-//    the VALU and feeds it, still in registers, to the matrix cores.  FP32:
-//    v_mfma_f32_16x16x4_f32 (A = Tp, 16 states x 4 pairs), with the FP32
-//    MFMA sums of every 32 pairs folded into FP64 totals, which bounds the
-//    rounding error of the long, cancelling pair sum.  Split-BF16 (template
-//    flag BF): G and Tp as hi + lo BF16 halves, lo*hi + hi*hi + hi*lo of one
-//    unit (8 pairs) in one v_mfma_f32_16x16x32_bf16 with FP32 accumulation.
+//    axis.  They are evaluated in FP64 (phase q*P with range reduction,
+//    Gaussian, polynomial) and rounded once to FP32: the polynomial can
+//    cancel, and FP32 evaluation would leave errors proportional to its bound
+//    rather than to its value.  Exported only; the grid kernel reads
+//    xytable_kernel's and ztable_kernel's layouts of the same values.
+//  * grid_kernel: the sum contracted over z rows on the f16 matrix cores (hi +
+//    lo halves, FP32 accumulation; FP32 precision folds into FP64 totals); the
+//    operand is formed on the VALU.  grid_batch_kernel: the same tiles popped
+//    from a queue of several requests.
 //  * points_kernel: the same sum at arbitrary points (VALU only), V
 //    evaluated on the fly.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <type_traits>
 
@@ -40,32 +35,8 @@ namespace scff {
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
-// Two FP32 values -> two round-to-nearest-even BF16 in one dword (a in the low half).
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{a, b}, bf16x2));
-}
-// Split-BF16 of two values: hi = RNE(g), lo = RNE(g - hi).  g - hi is exact
-// in FP32 (hi is a multiple of g's FP32 ulp and |g - hi| needs at most 16
-// significant bits), so any correctly rounded evaluation of it gives the same
-// value; a BF16 dot product hi . (-1, -0) + g forms it in one instruction,
-// without unpacking hi.  The weights carry -0 rather than +0 in the other
-// half: the compiler encodes (-1, +0) as the inline constant -1.0, which the
-// instruction reads as the FP32 pattern of -1.0, i.e. the BF16 pair (+0, -1);
-// (-1, -0) and (-0, -1) have no inline form and go as literals.
-__device__ __forceinline__ void split_bf16(float g0, float g1, uint32_t& hi, uint32_t& lo) {
-    const bf16x2 h = __builtin_convertvector(floatx2{g0, g1}, bf16x2);
-    const float l0 = __builtin_amdgcn_fdot2_f32_bf16(h, bf16x2{(__bf16)-1.0f, (__bf16)-0.0f}, g0, false);
-    const float l1 = __builtin_amdgcn_fdot2_f32_bf16(h, bf16x2{(__bf16)-0.0f, (__bf16)-1.0f}, g1, false);
-    hi = __builtin_bit_cast(uint32_t, h);
-    lo = pack_bf16(l0, l1);
-}
-// Eight BF16 k-items of a 16x16x32 operand, two per dword (low half first).
-__device__ __forceinline__ bf16x8 bf16x8_of(uint32_t a0, uint32_t a1, uint32_t b0, uint32_t b1) {
-    return __builtin_bit_cast(bf16x8, uintx4{a0, a1, b0, b1});
-}
+typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 
 constexpr int kPointFoldUnits = 4;   // points kernel: units (32 pairs) per FP32 block sum
 
@@ -96,37 +67,112 @@ __global__ void vtable_kernel(const VRowDev* __restrict__ rows, int nrows, int v
     }
 }
 
+// The x and y rows' tables of the grid kernel.  x: value-major V[qx][row], so
+// that the rows of neighbouring terms (which neighbour each other) share cache
+// lines; y: blocks of 8 values, V[qy / 8][row][8], so that a tile's lines read
+// whole 64-byte runs.  rows: the zero row, the x rows, the y rows; nxr and nyr
+// count the zero row too.
+__global__ __launch_bounds__(256) void xytable_kernel(const VRowDev* __restrict__ rows, int nxr, int nyr, int nx, int ny,
+                                                      double2 qmin, double2 dq, float2* __restrict__ X,
+                                                      float2* __restrict__ Y) {
+    const long long tx = (long long)nx * nxr, tot = tx + (long long)((ny + 7) & ~7) * nyr;
+    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < tot;
+         i += (long long)gridDim.x * blockDim.x) {
+        if (i < tx) {
+            const int q = (int)(i / nxr), r = (int)(i - (long long)q * nxr);
+            X[i] = eval_row(rows[r], qmin.x + dq.x * (double)q);
+        } else {
+            const long long o = i - tx;
+            const int v = (int)(o & 7);
+            const long long br = o >> 3;
+            const int b = (int)(br / nyr), r = (int)(br - (long long)b * nyr), q = 8 * b + v;
+            Y[o] = q < ny ? eval_row(rows[r ? nxr - 1 + r : 0], qmin.y + dq.y * (double)q) : make_float2(0.f, 0.f);
+        }
+    }
+}
+
+// V block of the z axis in the grid kernel's operand order: fragment
+// ((k-step * ncg + column group) * 4 + plane) of 64 lanes x 16 bytes, lane
+// (g, n) = z rows 8 g .. 8 g + 7 of the k-step at column n, planes re hi, re
+// lo, im hi, im lo (f16 halves of the row scaled by its power of two; lo from
+// the FP64 value).  One thread per (8 z rows, column).
+__global__ __launch_bounds__(256) void ztable_kernel(const VRowDev* __restrict__ rows, const int2* __restrict__ zslots,
+                                                     int n_oct, int ncg, int ncol, int iz0, double qmin, double dq,
+                                                     uint4* __restrict__ Bt) {
+    const long long tot = (long long)n_oct * ncg * 16;
+    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < tot;
+         i += (long long)gridDim.x * blockDim.x) {
+        const int oct = (int)(i / (ncg * 16)), col = (int)(i - (long long)oct * ncg * 16);
+        halfx8 pl[4];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            double2 v = make_double2(0.0, 0.0);
+            if (col < ncol) {
+                const int2 zs = zslots[oct * 8 + j];
+                v = eval_row_fp64(rows[zs.x], qmin + dq * (double)(iz0 + col));
+                v.x = ldexp(v.x, zs.y);
+                v.y = ldexp(v.y, zs.y);
+            }
+            const _Float16 hr = (_Float16)(float)v.x, hi = (_Float16)(float)v.y;
+            pl[0][j] = hr;
+            pl[1][j] = (_Float16)(float)(v.x - (double)hr);
+            pl[2][j] = hi;
+            pl[3][j] = (_Float16)(float)(v.y - (double)hi);
+        }
+        uint4* o = Bt + (((size_t)(oct >> 2) * ncg + (col >> 4)) * 4) * 64 + (oct & 3) * 16 + (col & 15);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) o[p * 64] = __builtin_bit_cast(uint4, pl[p]);
+    }
+}
+
 // ---------------------------------------------------------------- grid kernel
 //
-// Workgroup = NW waves (4 or 8), tile = 4 qx x 8 qy lines x TZ qz
-// (TZ = 4*QZL per q_x line of waves; 8 waves put two waves on each q_x line,
-// one per half of the q_z range, so the chunk staging serves twice the q
-// values).
-// The packed pairs come in units of 8 component pairs with npp terms each
-// (npp <= 9); a chunk is a run of 1..4 consecutive units with the same npp
-// and at most 72 terms (up to 32 pairs when npp <= 2).  Per chunk, for every
-// term t (index ptl = (unit*8 + pair)*npp + term):
-//   raw slices  Vx[t][4], Vy[t][8], Vz[t][TZ]   global -> LDS by direct DMA
-//   W[t][line] = Vx * Vy                        cooperative, in LDS
-// plus the chunk's packed weights Tp[pairs][16*SB] (DMA as well).  The raw
-// slices and Tp are double-buffered: the DMA for chunk c+1 is issued at the
-// start of chunk c and completes under chunk c's W phase and main loop; the
-// row ids it needs were loaded one chunk earlier.  With one state block (SB =
-// 1) V^x and V^y, which only the W phase reads, have a single buffer of
-// their own, refilled for chunk c+1 right after chunk c's W phase: 50 KB of
-// LDS per workgroup instead of 60, which lets the split-BF16 variants (156-160
-// VGPRs) hold three workgroups per CU; the variants with two state blocks
-// keep all slices of a term in one double-buffered row (their registers
-// allow two workgroups per CU either way).  A term row holds RP float4
-// slices (8 in the split buffers, 16 otherwise) and thread tid always moves
-// slice `tid % RP` of terms tid/RP + (NT/RP)j, so the LDS destination of a
-// wave's DMA is contiguous (lane * 16 bytes), as the instruction requires.
-// Lane (kk, ln): pair kk of the current MFMA k-step, 2 lines x QZL qz.
+// The pair sum is contracted in the order
+//   U_s(z, line) = sum_{t with z row z} T'_s(t) Vx_t(qx) Vy_t(qy)     (VALU)
+//   f_s(line, qz) = sum_z U_s(z, line) Vz(z, qz)                      (matrix cores)
+// z runs over the distinct 1D rows of the z axis (one per primitive pair and
+// power pair; about half as many as terms), line over the (qx, qy) pairs.
+// The second sum is a real matrix product of [Re U; Im U] (rows: state, line)
+// with [Re V | Im V] (columns: qz), K = z rows, whose four blocks
+//   P = Ur Vr, Q = Ui Vi, R = Ur Vi, S = Ui Vr
+// give f = (P - Q) + i (R + S).  V(-q) = V(q)* for every 1D row, so on an axis
+// with qmin_z = -qmax_z the columns are the upper half of the axis only and
+// the mirror value is (P + Q) + i (S - R): the same products serve both.
+//
+// Products run on the f16 matrix cores with U and V split into hi + lo halves
+// (22 significant bits and more), hi hi + hi lo + lo hi per pair of values,
+// FP32 accumulation.  Exact powers of two bring V's rows to |V| < 2^14 and
+// U to |U| < 2^15 (prep.hip, from q-independent bounds), so the halves keep
+// their bits and nothing overflows; the epilogue removes them.  FOLD (FP32
+// precision): the FP32 sums of two k-steps go to FP64 totals (the sum over z
+// cancels); without it (split-BF16's bounds) they run through.
+//
+// A workgroup is 4 waves; its tile 64 rows (row = line * states + state, lines
+// padded to pairs per qx) by 16 CG columns.  Each wave forms its own 16 rows'
+// operand: lane (g, m) holds U of row m for the z rows 8 g .. 8 g + 7 of a k-step
+// of 32, i.e. exactly its share of a 16x16x32 A operand, so U goes from registers
+// to the matrix cores.  The products W = Vx Vy, which the states of a line
+// share, are formed once per workgroup, two lines per gather (a pair's y values
+// are 16 adjacent bytes), and pass through LDS; the V block of a k-step (stored
+// in operand order by ztable_kernel) and the weights come to LDS by DMA.  All of
+// it goes out one step (one or two terms of a k-step) ahead, one barrier a step.
+//
+// Why: the kernel before formed G = sum_t Vx Vy Vz per (pair, q) on the VALU (4
+// FMAs per term and q) and contracted with FP32 matrix instructions; here the
+// VALU's part does not depend on the number of columns.  A version whose waves
+// formed W each for itself was bound by its gathers (64 cache lines per
+// instruction): 46.8 ms on a 30-heavy-atom molecule with 24 states on 96^3, FP32;
+// sharing W: 40.2 ms; the kernel before: 96.8 ms (split-BF16 48.9 -> 31.6 ms; 10
+// heavy atoms, 12 states, 64^3: 3.56 -> 1.67 ms).  What bounds it now: instruction issue
+// of two waves per SIMD (48 CG registers of accumulators and FP64 totals; three
+// waves without the totals) - about 190 VALU and 36 matrix instructions per wave
+// and k-step at CG = 3, matrix cores busy 29 %, a third of the cycles in waits.
+// Folding every four k-steps instead of two is 5 % faster but raises the error
+// (1.2 -> 1.4e-7, above the kernel before), three waves per SIMD at CG = 2 with totals
+// spill (2.05 -> 2.47 ms); neither is done.
 
-constexpr int kFoldUnits = 4;  // units (32 pairs) per FP64 fold of the FP32 MFMA sums
-constexpr int kWStride = 34;   // float2 per term row of W (32 lines + pad)
-constexpr int kNPT = kMaxChunkTerms;   // 72 terms per chunk at most
-constexpr int kParts = 16;     // float4 slices per term row of a raw buffer holding all three axes
+constexpr int kGridWaves = 4;
+constexpr int kFoldSteps = 2;   // k-steps per FP64 fold
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 
@@ -155,470 +201,315 @@ __device__ __forceinline__ void dma_b128(uint32_t voff, const void* sbase, uint3
     asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(bu), "{m0}"(m0) : "memory");
 }
 
-typedef int sint4 __attribute__((ext_vector_type(4)));
 
-// One 16-byte entry of a wave-uniform table (the chunk table) read through
-// the scalar cache into scalar registers.  A load the compiler would issue
-// itself after the DMA asm (which clobbers memory) goes through vector
-// memory, and its wait would also wait for the DMA in flight.  The wait for
-// the result is in the same asm block; s_nop 4 covers a VALU-written base.
-__device__ __forceinline__ int4 sload_int4(const int4* p) {
-    const uint64_t b = (uint64_t)(uintptr_t)p;
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
-    const uint64_t bu = ((uint64_t)hi << 32) | (uint64_t)lo;
-    sint4 r;
-    asm volatile("s_nop 4\n\ts_load_dwordx4 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(r) : "s"(bu) : "memory");
-    return make_int4(r.x, r.y, r.z, r.w);
-}
-
-// LDS-only barrier: prior LDS reads/writes of this wave complete, DMA may
-// still be in flight.
-__device__ __forceinline__ void barrier_lds() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-// Full barrier: this wave's DMA into LDS has landed as well.  The wait is the
-// compiler's own s_waitcnt (vmcnt(0) lgkmcnt(0)), so it knows that every
-// earlier vector-memory load is complete here.
+// Barrier with this wave's LDS accesses and DMA into LDS complete.  The wait
+// is the compiler's own s_waitcnt (vmcnt(0) lgkmcnt(0)), so it knows that
+// every earlier vector-memory load is complete here.
 __device__ __forceinline__ void barrier_dma() {
     __builtin_amdgcn_s_waitcnt(0x0070);
     asm volatile("s_barrier" ::: "memory");
 }
 
-// One tile of one evaluation (blk = split * tiles + tile, as the single-request
-// launch numbers its workgroups).  Shared by the single-request kernel (one
-// tile per workgroup) and the persistent batch kernel (tiles of several
-// requests popped from a queue), so a tile's values do not depend on which
-// of the two computed it.
-template <int SB, int QZL, bool BF, int NW>
-__device__ __forceinline__ void grid_tile(const GridDesc& d, int blk) {
-    const float2* __restrict__ V = d.V;
-    const int vstride = d.vstride, vrows = d.vrows;
-    const int4* __restrict__ terms = d.terms;
-    const int4* __restrict__ chunks = d.chunks;
-    const ChunkSplit& sp = d.sp;
-    const uint32_t* __restrict__ Tp = d.Tp;
-    const int3 n = d.n, ntiles = d.ntiles;
-    const int nx_eval = d.nx_eval, n_states = d.n_states;
-    float2* __restrict__ f = d.f;
-    float* __restrict__ f2 = d.f2;
-    double2* __restrict__ partial = d.partial;
-    const long long part_stride = d.part_stride;
-
-    constexpr int NT = NW * 64;        // threads
-    constexpr int ZH = NW / 4;         // waves per q_x line of the tile (q_z halves)
-    constexpr int TZ = 4 * QZL * ZH;   // q_z values of the tile
-    constexpr int ZPARTS = TZ / 2;     // float4 slices of a Z row
-    constexpr int SLOTS = 2 * QZL;     // q values per lane
-    constexpr int SW = 16 * SB;        // padded state count
-    // V^x / V^y in a buffer of their own (one state block), or all slices of a
-    // term in one row of the double-buffered raw buffer
-    constexpr bool SXY = SB == 1;
-    constexpr int RP = SXY ? 8 : kParts;      // float4 slices per term row of a raw buffer
-    constexpr int ZOFF = SXY ? 0 : 6;         // first V^z slice of a row
-    constexpr int TPW8 = 64 / RP;             // terms per wave per DMA pass
-    constexpr int TPP = NT / RP;              // terms per DMA pass (RP slice-threads per term)
-    constexpr int NJ = (kNPT + TPP - 1) / TPP;   // term groups per slice-thread
-    static_assert(NW == 4 || NW == 8, "4 or 8 waves per workgroup");
-    constexpr int TPW = kMaxUnitsPerChunk * kChunk * SW;   // Tp words per chunk at most
-    static_assert(SXY ? (2 + 4 <= RP && ZPARTS <= RP) : (2 + 4 + ZPARTS <= RP), "slices per term");
-    static_assert(QZL % 2 == 0, "q_z values per lane come in float4 pairs");
-    static_assert(TPW / 4 <= 256, "Tp block per chunk fits one DMA per thread");
-    // software prefetch of the next term's LDS slices (12 VGPRs): only where
-    // the register budget has room for it (not next to the 128 VGPRs of FP64
-    // fold totals that the FP32 path needs at QZL = 4)
-    constexpr bool PF = BF || QZL <= 2;
-
-    // raw slice buffers: V^z (split) or all slices (not split), double-buffered
-    __shared__ __align__(16) float4 Z0[kNPT * RP];
-    __shared__ __align__(16) float4 Z1[kNPT * RP];
-    __shared__ __align__(16) float4 XY[SXY ? kNPT * RP : 1];
-    // Tp words: FP32 bits, or (BF) hi | lo << 16 split-BF16 halves
-    __shared__ __align__(16) uint32_t T0[TPW];
-    __shared__ __align__(16) uint32_t T1[TPW];
-    __shared__ __align__(16) float2 Wl[kNPT * kWStride];
-
-    const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wxq = wave & 3;          // q_x line of the tile
-    const int wzh = wave >> 2;         // q_z half of the tile (8 waves)
-    const int lane = tid & 63;
-    const int kk = lane >> 4;          // pair within an MFMA k-step
-    const int ln = lane & 15;          // MFMA column (q) / A-row (state) index
-    const int lpair = ln >> 2;         // lines 2*lpair, 2*lpair+1 of the wave
-    const int zgrp = ln & 3;           // qz values zgrp*QZL .. zgrp*QZL+QZL-1
-
-    // block = (split of the chunk list, tile); a split sums chunks [c_lo, c_hi)
-    int b = blk;
-    const int split = b / (ntiles.x * ntiles.y * ntiles.z);
-    b -= split * (ntiles.x * ntiles.y * ntiles.z);
-    const int c_lo = sp.lo[split], c_hi = sp.lo[split + 1];
-    const int tz = b % ntiles.z;
-    b /= ntiles.z;
-    const int ty = b % ntiles.y;
-    const int tx = b / ntiles.y;
-    const int qx0 = tx * 4, qy0 = ty * 8, qz0 = tz * TZ;
-
-    // ---- this thread's slices: axis and offset of its 16 bytes in a table
-    // row.  Split: for the V^x / V^y buffer (spare slices re-read a valid V^y
-    // slice) and for the V^z buffer; not split: one slice of a whole row.
-    // Idle slices re-read a valid V^z slice.
-    const int part = tid & (RP - 1);
-    const int axis_xy = part < 2 ? 0 : 1;
-    const int qoff_xy = part < 2 ? qx0 + 2 * part : qy0 + 2 * min(part - 2, 3);
-    const int axis_z = SXY ? 2 : (part < 2 ? 0 : (part < 6 ? 1 : 2));
-    const int qoff_z = SXY ? qz0 + 2 * min(part, ZPARTS - 1)
-                           : (part < 6 ? qoff_xy : qz0 + 2 * min(part - 6, ZPARTS - 1));
-
-    // row ids of the slices of chunk c (loaded one chunk ahead of the DMA)
-    int rid_xy[NJ], rid_z[NJ];
-    auto load_rows = [&](int c) {
-        const int4 ch = sload_int4(chunks + c);   // (first unit, units, npp, first slot)
-        const int nptl = ch.y * kChunk * ch.z;
-        const int* tc = reinterpret_cast<const int*>(terms + ch.w);
-        // lane indices recomputed here rather than kept live across the loop
-        int t0 = threadIdx.x;
-        asm volatile("" : "+v"(t0));
-        const int p0 = SXY ? t0 >> 3 : t0 >> 4;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const int* tr = tc + 4 * min(p0 + TPP * j, nptl - 1);
-            if constexpr (SXY) rid_xy[j] = tr[axis_xy];
-            rid_z[j] = tr[axis_z];
-        }
-    };
-    // DMA of this thread's slices of a chunk into the raw buffer at rbase;
-    // wave w of term group j covers terms TPP*j + TPW8*w .. + TPW8-1.  Row ids
-    // are clamped to the table where they are used (after the barrier that
-    // waits for their loads), so no DMA can leave the table whatever the slot
-    // table holds
-    auto dma_slices = [&](const int (&rid)[NJ], int qoff, uint32_t rbase) {
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            if (TPP * j + TPW8 * wave < kNPT) {
-                const uint32_t r = min((uint32_t)rid[j], (uint32_t)(vrows - 1));
-                dma_b128(8u * (__umul24(r, vstride) + qoff), V, rbase + (TPP * j + TPW8 * wave) * RP * 16);
-            }
-        }
-    };
-    // DMA of chunk c's V^x / V^y slices into XY (split buffers only)
-    auto issue_dma_xy = [&]() {
-        if constexpr (SXY) dma_slices(rid_xy, qoff_xy, lds_addr(XY));
-    };
-    // DMA of chunk c's V^z slices (or all its slices) into buffer zbase and
-    // its Tp block into tbase
-    auto issue_dma = [&](int c, uint32_t zbase, uint32_t tbase) {
-        dma_slices(rid_z, qoff_z, zbase);
-        const int4 ch = sload_int4(chunks + c);
-        const int tpf4 = ch.y * (kChunk * SW / 4);   // float4 of Tp in this chunk
-        if (64 * wave < tpf4 && lane < tpf4 - 64 * wave)
-            dma_b128(16u * (64 * wave + lane), Tp + (size_t)ch.x * kChunk * SW, tbase + 1024 * wave);
-    };
-
-    floatx4 acc_r[SB][SLOTS], acc_i[SB][SLOTS];
-    double tot_r[SB][SLOTS][4], tot_i[SB][SLOTS][4];
-#pragma unroll
-    for (int sb = 0; sb < SB; ++sb)
-#pragma unroll
-        for (int s = 0; s < SLOTS; ++s) {
-            acc_r[sb][s] = floatx4{0.f, 0.f, 0.f, 0.f};
-            acc_i[sb][s] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) tot_r[sb][s][i] = tot_i[sb][s][i] = 0.0;
-        }
-    // exact fold of the short FP32 MFMA block into FP64 totals (FP32 path)
-    auto fold = [&]() {
-#pragma unroll
-        for (int sb = 0; sb < SB; ++sb)
-#pragma unroll
-            for (int s = 0; s < SLOTS; ++s) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    tot_r[sb][s][i] += (double)acc_r[sb][s][i];
-                    tot_i[sb][s][i] += (double)acc_i[sb][s][i];
-                }
-                acc_r[sb][s] = floatx4{0.f, 0.f, 0.f, 0.f};
-                acc_i[sb][s] = floatx4{0.f, 0.f, 0.f, 0.f};
-            }
-    };
-
-    int units_done = 0;   // units contracted so far (fold cadence of the FP32 path)
-
-    auto chunk_body = [&](int c, const float4* Z, const uint32_t* T, auto after_w) {
-        const int4 ch = sload_int4(chunks + c);
-        const int nu = ch.y;
-        const int npp = ch.z;
-        // W = Vx * Vy: item = (term, qx, pair of q_y lines).  The 16 items of
-        // a term are 16 consecutive threads, so the LDS reads of a quarter
-        // wave touch one term row (no two terms' rows, 64 dwords apart, meet
-        // in a bank).  The thread index is re-read (not kept live across the
-        // loop) to spare a register.
-        int i0 = threadIdx.x;
-        asm volatile("" : "+v"(i0));
-        for (int i = i0; i < nu * kChunk * npp * 16; i += NT) {
-            const int ptl = i >> 4, xq = (i >> 2) & 3, h = i & 3;
-            const float4* xy = SXY ? XY : Z;   // this chunk's V^x / V^y
-            const float2 vx = reinterpret_cast<const float2*>(xy + ptl * RP)[xq];
-            const float4 y = xy[ptl * RP + 2 + h];
-            reinterpret_cast<float4*>(Wl + ptl * kWStride + xq * 8)[h] =
-                make_float4(vx.x * y.x - vx.y * y.y, vx.x * y.y + vx.y * y.x, vx.x * y.z - vx.y * y.w,
-                            vx.x * y.w + vx.y * y.z);
-        }
-        barrier_lds();
-        after_w();   // XY is free: the next chunk's V^x / V^y DMA
-        // G of one component pair (index p in the chunk) for this lane's 2
-        // lines x QZL q_z values, G = sum_t W_t(line) Vz_t(qz).  The first term
-        // initialises G; in the prefetching variant the slices of term t+1 are
-        // read from LDS while the FMAs of term t run.
-        auto gen = [&](int p, float (&gr)[SLOTS], float (&gi)[SLOTS]) {
-            // 24-bit index arithmetic: keeps the compiler from forming 64-bit
-            // multiply-adds whose unused high half may name a register with a
-            // load still in flight (which would make it wait for that load)
-            const int pt = __umul24(p, npp);
-            const float2* wp = Wl + (__umul24(pt, kWStride) + wxq * 8 + 2 * lpair);
-            const float2* zp = reinterpret_cast<const float2*>(Z) +
-                               (__umul24(pt, 2 * RP) + 2 * ZOFF + wzh * (4 * QZL) + zgrp * QZL);
-            auto load = [&](int t, float4& w, float4 (&zz)[QZL / 2]) {
-                w = *reinterpret_cast<const float4*>(wp + t * kWStride);
-#pragma unroll
-                for (int j = 0; j < QZL / 2; ++j) zz[j] = *reinterpret_cast<const float4*>(zp + t * (2 * RP) + 2 * j);
-            };
-            auto zval = [&](const float4 (&zz)[QZL / 2], int j) {
-                return (j & 1) ? make_float2(zz[j >> 1].z, zz[j >> 1].w) : make_float2(zz[j >> 1].x, zz[j >> 1].y);
-            };
-            auto fma_term = [&](const float4& w, const float4 (&zz)[QZL / 2]) {
-#pragma unroll
-                for (int j = 0; j < QZL; ++j) {
-                    const float2 z = zval(zz, j);
-                    gr[j] = fmaf(w.x, z.x, gr[j]);
-                    gr[j] = fmaf(-w.y, z.y, gr[j]);
-                    gi[j] = fmaf(w.x, z.y, gi[j]);
-                    gi[j] = fmaf(w.y, z.x, gi[j]);
-                    gr[QZL + j] = fmaf(w.z, z.x, gr[QZL + j]);
-                    gr[QZL + j] = fmaf(-w.w, z.y, gr[QZL + j]);
-                    gi[QZL + j] = fmaf(w.z, z.y, gi[QZL + j]);
-                    gi[QZL + j] = fmaf(w.w, z.x, gi[QZL + j]);
-                }
-            };
-            float4 wa, za[QZL / 2], wb, zb[QZL / 2];
-            load(0, wa, za);
-            if (PF && npp > 1) load(1, wb, zb);
-#pragma unroll
-            for (int j = 0; j < QZL; ++j) {   // the first term initialises G
-                const float2 z = zval(za, j);
-                gr[j] = fmaf(-wa.y, z.y, wa.x * z.x);
-                gi[j] = fmaf(wa.y, z.x, wa.x * z.y);
-                gr[QZL + j] = fmaf(-wa.w, z.y, wa.z * z.x);
-                gi[QZL + j] = fmaf(wa.w, z.x, wa.z * z.y);
-            }
-            if constexpr (PF) {
-                // ping-pong register sets: (wb, zb) holds term t, (wa, za) term t+1
-                int t = 1;
-                for (; t + 1 < npp; t += 2) {
-                    load(t + 1, wa, za);
-                    fma_term(wb, zb);
-                    load(min(t + 2, npp - 1), wb, zb);   // clamped: no conditional register set
-                    fma_term(wa, za);
-                }
-                if (t < npp) fma_term(wb, zb);
-            } else {
-                for (int t = 1; t < npp; ++t) {
-                    load(t, wa, za);
-                    fma_term(wa, za);
-                }
-            }
-        };
-        for (int u = 0; u < nu; ++u) {
-            // two MFMA k-steps of 4 pairs each; lane (kk, ln) handles pair 4*step + kk of the unit
-            float gr[2][SLOTS], gi[2][SLOTS];
-            uint32_t a_op[2][SB];
-#pragma unroll
-            for (int step = 0; step < kChunk / 4; ++step) {
-                const int p = u * kChunk + step * 4 + kk;
-#pragma unroll
-                for (int sb = 0; sb < SB; ++sb) a_op[step][sb] = T[p * SW + sb * 16 + ln];
-                gen(p, gr[step], gi[step]);
-                if constexpr (!BF) {
-                    // raised wave priority while the matrix instructions
-                    // issue (four-wave variants; the eight-wave one measured
-                    // slower with it)
-                    if constexpr (NW == 4) __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-                    for (int sb = 0; sb < SB; ++sb)
-#pragma unroll
-                        for (int s = 0; s < SLOTS; ++s) {
-                            const float a = __uint_as_float(a_op[step][sb]);
-                            acc_r[sb][s] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, gr[step][s], acc_r[sb][s], 0, 0, 0);
-                            acc_i[sb][s] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, gi[step][s], acc_i[sb][s], 0, 0, 0);
-                        }
-                    if constexpr (NW == 4) __builtin_amdgcn_s_setprio(0);
-                }
-            }
-            ++units_done;
-            if constexpr (BF) {
-                // Split-BF16 contraction of this unit in one 16x16x32 MFMA per
-                // output block.  A lane's eight k-items are its two k-steps
-                // (pairs kk and 4 + kk of the unit) four times over:
-                //   A = (Tp lo | 0 | Tp hi | Tp hi),  B = (G hi | G lo | G hi | G lo)
-                // so the items give lo*hi, 0, hi*hi, hi*lo.  A and B map lane and
-                // item to k alike, so this item order is a valid k order.  One
-                // unit per MFMA, so no state is carried between units (pairing
-                // units for a 16-pair group made the compiler copy the
-                // accumulators on every unit).
-                // The split and the matrix instructions run at raised wave
-                // priority, so that a wave holding a unit's products is issued
-                // ahead of a wave in its generator loop on the same SIMD.
-                __builtin_amdgcn_s_setprio(1);
-                uint32_t hr[SLOTS], lr[SLOTS], hi[SLOTS], li[SLOTS];
-#pragma unroll
-                for (int s = 0; s < SLOTS; ++s) {
-                    split_bf16(gr[0][s], gr[1][s], hr[s], lr[s]);
-                    split_bf16(gi[0][s], gi[1][s], hi[s], li[s]);
-                }
-#pragma unroll
-                for (int sb = 0; sb < SB; ++sb) {
-                    const uint32_t ah = (a_op[0][sb] & 0xffffu) | (a_op[1][sb] << 16);
-                    const uint32_t al = (a_op[0][sb] >> 16) | (a_op[1][sb] & 0xffff0000u);
-                    const bf16x8 A = bf16x8_of(al, 0u, ah, ah);
-#pragma unroll
-                    for (int s = 0; s < SLOTS; ++s) {
-                        const bf16x8 Br = bf16x8_of(hr[s], lr[s], hr[s], lr[s]);
-                        const bf16x8 Bi = bf16x8_of(hi[s], li[s], hi[s], li[s]);
-                        acc_r[sb][s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, Br, acc_r[sb][s], 0, 0, 0);
-                        acc_i[sb][s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, Bi, acc_i[sb][s], 0, 0, 0);
-                    }
-                }
-                __builtin_amdgcn_s_setprio(0);
-            } else {
-                if ((units_done & (kFoldUnits - 1)) == 0) fold();
-            }
-        }
-    };
-
-    if (c_hi > c_lo) {
-        load_rows(c_lo);
-        issue_dma_xy();
-        issue_dma(c_lo, lds_addr(Z0), lds_addr(T0));
-        if (c_lo + 1 < c_hi) load_rows(c_lo + 1);
-    }
-    // two chunks per iteration so each buffer is a distinct LDS object.  The
-    // row ids held at the start of chunk c are chunk c+1's: its V^z / Tp DMA
-    // goes out at once, its V^x / V^y DMA once chunk c's W phase has read XY,
-    // and then the row ids of chunk c+2 are loaded
-    for (int c = c_lo; c < c_hi; c += 2) {
-        barrier_dma();                                  // chunk c landed in Z0/T0 (and XY); Z1, T1 and Wl are free
-        if (c + 1 < c_hi) {
-            issue_dma(c + 1, lds_addr(Z1), lds_addr(T1));
-            if (!SXY && c + 2 < c_hi) load_rows(c + 2);
-        }
-        chunk_body(c, Z0, T0, [&]() {
-            if (SXY && c + 1 < c_hi) {
-                issue_dma_xy();
-                if (c + 2 < c_hi) load_rows(c + 2);
-            }
-        });
-        if (c + 1 >= c_hi) break;
-        barrier_dma();                                  // chunk c+1 landed in Z1/T1 (and XY); Z0, T0 and Wl are free
-        if (c + 2 < c_hi) {
-            issue_dma(c + 2, lds_addr(Z0), lds_addr(T0));
-            if (!SXY && c + 3 < c_hi) load_rows(c + 3);
-        }
-        chunk_body(c + 1, Z1, T1, [&]() {
-            if (SXY && c + 2 < c_hi) {
-                issue_dma_xy();
-                if (c + 3 < c_hi) load_rows(c + 3);
-            }
-        });
-    }
-    if constexpr (!BF) {
-        if (units_done & (kFoldUnits - 1)) fold();
-    }
-
-    // Epilogue, coalesced through LDS.  Lane (kk, ln) holds states
-    // sb*16 + 4kk + i of its q values (lines 2*lpair + a, q_z zgrp*QZL + j).
-    // One pass per (sb, i, a): every lane writes its QZL values to the wave's
-    // own LDS region as 16 rows (kk, lpair) of 4*QZL q_z, then the wave reads
-    // the rows back with consecutive lanes on consecutive q_z and stores them,
-    // so every row of the output (fixed state, q_x, q_y) is written as one
-    // contiguous run.  The staging reuses the W buffer and a V^z buffer (no
-    // wave reads them after the barrier below, and no DMA is in flight).
-    constexpr int RQ = 4 * QZL;          // q_z values of a row
-    constexpr int RPI = 64 / RQ;         // rows per wave-wide read
-    barrier_lds();
-    const int qx = qx0 + wxq;
-    const bool plane_ok = qx < nx_eval;
-    // per wave: 16 rows x RQ values; f (float2) or partial (double2) in Wl
-    // (split) or Z0, f2 (float) in Z0 (split) or Z1
-    static_assert(SXY ? (NW * 16 * RQ * sizeof(double2) <= sizeof(Wl) && NW * 16 * RQ * sizeof(float) <= sizeof(Z0))
-                      : (NW * 16 * RQ * sizeof(double2) <= sizeof(Z0) && NW * 16 * RQ * sizeof(float) <= sizeof(Z1)),
-                  "epilogue staging fits");
-    void* s_f = SXY ? (void*)Wl : (void*)Z0;
-    double2* sp2 = reinterpret_cast<double2*>(s_f) + wave * 16 * RQ;
-    float2* sf = reinterpret_cast<float2*>(s_f) + wave * 16 * RQ;
-    float* sf2 = reinterpret_cast<float*>(SXY ? Z0 : Z1) + wave * 16 * RQ;
-    const int wrow = kk * 4 + lpair;     // the row this lane's values belong to
-#pragma unroll
-    for (int sb = 0; sb < SB; ++sb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int a = 0; a < 2; ++a) {
-#pragma unroll
-                for (int j = 0; j < QZL; ++j) {
-                    const int sl = a * QZL + j;
-                    const double vr = BF ? (double)acc_r[sb][sl][i] : tot_r[sb][sl][i];
-                    const double vi = BF ? (double)acc_i[sb][sl][i] : tot_i[sb][sl][i];
-                    const int e = wrow * RQ + zgrp * QZL + j;
-                    if (partial) {
-                        sp2[e] = make_double2(vr, vi);
-                    } else {
-                        sf[e] = make_float2((float)vr, (float)vi);
-                        sf2[e] = (float)(vr * vr + vi * vi);
-                    }
-                }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's rows are in LDS
-#pragma unroll
-                for (int r0 = 0; r0 < 16; r0 += RPI) {
-                    const int row = r0 + lane / RQ, col = lane % RQ;
-                    const int rk = row >> 2, rl = row & 3;
-                    const int st = sb * 16 + 4 * rk + i;
-                    const int qy = qy0 + 2 * rl + a;
-                    const int qz = qz0 + wzh * RQ + col;
-                    const int e = row * RQ + col;
-                    if (plane_ok && st < n_states && qy < n.y && qz < n.z) {
-                        const size_t o = (((size_t)st * n.x + qx) * n.y + qy) * n.z + qz;
-                        if (partial) {   // split pair sum: FP64 partial, summed by reduce_kernel
-                            partial[(size_t)split * part_stride + o] = sp2[e];
-                        } else {
-                            if (f) f[o] = sf[e];
-                            if (f2) f2[o] = sf2[e];
-                        }
-                    }
-                }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before the next pass writes
-            }
+// Split of two FP32 values into f16 halves: hi = RNE(v), lo = RNE(v - hi)
+// (v - hi is exact in FP32), two values per dword.  The mixed-precision FMA
+// forms v - hi in one instruction without unpacking hi.
+__device__ __forceinline__ void split_f16(float v0, float v1, uint32_t& hi, uint32_t& lo) {
+    const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{v0, v1}, halfx2));
+    float r0, r1;
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r0) : "v"(h), "v"(v0));
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r1) : "v"(h), "v"(v1));
+    hi = h;
+    lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{r0, r1}, halfx2));
 }
 
-template <int SB, int QZL, int WPE, bool BF, int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void grid_kernel(GridDesc d) {
-    grid_tile<SB, QZL, BF, NW>(d, blockIdx.x);
+// One tile of one evaluation (blk = (split * row tiles + row tile) * column
+// tiles + column tile).  Shared by the single-request kernel (one tile per
+// workgroup) and the persistent batch kernel (tiles of several requests popped
+// from a queue), so a tile's values do not depend on which of the two computed
+// it; nor do they depend on the tile a row falls into.
+//
+// LDS (floats): V blocks [2][CG 4 256 x 4], weights [2][tcm 48 ns],
+// W [2][tcm][2 np lines][kWLine].
+template <int CG, bool FOLD>
+__device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, m = lane & 15;
+    const int ns = d.n_states, tcm = d.tcm;           // tcm: 1 or 2
+    constexpr int BW = CG * 4 * 256;                  // floats of a V block
+    const int TW = tcm * 48 * ns;                     // floats of a weight buffer
+    const int WT = 2 * d.np * kWLine;                 // floats of W, one term
+    float* const Tl = lds + 2 * BW;
+    float* const Wl = Tl + 2 * TW;
+
+    const int ct = blk % d.ntc;
+    const int bl = blk / d.ntc;
+    const int split = bl / d.ntl, lt = bl - split * d.ntl;
+    const int k_lo = d.sp.lo[split], k_hi = d.sp.lo[split + 1];
+
+    // the tile's line pairs; the lane's row (clamped into the problem)
+    const int nlines = d.nx_eval * d.nyp, nrows = nlines * ns;
+    const int row0 = lt * kGridWaves * 16;
+    const int pair0 = row0 / ns >> 1;
+    const int npair = (min(row0 + kGridWaves * 16, nrows) - 1) / ns / 2 - pair0 + 1;
+    const int row = min(row0 + 16 * wave + m, nrows - 1);
+    const int line = row / ns, st = row - line * ns;
+    const float* const tl = Tl + (g * ns + st) * 12;
+    const float* const wl = Wl + (line - 2 * pair0) * kWLine + g * 20;
+
+    // W items: (pair, term, z row); a lane's term and z row are fixed, its pairs
+    // come ppass apart
+    const int lt2 = tcm == 2 ? 6 : 5;
+    const int wz = tid & 31, wt = (tid & ((1 << lt2) - 1)) >> 5, wp = tid >> lt2, ppass = kGridWaves * 64 >> lt2;
+    auto offsets = [&](int pair, uint32_t& ox, uint32_t& oy) {
+        const int l = 2 * (pair0 + min(pair, npair - 1));
+        const int qx = l / d.nyp, qy = l - qx * d.nyp;
+        ox = 8u * (uint32_t)qx * (uint32_t)d.nxr;
+        oy = d.ybase + 64u * (uint32_t)(qy >> 3) * (uint32_t)d.nyr + 8u * (uint32_t)(qy & 7);
+    };
+    uint32_t ox[kWPasses], oy[kWPasses];
+#pragma unroll
+    for (int i = 0; i < kWPasses; ++i) offsets(wp + i * ppass, ox[i], oy[i]);
+    const char* const Vb = reinterpret_cast<const char*>(d.V);
+    float* const wst = Wl + wt * WT + 2 * wp * kWLine + (wz >> 3) * 20 + (wz & 7) * 2;
+
+    // a step: terms t0 .. t0 + tc - 1 of the n terms of k-step k, which start at c
+    // (in terms per z row); the k-steps before kn have n terms
+    struct Pos {
+        int k, t0, n, c, kn;
+    };
+    auto next = [&](const Pos& p) {   // past the last k-step: stays on its last step
+        Pos q = p;
+        if (p.t0 + tcm < p.n) {
+            q.t0 += tcm;
+        } else if (p.k + 1 < k_hi) {
+            q.c += p.n;
+            q.t0 = 0;
+            ++q.k;
+            while (q.k >= q.kn) q.kn = d.steps.kend[--q.n];
+        }
+        return q;
+    };
+    auto terms_of = [&](const Pos& p) { return min(tcm, p.n - p.t0); };
+    auto dma_w = [&](const Pos& p, int buf) {
+        const float* src = d.Tw + (size_t)(p.c + p.t0) * (size_t)(48 * ns);
+        const uint32_t dst = lds_addr(Tl + buf * TW);
+        const int units = terms_of(p) * 12 * ns;   // 16 bytes each
+        for (int u = 64 * wave; u < units; u += 64 * kGridWaves)
+            if (u + lane < units) dma_b128(16u * (u + lane), src, dst + 16u * u);
+    };
+    auto dma_v = [&](int k) {
+        const uint4* src = d.Bt + ((size_t)k * d.ncg + ct * CG) * 256;
+        const uint32_t dst = lds_addr(lds + (k & 1) * BW);
+#pragma unroll
+        for (int i = 0; i < CG; ++i)
+            dma_b128(16u * (64 * (4 * i + wave) + lane), src, dst + 1024u * (4 * i + wave));
+    };
+    // term record (x row, y row) of the lane's item
+    auto load_rec = [&](const Pos& p) { return d.terms[(p.c + p.t0 + min(wt, terms_of(p) - 1)) * 32 + wz]; };
+    auto load_xy = [&](int2 rec, uint32_t px, uint32_t py, float2& x, float4& y) {
+        x = *reinterpret_cast<const float2*>(Vb + (size_t)(px + 8u * (uint32_t)rec.x));
+        y = *reinterpret_cast<const float4*>(Vb + (size_t)(py + 64u * (uint32_t)rec.y));
+    };
+    float2 vx[kWPasses];
+    float4 vy[kWPasses];
+    auto gather = [&](int tc, int2 rec) {
+#pragma unroll
+        for (int i = 0; i < kWPasses; ++i)
+            if (wt < tc && wp + i * ppass < npair) load_xy(rec, ox[i], oy[i], vx[i], vy[i]);
+    };
+    auto put_w = [&](float2 x, float4 y, float* dst) {   // the pair's two lines
+        *reinterpret_cast<float2*>(dst) = make_float2(fmaf(-x.y, y.y, x.x * y.x), fmaf(x.y, y.x, x.x * y.y));
+        *reinterpret_cast<float2*>(dst + kWLine) =
+            make_float2(fmaf(-x.y, y.w, x.x * y.z), fmaf(x.y, y.z, x.x * y.w));
+    };
+    auto write_w = [&](int tc, int2 rec, int buf) {
+        float* const w = wst + buf * tcm * WT;
+#pragma unroll
+        for (int i = 0; i < kWPasses; ++i)
+            if (wt < tc && wp + i * ppass < npair) put_w(vx[i], vy[i], w + i * 2 * ppass * kWLine);
+        for (int p = wp + kWPasses * ppass; p < npair; p += ppass) {   // tiles of many lines (few states)
+            if (wt >= tc) break;
+            uint32_t px, py;
+            offsets(p, px, py);
+            float2 x;
+            float4 y;
+            load_xy(rec, px, py, x, y);
+            put_w(x, y, w + 2 * (p - wp) * kWLine);
+        }
+    };
+
+    floatx4 acc[CG][2][2];
+    double tot[FOLD ? CG : 1][2][2][4];
+#pragma unroll
+    for (int q = 0; q < CG; ++q)
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                acc[q][a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+                if constexpr (FOLD)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) tot[q][a][b][i] = 0.0;
+            }
+    float ur[8], ui[8];
+
+    if (k_hi > k_lo) {
+        const int n0 = ksteps_terms(d.steps, k_lo);
+        Pos p0{k_lo, 0, n0, ksteps_first(d.steps, k_lo), d.steps.kend[n0]}, p1 = next(p0);
+        dma_v(k_lo);
+        dma_w(p0, 0);
+        int2 rec = load_rec(p0);
+        gather(terms_of(p0), rec);
+        write_w(terms_of(p0), rec, 0);
+        rec = load_rec(p1);
+        barrier_dma();
+        for (int i = 0;; i ^= 1) {
+            const int tc = terms_of(p0), tc1 = terms_of(p1);
+            const bool last_term = p0.t0 + tc >= p0.n, last = last_term && p0.k + 1 >= k_hi;
+            const Pos p2 = next(p1);
+            int2 rec2 = rec;
+            // the next step's loads and copies go out first
+            if (!last) {
+                gather(tc1, rec);
+                rec2 = load_rec(p2);
+                dma_w(p1, i ^ 1);
+                if (last_term) dma_v(p1.k);
+            }
+            // U of the lane's row: eight z rows
+            auto add = [&](int t, bool first) {
+                const float* T = tl + i * TW + t * 48 * ns;
+                const float* w = wl + (i * tcm + t) * WT;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const floatx4 tv = *reinterpret_cast<const floatx4*>(T + 4 * h);
+                    const floatx4 ab[2] = {*reinterpret_cast<const floatx4*>(w + 8 * h),
+                                           *reinterpret_cast<const floatx4*>(w + 8 * h + 4)};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float wr = ab[j >> 1][2 * (j & 1)], wi = ab[j >> 1][2 * (j & 1) + 1];
+                        ur[4 * h + j] = first ? tv[j] * wr : fmaf(tv[j], wr, ur[4 * h + j]);
+                        ui[4 * h + j] = first ? tv[j] * wi : fmaf(tv[j], wi, ui[4 * h + j]);
+                    }
+                }
+            };
+            if (p0.t0 == 0) add(0, true);
+            else add(0, false);
+            if (tc > 1) add(1, false);
+            if (last_term) {
+                halfx8 A[2][2];   // [re/im][hi/lo]
+#pragma unroll
+                for (int a = 0; a < 2; ++a) {
+                    const float(&u)[8] = a ? ui : ur;
+                    uintx4 hi, lo;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        uint32_t h, l;
+                        split_f16(u[2 * j], u[2 * j + 1], h, l);
+                        hi[j] = h;
+                        lo[j] = l;
+                    }
+                    A[a][0] = __builtin_bit_cast(halfx8, hi);
+                    A[a][1] = __builtin_bit_cast(halfx8, lo);
+                }
+                const uint4* B = reinterpret_cast<const uint4*>(lds + (p0.k & 1) * BW) + lane;
+#pragma unroll
+                for (int q = 0; q < CG; ++q) {
+                    halfx8 V[2][2];
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) V[b >> 1][b & 1] = __builtin_bit_cast(halfx8, B[(q * 4 + b) * 64]);
+                    // lo hi, hi lo, hi hi
+#pragma unroll
+                    for (int pr = 0; pr < 3; ++pr)
+#pragma unroll
+                        for (int a = 0; a < 2; ++a)
+#pragma unroll
+                            for (int b = 0; b < 2; ++b)
+                                acc[q][a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[a][pr == 0], V[b][pr == 1],
+                                                                                     acc[q][a][b], 0, 0, 0);
+                }
+                if (FOLD && ((p0.k - k_lo) % kFoldSteps == kFoldSteps - 1 || last)) {
+#pragma unroll
+                    for (int q = 0; q < (FOLD ? CG : 0); ++q)
+#pragma unroll
+                        for (int a = 0; a < 2; ++a)
+#pragma unroll
+                            for (int b = 0; b < 2; ++b) {
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) tot[q][a][b][e] += (double)acc[q][a][b][e];
+                                acc[q][a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+                            }
+                }
+            }
+            if (last) break;
+            write_w(tc1, rec, i ^ 1);
+            barrier_dma();
+            p0 = p1;
+            p1 = p2;
+            rec = rec2;
+        }
+    }
+
+    // epilogue: lane (g, m) holds rows 4 g + i, column m of its quads
+    const long long plane = (long long)d.n.y * d.n.z;
+    const int rw = row0 + 16 * wave + 4 * g;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int ln = (rw + i) / ns, s = rw + i - ln * ns;
+        const int qx = ln / d.nyp, qy = ln - qx * d.nyp;
+        if (rw + i >= nrows || qy >= d.n.y) continue;
+        const double sc = d.sinv[s];
+        const size_t base = (size_t)s * d.n.x * plane + (size_t)qx * plane + (size_t)qy * d.n.z;
+#pragma unroll
+        for (int q = 0; q < CG; ++q) {
+            const int col = (ct * CG + q) * 16 + m;
+            if (col >= d.ncol) continue;
+            double v[2][2];
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) v[a][b] = sc * (FOLD ? tot[FOLD ? q : 0][a][b][i] : (double)acc[q][a][b][i]);
+            auto put = [&](int iz, double re, double im) {
+                const size_t o = base + iz;
+                if (d.partial) {   // split pair sum: FP64 partial, summed by reduce_kernel
+                    d.partial[(size_t)split * d.part_stride + o] = make_double2(re, im);
+                } else {
+                    if (d.f) d.f[o] = make_float2((float)re, (float)im);
+                    if (d.f2) d.f2[o] = (float)(re * re + im * im);
+                }
+            };
+            const int iz = d.iz0 + col, im = d.n.z - 1 - iz;
+            put(iz, v[0][0] - v[1][1], v[0][1] + v[1][0]);
+            if (d.reflect && im != iz) put(im, v[0][0] + v[1][1], v[1][0] - v[0][1]);
+        }
+    }
+}
+
+template <int CG, bool FOLD>
+__global__ __launch_bounds__(kGridWaves * 64) __attribute__((amdgpu_waves_per_eu(FOLD && CG > 1 ? 2 : 3, FOLD && CG > 1 ? 2 : 3))) void grid_kernel(GridDesc d) {
+    extern __shared__ __align__(16) float grid_lds[];
+    grid_tile<CG, FOLD>(d, blockIdx.x, grid_lds);
 }
 
 // Persistent batch kernel: every workgroup pops (request, tile) items from a
 // device queue (items[i] = (descriptor index, tile of that request's launch))
 // through an atomic counter until the queue is exhausted, so the tiles of
 // several requests share one launch.  Every workgroup leaves the loop once
-// the counter passes n_items; the counter must be 0 at launch.
-template <int SB, int QZL, int WPE, bool BF, int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void grid_batch_kernel(
+// the counter passes n_items; the counter must be 0 at launch.  The launch's
+// LDS holds the largest of its requests' needs after the 16 bytes of the queue.
+template <int CG, bool FOLD>
+__global__ __launch_bounds__(kGridWaves * 64) __attribute__((amdgpu_waves_per_eu(FOLD && CG > 1 ? 2 : 3, FOLD && CG > 1 ? 2 : 3))) void grid_batch_kernel(
     const GridDesc* __restrict__ descs, const int2* __restrict__ items, int n_items, int* __restrict__ counter) {
-    __shared__ int s_item;
+    extern __shared__ __align__(16) float grid_lds[];
+    int* s_item = reinterpret_cast<int*>(grid_lds);
     for (;;) {
-        __syncthreads();   // the previous tile's LDS use (epilogue staging) is over
-        if (threadIdx.x == 0) s_item = atomicAdd(counter, 1);
+        __syncthreads();   // the previous tile's LDS use is over
+        if (threadIdx.x == 0) s_item[0] = atomicAdd(counter, 1);
         __syncthreads();
-        const int it = __builtin_amdgcn_readfirstlane(s_item);
+        const int it = __builtin_amdgcn_readfirstlane(s_item[0]);
         if (it >= n_items) break;
         const int2 w = items[it];
-        grid_tile<SB, QZL, BF, NW>(descs[w.x], w.y);
+        grid_tile<CG, FOLD>(descs[w.x], w.y, grid_lds + 4);
     }
 }
 
@@ -759,94 +650,154 @@ hipError_t launch_vtable(const VRowDev* rows, int nrows, int vstride, const int 
     return hipGetLastError();
 }
 
-// Kernel variant of an evaluation: class = (state blocks - 1) + 2 * precision.
-//   4 q_z per lane (8 q values) except for the FP32 contraction of 17..32
-//   states (2 q_z per lane, 8 waves per tile), whose accumulators and FP64
-//   fold totals would not fit 2 waves per SIMD otherwise.
-// Every variant's tile covers 16 q_z values: 4 per lane on one wave per q_x
-// line, or 2 per lane on two waves per line.  Workgroups resident per CU:
-// three of 4 waves for split-BF16 with <= 16 states (156-160 VGPRs, 50 KB of
-// LDS), one of 8 for FP32 with 17..32 states, two of 4 otherwise (their
-// registers allow 2 waves per SIMD).
-static int tile_qz(int, int) { return 16; }
-int grid_wg_per_cu(int state_blocks, int precision) {
-    if (state_blocks == 2 && precision == 0) return 1;
-    return state_blocks == 1 && precision == 1 ? 3 : 2;
-}
-int grid_class(int state_blocks, int precision) { return (state_blocks - 1) + 2 * precision; }
-static int class_waves(int cls) { return cls == 1 ? 8 : 4; }
-
-long long grid_tiles(int state_blocks, int precision, const int n[3], int nx_eval) {
-    const int tz = tile_qz(state_blocks, precision);
-    return (long long)((nx_eval + 3) / 4) * ((n[1] + 7) / 8) * ((n[2] + tz - 1) / tz);
-}
-
-// Row stride of the 1D tables: every tile may read up to 16 values past the
-// last grid point of an axis (zero padding written by vtable_kernel).
+// Row stride of the x / y tables.
 int vtable_stride(const int n[3]) {
     int m = n[0] > n[1] ? n[0] : n[1];
     m = m > n[2] ? m : n[2];
     return ((m + 15) / 16) * 16 + 16;
 }
 
-hipError_t grid_desc(int state_blocks, int precision, const float2* V, int vstride, int vrows, const int4* terms,
-                     const int4* chunks, const ChunkSplit& sp, const float* Tp, const uint32_t* tp_bf,
-                     const int n[3], int nx_eval, int n_states, float2* f, float* f2, double2* part, GridDesc* d,
-                     long long* blocks) {
-    if (precision != 0 && precision != 1) return hipErrorInvalidValue;
-    if (state_blocks != 1 && state_blocks != 2) return hipErrorInvalidValue;
-    if (vstride < vtable_stride(n) || vrows < 1) return hipErrorInvalidValue;
-    if (nx_eval < 1 || nx_eval > n[0]) return hipErrorInvalidValue;
+hipError_t launch_xytable(const VRowDev* rows, int nxr, int nyr, const int n[3], const double qmin[3], const double dq[3],
+                          float2* X, float2* Y, hipStream_t st) {
+    const long long tot = (long long)n[0] * nxr + (long long)((n[1] + 7) & ~7) * nyr;
+    const int blocks = (int)std::min<long long>((tot + 255) / 256, 65536);
+    hipLaunchKernelGGL(xytable_kernel, dim3(blocks), dim3(256), 0, st, rows, nxr, nyr, n[0], n[1],
+                       make_double2(qmin[0], qmin[1]), make_double2(dq[0], dq[1]), X, Y);
+    return hipGetLastError();
+}
+
+hipError_t launch_ztable(const VRowDev* rows, const int2* zslots, int n_zpad, const GridShape& g, double qmin, double dq,
+                         uint4* Bt, hipStream_t st) {
+    const int n_oct = n_zpad / 8;
+    const long long tot = (long long)n_oct * g.ncg * 16;
+    const int blocks = (int)std::min<long long>((tot + 255) / 256, 65536);
+    if (blocks < 1) return hipSuccess;
+    hipLaunchKernelGGL(ztable_kernel, dim3(blocks), dim3(256), 0, st, rows, zslots, n_oct, g.ncg, g.ncol, g.iz0, qmin,
+                       dq, Bt);
+    return hipGetLastError();
+}
+
+// Tiling: column groups per tile (CG), chosen for the least time among those
+// whose LDS fits.  A wave's k-step costs its products (12 CG matrix instructions
+// and, in FP32, their fold) and forming U, which every column tile repeats: about
+// 16 CG + 30 (in units of one matrix instruction).  Two terms per step where
+// the LDS allows (one barrier for both), else one (one or two states: W has up to
+// 64 lines).
+GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect) {
+    GridShape g{};
+    g.reflect = reflect ? 1 : 0;
+    g.ncol = reflect ? (n[2] + 1) / 2 : n[2];
+    g.iz0 = reflect ? n[2] - g.ncol : 0;
+    g.nyp = (n[1] + 1) & ~1;   // lines in pairs of one qx
+    const int ng = (g.ncol + 15) / 16, tr = 16 * kGridWaves;
+    const long long nrows = (long long)nx_eval * g.nyp * n_states;
+    g.ntl = (int)((nrows + tr - 1) / tr);
+    // most line pairs that a tile's rows touch
+    g.np = 1;
+    for (long long r = 0; r < std::min(2LL * tr * n_states, nrows); r += tr) {
+        const int p = (int)((r + tr - 1) / n_states / 2 - r / n_states / 2 + 1);
+        g.np = std::max(g.np, p);
+    }
+    long long best = 0;
+    for (int cg = 1; cg <= 4; ++cg) {
+        int tcm = 2;
+        auto bytes = [&] { return 4 * (2 * cg * 1024 + 2 * tcm * (48 * n_states + 2 * g.np * kWLine)); };
+        if (bytes() > kGridLds) tcm = 1;
+        if (bytes() > kGridLds) break;
+        const int nt = (ng + cg - 1) / cg;
+        const long long cost = (long long)nt * (16 * cg + 30);
+        if (!g.cg || cost < best) {
+            best = cost;
+            g.cg = cg;
+            g.ntc = nt;
+            g.tcm = tcm;
+            g.lds = bytes();
+        }
+    }
+    g.ncg = g.ntc * g.cg;
+    return g;
+}
+
+// Workgroups resident per CU: what the registers allow (FP64 totals of two and
+// more quads: two waves per SIMD, else three), and the 160 KB of LDS.
+int grid_wgs_per_cu(int cls, int lds) {
+    const int by_regs = cls >= 1 && cls <= 3 ? 2 : 3;
+    return std::min(by_regs, 160 * 1024 / (lds + 1024));
+}
+
+int grid_class(const GridShape& g, int precision) { return (g.cg - 1) + 4 * precision; }
+
+hipError_t grid_desc(const GridShape& g, const float2* V, int nxr, int nyr, uint32_t ybase, const uint4* Bt, const KSteps& steps,
+                     const int2* terms, const float* Tw, const double* sinv, const ChunkSplit& sp, const int n[3],
+                     int nx_eval, int n_states, float2* f, float* f2, double2* part, GridDesc* d, long long* blocks) {
+    if (nxr < 1 || nyr < 1 || (size_t)ybase < (size_t)n[0] * nxr * sizeof(float2)) return hipErrorInvalidValue;
+    if (nx_eval < 1 || nx_eval > n[0] || n_states < 1 || n_states > kMaxStates) return hipErrorInvalidValue;
+    if (g.cg < 1 || g.cg > 4 || g.ncg != g.cg * g.ntc || g.ncg * 16 < g.ncol || g.tcm < 1 || g.tcm > 2)
+        return hipErrorInvalidValue;
+    if ((long long)nx_eval * g.nyp * n_states > 0x7fffffff - 64) return hipErrorInvalidValue;
     if (sp.n < 1 || sp.n > kMaxSplit || sp.lo[0] != 0) return hipErrorInvalidValue;
     for (int j = 0; j < sp.n; ++j)
         if (sp.lo[j + 1] < sp.lo[j]) return hipErrorInvalidValue;
     if (sp.n > 1 && !part) return hipErrorInvalidValue;
-    const int tz = tile_qz(state_blocks, precision);
     d->V = V;
-    d->vstride = vstride;
-    d->vrows = vrows;
+    d->nxr = nxr;
+    d->nyr = nyr;
+    d->ybase = ybase;
+    d->Bt = Bt;
+    d->steps = steps;
     d->terms = terms;
-    d->chunks = chunks;
+    d->Tw = Tw;
+    d->sinv = sinv;
     d->sp = sp;
-    d->Tp = precision == 1 ? tp_bf : reinterpret_cast<const uint32_t*>(Tp);
     d->n = make_int3(n[0], n[1], n[2]);
-    d->ntiles = make_int3((nx_eval + 3) / 4, (n[1] + 7) / 8, (n[2] + tz - 1) / tz);
     d->nx_eval = nx_eval;
     d->n_states = n_states;
+    d->nyp = g.nyp;
+    d->tcm = g.tcm;
+    d->np = g.np;
+    d->ntl = g.ntl;
+    d->ntc = g.ntc;
+    d->ncg = g.ncg;
+    d->ncol = g.ncol;
+    d->iz0 = g.iz0;
+    d->reflect = g.reflect;
     d->f = f;
     d->f2 = f2;
     d->partial = sp.n > 1 ? part : nullptr;
     d->part_stride = (long long)n_states * n[0] * n[1] * n[2];
-    *blocks = (long long)d->ntiles.x * d->ntiles.y * d->ntiles.z * sp.n;
+    *blocks = (long long)g.ntl * g.ntc * sp.n;
     return hipSuccess;
 }
 
-hipError_t launch_grid_desc(int cls, const GridDesc& d, long long blocks, hipStream_t st) {
-    const dim3 grid((unsigned)blocks);
-    switch (cls) {
-        case 0: hipLaunchKernelGGL((grid_kernel<1, 4, 2, false, 4>), grid, dim3(256), 0, st, d); break;
-        case 1: hipLaunchKernelGGL((grid_kernel<2, 2, 2, false, 8>), grid, dim3(512), 0, st, d); break;
-        case 2: hipLaunchKernelGGL((grid_kernel<1, 4, 3, true, 4>), grid, dim3(256), 0, st, d); break;
-        case 3: hipLaunchKernelGGL((grid_kernel<2, 4, 2, true, 4>), grid, dim3(256), 0, st, d); break;
-        default: return hipErrorInvalidValue;
+#define SCFF_GRID_CASES(KERNEL, ...)                                              \
+    switch (cls) {                                                                \
+        case 0: hipLaunchKernelGGL((KERNEL<1, true>), __VA_ARGS__); break;        \
+        case 1: hipLaunchKernelGGL((KERNEL<2, true>), __VA_ARGS__); break;        \
+        case 2: hipLaunchKernelGGL((KERNEL<3, true>), __VA_ARGS__); break;        \
+        case 3: hipLaunchKernelGGL((KERNEL<4, true>), __VA_ARGS__); break;        \
+        case 4: hipLaunchKernelGGL((KERNEL<1, false>), __VA_ARGS__); break;       \
+        case 5: hipLaunchKernelGGL((KERNEL<2, false>), __VA_ARGS__); break;       \
+        case 6: hipLaunchKernelGGL((KERNEL<3, false>), __VA_ARGS__); break;       \
+        case 7: hipLaunchKernelGGL((KERNEL<4, false>), __VA_ARGS__); break;       \
+        default: return hipErrorInvalidValue;                                     \
     }
+
+hipError_t launch_grid(int cls, const GridShape& g, const GridDesc& d, long long blocks, hipStream_t st) {
+    if (blocks < 1 || blocks > 0x7fffffffLL || g.lds > kGridLds) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks), block(kGridWaves * 64);
+    SCFF_GRID_CASES(grid_kernel, grid, block, g.lds, st, d)
     return hipGetLastError();
 }
 
 // Persistent launch over a queue of (descriptor, tile) items of class cls:
 // `wgs` workgroups (the device's resident capacity), each looping until the
-// queue is exhausted.  *counter must be 0 when the launch starts.
-hipError_t launch_grid_batch(int cls, const GridDesc* descs, const int2* items, int n_items, int* counter, int wgs,
-                             hipStream_t st) {
-    if (n_items < 1 || wgs < 1) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)wgs), block(class_waves(cls) * 64);
-    switch (cls) {
-        case 0: hipLaunchKernelGGL((grid_batch_kernel<1, 4, 2, false, 4>), grid, block, 0, st, descs, items, n_items, counter); break;
-        case 1: hipLaunchKernelGGL((grid_batch_kernel<2, 2, 2, false, 8>), grid, block, 0, st, descs, items, n_items, counter); break;
-        case 2: hipLaunchKernelGGL((grid_batch_kernel<1, 4, 3, true, 4>), grid, block, 0, st, descs, items, n_items, counter); break;
-        case 3: hipLaunchKernelGGL((grid_batch_kernel<2, 4, 2, true, 4>), grid, block, 0, st, descs, items, n_items, counter); break;
-        default: return hipErrorInvalidValue;
-    }
+// queue is exhausted; lds: the largest GridShape::lds of the requests.
+// *counter must be 0 when the launch starts.
+hipError_t launch_grid_batch(int cls, int lds, const GridDesc* descs, const int2* items, int n_items, int* counter,
+                             int wgs, hipStream_t st) {
+    if (n_items < 1 || wgs < 1 || lds > kGridLds) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)wgs), block(kGridWaves * 64);
+    SCFF_GRID_CASES(grid_batch_kernel, grid, block, lds + 16, st, descs, items, n_items, counter)
     return hipGetLastError();
 }
 
@@ -854,18 +805,6 @@ hipError_t launch_zero_counters(int* c, int n, hipStream_t st) {
     if (n < 1 || n > 256) return hipErrorInvalidValue;
     hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(256), 0, st, c, n);
     return hipGetLastError();
-}
-
-hipError_t launch_grid(int state_blocks, int precision, const float2* V, int vstride, int vrows,
-                       const int4* terms, const int4* chunks, const ChunkSplit& sp, const float* Tp,
-                       const uint32_t* tp_bf, const int n[3], int nx_eval, int n_states, float2* f, float* f2,
-                       double2* part, hipStream_t st) {
-    GridDesc d;
-    long long blocks = 0;
-    const hipError_t e = grid_desc(state_blocks, precision, V, vstride, vrows, terms, chunks, sp, Tp, tp_bf, n,
-                                   nx_eval, n_states, f, f2, part, &d, &blocks);
-    if (e != hipSuccess) return e;
-    return launch_grid_desc(grid_class(state_blocks, precision), d, blocks, st);
 }
 
 hipError_t launch_reduce(const double2* part, int n_split, const int n[3], int nx_eval, int n_states, float2* f,

@@ -19,12 +19,20 @@
 //   thresh_kernel   largest 2^b with sum_{e <= b} count_e 2^e <= eps: dropping
 //                   every w < 2^b keeps, for every transition, the dropped
 //                   bounds below eps * tot_s
+// Grid kernel's layout (run_prep):
+//   zcount_kernel   kept terms of every z row (one per primitive pair and
+//                   power pair of the z axis), flags of the referenced rows, and
+//                   per shell pair and state the largest bound of the row's
+//                   contribution
+//   compact         rows compacted: a zero row, the x and y rows, the z rows
+//   zlayout_kernel  z rows sorted by term count (stable radix sort: most terms
+//                   first -> deterministic layout) in k-steps of 32; their term
+//                   records (x row, y row), scaled weights and scales
+// Layout by component pairs, for the other paths (run_prep_pairs):
 //   count/vkeys     kept terms per component pair, split into virtual pairs
-//                   of <= 9 terms, keyed by length (stable radix sort: longest
-//                   first, ties in pair order -> deterministic layout)
-//   chunk/layout    chunks of 8 virtual pairs, term slots, packed FP32 Tp and
-//                   its split-BF16 copy; referenced rows are flagged
-//   compact/remap   rows compacted (row 0 = all-zero row for padded slots)
+//                   of <= 9 terms, keyed by length (longest first, ties in pair
+//                   order)
+//   unit/layout     units of 8 virtual pairs, term slots, packed FP32 Tp
 #include <hip/hip_runtime.h>
 #include <hipcub/hipcub.hpp>
 
@@ -291,20 +299,53 @@ __device__ __forceinline__ bool term_kept(double w, double thr) {
     return thr < 0.0 || (w > 0.0 && w >= thr);
 }
 
+// Virtual pairs of a component pair with n kept terms: ceil(n / 9), of lengths
+// (n - pos) / (left) as vkeys_kernel cuts them.  stats: pairs with a term,
+// terms; hist: virtual pairs per length.
+__global__ __launch_bounds__(256) void stats_kernel(const int* __restrict__ cp_first, const int* __restrict__ cp_nterms,
+                                                    const double* __restrict__ w, const double* __restrict__ thr,
+                                                    int ncp, unsigned long long* __restrict__ stats,
+                                                    int* __restrict__ hist) {
+    __shared__ int lh[16], lp;
+    __shared__ unsigned long long lt;
+    if (threadIdx.x < 16) lh[threadIdx.x] = 0;
+    if (threadIdx.x == 0) {
+        lp = 0;
+        lt = 0ull;
+    }
+    __syncthreads();
+    const double th = thr[0];
+    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < ncp; k += gridDim.x * blockDim.x) {
+        int n = 0;
+        for (int t = 0; t < cp_nterms[k]; ++t) n += term_kept(w[cp_first[k] + t], th) ? 1 : 0;
+        if (n == 0) continue;
+        atomicAdd(&lp, 1);
+        atomicAdd(&lt, (unsigned long long)n);
+        const int m = (n + kMaxTermsPerPair - 1) / kMaxTermsPerPair;
+        int pos = 0;
+        for (int v = 0; v < m; ++v) {
+            const int take = (n - pos) / (m - v);
+            atomicAdd(&lh[take], 1);
+            pos += take;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < 16 && lh[threadIdx.x]) atomicAdd(&hist[threadIdx.x], lh[threadIdx.x]);
+    if (threadIdx.x == 0 && lp) {
+        atomicAdd(&stats[0], (unsigned long long)lp);
+        atomicAdd(&stats[1], lt);
+    }
+}
+
 __global__ void count_kernel(const int* __restrict__ cp_first, const int* __restrict__ cp_nterms,
                              const double* __restrict__ w, const double* __restrict__ thr, int ncp,
-                             int* __restrict__ nk, int* __restrict__ nv,
-                             unsigned long long* __restrict__ stats) {
+                             int* __restrict__ nk, int* __restrict__ nv) {
     for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < ncp; k += gridDim.x * blockDim.x) {
         const double th = thr[0];
         int n = 0;
         for (int t = 0; t < cp_nterms[k]; ++t) n += term_kept(w[cp_first[k] + t], th) ? 1 : 0;
         nk[k] = n;
         nv[k] = (n + kMaxTermsPerPair - 1) / kMaxTermsPerPair;
-        if (n > 0) {
-            atomicAdd(&stats[0], 1ull);                 // K
-            atomicAdd(&stats[1], (unsigned long long)n); // R
-        }
     }
 }
 
@@ -326,14 +367,12 @@ __global__ void vkeys_kernel(const int* __restrict__ nk, const int* __restrict__
 }
 
 __global__ void unit_kernel(const int* __restrict__ order, const int4* __restrict__ vinfo, int nv,
-                            int n_chunks, int* __restrict__ cnpp, int* __restrict__ csize,
-                            int* __restrict__ uhist) {
+                            int n_chunks, int* __restrict__ cnpp, int* __restrict__ csize) {
     for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < n_chunks; c += gridDim.x * blockDim.x) {
         const int o = c * kChunk;
         const int npp = o < nv ? max(1, vinfo[order[o]].z) : 1;
         cnpp[c] = npp;
         csize[c] = kChunk * npp;
-        atomicAdd(&uhist[npp], 1);   // units per term count (units are sorted by it, longest first)
     }
 }
 
@@ -342,8 +381,8 @@ __global__ void layout_kernel(const int* __restrict__ order, const int4* __restr
                               const int* __restrict__ cp_first, const int* __restrict__ cp_nterms,
                               const int4* __restrict__ trow, const double* __restrict__ w,
                               const double* __restrict__ thr, const double* __restrict__ tp64, int ns,
-                              int SW, int4* __restrict__ slots, float* __restrict__ tp32,
-                              uint32_t* __restrict__ tpbf, int* __restrict__ row_used, int* __restrict__ vcp) {
+                              int SW, const int* __restrict__ newid, int nr, int4* __restrict__ slots,
+                              float* __restrict__ tp32, int* __restrict__ vcp) {
     for (int o = blockIdx.x * blockDim.x + threadIdx.x; o < n_vpairs; o += gridDim.x * blockDim.x) {
         const int c = o / kChunk, j = o - c * kChunk;
         const int npp = cnpp[c];
@@ -360,47 +399,195 @@ __global__ void layout_kernel(const int* __restrict__ order, const int4* __restr
                 if (!term_kept(w[ti], th)) continue;
                 if (seen++ < vi.y) continue;
                 const int4 tr = trow[ti];
-                dst[q++] = make_int4(tr.x, tr.y, tr.z, 1);
-                row_used[tr.x] = 1;
-                row_used[tr.y] = 1;
-                row_used[tr.z] = 1;
+                dst[q++] = make_int4(1 + newid[tr.x], 1 + newid[nr + tr.y], 1 + newid[2 * nr + tr.z], 1);
             }
         }
-        for (int q = len; q < npp; ++q) dst[q] = make_int4(-1, -1, -1, 0);
+        for (int q = len; q < npp; ++q) dst[q] = make_int4(0, 0, 0, 0);   // the zero row
         vcp[o] = k;   // component pair of this packed pair (-1: padding), for the FP64 weights
         for (int st = 0; st < SW; ++st) {
-            const float v = (k >= 0 && st < ns) ? (float)tp64[(size_t)k * ns + st] : 0.0f;
-            tp32[(size_t)o * SW + st] = v;
-            // split-BF16: hi = RNE(v), lo = RNE(v - hi); packed (hi | lo << 16)
-            const uint32_t u = __float_as_uint(v);
-            const uint32_t hi = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-            const float r = v - __uint_as_float(hi << 16);
-            const uint32_t ur = __float_as_uint(r);
-            const uint32_t lo = (ur + 0x7fffu + ((ur >> 16) & 1u)) >> 16;
-            tpbf[(size_t)o * SW + st] = hi | (lo << 16);
+            tp32[(size_t)o * SW + st] = (k >= 0 && st < ns) ? (float)tp64[(size_t)k * ns + st] : 0.0f;
         }
     }
 }
 
+// used: flags of the x rows in [0, nrows), of the y rows in [nrows, 2 nrows), of
+// the z rows in [2 nrows, 3 nrows)
 __global__ void compact_kernel(const VRowDev* __restrict__ rows, const int* __restrict__ used,
                                const int* __restrict__ newid, int nrows, VRowDev* __restrict__ out) {
-    for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < nrows; r += gridDim.x * blockDim.x) {
+    for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < 3 * nrows; r += gridDim.x * blockDim.x) {
         if (r == 0) {
             VRowDev z{};
             z.inv4p = 1.0;
             out[0] = z;
         }
-        if (used[r]) out[1 + newid[r]] = rows[r];
+        if (used[r]) out[1 + newid[r]] = rows[r % nrows];
     }
 }
 
-__global__ void remap_kernel(int4* __restrict__ slots, long long nslots, const int* __restrict__ newid) {
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < nslots;
-         i += (long long)gridDim.x * blockDim.x) {
-        int4 s = slots[i];
-        if (s.w) s = make_int4(1 + newid[s.x], 1 + newid[s.y], 1 + newid[s.z], 1);
-        else s = make_int4(0, 0, 0, 0);
-        slots[i] = s;
+// Component pairs of a shell pair by the powers (i, j) of the z axis, in
+// component order: for every (lA, lB, same shell), class i (lB + 1) + j ->
+// count and component pairs.
+struct ZClasses {
+    unsigned char n[18][9], c[18][9][kZTerms];
+};
+constexpr ZClasses make_zclasses() {
+    constexpr int cz[3][6] = {{0}, {0, 0, 1}, {0, 0, 1, 0, 1, 2}};
+    ZClasses t{};
+    for (int k = 0; k < 18; ++k) {
+        const int lA = k / 6, lB = k / 2 % 3, same = k & 1;
+        const int ncA = (lA + 1) * (lA + 2) / 2, ncB = (lB + 1) * (lB + 2) / 2;
+        if (same && lA != lB) continue;
+        int c = 0;
+        for (int c1 = 0; c1 < ncA; ++c1)
+            for (int c2 = same ? c1 : 0; c2 < ncB; ++c2, ++c) {
+                const int cls = cz[lA][c1] * (lB + 1) + cz[lB][c2];
+                t.c[k][cls][t.n[k][cls]++] = (unsigned char)c;
+            }
+    }
+    return t;
+}
+__device__ __constant__ ZClasses kZClasses = make_zclasses();
+
+// Scale of a z row: V 2^e with |V| <= bound < 2^(14 - e).
+__device__ __forceinline__ int z_exponent(double bound) {
+    return bound > 0.0 && bound < 1e300 ? max(-900, min(900, 13 - ilogb(bound))) : 0;
+}
+
+// Per z row (index row offset / 3 + pp ncls + class): sort key 9 - (kept
+// terms), 15 if none, and (shell pair, pp ncls + class).  part: per shell pair
+// and state the largest sum of |Tp| x bound x y bound over a row's terms,
+// divided by the row's scale.
+__global__ __launch_bounds__(128) void zcount_kernel(const PrepShell* __restrict__ sh, const int4* __restrict__ sp,
+                                                    const int4* __restrict__ trow, const double* __restrict__ rowsum,
+                                                    const double* __restrict__ w, const double* __restrict__ thr,
+                                                    const double* __restrict__ tp64, int ns, int nr,
+                                                    int* __restrict__ used, unsigned* __restrict__ key,
+                                                    int* __restrict__ val, int2* __restrict__ zinfo,
+                                                    int* __restrict__ zhist, double* __restrict__ part) {
+    __shared__ int lh[16];
+    __shared__ unsigned long long mx[kMaxStates];
+    const int isp = blockIdx.x;
+    const int4 s = sp[isp];
+    const int lA = sh[s.x].l, lB = sh[s.y].l, npp = sh[s.x].nprim * sh[s.y].nprim;
+    const bool same = s.x == s.y;
+    const int ncls = (lA + 1) * (lB + 1);
+    const double th = thr[0];
+    if (threadIdx.x < 16) lh[threadIdx.x] = 0;
+    if (threadIdx.x < kMaxStates) mx[threadIdx.x] = 0ull;
+    __syncthreads();
+    const int kc = lA * 6 + lB * 2 + (same ? 1 : 0), nz = npp * ncls;
+    for (int z = threadIdx.x; z < nz; z += blockDim.x) {
+        const int pp = z / ncls, cls = z - pp * ncls;
+        int n = 0;
+        for (int k = 0; k < kZClasses.n[kc][cls]; ++k) {
+            const int t = s.w + kZClasses.c[kc][cls][k] * npp + pp;
+            if (!term_kept(w[t], th)) continue;
+            const int4 tr = trow[t];
+            used[tr.x] = 1;
+            used[nr + tr.y] = 1;
+            ++n;
+        }
+        const int id = s.z / 3 + z;
+        key[id] = n ? (unsigned)(kZTerms - n) : 15u;
+        val[id] = id;
+        zinfo[id] = make_int2(isp, z);
+        if (!n) continue;
+        used[2 * nr + s.z + pp * 3 * ncls + 2 * ncls + cls] = 1;
+        atomicAdd(&lh[n], 1);
+    }
+    for (int i = threadIdx.x; i < nz * ns; i += blockDim.x) {
+        const int z = i / ns, st = i - z * ns;
+        const int pp = z / ncls, cls = z - pp * ncls;
+        double b = 0.0;
+        for (int k = 0; k < kZClasses.n[kc][cls]; ++k) {
+            const int t = s.w + kZClasses.c[kc][cls][k] * npp + pp;
+            if (!term_kept(w[t], th)) continue;
+            const int4 tr = trow[t];
+            b += fabs(tp64[(size_t)tr.w * ns + st]) * rowsum[tr.x] * rowsum[tr.y];
+        }
+        b *= ldexp(1.0, -z_exponent(rowsum[s.z + pp * 3 * ncls + 2 * ncls + cls]));
+        // non-negative doubles order like their bit patterns; NaN and infinity are left out
+        if (b > 0.0 && b < 1e300) atomicMax(&mx[st], (unsigned long long)__double_as_longlong(b));
+    }
+    __syncthreads();
+    if (threadIdx.x < 16 && lh[threadIdx.x]) atomicAdd(&zhist[threadIdx.x], lh[threadIdx.x]);
+    for (int st = threadIdx.x; st < ns; st += blockDim.x)
+        part[(size_t)isp * ns + st] = __longlong_as_double((long long)mx[st]);
+}
+
+// Per state: its largest z-row bound, as the exponent ks with bound 2^ks <
+// 2^15 (weights are scaled by 2^ks) and the factor 2^-ks of the results.
+__global__ __launch_bounds__(256) void zscale_kernel(const double* __restrict__ part, int nsp, int ns,
+                                                     int* __restrict__ ks, double* __restrict__ sinv) {
+    __shared__ double red[256];
+    const int st = blockIdx.x;
+    double a = 0.0;
+    for (int i = threadIdx.x; i < nsp; i += 256) a = fmax(a, part[(size_t)i * ns + st]);
+    red[threadIdx.x] = a;
+    __syncthreads();
+    for (int h = 128; h > 0; h >>= 1) {
+        if ((int)threadIdx.x < h) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + h]);
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        const int k = red[0] > 0.0 ? max(-900, min(900, 14 - ilogb(red[0]))) : 0;
+        ks[st] = k;
+        sinv[st] = ldexp(1.0, -k);
+    }
+}
+
+// One thread per (sorted z row, state): term records,
+// weights T 2^(ks - e) and (thread of state 0) the z slot (row, e).
+__global__ __launch_bounds__(256) void zlayout_kernel(const PrepShell* __restrict__ sh, const int4* __restrict__ sp,
+                                                      const int4* __restrict__ trow, const double* __restrict__ rowsum,
+                                                      const double* __restrict__ w, const double* __restrict__ thr,
+                                                      const double* __restrict__ tp64, int ns, int nr,
+                                                      const int* __restrict__ newid, const int* __restrict__ order,
+                                                      const int2* __restrict__ zinfo, int nz, int nzpad,
+                                                      KSteps steps, const int* __restrict__ ks,
+                                                      int2* __restrict__ zslots, int2* __restrict__ terms,
+                                                      float* __restrict__ Tw) {
+    const long long tot = (long long)nzpad * ns;
+    for (long long gi = blockIdx.x * (long long)blockDim.x + threadIdx.x; gi < tot;
+         gi += (long long)gridDim.x * blockDim.x) {
+        const int p = (int)(gi / ns), st = (int)(gi - (long long)p * ns);
+        const int zn = ksteps_terms(steps, p / kZStep), zc = ksteps_first(steps, p / kZStep);
+        // record t of the row at rec[32 t], weight t at tw[grid_term_weights t]
+        const int zl = p % kZStep;
+        int2* rec = terms + zc * kZStep + zl;
+        float* tw = Tw + (size_t)zc * grid_term_weights(ns) + ((zl >> 3) * ns + st) * 12 + (zl & 7);
+        const int tstep = grid_term_weights(ns);
+        int n = 0;
+        if (p < nz) {
+            const int2 zi = zinfo[order[p]];
+            const int4 s = sp[zi.x];
+            const int lA = sh[s.x].l, lB = sh[s.y].l, npp = sh[s.x].nprim * sh[s.y].nprim;
+            const int ncls = (lA + 1) * (lB + 1), pp = zi.y / ncls, cls = zi.y - pp * ncls;
+            const int rz = s.z + pp * 3 * ncls + 2 * ncls + cls;
+            const int e = z_exponent(rowsum[rz]);
+            const double th = thr[0], sc = ldexp(1.0, ks[st] - e);
+            const int kc = lA * 6 + lB * 2 + (s.x == s.y ? 1 : 0);
+            for (int k = 0; k < kZClasses.n[kc][cls]; ++k) {
+                const int t = s.w + kZClasses.c[kc][cls][k] * npp + pp;
+                if (!term_kept(w[t], th)) continue;
+                const int4 tr = trow[t];
+                // rows of the x and y tables, whose row 0 is the zero row
+                if (st == 0) rec[kZStep * n] = make_int2(1 + newid[tr.x], 1 + newid[nr + tr.y] - newid[nr]);
+                const double tp = tp64[(size_t)tr.w * ns + st];
+                float v = (float)(tp * sc);
+                // finite weights stay finite (a row bound that underflows)
+                if (isinf(v) && !isinf(tp)) v = copysignf(3e38f, v);
+                tw[n * tstep] = v;
+                ++n;
+            }
+            if (st == 0) zslots[p] = make_int2(1 + newid[2 * nr + rz], e);
+        } else if (st == 0) {
+            zslots[p] = make_int2(0, 0);
+        }
+        for (; n < zn; ++n) {   // padding: the zero row, weight zero
+            if (st == 0) rec[kZStep * n] = make_int2(0, 0);
+            tw[n * tstep] = 0.f;
+        }
     }
 }
 
@@ -417,35 +604,38 @@ int blocks_for(long long n, int bs) {
 
 }  // namespace
 
-// Runs the whole precompute on `st`.  Buffers in `w` are (re)allocated through
+#define CK(x)                                  \
+    do {                                       \
+        if ((e = (x)) != hipSuccess) return e; \
+    } while (0)
+
+// Runs the precompute and the grid kernel's layout on `st`.  Buffers in `w` are (re)allocated through
 // `alloc`, which enforces the caller's memory budget.  Returns hipSuccess or
 // the first HIP error; sizes and statistics are written to `res`.
 hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStream_t st,
                     const std::function<hipError_t(DeviceBuffer&, size_t)>& alloc) {
     hipError_t e;
-#define CK(x)                                  \
-    do {                                       \
-        if ((e = (x)) != hipSuccess) return e; \
-    } while (0)
     const long long NR = in.n_rows_all, NT = in.n_terms_all;
     const int NCP = in.n_cp, NSP = in.n_sp, ns = in.n_states;
-    const int SW = kStateBlock * ((ns + kStateBlock - 1) / kStateBlock);
+    const int NZ = (int)(NR / 3);   // z rows
     CK(alloc(w.rows_all, (size_t)NR * sizeof(VRowDev)));
     CK(alloc(w.rowsum, (size_t)NR * sizeof(double)));
     CK(alloc(w.trow, (size_t)NT * sizeof(int4)));
-    CK(alloc(w.tbound, (size_t)NT * sizeof(double)));
+    CK(alloc(w.tbound, std::max((size_t)NT * sizeof(double), (size_t)NZ * 24)));
     CK(alloc(w.wt, (size_t)NT * sizeof(double)));
     CK(alloc(w.cpmn, (size_t)NCP * sizeof(int2)));
     CK(alloc(w.tp64, (size_t)NCP * ns * sizeof(double)));
     CK(alloc(w.bsum, (size_t)NCP * sizeof(double)));
     CK(alloc(w.part, (size_t)NSP * ns * sizeof(double)));
     CK(alloc(w.small, 4096 + kHistBins * sizeof(unsigned) + 64));
-    CK(alloc(w.nk, (size_t)NCP * sizeof(int)));
-    CK(alloc(w.nv, (size_t)NCP * sizeof(int)));
-    CK(alloc(w.vbase, (size_t)NCP * sizeof(int)));
+    if (NR > INT32_MAX / 3) return hipErrorInvalidValue;
+    CK(alloc(w.row_used, (size_t)NR * 3 * sizeof(int)));
+    CK(alloc(w.newid, (size_t)NR * 3 * sizeof(int)));
     double* tot = (double*)w.small.p;                                    // [<= 32]
     double* thr = tot + 64;                                              // [1]
-    unsigned long long* stats = (unsigned long long*)(thr + 8);          // [2]
+    double* sinv = (double*)((char*)w.small.p + kSmallSinv);             // [<= 32]
+    int* ks = (int*)((char*)w.small.p + kSmallKs);                       // [<= 32]
+    int* zhist = (int*)((char*)w.small.p + kSmallZhist);                 // [16]
     unsigned* hist = (unsigned*)((char*)w.small.p + 4096);               // [kHistBins]
 
     CK(hipMemsetAsync(w.small.p, 0, w.small.bytes, st));
@@ -467,36 +657,154 @@ hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStrea
     CK(hipGetLastError());
     hipLaunchKernelGGL(thresh_kernel, dim3(1), dim3(64), 0, st, (const unsigned*)hist, in.eps, thr);
     CK(hipGetLastError());
+    // the term bounds were last read by weight_kernel: their buffer holds the
+    // z rows' sort arrays from here on
+    int2* zinfo = (int2*)w.tbound.p;
+    unsigned* zk_in = (unsigned*)(zinfo + NZ);
+    unsigned* zk_out = zk_in + NZ;
+    int* zv_in = (int*)(zk_out + NZ);
+    int* zv_out = zv_in + NZ;
+    CK(hipMemsetAsync(w.row_used.p, 0, (size_t)NR * 3 * sizeof(int), st));
+    hipLaunchKernelGGL(zcount_kernel, dim3(NSP), dim3(128), 0, st, in.shells, in.sp, (const int4*)w.trow.p,
+                       (const double*)w.rowsum.p, (const double*)w.wt.p, (const double*)thr, (const double*)w.tp64.p, ns,
+                       (int)NR, (int*)w.row_used.p, zk_in, zv_in, zinfo, zhist, (double*)w.part.p);
+    CK(hipGetLastError());
+    hipLaunchKernelGGL(zscale_kernel, dim3(ns), dim3(256), 0, st, (const double*)w.part.p, NSP, ns, ks, sinv);
+    CK(hipGetLastError());
+    size_t tmp_bytes = 0;
+    CK(hipcub::DeviceScan::ExclusiveSum(nullptr, tmp_bytes, (int*)w.row_used.p, (int*)w.newid.p, (int)(3 * NR), st));
+    CK(alloc(w.tmp4, tmp_bytes + 256));
+    CK(hipcub::DeviceScan::ExclusiveSum(w.tmp4.p, tmp_bytes, (int*)w.row_used.p, (int*)w.newid.p, (int)(3 * NR), st));
+    // readbacks of sizes land in the context's pinned host memory when it has
+    // some (a DMA; pageable destinations are staged by the runtime)
+    alignas(16) unsigned char local_rb[256];
+    unsigned char* rb = w.pinned ? (unsigned char*)w.pinned : local_rb;
+    int* zh = (int*)rb;                 // [16]
+    int* lastr = (int*)(rb + 64);       // [4]: first y id, first z id; last id and flag
+    CK(hipMemcpyAsync(zh, zhist, 16 * sizeof(int), hipMemcpyDeviceToHost, st));
+    CK(hipMemcpyAsync(&lastr[0], (int*)w.newid.p + NR, sizeof(int), hipMemcpyDeviceToHost, st));
+    CK(hipMemcpyAsync(&lastr[1], (int*)w.newid.p + 2 * NR, sizeof(int), hipMemcpyDeviceToHost, st));
+    CK(hipMemcpyAsync(&lastr[2], (int*)w.newid.p + 3 * NR - 1, sizeof(int), hipMemcpyDeviceToHost, st));
+    CK(hipMemcpyAsync(&lastr[3], (int*)w.row_used.p + 3 * NR - 1, sizeof(int), hipMemcpyDeviceToHost, st));
+    size_t sort_bytes = 0;
+    CK(hipcub::DeviceRadixSort::SortPairs(nullptr, sort_bytes, zk_in, zk_out, zv_in, zv_out, NZ, 0, 4, st));
+    CK(alloc(w.tmp2, sort_bytes + 256));
+    CK(hipcub::DeviceRadixSort::SortPairs(w.tmp2.p, sort_bytes, zk_in, zk_out, zv_in, zv_out, NZ, 0, 4, st));
+    CK(hipStreamSynchronize(st));
+    const int nrows_used = lastr[2] + lastr[3];
+    // k-steps of kZStep sorted z rows; every row is padded to the count of the
+    // k-step's first (a single k-step of zero rows if nothing is kept)
+    KSteps steps{};
+    int nz = 0;
+    for (int n = kZTerms; n >= 1; --n) {
+        nz += zh[n];
+        steps.kend[n] = (nz + kZStep - 1) / kZStep;
+    }
+    if (nz == 0) steps.kend[1] = 1;
+    const int n_ksteps = steps.kend[1], nzpad = n_ksteps * kZStep;
+    long long nc = 0;
+    for (int n = 1; n <= kZTerms; ++n) nc += steps.kend[n];
+    const long long nterm = nc * kZStep, nw = nc * grid_term_weights(ns);
+    if (nz > nrows_used || nterm > INT32_MAX || nw > INT32_MAX) return hipErrorUnknown;
+    CK(alloc(w.zslots, (size_t)nzpad * sizeof(int2)));
+    CK(alloc(w.zterms, (size_t)nterm * sizeof(int2)));
+    CK(alloc(w.zw, (size_t)nw * sizeof(float)));
+    CK(alloc(w.rows, (size_t)(nrows_used + 1) * sizeof(VRowDev)));
+    hipLaunchKernelGGL(compact_kernel, dim3(blocks_for(3 * NR, 256)), dim3(256), 0, st, (const VRowDev*)w.rows_all.p,
+                       (const int*)w.row_used.p, (const int*)w.newid.p, (int)NR, (VRowDev*)w.rows.p);
+    CK(hipGetLastError());
+    hipLaunchKernelGGL(zlayout_kernel, dim3(blocks_for((long long)nzpad * ns, 256)), dim3(256), 0, st, in.shells, in.sp,
+                       (const int4*)w.trow.p, (const double*)w.rowsum.p, (const double*)w.wt.p, (const double*)thr,
+                       (const double*)w.tp64.p, ns, (int)NR, (const int*)w.newid.p, (const int*)zv_out,
+                       (const int2*)zinfo, nz, nzpad, steps, (const int*)ks, (int2*)w.zslots.p,
+                       (int2*)w.zterms.p, (float*)w.zw.p);
+    CK(hipGetLastError());
+    res = PrepResult{};
+    res.n_rows = nrows_used + 1;
+    res.n_x = lastr[0];
+    res.n_y = lastr[1] - lastr[0];
+    res.n_ksteps = n_ksteps;
+    res.ksteps = steps;
+    res.n_zterms = nterm;
+    res.n_zweights = nw;
+    res.state_blocks = (ns + kStateBlock - 1) / kStateBlock;
+    return hipSuccess;
+}
+
+// Pairs and terms kept, and the sizes of the layout by component pairs.
+hipError_t run_prep_stats(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStream_t st) {
+    hipError_t e;
+    const double* thr = (const double*)w.small.p + 64;
+    unsigned long long* stats = (unsigned long long*)((char*)w.small.p + kSmallStats);   // [2], then int [16]
+    constexpr size_t nb = 2 * sizeof(unsigned long long) + 16 * sizeof(int);
+    CK(hipMemsetAsync(stats, 0, nb, st));
+    hipLaunchKernelGGL(stats_kernel, dim3(std::min(blocks_for(in.n_cp, 256), 256)), dim3(256), 0, st, in.cp_first,
+                       in.cp_nterms, (const double*)w.wt.p, thr, in.n_cp, stats, (int*)(stats + 2));
+    CK(hipGetLastError());
+    alignas(16) unsigned char local_rb[nb];
+    unsigned char* rb = w.pinned ? (unsigned char*)w.pinned : local_rb;
+    CK(hipMemcpyAsync(rb, stats, nb, hipMemcpyDeviceToHost, st));
+    CK(hipStreamSynchronize(st));
+    const unsigned long long* kr = (const unsigned long long*)rb;
+    const int* hist = (const int*)(kr + 2);
+    res.pairs_kept = (long long)kr[0];
+    res.terms_kept = (long long)kr[1];
+    // virtual pairs sorted longest first, in units of kChunk padded to their
+    // first pair's length; chunks are runs of units of equal length, at most
+    // kMaxUnitsPerChunk units and kMaxChunkTerms terms
+    int units[16] = {};
+    long long nv = 0, slots = 0;
+    for (int v = kMaxTermsPerPair; v >= 1; --v) {
+        const long long u0 = (nv + kChunk - 1) / kChunk, u1 = (nv + hist[v] + kChunk - 1) / kChunk;
+        units[v] = (int)(u1 - u0);
+        nv += hist[v];
+    }
+    res.n_virtual = (int)nv;
+    if (nv == 0) units[1] = 1;   // one padded unit
+    res.n_units = res.n_chunks = 0;
+    for (int v = kMaxTermsPerPair; v >= 1; --v) {
+        const int um = std::min(kMaxUnitsPerChunk, kMaxChunkTerms / (kChunk * v));
+        res.n_units += units[v];
+        res.n_chunks += (units[v] + um - 1) / um;
+        slots += (long long)units[v] * kChunk * v;
+    }
+    res.n_slots = slots;
+    res.n_vpairs = res.n_units * kChunk;
+    return hipSuccess;
+}
+
+// The layout by component pairs (units of packed weights and term slots) of
+// the paths other than the grid kernel, after run_prep and run_prep_stats on
+// the same inputs.
+hipError_t run_prep_pairs(const PrepInputs& in, PrepWork& w, const PrepResult& res, hipStream_t st,
+                          const std::function<hipError_t(DeviceBuffer&, size_t)>& alloc) {
+    hipError_t e;
+    const int NCP = in.n_cp, ns = in.n_states;
+    const long long NR = in.n_rows_all;
+    const int SW = kStateBlock * ((ns + kStateBlock - 1) / kStateBlock);
+    const double* thr = (const double*)w.small.p + 64;
+    const int NV = res.n_virtual, NVA = NV > 0 ? NV : 1;
+    const int n_vpairs = res.n_vpairs, n_units = res.n_units;
+    CK(alloc(w.nk, (size_t)NCP * sizeof(int)));
+    CK(alloc(w.nv, (size_t)NCP * sizeof(int)));
+    CK(alloc(w.vbase, (size_t)NCP * sizeof(int)));
+    CK(alloc(w.key, (size_t)NVA * sizeof(unsigned) * 2));
+    CK(alloc(w.val, (size_t)NVA * sizeof(int) * 2));
+    CK(alloc(w.vinfo, (size_t)NVA * sizeof(int4)));
+    CK(alloc(w.cnpp, (size_t)n_units * sizeof(int)));
+    CK(alloc(w.csize, (size_t)n_units * sizeof(int)));
+    CK(alloc(w.coff, (size_t)n_units * sizeof(int)));
+    CK(alloc(w.slots, (size_t)res.n_slots * sizeof(int4)));
+    CK(alloc(w.tp32, (size_t)n_vpairs * SW * sizeof(float)));
+    CK(alloc(w.vcp, (size_t)n_vpairs * sizeof(int)));
     hipLaunchKernelGGL(count_kernel, dim3(blocks_for(NCP, 256)), dim3(256), 0, st, in.cp_first,
-                       in.cp_nterms, (const double*)w.wt.p, (const double*)thr, NCP, (int*)w.nk.p,
-                       (int*)w.nv.p, stats);
+                       in.cp_nterms, (const double*)w.wt.p, (const double*)thr, NCP, (int*)w.nk.p, (int*)w.nv.p);
     CK(hipGetLastError());
     // exclusive scan of virtual pairs per component pair
     size_t tmp_bytes = 0;
     CK(hipcub::DeviceScan::ExclusiveSum(nullptr, tmp_bytes, (int*)w.nv.p, (int*)w.vbase.p, NCP, st));
     CK(alloc(w.tmp, tmp_bytes + 256));
     CK(hipcub::DeviceScan::ExclusiveSum(w.tmp.p, tmp_bytes, (int*)w.nv.p, (int*)w.vbase.p, NCP, st));
-    // readbacks of sizes land in the context's pinned host memory when it has
-    // some (a DMA; pageable destinations are staged by the runtime)
-    alignas(16) unsigned char local_rb[256];
-    unsigned char* rb = w.pinned ? (unsigned char*)w.pinned : local_rb;
-    int* last = (int*)rb;                                  // [2]
-    unsigned long long* kr = (unsigned long long*)(rb + 16);   // [2]
-    int* lastc = (int*)(rb + 32);                          // [2]
-    int* uhist = (int*)(rb + 64);                          // [16]
-    int* lastr = (int*)(rb + 128);                         // [2]
-    // total virtual pairs, K and R
-    CK(hipMemcpyAsync(&last[0], (int*)w.vbase.p + NCP - 1, sizeof(int), hipMemcpyDeviceToHost, st));
-    CK(hipMemcpyAsync(&last[1], (int*)w.nv.p + NCP - 1, sizeof(int), hipMemcpyDeviceToHost, st));
-    CK(hipMemcpyAsync(kr, stats, 2 * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
-    CK(hipStreamSynchronize(st));
-    const int NV = last[0] + last[1];
-    res.pairs_kept = (long long)kr[0];
-    res.terms_kept = (long long)kr[1];
-    const int NVA = NV > 0 ? NV : 1;
-    CK(alloc(w.key, (size_t)NVA * sizeof(unsigned) * 2));
-    CK(alloc(w.val, (size_t)NVA * sizeof(int) * 2));
-    CK(alloc(w.vinfo, (size_t)NVA * sizeof(int4)));
     unsigned* key_in = (unsigned*)w.key.p;
     unsigned* key_out = key_in + NVA;
     int* val_in = (int*)w.val.p;
@@ -511,100 +819,22 @@ hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStrea
         CK(hipcub::DeviceRadixSort::SortPairs(w.tmp2.p, sort_bytes, key_in, key_out, val_in, val_out, NV, 0, 4, st));
     }
     // units of kChunk sorted virtual pairs, each padded to its first pair's term count
-    const int n_vpairs = ((NVA + kChunk - 1) / kChunk) * kChunk;
-    const int n_chunks = n_vpairs / kChunk;   // units
-    CK(alloc(w.cnpp, (size_t)n_chunks * sizeof(int)));
-    CK(alloc(w.csize, (size_t)n_chunks * sizeof(int)));
-    CK(alloc(w.coff, (size_t)n_chunks * sizeof(int)));
-    CK(alloc(w.uhist, 16 * sizeof(int)));
-    CK(hipMemsetAsync(w.uhist.p, 0, 16 * sizeof(int), st));
-    hipLaunchKernelGGL(unit_kernel, dim3(blocks_for(n_chunks, 256)), dim3(256), 0, st, (const int*)val_out,
-                       (const int4*)w.vinfo.p, NV, n_chunks, (int*)w.cnpp.p, (int*)w.csize.p, (int*)w.uhist.p);
+    hipLaunchKernelGGL(unit_kernel, dim3(blocks_for(n_units, 256)), dim3(256), 0, st, (const int*)val_out,
+                       (const int4*)w.vinfo.p, NV, n_units, (int*)w.cnpp.p, (int*)w.csize.p);
     CK(hipGetLastError());
     size_t tmp3 = 0;
-    CK(hipcub::DeviceScan::ExclusiveSum(nullptr, tmp3, (int*)w.csize.p, (int*)w.coff.p, n_chunks, st));
+    CK(hipcub::DeviceScan::ExclusiveSum(nullptr, tmp3, (int*)w.csize.p, (int*)w.coff.p, n_units, st));
     CK(alloc(w.tmp3, tmp3 + 256));
-    CK(hipcub::DeviceScan::ExclusiveSum(w.tmp3.p, tmp3, (int*)w.csize.p, (int*)w.coff.p, n_chunks, st));
-    CK(hipMemcpyAsync(&lastc[0], (int*)w.coff.p + n_chunks - 1, sizeof(int), hipMemcpyDeviceToHost, st));
-    CK(hipMemcpyAsync(&lastc[1], (int*)w.csize.p + n_chunks - 1, sizeof(int), hipMemcpyDeviceToHost, st));
-    CK(hipMemcpyAsync(uhist, w.uhist.p, 16 * sizeof(int), hipMemcpyDeviceToHost, st));
-    CK(hipStreamSynchronize(st));
-    // grid-kernel chunks: runs of consecutive units with equal npp (units come
-    // longest first), at most kMaxUnitsPerChunk units and kMaxChunkTerms terms.
-    // Entry = (first unit, units, npp, first term slot); the slot offsets of
-    // the units follow from the same counts (kChunk * npp slots per unit).
-    std::vector<int>& ch = w.chunk_host;
-    ch.clear();
-    {
-        int u0 = 0;
-        long long slot = 0;
-        for (int v = kMaxTermsPerPair; v >= 1; --v) {
-            const int cnt = uhist[v];
-            int um = kMaxChunkTerms / (kChunk * v);
-            if (um > kMaxUnitsPerChunk) um = kMaxUnitsPerChunk;
-            for (int k = 0; k < cnt; k += um) {
-                const int nu = cnt - k < um ? cnt - k : um;
-                ch.push_back(u0 + k);
-                ch.push_back(nu);
-                ch.push_back(v);
-                ch.push_back((int)slot);
-                slot += (long long)nu * kChunk * v;
-            }
-            u0 += cnt;
-        }
-        // every unit has 1 <= npp <= kMaxTermsPerPair; slots agree with the device scan
-        if (u0 != n_chunks || slot != (long long)lastc[0] + lastc[1]) return hipErrorUnknown;
-    }
-    const int n_grid_chunks = (int)(ch.size() / 4);
-    CK(alloc(w.chunks, ch.size() * sizeof(int)));
-    {
-        // through pinned memory when it fits; the copy is complete at the
-        // synchronisation below, before the buffer can be written again
-        const size_t cb = ch.size() * sizeof(int);
-        const void* src = ch.data();
-        if (w.pinned && cb <= kPinnedBytes - kPinnedTables) {
-            std::memcpy((unsigned char*)w.pinned + kPinnedTables, ch.data(), cb);
-            src = (unsigned char*)w.pinned + kPinnedTables;
-        }
-        CK(hipMemcpyAsync(w.chunks.p, src, cb, hipMemcpyHostToDevice, st));
-    }
-    const long long nslots = (long long)lastc[0] + lastc[1];
-    CK(alloc(w.slots, (size_t)nslots * sizeof(int4)));
-    CK(alloc(w.tp32, (size_t)n_vpairs * SW * sizeof(float)));
-    CK(alloc(w.tpbf, (size_t)n_vpairs * SW * sizeof(uint32_t)));
-    CK(alloc(w.vcp, (size_t)n_vpairs * sizeof(int)));
-    CK(alloc(w.row_used, (size_t)NR * sizeof(int)));
-    CK(alloc(w.newid, (size_t)NR * sizeof(int)));
-    CK(hipMemsetAsync(w.row_used.p, 0, (size_t)NR * sizeof(int), st));
+    CK(hipcub::DeviceScan::ExclusiveSum(w.tmp3.p, tmp3, (int*)w.csize.p, (int*)w.coff.p, n_units, st));
     hipLaunchKernelGGL(layout_kernel, dim3(blocks_for(n_vpairs, 128)), dim3(128), 0, st, (const int*)val_out,
                        (const int4*)w.vinfo.p, NV, n_vpairs, (const int*)w.cnpp.p, (const int*)w.coff.p,
                        in.cp_first, in.cp_nterms, (const int4*)w.trow.p, (const double*)w.wt.p,
-                       (const double*)thr, (const double*)w.tp64.p, ns, SW, (int4*)w.slots.p,
-                       (float*)w.tp32.p, (uint32_t*)w.tpbf.p, (int*)w.row_used.p, (int*)w.vcp.p);
+                       (const double*)thr, (const double*)w.tp64.p, ns, SW, (const int*)w.newid.p, (int)NR,
+                       (int4*)w.slots.p, (float*)w.tp32.p, (int*)w.vcp.p);
     CK(hipGetLastError());
-    size_t tmp4 = 0;
-    CK(hipcub::DeviceScan::ExclusiveSum(nullptr, tmp4, (int*)w.row_used.p, (int*)w.newid.p, (int)NR, st));
-    CK(alloc(w.tmp4, tmp4 + 256));
-    CK(hipcub::DeviceScan::ExclusiveSum(w.tmp4.p, tmp4, (int*)w.row_used.p, (int*)w.newid.p, (int)NR, st));
-    CK(hipMemcpyAsync(&lastr[0], (int*)w.newid.p + NR - 1, sizeof(int), hipMemcpyDeviceToHost, st));
-    CK(hipMemcpyAsync(&lastr[1], (int*)w.row_used.p + NR - 1, sizeof(int), hipMemcpyDeviceToHost, st));
-    CK(hipStreamSynchronize(st));
-    const int nrows_used = lastr[0] + lastr[1];
-    CK(alloc(w.rows, (size_t)(nrows_used + 1) * sizeof(VRowDev)));
-    hipLaunchKernelGGL(compact_kernel, dim3(blocks_for(NR, 256)), dim3(256), 0, st, (const VRowDev*)w.rows_all.p,
-                       (const int*)w.row_used.p, (const int*)w.newid.p, (int)NR, (VRowDev*)w.rows.p);
-    CK(hipGetLastError());
-    hipLaunchKernelGGL(remap_kernel, dim3(blocks_for(nslots, 256)), dim3(256), 0, st, (int4*)w.slots.p, nslots,
-                       (const int*)w.newid.p);
-    CK(hipGetLastError());
-    res.n_vpairs = n_vpairs;
-    res.n_units = n_chunks;
-    res.n_chunks = n_grid_chunks;
-    res.n_slots = nslots;
-    res.n_rows = nrows_used + 1;
-    res.state_blocks = SW / kStateBlock;
     return hipSuccess;
-#undef CK
 }
+
+#undef CK
 
 }  // namespace scff

@@ -18,19 +18,20 @@ namespace scff {
 hipError_t launch_vtable(const VRowDev* rows, int nrows, int vstride, const int n[3],
                          const double qmin[3], const double dq[3], float2* V, hipStream_t st);
 int vtable_stride(const int n[3]);
-hipError_t launch_grid(int state_blocks, int precision, const float2* V, int vstride, int vrows,
-                       const int4* terms, const int4* chunks, const ChunkSplit& sp, const float* Tp,
-                       const uint32_t* tp_bf, const int n[3], int nx_eval, int n_states, float2* f, float* f2,
-                       double2* part, hipStream_t st);
+hipError_t launch_xytable(const VRowDev* rows, int nxr, int nyr, const int n[3], const double qmin[3], const double dq[3],
+                          float2* X, float2* Y, hipStream_t st);
+hipError_t launch_ztable(const VRowDev* rows, const int2* zslots, int n_zpad, const GridShape& g, double qmin, double dq,
+                         uint4* Bt, hipStream_t st);
+GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect);
+int grid_wgs_per_cu(int cls, int lds);
+hipError_t launch_grid(int cls, const GridShape& g, const GridDesc& d, long long blocks, hipStream_t st);
 hipError_t launch_reduce(const double2* part, int n_split, const int n[3], int nx_eval, int n_states, float2* f,
                          float* f2, hipStream_t st);
 hipError_t launch_mirror(const int n[3], int nx_eval, int n_states, float2* f, float* f2, hipStream_t st);
-long long grid_tiles(int state_blocks, int precision, const int n[3], int nx_eval);
-int grid_class(int state_blocks, int precision);
-hipError_t grid_desc(int state_blocks, int precision, const float2* V, int vstride, int vrows, const int4* terms,
-                     const int4* chunks, const ChunkSplit& sp, const float* Tp, const uint32_t* tp_bf,
-                     const int n[3], int nx_eval, int n_states, float2* f, float* f2, double2* part, GridDesc* d,
-                     long long* blocks);
+int grid_class(const GridShape& g, int precision);
+hipError_t grid_desc(const GridShape& g, const float2* V, int nxr, int nyr, uint32_t ybase, const uint4* Bt, const KSteps& steps,
+                     const int2* terms, const float* Tw, const double* sinv, const ChunkSplit& sp, const int n[3],
+                     int nx_eval, int n_states, float2* f, float* f2, double2* part, GridDesc* d, long long* blocks);
 hipError_t launch_points(int state_blocks, const VRowDev* rows, const int4* terms, const int* coff,
                          const int* cnpp, int n_chunks, const float* Tp, const double* q, int nq,
                          int n_states, float2* f, float* f2, hipStream_t st);
@@ -85,8 +86,9 @@ struct scff_ctx {
     PrepWork prep;
     PrepResult pres;
     bool prepared = false;
+    // of the current precompute: its statistics, and its layout by component pairs
+    bool stats_ready = false, pairs_ready = false;
     DeviceBuffer d_vtab, d_f, d_f2, d_q;
-    int vtab_rows = 0, vtab_stride = 0;
     // timing
     bool timing = false;
     hipEvent_t ev[EV_N] = {};
@@ -197,6 +199,11 @@ int set_device(scff_ctx* c) { return hip_check(hipSetDevice(c->device), "hipSetD
 // the context's previous asynchronous work with an event, so a call on stream
 // B never overtakes a call still running on stream A.
 int order_after(scff_ctx* c, hipStream_t st) {
+    if (c->async_open) {   // an earlier call failed half-way: its work is on a stream nobody marked
+        GateShared g(device_gate());
+        const int rc = hip_check(hipDeviceSynchronize(), "device sync");
+        if (rc) return rc;
+    }
     c->async_open = true;
     if (!c->order_pending || st == c->order_st) return SCFF_OK;
     return hip_check(hipStreamWaitEvent(st, c->order_ev, 0), "stream ordering");
@@ -234,41 +241,43 @@ int record(scff_ctx* c, int which, hipStream_t st) {
 }
 
 // Host check of the tables the grid kernel indexes with (on request): every
-// term slot names a 1D-table row in [0, rows) and every chunk lies inside the
-// unit and slot arrays.  A violation is an engine bug; it is reported as
-// SCFF_EDEVICE before any kernel reads the tables.
+// term record names an x row in [0, n_x] and a y row in [0, n_y], every z slot
+// a row in [0, n_rows), and the k-steps lie inside the term arrays.  A violation is an
+// engine bug; it is reported as SCFF_EDEVICE before any kernel reads the
+// tables.
 int validate_prep(scff_ctx* c, hipStream_t st) {
     const PrepResult& p = c->pres;
-    std::vector<int> slots((size_t)p.n_slots * 4);
+    std::vector<int> terms((size_t)p.n_zterms * 2), zs((size_t)p.n_ksteps * kZStep * 2);
     int rc;
-    if (!slots.empty() &&
-        (rc = hip_check(hipMemcpyAsync(slots.data(), c->prep.slots.p, slots.size() * sizeof(int),
-                                       hipMemcpyDeviceToHost, st), "D2H slots")))
+    if ((rc = hip_check(hipMemcpyAsync(terms.data(), c->prep.zterms.p, terms.size() * sizeof(int),
+                                       hipMemcpyDeviceToHost, st), "D2H terms")) ||
+        (rc = hip_check(hipMemcpyAsync(zs.data(), c->prep.zslots.p, zs.size() * sizeof(int), hipMemcpyDeviceToHost, st),
+                        "D2H z slots")) ||
+        (rc = hip_check(hipStreamSynchronize(st), "validation sync")))
         return rc;
-    if ((rc = hip_check(hipStreamSynchronize(st), "validation sync"))) return rc;
-    for (size_t i = 0; i < slots.size(); i += 4)
-        for (int a = 0; a < 3; ++a)
-            if (slots[i + a] < 0 || slots[i + a] >= p.n_rows)
-                return fail(SCFF_EDEVICE, "precompute produced a term slot outside the 1D tables (slot " +
-                                              std::to_string(i / 4) + ", axis " + std::to_string(a) + ", row " +
-                                              std::to_string(slots[i + a]) + " of " + std::to_string(p.n_rows) + ")");
-    const std::vector<int>& ch = c->prep.chunk_host;
-    if ((int)ch.size() < 4 * p.n_chunks) return fail(SCFF_EDEVICE, "chunk table shorter than its chunk count");
-    for (int k = 0; k < p.n_chunks; ++k) {
-        const long long u0 = ch[4 * k], nu = ch[4 * k + 1], npp = ch[4 * k + 2], s0 = ch[4 * k + 3];
-        if (u0 < 0 || nu < 1 || nu > kMaxUnitsPerChunk || u0 + nu > p.n_units || npp < 1 ||
-            npp > kMaxTermsPerPair || nu * kChunk * npp > kMaxChunkTerms || s0 < 0 ||
-            s0 + nu * kChunk * npp > p.n_slots)
-            return fail(SCFF_EDEVICE, "precompute produced a chunk outside the unit or slot arrays (chunk " +
-                                          std::to_string(k) + ")");
+    for (size_t i = 0; i < terms.size(); ++i) {
+        const int top = i % 2 ? p.n_y : p.n_x;
+        if (terms[i] < 0 || terms[i] > top)
+            return fail(SCFF_EDEVICE, "precompute produced a term outside the 1D tables (term " + std::to_string(i / 2) +
+                                          ", axis " + std::to_string(i % 2) + ", row " + std::to_string(terms[i]) +
+                                          " of " + std::to_string(top + 1) + ")");
     }
+    for (size_t i = 0; i < zs.size(); i += 2)
+        if (zs[i] < 0 || zs[i] >= p.n_rows)
+            return fail(SCFF_EDEVICE, "precompute produced a z slot outside the row table (slot " +
+                                          std::to_string(i / 2) + ", row " + std::to_string(zs[i]) + " of " +
+                                          std::to_string(p.n_rows) + ")");
+    for (int n = 1; n <= kZTerms; ++n)
+        if (p.ksteps.kend[n] < 0 || p.ksteps.kend[n] > (n > 1 ? p.ksteps.kend[n - 1] : p.n_ksteps))
+            return fail(SCFF_EDEVICE, "precompute produced k-steps out of order");
+    const long long nc = ksteps_first(p.ksteps, p.n_ksteps);
+    if (p.ksteps.kend[1] != p.n_ksteps || nc * kZStep != p.n_zterms ||
+        nc * grid_term_weights(c->n_states) != p.n_zweights)
+        return fail(SCFF_EDEVICE, "precompute produced k-steps outside the term arrays");
     return SCFF_OK;
 }
 
-int ensure_prepared(scff_ctx* c, hipStream_t st) {
-    if (!c->have_mol) return fail(SCFF_ESTATE, "no molecule loaded");
-    if (!c->have_T) return fail(SCFF_ESTATE, "no transitions loaded");
-    if (c->prepared) return SCFF_OK;
+PrepInputs prep_inputs(scff_ctx* c) {
     const Basis& b = c->basis;
     PrepInputs in{};
     const unsigned char* m = (const unsigned char*)c->d_mol.p;
@@ -292,16 +301,46 @@ int ensure_prepared(scff_ctx* c, hipStream_t st) {
     in.n_terms_all = b.n_terms;
     in.eps = c->eps;
     in.spin = c->spin;
+    return in;
+}
+
+// The precompute and the grid kernel's layout.
+int ensure_prepared(scff_ctx* c, hipStream_t st) {
+    if (!c->have_mol) return fail(SCFF_ESTATE, "no molecule loaded");
+    if (!c->have_T) return fail(SCFF_ESTATE, "no transitions loaded");
+    if (c->prepared) return SCFF_OK;
     PrepResult res;
     int rc;
     if ((rc = record(c, EV_PREP0, st))) return rc;
-    hipError_t e = run_prep(in, c->prep, res, st, [c](DeviceBuffer& buf, size_t n) { return dev_reserve_raw(c, buf, n); });
+    hipError_t e = run_prep(prep_inputs(c), c->prep, res, st,
+                            [c](DeviceBuffer& buf, size_t n) { return dev_reserve_raw(c, buf, n); });
     if (e != hipSuccess) return hip_check(e, "pair precompute");
     if ((rc = record(c, EV_PREP1, st))) return rc;
     c->ev_prep = c->timing;
     c->pres = res;
+    c->stats_ready = c->pairs_ready = false;
     if (c->validate && (rc = validate_prep(c, st))) return rc;
     c->prepared = true;
+    return SCFF_OK;
+}
+
+// The precompute with its statistics.
+int ensure_stats(scff_ctx* c, hipStream_t st) {
+    int rc = ensure_prepared(c, st);
+    if (rc || c->stats_ready) return rc;
+    if ((rc = hip_check(run_prep_stats(prep_inputs(c), c->prep, c->pres, st), "pair statistics"))) return rc;
+    c->stats_ready = true;
+    return SCFF_OK;
+}
+
+// The precompute with the layout by component pairs too.
+int ensure_pairs(scff_ctx* c, hipStream_t st) {
+    int rc = ensure_stats(c, st);
+    if (rc || c->pairs_ready) return rc;
+    const hipError_t e = run_prep_pairs(prep_inputs(c), c->prep, c->pres, st,
+                                        [c](DeviceBuffer& buf, size_t n) { return dev_reserve_raw(c, buf, n); });
+    if (e != hipSuccess) return hip_check(e, "pair layout");
+    c->pairs_ready = true;
     return SCFF_OK;
 }
 
@@ -315,22 +354,43 @@ int validate_grid(const scff_grid* g) {
     return SCFF_OK;
 }
 
-// 1D tables for the grid axes
-int build_vtables(scff_ctx* c, const scff_grid* g, hipStream_t st) {
-    const int nrows = c->pres.n_rows;
-    const int stride = vtable_stride(g->n);
-    // the grid kernel addresses the tables with 32-bit byte offsets
-    if ((size_t)nrows * stride * sizeof(float2) > 0xffffffffull)
-        return fail(SCFF_EINVAL, "1D tables of this grid exceed 4 GiB: evaluate it in slabs");
-    int rc = dev_reserve(c, c->d_vtab, (size_t)nrows * stride * sizeof(float2));
-    if (rc) return rc;
-    double dq[3];
+// Spacing of the grid axes.
+void grid_spacing(const scff_grid* g, double dq[3]) {
     for (int a = 0; a < 3; ++a) dq[a] = g->n[a] > 1 ? (g->qmax[a] - g->qmin[a]) / (g->n[a] - 1) : 0.0;
-    c->vtab_rows = nrows;
-    c->vtab_stride = stride;
-    return hip_check(launch_vtable((const VRowDev*)c->prep.rows.p, nrows, stride, g->n, g->qmin, dq,
-                                   (float2*)c->d_vtab.p, st),
-                     "vtable kernel launch");
+}
+
+// Device bytes of a grid's 1D tables: the x table, the y table, then the z
+// axis' operand blocks.
+struct TableBytes {
+    size_t y, z, total;   // offsets of the y table and the blocks; total
+};
+TableBytes table_bytes(const scff_ctx* c, const scff_grid* g, const GridShape& sh) {
+    auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    TableBytes t;
+    t.y = up((size_t)(c->pres.n_x + 1) * g->n[0] * sizeof(float2));
+    t.z = t.y + up((size_t)(c->pres.n_y + 1) * ((g->n[1] + 7) & ~7) * sizeof(float2));
+    t.total = t.z + (size_t)c->pres.n_ksteps * sh.ncg * 4 * 1024;
+    return t;
+}
+
+// Largest grid: the tables of all rows at the row stride within 4 GiB.
+int check_tables(const scff_ctx* c, const scff_grid* g) {
+    if ((size_t)c->pres.n_rows * vtable_stride(g->n) * sizeof(float2) > 0xffffffffull)
+        return fail(SCFF_EINVAL, "1D tables of this grid exceed 4 GiB: evaluate it in slabs");
+    return SCFF_OK;
+}
+
+int launch_tables(scff_ctx* c, const scff_grid* g, const GridShape& sh, void* tab, hipStream_t st) {
+    double dq[3];
+    grid_spacing(g, dq);
+    const TableBytes tb = table_bytes(c, g, sh);
+    int rc = hip_check(launch_xytable((const VRowDev*)c->prep.rows.p, c->pres.n_x + 1, c->pres.n_y + 1, g->n, g->qmin, dq,
+                                      (float2*)tab, (float2*)((char*)tab + tb.y), st),
+                       "x / y table kernel launch");
+    if (rc) return rc;
+    return hip_check(launch_ztable((const VRowDev*)c->prep.rows.p, (const int2*)c->prep.zslots.p,
+                                   c->pres.n_ksteps * kZStep, sh, g->qmin[2], dq[2], (uint4*)((char*)tab + tb.z), st),
+                     "z table kernel launch");
 }
 
 // every axis holds -q with q: index i and n-1-i are q and -q.  An axis of
@@ -347,76 +407,96 @@ bool grid_symmetric(const scff_grid* g) {
     return true;
 }
 
+// The z axis holds -q with q: only its upper half is computed (V(-q) = V(q)*
+// for every 1D row).
+bool z_reflects(const scff_grid* g) { return g->n[2] > 1 && g->qmin[2] == -g->qmax[2]; }
+
 // How scff_eval_grid evaluates grid g: the planes it computes (ix < nx_eval;
-// the rest are mirrored in the symmetric mode) and the split of the chunk
-// list.  Every tile costs the same (it runs the whole chunk list), and the
-// device holds two workgroups of 4 waves (or one of 8) per CU at once (the grid kernel's occupancy),
-// so a launch of `tiles` workgroups takes ceil(tiles / slots) rounds: 64 or
-// 1728 tiles on 512 slots leave most of one round idle.  Cutting the chunk
-// list into S ranges of about equal work (a chunk costs units * (npp + 2):
-// generator terms plus the contraction), one workgroup per tile and range,
-// takes ceil(tiles * S / slots) rounds of 1/S the work; the FP64 partial sums
-// are reduced afterwards (a pass over S x 16 bytes per output value, small
-// next to the kernel).  S is the smallest value within 2 % of the best; a split
-// must save at least 5 %, and its partial buffer is kept under
-// kMaxPartBytes.  allow_split = false gives the unsplit plan.
+// the rest are mirrored in the symmetric mode), the tiling, and the split of
+// the k-steps.  Every tile costs the same (it runs all k-steps) and the device
+// holds two or three workgroups per CU (slots), so a launch of `tiles` workgroups takes
+// ceil(tiles / slots) rounds; a small grid leaves most of a round idle.  Cutting
+// the k-steps into S ranges of about equal work, one workgroup per tile and
+// range, takes ceil(tiles S / slots) rounds of 1/S the work plus, per range, the
+// workgroup's start and epilogue (about six k-steps' time, kStartSteps) and a
+// pass over S x 16 bytes per output value (kPassSteps per byte: 4 TB/s against
+// ~0.5 us a k-step).  S is the smallest value within 3 % of the best;
+// its partial buffer is kept under kMaxPartBytes.  allow_split = false gives
+// the unsplit plan.
 constexpr size_t kMaxPartBytes = (size_t)1 << 30;
+constexpr double kStartSteps = 6.0, kPassSteps = 1.0 / (4e12 * 0.5e-6);
 
 struct EvalPlan {
     int nx_eval;
+    GridShape shape;
     ChunkSplit sp;
 };
 
 EvalPlan plan_eval(const scff_ctx* c, const scff_grid* g, int precision, bool allow_split = true) {
     EvalPlan e{};
     e.nx_eval = (c->symmetry && grid_symmetric(g)) ? (g->n[0] + 1) / 2 : g->n[0];
-    const int nch = c->pres.n_chunks;
-    const long long tiles = grid_tiles(c->pres.state_blocks, precision, g->n, e.nx_eval);
-    const long long slots = (long long)grid_wg_per_cu(c->pres.state_blocks, precision) * c->n_cu;
+    e.shape = grid_shape(g->n, e.nx_eval, c->n_states, z_reflects(g));
+    const int nst = c->pres.n_ksteps;
+    const long long tiles = (long long)e.shape.ntl * e.shape.ntc, 
+                    slots = (long long)grid_wgs_per_cu(grid_class(e.shape, precision), e.shape.lds) * c->n_cu;
     const size_t part1 = (size_t)g->n[0] * g->n[1] * g->n[2] * (size_t)c->n_states * sizeof(double2);
-    long long smax = std::min<long long>(kMaxSplit, nch);
+    long long smax = std::min<long long>(kMaxSplit, nst);
     smax = std::min<long long>(smax, part1 ? (long long)(kMaxPartBytes / part1) : kMaxSplit);
     if (!allow_split) smax = 1;
-    auto rounds_per_work = [&](long long S) { return (double)((tiles * S + slots - 1) / slots) / (double)S; };
+    auto cost = [&](long long S) {
+        const double rounds = (double)((tiles * S + slots - 1) / slots);
+        return rounds * ((double)nst / (double)S + kStartSteps) +
+               (S > 1 ? 2.0 * kPassSteps * (double)part1 * (double)S : 0.0);
+    };
     long long S = 1;
-    double best = rounds_per_work(1);
+    double best = cost(1);
     for (long long s2 = 2; s2 <= smax; ++s2) {
-        const double r = rounds_per_work(s2);
-        if (r < 0.98 * best) {
+        const double r = cost(s2);
+        if (r < 0.97 * best) {
             best = r;
             S = s2;
         }
     }
-    if (best > 0.95 * rounds_per_work(1)) S = 1;
-    e.sp.n = (int)std::max<long long>(S, 1);
-    const std::vector<int>& ch = c->prep.chunk_host;   // (first unit, units, npp, first slot) per chunk
-    std::vector<double> pre(nch + 1, 0.0);
-    for (int k = 0; k < nch; ++k) pre[k + 1] = pre[k] + (double)ch[4 * k + 1] * (ch[4 * k + 2] + 2.0);
+    e.sp.n = (int)S;
+    // a k-step costs about two units for its products and one per term of its rows
+    std::vector<double> pre(nst + 1, 0.0);
+    for (int k = 0; k < nst; ++k) pre[k + 1] = pre[k] + 2.0 + (double)ksteps_terms(c->pres.ksteps, k);
     e.sp.lo[0] = 0;
     int k = 0;
     for (int j = 1; j < e.sp.n; ++j) {
-        const double w = pre[nch] * j / e.sp.n;
-        while (k < nch && pre[k] < w) ++k;
+        const double w = pre[nst] * j / e.sp.n;
+        while (k < nst && pre[k] < w) ++k;
         e.sp.lo[j] = k;
     }
-    e.sp.lo[e.sp.n] = nch;
+    e.sp.lo[e.sp.n] = nst;
     return e;
 }
 
+// The grid kernel's descriptor on tables tab.
+int make_desc(scff_ctx* c, const scff_grid* g, const EvalPlan& pl, const void* tab, double2* part, float2* df, float* df2,
+              GridDesc* d, long long* blocks) {
+    const PrepWork& w = c->prep;
+    const TableBytes tb = table_bytes(c, g, pl.shape);
+    return hip_check(grid_desc(pl.shape, (const float2*)tab, c->pres.n_x + 1, c->pres.n_y + 1, (uint32_t)tb.y,
+                               (const uint4*)((const char*)tab + tb.z),
+                               c->pres.ksteps, (const int2*)w.zterms.p, (const float*)w.zw.p,
+                               (const double*)((const char*)w.small.p + kSmallSinv), pl.sp, g->n, pl.nx_eval, c->n_states,
+                               df, df2, part, d, blocks),
+                     "grid descriptor");
+}
+
 // The fused grid kernel (with the split reduction and the symmetric-mode
-// mirror when the plan asks for them) on tables V, events around it.
-int run_grid(scff_ctx* c, const scff_grid* g, int precision, const float2* V, int vstride, int vrows,
-             const EvalPlan& pl, double2* part, float2* df, float* df2, hipStream_t st) {
+// mirror when the plan asks for them) on tables tab, events around it.
+int run_grid(scff_ctx* c, const scff_grid* g, int precision, const void* tab, const EvalPlan& pl, double2* part,
+             float2* df, float* df2, hipStream_t st) {
     int rc;
     if ((rc = record(c, EV_GRID0, st))) return rc;
-    const PrepResult& p = c->pres;
+    GridDesc d;
+    long long blocks = 0;
+    if ((rc = make_desc(c, g, pl, tab, part, df, df2, &d, &blocks))) return rc;
     // f(-q) = f(q)* for real T: on a grid symmetric about q = 0 the planes
     // ix >= ceil(nx/2) are the conjugates of computed ones (symmetric mode)
-    rc = hip_check(launch_grid(p.state_blocks, precision, V, vstride, vrows, (const int4*)c->prep.slots.p,
-                               (const int4*)c->prep.chunks.p, pl.sp, (const float*)c->prep.tp32.p,
-                               (const uint32_t*)c->prep.tpbf.p, g->n, pl.nx_eval, c->n_states, df, df2, part, st),
-                   "grid kernel launch");
-    if (rc) return rc;
+    if ((rc = hip_check(launch_grid(grid_class(pl.shape, precision), pl.shape, d, blocks, st), "grid kernel launch"))) return rc;
     if (pl.sp.n > 1 &&
         (rc = hip_check(launch_reduce(part, pl.sp.n, g->n, pl.nx_eval, c->n_states, df, df2, st), "reduce launch")))
         return rc;
@@ -443,8 +523,8 @@ void free_all(scff_ctx* c) {
     PrepWork& w = c->prep;
     for (DeviceBuffer* b : {&w.rows_all, &w.rowsum, &w.trow, &w.tbound, &w.wt, &w.cpmn, &w.tp64, &w.bsum,
                             &w.part, &w.small, &w.nk, &w.nv, &w.vbase, &w.tmp, &w.key, &w.val, &w.vinfo,
-                            &w.tmp2, &w.cnpp, &w.csize, &w.coff, &w.tmp3, &w.slots, &w.tp32, &w.tpbf,
-                            &w.row_used, &w.newid, &w.tmp4, &w.rows, &w.uhist, &w.chunks, &w.vcp})
+                            &w.tmp2, &w.cnpp, &w.csize, &w.coff, &w.tmp3, &w.slots, &w.tp32,
+                            &w.row_used, &w.newid, &w.tmp4, &w.rows, &w.zslots, &w.zterms, &w.zw, &w.vcp})
         dev_free(c, *b);
 }
 
@@ -473,12 +553,12 @@ int scff::ctx_prepare(scff_ctx* c, const scff_grid* g, int precision, hipStream_
     if ((rc = hip_check(hipStreamSynchronize(st), "precompute sync"))) return rc;
     order_done(c);
     const size_t npts = (size_t)g->n[0] * g->n[1] * g->n[2];
-    const int stride = vtable_stride(g->n);
+    (void)precision;
     // the 1D tables and output staging reuse buffers the context already
     // holds when those are large enough (a reused context)
-    const size_t vt = (size_t)c->pres.n_rows * stride * sizeof(float2);
-    const size_t of = npts * (size_t)c->n_states * sizeof(float2), of2 = npts * (size_t)c->n_states * sizeof(float);
     const EvalPlan pl = plan_eval(c, g, precision);
+    const size_t vt = table_bytes(c, g, pl.shape).total;
+    const size_t of = npts * (size_t)c->n_states * sizeof(float2), of2 = npts * (size_t)c->n_states * sizeof(float);
     const size_t op = pl.sp.n > 1 ? (size_t)pl.sp.n * npts * (size_t)c->n_states * sizeof(double2) : 0;
     const size_t held = c->d_vtab.bytes + c->d_f.bytes + c->d_f2.bytes + c->d_part.bytes;
     *bytes_needed = c->used - held + std::max(c->d_vtab.bytes, vt) + std::max(c->d_f.bytes, of) +
@@ -498,13 +578,11 @@ int scff::ctx_batch_reserve(scff_ctx* c, const scff_grid* g, int precision, bool
     if (!c->prepared) return fail(SCFF_ESTATE, "batch evaluation of a context that is not prepared");
     if ((rc = set_device(c))) return rc;
     const size_t nout = (size_t)g->n[0] * g->n[1] * g->n[2] * (size_t)c->n_states;
-    const int stride = vtable_stride(g->n);
-    if ((size_t)c->pres.n_rows * stride * sizeof(float2) > 0xffffffffull)
-        return fail(SCFF_EINVAL, "1D tables of this grid exceed 4 GiB: evaluate it in slabs");
-    if ((rc = dev_reserve(c, c->d_vtab, (size_t)c->pres.n_rows * stride * sizeof(float2)))) return rc;
+    if ((rc = check_tables(c, g))) return rc;
+    EvalPlan pl = plan_eval(c, g, precision);
+    if ((rc = dev_reserve(c, c->d_vtab, table_bytes(c, g, pl.shape).total))) return rc;
     if (want_f && (rc = dev_reserve(c, c->d_f, nout * sizeof(float2)))) return rc;
     if (want_f2 && (rc = dev_reserve(c, c->d_f2, nout * sizeof(float)))) return rc;
-    EvalPlan pl = plan_eval(c, g, precision);
     double2* part = nullptr;
     if (pl.sp.n > 1) {
         if (dev_reserve(c, c->d_part, (size_t)pl.sp.n * nout * sizeof(double2)) == SCFF_OK)
@@ -512,29 +590,20 @@ int scff::ctx_batch_reserve(scff_ctx* c, const scff_grid* g, int precision, bool
         else
             pl = plan_eval(c, g, precision, false);
     }
-    const PrepResult& p = c->pres;
-    hipError_t e = grid_desc(p.state_blocks, precision, (const float2*)c->d_vtab.p, stride, p.n_rows,
-                             (const int4*)c->prep.slots.p, (const int4*)c->prep.chunks.p, pl.sp,
-                             (const float*)c->prep.tp32.p, (const uint32_t*)c->prep.tpbf.p, g->n, pl.nx_eval,
-                             c->n_states, want_f ? (float2*)c->d_f.p : nullptr, want_f2 ? (float*)c->d_f2.p : nullptr,
-                             part, &be->desc, &be->blocks);
-    if (e != hipSuccess) return hip_check(e, "grid descriptor");
-    be->cls = grid_class(p.state_blocks, precision);
+    if ((rc = make_desc(c, g, pl, c->d_vtab.p, part, want_f ? (float2*)c->d_f.p : nullptr,
+                        want_f2 ? (float*)c->d_f2.p : nullptr, &be->desc, &be->blocks)))
+        return rc;
+    be->cls = grid_class(pl.shape, precision);
+    be->shape = pl.shape;
     be->n_split = pl.sp.n;
     be->nx_eval = pl.nx_eval;
     be->nout = nout;
-    c->vtab_rows = p.n_rows;
-    c->vtab_stride = stride;
     c->async_open = true;   // device work follows on the batch stream
     return ok();
 }
 
-int scff::ctx_batch_tables(scff_ctx* c, const scff_grid* g, hipStream_t st) {
-    double dq[3];
-    for (int a = 0; a < 3; ++a) dq[a] = g->n[a] > 1 ? (g->qmax[a] - g->qmin[a]) / (g->n[a] - 1) : 0.0;
-    return hip_check(launch_vtable((const VRowDev*)c->prep.rows.p, c->vtab_rows, c->vtab_stride, g->n, g->qmin, dq,
-                                   (float2*)c->d_vtab.p, st),
-                     "vtable kernel launch");
+int scff::ctx_batch_tables(scff_ctx* c, const scff_grid* g, const BatchEval& be, hipStream_t st) {
+    return launch_tables(c, g, be.shape, c->d_vtab.p, st);
 }
 
 int scff::ctx_batch_finish(scff_ctx* c, const scff_grid* g, const BatchEval& be, float* host_f, float* host_f2,
@@ -728,9 +797,9 @@ int scff_query(scff_ctx* c, scff_info* info) {
     if (c->have_mol && c->have_T) {
         int rc;
         if ((rc = set_device(c))) return rc;
-        if (!c->prepared) {
+        if (!c->prepared || !c->stats_ready) {
             if ((rc = order_after(c, nullptr))) return rc;
-            if ((rc = ensure_prepared(c, nullptr))) return rc;
+            if ((rc = ensure_stats(c, nullptr))) return rc;
             if ((rc = hip_check(hipStreamSynchronize(nullptr), "precompute sync"))) return rc;
             order_done(c);
         }
@@ -765,11 +834,14 @@ int scff_eval_grid(scff_ctx* c, const scff_grid* g, int precision, float* f, flo
         df2 = f2 ? (float*)c->d_f2.p : nullptr;
     }
     if ((rc = record(c, EV_VT0, st))) return rc;
-    if ((rc = build_vtables(c, g, st))) return rc;
+    if ((rc = check_tables(c, g))) return rc;
+    EvalPlan pl = plan_eval(c, g, precision);
+    if ((rc = dev_reserve(c, c->d_vtab, table_bytes(c, g, pl.shape).total)) ||
+        (rc = launch_tables(c, g, pl.shape, c->d_vtab.p, st)))
+        return rc;
     // the partial buffer is the last reservation: a split that the context's
     // HBM budget cannot hold falls back to the unsplit evaluation (the same
     // values up to the order of the FP64 sums)
-    EvalPlan pl = plan_eval(c, g, precision);
     double2* part = nullptr;
     if (pl.sp.n > 1) {
         if (dev_reserve(c, c->d_part, (size_t)pl.sp.n * nout * sizeof(double2)) == SCFF_OK)
@@ -777,9 +849,7 @@ int scff_eval_grid(scff_ctx* c, const scff_grid* g, int precision, float* f, flo
         else
             pl = plan_eval(c, g, precision, false);
     }
-    if ((rc = run_grid(c, g, precision, (const float2*)c->d_vtab.p, c->vtab_stride, c->vtab_rows, pl, part, df,
-                       df2, st)))
-        return rc;
+    if ((rc = run_grid(c, g, precision, c->d_vtab.p, pl, part, df, df2, st))) return rc;
     if (!out_on_device) {
         if ((rc = copy_out(df, f, df2, f2, nout, st))) return rc;
         if ((rc = hip_check(hipStreamSynchronize(st), "stream sync"))) return rc;
@@ -801,36 +871,32 @@ int scff_eval_grid_noalloc(scff_ctx* c, const scff_grid* g, int precision, float
         return fail(SCFF_ESTATE, "the precompute of the loaded problem has not run (call scff_query or an "
                                  "evaluation after the last load or option change)");
     if (!c->scratch || !c->order_ev) return fail(SCFF_EDEVICE, "static scratch of the device is not available");
-    // 1D tables first, then (when they fit) the partial sums of a split
-    const int stride = vtable_stride(g->n);
-    const size_t vt = (size_t)c->pres.n_rows * stride * sizeof(float2);
-    const size_t vt_al = (vt + 255) & ~(size_t)255;
+    // 1D tables first, then (when they fit) the partial sums of a split.  The
+    // limit is on the tables of all rows at the row stride; the tables built
+    // take less, or at most kScratchSlack more where few rows pad to a k-step
+    const size_t vt = (size_t)c->pres.n_rows * vtable_stride(g->n) * sizeof(float2);
     if (vt > kScratchBytes || vt > 0xffffffffull)
         return fail(SCFF_EINVAL, "1D tables of this grid need " + std::to_string(vt) + " bytes; the static scratch "
                                  "holds " + std::to_string(kScratchBytes) + " (use scff_eval_grid)");
+    EvalPlan pl = plan_eval(c, g, precision);
+    const size_t vt_al = (table_bytes(c, g, pl.shape).total + 255) & ~(size_t)255;
+    if (vt_al > kScratchBytes + kScratchSlack) return fail(SCFF_EINVAL, "1D tables of this grid exceed the static scratch");
     if ((rc = set_device(c))) return rc;
     hipStream_t st = (hipStream_t)hip_stream;
     c->ev_prep = false;
     if ((rc = order_after(c, st))) return rc;
     unsigned char* base = (unsigned char*)c->scratch;
-    float2* V = (float2*)base;
-    double dq[3];
-    for (int a = 0; a < 3; ++a) dq[a] = g->n[a] > 1 ? (g->qmax[a] - g->qmin[a]) / (g->n[a] - 1) : 0.0;
     if ((rc = record(c, EV_VT0, st))) return rc;
-    if ((rc = hip_check(launch_vtable((const VRowDev*)c->prep.rows.p, c->pres.n_rows, stride, g->n, g->qmin, dq, V,
-                                      st),
-                        "vtable kernel launch")))
-        return rc;
+    if ((rc = launch_tables(c, g, pl.shape, base, st))) return rc;
     const size_t nout = (size_t)g->n[0] * g->n[1] * g->n[2] * (size_t)c->n_states;
-    EvalPlan pl = plan_eval(c, g, precision);
     double2* part = nullptr;
     if (pl.sp.n > 1) {
-        if (vt_al + (size_t)pl.sp.n * nout * sizeof(double2) <= kScratchBytes)
+        if (vt_al + (size_t)pl.sp.n * nout * sizeof(double2) <= kScratchBytes + kScratchSlack)
             part = (double2*)(base + vt_al);
         else
             pl = plan_eval(c, g, precision, false);
     }
-    if ((rc = run_grid(c, g, precision, V, stride, c->pres.n_rows, pl, part, (float2*)f, f2, st))) return rc;
+    if ((rc = run_grid(c, g, precision, base, pl, part, (float2*)f, f2, st))) return rc;
     if ((rc = order_mark(c, st))) return rc;
     return ok();
 }
@@ -922,7 +988,7 @@ int scff_eval_points(scff_ctx* c, int n_q, const double* q, int precision, float
     if ((rc = set_device(c))) return rc;
     hipStream_t st = (hipStream_t)hip_stream;
     if ((rc = order_after(c, st))) return rc;
-    if ((rc = ensure_prepared(c, st))) return rc;
+    if ((rc = ensure_pairs(c, st))) return rc;
     if ((rc = dev_reserve(c, c->d_q, (size_t)n_q * 3 * sizeof(double)))) return rc;
     if ((rc = hip_check(hipMemcpyAsync(c->d_q.p, q, (size_t)n_q * 3 * sizeof(double), hipMemcpyHostToDevice, st),
                         "upload q")))
@@ -958,7 +1024,7 @@ int scff_export_vtensors(scff_ctx* c, const scff_grid* g, long long* n_terms_out
     if ((rc = set_device(c))) return rc;
     hipStream_t st = nullptr;
     if ((rc = order_after(c, st))) return rc;
-    if ((rc = ensure_prepared(c, st))) return rc;
+    if ((rc = ensure_pairs(c, st))) return rc;
     const PrepResult& p = c->pres;
     *n_terms_out = p.terms_kept;
     if (!vx && !vy && !vz && !tp) {
@@ -966,9 +1032,17 @@ int scff_export_vtensors(scff_ctx* c, const scff_grid* g, long long* n_terms_out
         order_done(c);
         return ok();
     }
-    if ((rc = build_vtables(c, g, st))) return rc;
+    // the tables of all rows, z included
+    const int stride = vtable_stride(g->n);
+    double dq[3];
+    grid_spacing(g, dq);
+    if ((rc = check_tables(c, g)) || (rc = dev_reserve(c, c->d_vtab, (size_t)p.n_rows * stride * sizeof(float2))) ||
+        (rc = hip_check(launch_vtable((const VRowDev*)c->prep.rows.p, p.n_rows, stride, g->n, g->qmin, dq,
+                                      (float2*)c->d_vtab.p, st),
+                        "vtable kernel launch")))
+        return rc;
     const int SW = kStateBlock * p.state_blocks;
-    std::vector<float2> V((size_t)c->vtab_rows * c->vtab_stride);
+    std::vector<float2> V((size_t)p.n_rows * stride);
     std::vector<int> slots((size_t)p.n_slots * 4), coff(p.n_units), cnpp(p.n_units);
     std::vector<float> tp32((size_t)p.n_vpairs * SW);
     struct Cp {
@@ -996,7 +1070,7 @@ int scff_export_vtensors(scff_ctx* c, const scff_grid* g, long long* n_terms_out
                     if (!outs[a]) continue;
                     const int na = g->n[a];
                     for (int i = 0; i < na; ++i) {
-                        const float2 v = V[(size_t)tr[a] * c->vtab_stride + i];
+                        const float2 v = V[(size_t)tr[a] * stride + i];
                         outs[a][((size_t)t * na + i) * 2] = v.x;
                         outs[a][((size_t)t * na + i) * 2 + 1] = v.y;
                     }
@@ -1017,7 +1091,7 @@ int prepare_sync(scff_ctx* c) {
     int rc;
     if ((rc = set_device(c))) return rc;
     if ((rc = order_after(c, nullptr))) return rc;
-    return ensure_prepared(c, nullptr);
+    return ensure_pairs(c, nullptr);
 }
 
 int finish_sync(scff_ctx* c) {

@@ -3,7 +3,7 @@
 // after them, the FP64 partial sums of a split chunk list live in this
 // file-scope array instead of context buffers, so that call allocates no
 // device memory.  Each device the library runs on holds its own copy of the
-// array (kScratchBytes) until the process ends.
+// array (kScratchBytes + kScratchSlack) until the process ends.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -13,7 +13,7 @@
 namespace scff {
 
 namespace {
-__device__ __align__(256) unsigned char scratch[kScratchBytes];
+__device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchSlack];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_mu;

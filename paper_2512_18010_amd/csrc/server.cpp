@@ -449,7 +449,7 @@ struct Runner {
 
 constexpr size_t kMaxExecs = 32;
 constexpr int kRunners = 2;
-constexpr int kVariants = 4;
+constexpr int kVariants = scff::kGridClasses;
 
 int grow_device(void** p, size_t* cap, size_t need) {
     if (*cap >= need) return SCFF_OK;
@@ -498,7 +498,7 @@ int enqueue_batch(Runner& R, std::vector<Member*>& live, const int off[], size_t
         return SCFF_EDEVICE;
     }
     for (Member* m : live)
-        if (scff::ctx_batch_tables(m->r->ctx, &m->r->grid, R.st) != SCFF_OK) {
+        if (scff::ctx_batch_tables(m->r->ctx, &m->r->grid, m->be, R.st) != SCFF_OK) {
             err = scff_last_error();
             return SCFF_EDEVICE;
         }
@@ -506,8 +506,11 @@ int enqueue_batch(Runner& R, std::vector<Member*>& live, const int off[], size_t
     for (int v = 0; v < kVariants; ++v) {
         const int n = off[v + 1] - off[v];
         if (n == 0) continue;
-        const int wgs = std::min(n, ncu * scff::grid_wg_per_cu(v % 2 + 1, v / 2));
-        e = scff::launch_grid_batch(v, d_desc, d_items + off[v], n, R.d_cnt + v, wgs, R.st);
+                int lds = 0;
+        for (const Member* m : live)
+            if (m->be.cls == v) lds = std::max(lds, m->be.shape.lds);
+        const int wgs = std::min(n, ncu * scff::grid_wgs_per_cu(v, lds));
+        e = scff::launch_grid_batch(v, lds, d_desc, d_items + off[v], n, R.d_cnt + v, wgs, R.st);
         if (e != hipSuccess) {
             err = std::string("batch grid kernel: ") + hipGetErrorString(e);
             return SCFF_EDEVICE;
