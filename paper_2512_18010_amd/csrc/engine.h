@@ -167,6 +167,22 @@ struct PrepInputs {
     double eps, spin;
 };
 
+// Point evaluation (points.hip): the precompute's arrays, the points and what is
+// written (f, |f|^2, |f|^2 in FP64; each may be null).  part: FP64 sums per
+// share of the shell pairs, [n_split][state][point], null for one share.
+struct PointArgs {
+    const PrepShell* shells;
+    const int4* sp;
+    const int* sp_cp;
+    const VRowDev* rows;   // all rows, by shell pair
+    const double *wt, *thr, *tp64, *q;
+    int n_sp, ns, nq;
+    float2* f;
+    float* f2;
+    double* f2d;
+    double2* part;
+};
+
 // Device buffers of the precompute.  What the grid kernel reads: rows, zslots,
 // zterms, zw and the state factors in small; the layout by component
 // pairs (made when another path first needs it): slots, tp32, vcp and, per

@@ -19,8 +19,6 @@
 //    lo halves, FP32 accumulation; FP32 precision folds into FP64 totals); the
 //    operand is formed on the VALU.  grid_batch_kernel: the same tiles popped
 //    from a queue of several requests.
-//  * points_kernel: the same sum at arbitrary points (VALU only), V
-//    evaluated on the fly.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -38,7 +36,6 @@ typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
 typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 
-constexpr int kPointFoldUnits = 4;   // points kernel: units (32 pairs) per FP32 block sum
 
 // ---------------------------------------------------------------- 1D tables
 
@@ -579,63 +576,6 @@ __global__ void mirror_kernel(int3 n, int nx_eval, int n_states, float2* __restr
     }
 }
 
-// ---------------------------------------------------------------- points kernel
-
-template <int SB>
-__global__ __launch_bounds__(64) void points_kernel(
-    const VRowDev* __restrict__ rows, const int4* __restrict__ terms,
-    const int* __restrict__ chunk_off, const int* __restrict__ chunk_npp, int n_units,
-    const float* __restrict__ Tp, const double* __restrict__ qpts, int nq, int n_states,
-    float2* __restrict__ f, float* __restrict__ f2) {
-    constexpr int SW = 16 * SB;
-    const int iq = blockIdx.x * blockDim.x + threadIdx.x;
-    if (iq >= nq) return;
-    const double qx = qpts[3 * iq], qy = qpts[3 * iq + 1], qz = qpts[3 * iq + 2];
-    // FP32 sums over the pairs of kPointFoldUnits units, folded into FP64
-    // totals: the same accumulation as the grid kernel's FP32 path, which
-    // bounds the rounding error of the long, cancelling pair sum
-    float br[SW], bi[SW];
-    double tr_[SW], ti[SW];
-    for (int s = 0; s < SW; ++s) {
-        br[s] = bi[s] = 0.f;
-        tr_[s] = ti[s] = 0.0;
-    }
-    for (int c = 0; c < n_units; ++c) {
-        const int npp = chunk_npp[c];
-        const int4* tc = terms + chunk_off[c];
-        for (int pair = 0; pair < kChunk; ++pair) {
-            float gr = 0.f, gi = 0.f;
-            for (int t = 0; t < npp; ++t) {
-                const int4 tr = tc[pair * npp + t];
-                if (!tr.w) continue;
-                const float2 vx = eval_row(rows[tr.x], qx);
-                const float2 vy = eval_row(rows[tr.y], qy);
-                const float2 vz = eval_row(rows[tr.z], qz);
-                const float wr = vx.x * vy.x - vx.y * vy.y, wi = vx.x * vy.y + vx.y * vy.x;
-                gr = fmaf(wr, vz.x, fmaf(-wi, vz.y, gr));
-                gi = fmaf(wr, vz.y, fmaf(wi, vz.x, gi));
-            }
-            const float* tp = Tp + (size_t)(c * kChunk + pair) * SW;
-            for (int s = 0; s < n_states; ++s) {
-                br[s] = fmaf(tp[s], gr, br[s]);
-                bi[s] = fmaf(tp[s], gi, bi[s]);
-            }
-        }
-        if ((c + 1) % kPointFoldUnits == 0 || c + 1 == n_units)
-            for (int s = 0; s < SW; ++s) {
-                tr_[s] += (double)br[s];
-                ti[s] += (double)bi[s];
-                br[s] = bi[s] = 0.f;
-            }
-    }
-    for (int s = 0; s < n_states; ++s) {
-        const double vr = tr_[s], vi = ti[s];
-        const size_t o = (size_t)s * nq + iq;
-        if (f) f[o] = make_float2((float)vr, (float)vi);
-        if (f2) f2[o] = (float)(vr * vr + vi * vi);
-    }
-}
-
 // ---------------------------------------------------------------- launchers
 
 hipError_t launch_vtable(const VRowDev* rows, int nrows, int vstride, const int n[3],
@@ -828,19 +768,6 @@ hipError_t launch_mirror(const int n[3], int nx_eval, int n_states, float2* f, f
     if (blocks > 16384) blocks = 16384;
     hipLaunchKernelGGL(mirror_kernel, dim3(blocks), dim3(256), 0, st, make_int3(n[0], n[1], n[2]), nx_eval,
                        n_states, f, f2);
-    return hipGetLastError();
-}
-
-hipError_t launch_points(int state_blocks, const VRowDev* rows, const int4* terms, const int* coff,
-                         const int* cnpp, int n_units, const float* Tp, const double* q, int nq,
-                         int n_states, float2* f, float* f2, hipStream_t st) {
-    const int blocks = (nq + 63) / 64;
-    if (state_blocks == 1)
-        hipLaunchKernelGGL((points_kernel<1>), dim3(blocks), dim3(64), 0, st, rows, terms, coff, cnpp,
-                           n_units, Tp, q, nq, n_states, f, f2);
-    else
-        hipLaunchKernelGGL((points_kernel<2>), dim3(blocks), dim3(64), 0, st, rows, terms, coff, cnpp,
-                           n_units, Tp, q, nq, n_states, f, f2);
     return hipGetLastError();
 }
 

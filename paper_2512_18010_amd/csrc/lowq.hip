@@ -147,44 +147,6 @@ __global__ void sep_final_kernel(const double2* __restrict__ part, int n, int np
     out[i] = a;
 }
 
-// |f_s(q)|^2 at points, all in FP64: f2[s * nq + i]
-__global__ __launch_bounds__(64) void points64_kernel(const VRowDev* __restrict__ rows, const int4* __restrict__ slots,
-                                                      const int* __restrict__ coff, const int* __restrict__ cnpp,
-                                                      int n_units, const double* __restrict__ tp64,
-                                                      const int* __restrict__ vcp, int ns,
-                                                      const double* __restrict__ qpts, int nq,
-                                                      double* __restrict__ f2) {
-    const int iq = blockIdx.x * blockDim.x + threadIdx.x;
-    if (iq >= nq) return;
-    const double qx = qpts[3 * iq], qy = qpts[3 * iq + 1], qz = qpts[3 * iq + 2];
-    double fr[kMaxStates], fi[kMaxStates];
-    for (int s = 0; s < kMaxStates; ++s) fr[s] = fi[s] = 0.0;
-    for (int c = 0; c < n_units; ++c) {
-        const int npp = cnpp[c];
-        for (int j = 0; j < kChunk; ++j) {
-            const int o = c * kChunk + j;
-            const int k = vcp[o];
-            if (k < 0) continue;
-            const int4* tc = slots + coff[c] + j * npp;
-            double2 g = make_double2(0.0, 0.0);
-            for (int t = 0; t < npp; ++t) {
-                const int4 tr = tc[t];
-                if (!tr.w) continue;
-                const double2 p =
-                    cmul(cmul(eval_row_fp64(rows[tr.x], qx), eval_row_fp64(rows[tr.y], qy)), eval_row_fp64(rows[tr.z], qz));
-                g.x += p.x;
-                g.y += p.y;
-            }
-            for (int s = 0; s < ns; ++s) {
-                const double t = tp64[(size_t)k * ns + s];
-                fr[s] = fma(t, g.x, fr[s]);
-                fi[s] = fma(t, g.y, fi[s]);
-            }
-        }
-    }
-    for (int s = 0; s < ns; ++s) f2[(size_t)s * nq + iq] = fr[s] * fr[s] + fi[s] * fi[s];
-}
-
 int blocks_for(long long n, int b) {
     long long g = (n + b - 1) / b;
     if (g < 1) g = 1;
@@ -237,15 +199,6 @@ hipError_t launch_dipole(const VRowDev* rows, int nrows, const int4* slots, cons
                        (const double2*)S, 1, G);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     return launch_sep_reduce(tp64, vcp, nv, ns, G, 4, G + 4 * (size_t)nv, out, st);
-}
-
-hipError_t launch_points64(const VRowDev* rows, const int4* slots, const int* coff, const int* cnpp, int n_units,
-                           const double* tp64, const int* vcp, int ns, const double* q, int nq, double* f2,
-                           hipStream_t st) {
-    if (ns < 1 || ns > kMaxStates) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(points64_kernel, dim3((nq + 63) / 64), dim3(64), 0, st, rows, slots, coff, cnpp, n_units,
-                       tp64, vcp, ns, q, nq, f2);
-    return hipGetLastError();
 }
 
 }  // namespace scff

@@ -32,9 +32,8 @@ int grid_class(const GridShape& g, int precision);
 hipError_t grid_desc(const GridShape& g, const float2* V, int nxr, int nyr, uint32_t ybase, const uint4* Bt, const KSteps& steps,
                      const int2* terms, const float* Tw, const double* sinv, const ChunkSplit& sp, const int n[3],
                      int nx_eval, int n_states, float2* f, float* f2, double2* part, GridDesc* d, long long* blocks);
-hipError_t launch_points(int state_blocks, const VRowDev* rows, const int4* terms, const int* coff,
-                         const int* cnpp, int n_chunks, const float* Tp, const double* q, int nq,
-                         int n_states, float2* f, float* f2, hipStream_t st);
+int points_split(int nq, int ns, int n_sp);
+hipError_t launch_points(const PointArgs& a, int n_split, hipStream_t st);
 hipError_t launch_separable(const VRowDev* rows, int nrows, const int4* slots, const int* coff, const int* cnpp,
                             int n_units, const double* tp64, const int* vcp, int ns, const double2* w, const int n[3],
                             const double qmin[3], const double dq[3], double2* S, double2* G, double2* out,
@@ -42,9 +41,6 @@ hipError_t launch_separable(const VRowDev* rows, int nrows, const int4* slots, c
 hipError_t launch_dipole(const VRowDev* rows, int nrows, const int4* slots, const int* coff, const int* cnpp,
                          int n_units, const double* tp64, const int* vcp, int ns, double2* S, double2* G,
                          double2* out, hipStream_t st);
-hipError_t launch_points64(const VRowDev* rows, const int4* slots, const int* coff, const int* cnpp, int n_units,
-                           const double* tp64, const int* vcp, int ns, const double* q, int nq, double* f2,
-                           hipStream_t st);
 }  // namespace scff
 
 using namespace scff;
@@ -109,6 +105,7 @@ struct scff_ctx {
     // FP64 low-momentum and separable work: weights / points, per-row and
     // per-pair values, per-state results
     DeviceBuffer d_lq_in, d_lq_S, d_lq_G, d_lq_out;
+    DeviceBuffer d_pt_part;   // partial sums of the point evaluation
     // FFT method: packed weights, complex arrays of state pairs, partial
     // sums, Parseval sums, device copy of the density for host output
     DeviceBuffer d_fft_A, d_fft_Z, d_fft_part, d_fft_out, d_phi;
@@ -344,6 +341,26 @@ int ensure_pairs(scff_ctx* c, hipStream_t st) {
     return SCFF_OK;
 }
 
+// f, |f|^2 and/or FP64 |f|^2 at nq points on the device, after ensure_prepared.
+// The partial sums of a split take device memory; where the budget does not
+// allow them there are fewer shares, in the end one (none).
+int run_points(scff_ctx* c, const double* q, int nq, float2* f, float* f2, double* f2d, hipStream_t st) {
+    const PrepInputs in = prep_inputs(c);
+    const PrepWork& w = c->prep;
+    int n = points_split(nq, c->n_states, in.n_sp);
+    for (; n > 1; n /= 2) {
+        const hipError_t e =
+            dev_reserve_raw(c, c->d_pt_part, (size_t)n * c->n_states * (size_t)nq * sizeof(double2));
+        if (e == hipSuccess) break;
+        if (e != hipErrorOutOfMemory) return hip_check(e, "points partial sums");
+        (void)hipGetLastError();
+    }
+    const PointArgs a{in.shells, in.sp, in.sp_cp, (const VRowDev*)w.rows_all.p, (const double*)w.wt.p,
+                      (const double*)w.small.p + 64, (const double*)w.tp64.p, q, in.n_sp, c->n_states, nq, f, f2, f2d,
+                      n > 1 ? (double2*)c->d_pt_part.p : nullptr};
+    return hip_check(launch_points(a, n, st), "points kernels");
+}
+
 int validate_grid(const scff_grid* g) {
     if (!g) return fail(SCFF_EINVAL, "grid is NULL");
     for (int a = 0; a < 3; ++a) {
@@ -515,7 +532,7 @@ int check_precision(int precision) {
 
 void free_all(scff_ctx* c) {
     for (DeviceBuffer* b : {&c->d_mol, &c->d_T, &c->d_vtab, &c->d_part, &c->d_f, &c->d_f2, &c->d_q,
-                            &c->d_lq_in, &c->d_lq_S, &c->d_lq_G, &c->d_lq_out, &c->d_fft_A, &c->d_fft_Z,
+                            &c->d_lq_in, &c->d_lq_S, &c->d_lq_G, &c->d_lq_out, &c->d_pt_part, &c->d_fft_A, &c->d_fft_Z,
                             &c->d_fft_part, &c->d_fft_out, &c->d_phi, &c->d_sph_tab, &c->d_sph_geo,
                             &c->d_sph_gdat, &c->d_sph_Yc, &c->d_sph_W, &c->d_sph_B, &c->d_sph_q, &c->d_sph_Q, &c->d_sph_R,
                             &c->d_sph_F, &c->d_sph_avg, &c->d_sph_J})
@@ -988,7 +1005,7 @@ int scff_eval_points(scff_ctx* c, int n_q, const double* q, int precision, float
     if ((rc = set_device(c))) return rc;
     hipStream_t st = (hipStream_t)hip_stream;
     if ((rc = order_after(c, st))) return rc;
-    if ((rc = ensure_pairs(c, st))) return rc;
+    if ((rc = ensure_prepared(c, st))) return rc;
     if ((rc = dev_reserve(c, c->d_q, (size_t)n_q * 3 * sizeof(double)))) return rc;
     if ((rc = hip_check(hipMemcpyAsync(c->d_q.p, q, (size_t)n_q * 3 * sizeof(double), hipMemcpyHostToDevice, st),
                         "upload q")))
@@ -1002,13 +1019,7 @@ int scff_eval_points(scff_ctx* c, int n_q, const double* q, int precision, float
         df = f ? (float2*)c->d_f.p : nullptr;
         df2 = f2 ? (float*)c->d_f2.p : nullptr;
     }
-    const PrepResult& p = c->pres;
-    rc = hip_check(launch_points(p.state_blocks, (const VRowDev*)c->prep.rows.p, (const int4*)c->prep.slots.p,
-                                 (const int*)c->prep.coff.p, (const int*)c->prep.cnpp.p, p.n_units,
-                                 (const float*)c->prep.tp32.p, (const double*)c->d_q.p, n_q, c->n_states,
-                                 df, df2, st),
-                   "points kernel launch");
-    if (rc) return rc;
+    if ((rc = run_points(c, (const double*)c->d_q.p, n_q, df, df2, nullptr, st))) return rc;
     if (!out_on_device && (rc = copy_out(df, f, df2, f2, nout, st))) return rc;
     // the host q array was copied asynchronously: finish before returning
     if ((rc = hip_check(hipStreamSynchronize(st), "stream sync"))) return rc;
@@ -1474,8 +1485,7 @@ int scff_dipole_fit(scff_ctx* c, double q_fit, const double* dE, double* coef, d
     if (!(q_fit > 0.0) || !std::isfinite(q_fit)) return fail(SCFF_EINVAL, "q_fit must be positive and finite");
     if (f0_fit && !dE) return fail(SCFF_EINVAL, "oscillator strengths need the transition energies dE");
     int rc;
-    if ((rc = prepare_sync(c))) return rc;
-    const PrepResult& p = c->pres;
+    if ((rc = set_device(c)) || (rc = order_after(c, nullptr)) || (rc = ensure_prepared(c, nullptr))) return rc;
     const int ns = c->n_states;
     // kFitShells radii q_k = q_fit k / kFitShells; on each, the product rule
     // of kFitTheta Gauss-Legendre nodes in cos(theta) and kFitPhi equally
@@ -1505,11 +1515,7 @@ int scff_dipole_fit(scff_ctx* c, double q_fit, const double* dE, double* coef, d
                                        nullptr),
                         "upload points")))
         return rc;
-    if ((rc = hip_check(launch_points64((const VRowDev*)c->prep.rows.p, (const int4*)c->prep.slots.p,
-                                        (const int*)c->prep.coff.p, (const int*)c->prep.cnpp.p, p.n_units,
-                                        (const double*)c->prep.tp64.p, (const int*)c->prep.vcp.p, ns,
-                                        (const double*)c->d_lq_in.p, nq, (double*)c->d_lq_out.p, nullptr),
-                        "points64 kernel")))
+    if ((rc = run_points(c, (const double*)c->d_lq_in.p, nq, nullptr, nullptr, (double*)c->d_lq_out.p, nullptr)))
         return rc;
     std::vector<double> f2((size_t)ns * nq);
     if ((rc = hip_check(hipMemcpyAsync(f2.data(), c->d_lq_out.p, f2.size() * sizeof(double), hipMemcpyDeviceToHost,
