@@ -281,21 +281,44 @@ SphIndex sph_index();
 std::vector<double> sph_theta_table(const SphIndex& ix);
 // Gaunt[(lam mu)][(l m)][j], (lmax + 1)^2 harmonics l m, real.
 std::vector<double> sph_gaunt_table(int lmax);
+// The same in real harmonics (S_lm = (-1)^m sqrt(2) Re Y_l^m, S_l,-m = (-1)^m
+// sqrt(2) Im Y_l^m), whose coefficients are real.
+std::vector<double> sph_theta_real(const SphIndex& ix);
 // One geometry (shell pair, primitive pair) of the spherical method.
 struct SphGeom {
-    int isp, pp;      // shell pair, primitive pair within it
+    int pp;           // primitive pair within the shell pair
     int ncp, npp;     // component pairs and primitive pairs of the shell pair
     int term0;        // first term of the shell pair
+    int lsum;         // l_A + l_B; geometries are sorted by it, largest first
 };
+// Geometries of l_A + l_B >= lam.
+struct SphExt {
+    int n[kSphMaxN + 1];
+};
+// Work item of the contraction: a row tile, a range of geometries, where the
+// tile's second 16 rows end, the index of its partial sum (-1: the tile's only
+// range).
+struct SphItem {
+    int tile, k0, k1, kb, part;
+};
+// Partial sums first[t] .. first[t + 1] - 1 belong to row tile t, t < n_split.
+struct SphSegs {
+    int n_split;
+    int first[kMaxStates * (kSphMaxN + 1) * (kSphMaxN + 1) / 32 + 2];
+};
+inline int sph_geo_stride(int n_geo) { return (n_geo + 15) & ~15; }
+void sph_plan(const SphExt& ext, int ns, int Lmax, int n_q, bool split, std::vector<SphItem>& items,
+              SphSegs& segs);
 hipError_t launch_sph_geom(const SphGeom* geo, int n_geo, const VRowDev* rows, const int4* trow, const double* tp64,
-                           int ns, const double2* theta, const int* uvw_idx, const int* nfirst, int n_nlm, int Lmax,
-                           double4* gdat, double2* Yc, double2* W, hipStream_t st);
-// Bq: workspace of nqb radii x ns 25 rows x n_geo double2 (the row operands
-// of one batch of radii).
-hipError_t launch_sph_q(const double4* gdat, const double2* Yc, const double2* W, int n_geo, int ns, int Lmax,
-                        const int* nlm_of, const double* qs, int n_q, double* J, double2* Bq, int nqb, double2* Q,
-                        hipStream_t st);
-hipError_t launch_sph_couple(const double2* Q, const double* gaunt, int ns, int lmax, int Lmax, int n_q, double2* R,
+                           int ns, const double* theta, const int* uvw_idx, const int* nfirst, int n_nlm, int Lmax,
+                           double4* gdat, double* Y, double* W, hipStream_t st);
+// Bq: workspace of nqb radii x ns 25 rows x sph_geo_stride(n_geo) (the row
+// operands of one batch of radii); P: partial sums, 32 rows x columns per
+// (part, radius).
+hipError_t launch_sph_q(const double4* gdat, const double* Y, const double* W, const SphExt& ext, int n_geo, int ns,
+                        int Lmax, const int* nlm_of, const double* qs, int n_q, double* J, double* Bq, int nqb,
+                        const SphItem* items, int n_items, const SphSegs& segs, double* Q, double* P, hipStream_t st);
+hipError_t launch_sph_couple(const double* Q, const double* gaunt, int ns, int lmax, int Lmax, int n_q, double2* R,
                              hipStream_t st);
 hipError_t launch_sph_grid(const double2* R, int ns, int lmax, int n_q, int n_theta, int n_phi, double2* F,
                            float2* f, float* f2, hipStream_t st);

@@ -113,7 +113,9 @@ struct scff_ctx {
     // data, harmonics and W tensor, radii, contraction, R tensor, Legendre stage,
     // angular average
     DeviceBuffer d_sph_tab, d_sph_geo, d_sph_gdat, d_sph_Yc, d_sph_W, d_sph_B, d_sph_q, d_sph_Q, d_sph_R, d_sph_F, d_sph_avg,
-        d_sph_J;
+        d_sph_J, d_sph_P, d_sph_items;
+    bool sph_geo_ready = false;   // d_sph_geo and sph_ext are the loaded molecule's
+    SphExt sph_ext{};
     int sph_lmax = -1;
     size_t sph_off[5] = {};   // theta, uvw index, nfirst, nlm_of, gaunt
     size_t lds_block = 65536;   // LDS bytes one workgroup may use
@@ -535,7 +537,7 @@ void free_all(scff_ctx* c) {
                             &c->d_lq_in, &c->d_lq_S, &c->d_lq_G, &c->d_lq_out, &c->d_pt_part, &c->d_fft_A, &c->d_fft_Z,
                             &c->d_fft_part, &c->d_fft_out, &c->d_phi, &c->d_sph_tab, &c->d_sph_geo,
                             &c->d_sph_gdat, &c->d_sph_Yc, &c->d_sph_W, &c->d_sph_B, &c->d_sph_q, &c->d_sph_Q, &c->d_sph_R,
-                            &c->d_sph_F, &c->d_sph_avg, &c->d_sph_J})
+                            &c->d_sph_F, &c->d_sph_avg, &c->d_sph_J, &c->d_sph_P, &c->d_sph_items})
         dev_free(c, *b);
     PrepWork& w = c->prep;
     for (DeviceBuffer* b : {&w.rows_all, &w.rowsum, &w.trow, &w.tbound, &w.wt, &w.cpmn, &w.tp64, &w.bsum,
@@ -714,6 +716,7 @@ int scff_load_molecule(scff_ctx* c, int n_atoms, const double* xyz, int n_shells
     const bool had_T = c->have_T;
     const int old_nbf = c->basis.nbf;
     c->have_mol = false;
+    c->sph_geo_ready = false;
     c->have_T = false;
     c->prepared = false;
     {
@@ -1273,7 +1276,7 @@ int scff_eval_spherical(scff_ctx* c, int lmax, int n_q, const double* q, int n_t
     const SphIndex ix = sph_index();
     const int n_nlm = (int)ix.nlm.size();
     if (c->sph_lmax != lmax) {
-        const std::vector<double> th = sph_theta_table(ix);
+        const std::vector<double> th = sph_theta_real(ix);
         const std::vector<double> ga = sph_gaunt_table(lmax);
         std::vector<int> uvw_idx(125, -1), nfirst(kSphMaxN + 2, 0), nlm_of((kSphMaxN + 1) * 25, -1);
         for (size_t a = 0; a < ix.uvw.size(); ++a)
@@ -1298,33 +1301,42 @@ int scff_eval_spherical(scff_ctx* c, int lmax, int n_q, const double* q, int n_t
         if ((rc = upload_sync(c, c->d_sph_tab, stage.data(), total))) return rc;
         c->sph_lmax = lmax;
     }
-    // geometries: every primitive pair of every shell pair
+    // geometries: every primitive pair of every shell pair, the largest l_A + l_B
+    // first (kept until another molecule is loaded)
     const Basis& b = c->basis;
     std::vector<SphGeom> geo;
-    for (int isp = 0; isp < b.n_sp; ++isp) {
-        const int sA = b.sp[4 * isp], sB = b.sp[4 * isp + 1], term0 = b.sp[4 * isp + 3];
-        const int lA = b.sh_l[sA], lB = b.sh_l[sB];
-        const int ncA = (lA + 1) * (lA + 2) / 2, ncB = (lB + 1) * (lB + 2) / 2;
-        const int ncp = sA == sB ? ncA * (ncA + 1) / 2 : ncA * ncB;
-        const int npp = b.sh_nprim[sA] * b.sh_nprim[sB];
-        for (int pp = 0; pp < npp; ++pp) geo.push_back(SphGeom{isp, pp, ncp, npp, term0});
+    if (!c->sph_geo_ready) {
+        c->sph_ext = SphExt{};
+        for (int ls = kSphMaxN; ls >= 0; --ls) {
+            for (int isp = 0; isp < b.n_sp; ++isp) {
+                const int sA = b.sp[4 * isp], sB = b.sp[4 * isp + 1], term0 = b.sp[4 * isp + 3];
+                const int lA = b.sh_l[sA], lB = b.sh_l[sB];
+                if (lA + lB != ls) continue;
+                const int ncA = (lA + 1) * (lA + 2) / 2, ncB = (lB + 1) * (lB + 2) / 2;
+                const int ncp = sA == sB ? ncA * (ncA + 1) / 2 : ncA * ncB;
+                const int npp = b.sh_nprim[sA] * b.sh_nprim[sB];
+                for (int pp = 0; pp < npp; ++pp) geo.push_back(SphGeom{pp, ncp, npp, term0, ls});
+            }
+            c->sph_ext.n[ls] = (int)geo.size();
+        }
     }
-    const int n_geo = (int)geo.size();
+    const SphExt ext = c->sph_ext;
+    const int n_geo = ext.n[0], gs = sph_geo_stride(n_geo);
     const size_t nrows = (size_t)ns * 25;
     // row operands of the contraction for a batch of radii: all of them when
     // they fit 4 GiB (an eighth of a set HBM budget), else as many as fit (a
     // batch of few radii would leave part of the device idle)
-    const size_t per_q = nrows * (size_t)std::max(n_geo, 1) * sizeof(double2);
+    const size_t per_q = nrows * (size_t)std::max(gs, 1) * sizeof(double);
     const size_t bcap = c->budget ? std::min((size_t)4 << 30, c->budget / 8) : (size_t)4 << 30;
     const int nqb = (int)std::max<size_t>(1, std::min<size_t>((size_t)n_q, bcap / per_q));
-    if ((rc = dev_reserve(c, c->d_sph_geo, geo.size() * sizeof(SphGeom))) ||
-        (rc = dev_reserve(c, c->d_sph_gdat, geo.size() * sizeof(double4))) ||
-        (rc = dev_reserve(c, c->d_sph_Yc, (size_t)n_geo * nL * sizeof(double2))) ||
-        (rc = dev_reserve(c, c->d_sph_W, (size_t)n_geo * n_nlm * ns * sizeof(double2))) ||
+    if ((rc = dev_reserve(c, c->d_sph_geo, (size_t)n_geo * sizeof(SphGeom))) ||
+        (rc = dev_reserve(c, c->d_sph_gdat, (size_t)n_geo * sizeof(double4))) ||
+        (rc = dev_reserve(c, c->d_sph_Yc, (size_t)n_geo * nL * sizeof(double))) ||
+        (rc = dev_reserve(c, c->d_sph_W, (size_t)n_geo * n_nlm * ns * sizeof(double))) ||
         (rc = dev_reserve(c, c->d_sph_B, (size_t)nqb * per_q)) ||
         (rc = dev_reserve(c, c->d_sph_q, (size_t)n_q * sizeof(double))) ||
-        (rc = dev_reserve(c, c->d_sph_Q, (size_t)n_q * nrows * nL * sizeof(double2))) ||
-        (rc = dev_reserve(c, c->d_sph_J, (size_t)n_q * (Lmax + 2) * n_geo * sizeof(double))) ||
+        (rc = dev_reserve(c, c->d_sph_Q, (size_t)n_q * nrows * nL * sizeof(double))) ||
+        (rc = dev_reserve(c, c->d_sph_J, (size_t)n_q * (Lmax + 2) * gs * sizeof(double))) ||
         (rc = dev_reserve(c, c->d_sph_R, (size_t)ns * n_q * nl * sizeof(double2))))
         return rc;
     if ((f || f2) && (rc = dev_reserve(c, c->d_sph_F, (size_t)ns * n_q * n_theta * (2 * lmax + 1) * sizeof(double2))))
@@ -1344,28 +1356,53 @@ int scff_eval_spherical(scff_ctx* c, int lmax, int n_q, const double* q, int n_t
     } else if (R) {
         dR = (double2*)R;
     }
+    // the contraction's items, and the partial sums of its segments where they fit
+    // (at most as large as Q; last, so that they never take what the others need)
+    std::vector<SphItem> items;
+    SphSegs segs;
+    sph_plan(ext, ns, Lmax, n_q, true, items, segs);
+    if ((rc = dev_reserve(c, c->d_sph_items, items.size() * sizeof(SphItem)))) return rc;
+    const size_t pbytes = (size_t)segs.first[segs.n_split] * n_q * 32 * nL * sizeof(double);
+    if (segs.n_split) {
+        const hipError_t e = pbytes > kMaxPartBytes ? hipErrorOutOfMemory : dev_reserve_raw(c, c->d_sph_P, pbytes);
+        if (e == hipErrorOutOfMemory) {
+            (void)hipGetLastError();
+            sph_plan(ext, ns, Lmax, n_q, false, items, segs);
+        } else if (e != hipSuccess) {
+            return hip_check(e, "spherical partial sums");
+        }
+    }
     const unsigned char* tb = (const unsigned char*)c->d_sph_tab.p;
     c->sph_recorded = false;
-    if ((rc = hip_check(hipMemcpyAsync(c->d_sph_geo.p, geo.data(), geo.size() * sizeof(SphGeom),
-                                       hipMemcpyHostToDevice, st), "upload geometries")) ||
-        (rc = hip_check(hipMemcpyAsync(c->d_sph_q.p, q, (size_t)n_q * sizeof(double), hipMemcpyHostToDevice, st),
-                        "upload radii")))
+    if (!c->sph_geo_ready) {
+        if ((rc = hip_check(hipMemcpyAsync(c->d_sph_geo.p, geo.data(), geo.size() * sizeof(SphGeom),
+                                           hipMemcpyHostToDevice, st), "upload geometries")) ||
+            (rc = hip_check(hipStreamSynchronize(st), "stream sync")))
+            return rc;
+        c->sph_geo_ready = true;
+    }
+    if ((rc = hip_check(hipMemcpyAsync(c->d_sph_q.p, q, (size_t)n_q * sizeof(double), hipMemcpyHostToDevice, st),
+                        "upload radii")) ||
+        (rc = hip_check(hipMemcpyAsync(c->d_sph_items.p, items.data(), items.size() * sizeof(SphItem),
+                                       hipMemcpyHostToDevice, st), "upload work items")))
         return rc;
     if ((rc = record(c, EV_SPH0, st))) return rc;
     if ((rc = hip_check(launch_sph_geom((const SphGeom*)c->d_sph_geo.p, n_geo, (const VRowDev*)c->prep.rows_all.p,
                                         (const int4*)c->prep.trow.p, (const double*)c->prep.tp64.p, ns,
-                                        (const double2*)(tb + c->sph_off[0]), (const int*)(tb + c->sph_off[1]),
+                                        (const double*)(tb + c->sph_off[0]), (const int*)(tb + c->sph_off[1]),
                                         (const int*)(tb + c->sph_off[2]), n_nlm, Lmax, (double4*)c->d_sph_gdat.p,
-                                        (double2*)c->d_sph_Yc.p, (double2*)c->d_sph_W.p, st),
+                                        (double*)c->d_sph_Yc.p, (double*)c->d_sph_W.p, st),
                         "spherical geometry kernel")) ||
         (rc = record(c, EV_SPH1, st)) ||
-        (rc = hip_check(launch_sph_q((const double4*)c->d_sph_gdat.p, (const double2*)c->d_sph_Yc.p,
-                                     (const double2*)c->d_sph_W.p, n_geo, ns, Lmax, (const int*)(tb + c->sph_off[3]),
-                                     (const double*)c->d_sph_q.p, n_q, (double*)c->d_sph_J.p,
-                                     (double2*)c->d_sph_B.p, nqb, (double2*)c->d_sph_Q.p, st),
+        (rc = hip_check(launch_sph_q((const double4*)c->d_sph_gdat.p, (const double*)c->d_sph_Yc.p,
+                                     (const double*)c->d_sph_W.p, ext, n_geo, ns, Lmax,
+                                     (const int*)(tb + c->sph_off[3]), (const double*)c->d_sph_q.p, n_q,
+                                     (double*)c->d_sph_J.p, (double*)c->d_sph_B.p, nqb,
+                                     (const SphItem*)c->d_sph_items.p, (int)items.size(), segs,
+                                     (double*)c->d_sph_Q.p, (double*)c->d_sph_P.p, st),
                         "spherical contraction kernel")) ||
         (rc = record(c, EV_SPH2, st)) ||
-        (rc = hip_check(launch_sph_couple((const double2*)c->d_sph_Q.p, (const double*)(tb + c->sph_off[4]), ns, lmax,
+        (rc = hip_check(launch_sph_couple((const double*)c->d_sph_Q.p, (const double*)(tb + c->sph_off[4]), ns, lmax,
                                           Lmax, n_q, dR, st),
                         "spherical coupling kernel")))
         return rc;

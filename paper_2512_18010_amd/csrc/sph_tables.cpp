@@ -143,6 +143,21 @@ std::vector<double> sph_theta_table(const SphIndex& ix) {
     return out;
 }
 
+std::vector<double> sph_theta_real(const SphIndex& ix) {
+    // sum_mu c_mu Y^mu with c_-mu = (-1)^mu c_mu*: coefficient c_0 of S_0, and for
+    // mu > 0 sqrt(2) (-1)^mu Re c_mu of S_mu, -sqrt(2) (-1)^mu Im c_mu of S_-mu
+    const std::vector<double> th = sph_theta_table(ix);
+    const size_t nu = ix.uvw.size(), nn = ix.nlm.size();
+    std::vector<double> out(nu * nn);
+    for (size_t b = 0; b < nn; ++b) {
+        const int mu = ix.nlm[b][2], am = std::abs(mu);
+        const size_t bp = b - mu + am;   // (n, lam, |mu|)
+        const double k = mu == 0 ? 1.0 : std::sqrt(2.0) * (am & 1 ? -1.0 : 1.0) * (mu > 0 ? 1.0 : -1.0);
+        for (size_t a = 0; a < nu; ++a) out[a * nn + b] = k * th[2 * (a * nn + bp) + (mu < 0 ? 1 : 0)];
+    }
+    return out;
+}
+
 std::vector<double> sph_gaunt_table(int lmax) {
     // G[lm'][lm][j] = int Y_lam^mu Y_L^M Y_l^m* dOmega with L = |l - lam| + 2 j,
     // M = m - mu; real.  Degrees up to kSphMaxN + (lmax + kSphMaxN) + lmax.
