@@ -255,11 +255,12 @@ int fft_density_cb(int nbf_pad, size_t lds_limit);
 // precision: SCFF_FP32 (FP32 weights, Ap holds ns RB KS 64 floats) or
 // SCFF_BF16X3 (split-BF16 weights of 4 functions per lane, ns RB RB 64 uint4:
 // the same bytes).
-hipError_t launch_fft_pack(int precision, const double* T, const double* cnorm, int nbf, int ns, int RB, int KS,
+size_t fft_pack_bytes(int precision, int nbf_pad, int ns);   // of the array that launch_fft_pack fills
+hipError_t launch_fft_pack(int precision, const double* T, const double* cnorm, int nbf, int nbf_pad, int ns,
                            double spin, void* Ap, hipStream_t st);
-hipError_t launch_fft_density(int precision, const FftMol& m, const void* Ap, int nbf_pad, int ns, int RB, int KS,
-                              const int n[3], const double x0[3], const double h[3], float* Z, float* phi,
-                              double* psum, size_t lds_limit, long long* n_part, hipStream_t st);
+hipError_t launch_fft_density(int precision, const FftMol& m, const void* Ap, int nbf_pad, int ns, const int n[3],
+                              const double x0[3], const double h[3], float* Z, float* phi, double* psum,
+                              size_t lds_limit, long long* n_part, hipStream_t st);
 hipError_t launch_fft_lines(float2* Z, int nb, const int n[3], hipStream_t st);
 hipError_t launch_fft_finish(const float2* Z, const int n[3], int ns, double vpix, const double u[3], float2* f,
                              float* f2, double* psum, long long* n_part, hipStream_t st);

@@ -1,15 +1,16 @@
 // The FFT method (paper Sec. 3 and Sec. 5.2) on the device:
 //
-//   1. fft_pack_kernel /    transition weights as MFMA A operands:
-//      fft_pack_bf_kernel   s_f c_mu c_nu (T_{mu nu} + T_{nu mu}) per unordered
-//                           component pair (T_{mu mu} on the diagonal), FP32
-//                           or split into BF16 halves;
+//   1. fft_rowmax_kernel,   transition weights as MFMA A operands:
+//      fft_pack_kernel      s_f c_mu c_nu (T_{mu nu} + T_{nu mu}) per unordered
+//                           component pair (T_{mu mu} on the diagonal), split
+//                           into f16 halves (FP32 precision, rows scaled by
+//                           powers of two) or BF16 halves;
 //   2. fft_density_kernel   the transition density (eq. PhiTDM, AO form)
 //                             Phi_s(r) = sum_mu phi_mu(r) sum_{nu >= mu} Tp_s(mu,nu) phi_nu(r)
 //                           on a tile of up to 64 real-space points: the AO
-//                           values of the tile are formed in LDS (FP64 and
-//                           rounded once, or FP32 and split for the split-BF16
-//                           contraction), Y_s(mu, r) = sum_nu Tp_s(mu,nu) phi_nu(r)
+//                           values of the tile are formed in LDS (FP64,
+//                           rounded once, scaled per point and split into f16
+//                           halves; or FP32 and split into BF16 halves), Y_s(mu, r) = sum_nu Tp_s(mu,nu) phi_nu(r)
 //                           runs on the matrix cores (rows mu of one state,
 //                           k = nu, columns = points), and sum_mu phi_mu Y_s(mu)
 //                           is folded per 16 rows.  Two states share one
@@ -35,6 +36,8 @@ namespace scff {
 typedef float fft_floatx4 __attribute__((ext_vector_type(4)));
 typedef float fft_floatx2 __attribute__((ext_vector_type(2)));
 typedef unsigned int fft_uintx4 __attribute__((ext_vector_type(4)));
+typedef _Float16 fft_halfx2 __attribute__((ext_vector_type(2)));
+typedef _Float16 fft_halfx8 __attribute__((ext_vector_type(8)));
 typedef __bf16 fft_bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 fft_bf16x8 __attribute__((ext_vector_type(8)));
 
@@ -49,7 +52,18 @@ __device__ inline void fft_split(float v, uint32_t& hi, uint32_t& lo) {
     hi = __builtin_bit_cast(uint32_t, h);
     lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(fft_floatx2{r, 0.f}, fft_bf16x2));
 }
-// The same in one dword: hi in the low half, lo in the high half.
+// Split-f16 of one value, |v| < 2^16: hi = RNE(v), lo = RNE(v - hi) in one
+// dword, hi in the low half; 22 significant bits and more down to 2^-25 absolute.
+__device__ inline uint32_t fft_split_f16(float v) {
+    const _Float16 h = (_Float16)v;
+    return __builtin_bit_cast(uint32_t, fft_halfx2{h, (_Float16)(v - (float)h)});
+}
+// (hi, lo) of four values as the words (hi_0 hi_1, hi_2 hi_3, lo_0 lo_1, lo_2 lo_3)
+__device__ inline uint4 fft_halves(const uint32_t (&w)[4]) {
+    return make_uint4((w[0] & 0xffffu) | (w[1] << 16), (w[2] & 0xffffu) | (w[3] << 16),
+                      (w[0] >> 16) | (w[1] & 0xffff0000u), (w[2] >> 16) | (w[3] & 0xffff0000u));
+}
+// The BF16 split in one dword: hi in the low half, lo in the high half.
 __device__ inline uint32_t fft_split(float v) {
     uint32_t hi, lo;
     fft_split(v, hi, lo);
@@ -65,59 +79,69 @@ constexpr double kExpCut = 103.0;
 
 namespace {
 
-__global__ void fft_pack_kernel(const double* __restrict__ T, const double* __restrict__ cnorm, int nbf, int ns,
-                                int RB, int KS, double spin, float* __restrict__ Ap) {
-    const long long total = (long long)ns * RB * KS * 64;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
-         i += (long long)gridDim.x * blockDim.x) {
-        const int lane = (int)(i & 63);
-        long long r = i >> 6;
-        const int ks = (int)(r % KS);
-        r /= KS;
-        const int rb = (int)(r % RB);
-        const int s = (int)(r / RB);
-        const int mu = 16 * rb + (lane & 15), nu = 4 * ks + (lane >> 4);
-        double v = 0.0;
-        if (mu < nbf && nu < nbf && mu <= nu) {
-            const double* Ts = T + (size_t)s * nbf * nbf;
-            const double t = mu == nu ? Ts[(size_t)mu * nbf + mu] : Ts[(size_t)mu * nbf + nu] + Ts[(size_t)nu * nbf + mu];
-            v = spin * cnorm[mu] * cnorm[nu] * t;
-        }
-        Ap[i] = (float)v;
-    }
+__device__ __forceinline__ double fft_weight(const double* Ts, const double* cnorm, int nbf, double spin, int mu,
+                                             int nu) {
+    const double t = mu == nu ? Ts[(size_t)mu * nbf + mu] : Ts[(size_t)mu * nbf + nu] + Ts[(size_t)nu * nbf + mu];
+    return spin * cnorm[mu] * cnorm[nu] * t;
 }
 
-// Split-BF16 A operands for the same weights.  Function group g holds
-// nu = 16 g .. 16 g + 15; lane (row = lane % 16, kk = lane / 16) carries
-// nu_j = 16 g + 4 kk + j, j < 4, as the words (hi(nu_0) | hi(nu_1) << 16,
-// hi(nu_2) | hi(nu_3) << 16, lo(nu_0) | lo(nu_1) << 16, lo(nu_2) | lo(nu_3) << 16)
-// in Ap[((s RB + rb) RB + g) 64 + lane].
-__global__ void fft_pack_bf_kernel(const double* __restrict__ T, const double* __restrict__ cnorm, int nbf, int ns,
-                                   int RB, double spin, uint4* __restrict__ Ap) {
-    const long long total = (long long)ns * RB * RB * 64;
+// First function group of row block rb in the A operands of a state (groups
+// rb .. RB - 1 of every row block).
+__device__ __forceinline__ int fft_group0(int rb, int RB) { return rb * RB - rb * (rb - 1) / 2; }
+
+// Powers of two of the split-f16 rows: a with max_nu |W(mu, nu)| 2^a < 2^15, so
+// that the halves keep their bits.  One wave per (state, row).
+__global__ __launch_bounds__(256) void fft_rowmax_kernel(const double* __restrict__ T, const double* __restrict__ cnorm,
+                                                         int nbf, int nbf_pad, int ns, double spin,
+                                                         signed char* __restrict__ ra) {
+    const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (i >= ns * nbf_pad) return;
+    const int s = i / nbf_pad, mu = i - s * nbf_pad;
+    double a = 0.0;
+    if (mu < nbf)
+        for (int nu = mu + lane; nu < nbf; nu += 64)
+            a = fmax(a, fabs(fft_weight(T + (size_t)s * nbf * nbf, cnorm, nbf, spin, mu, nu)));
+    for (int h = 32; h > 0; h >>= 1) a = fmax(a, __shfl_xor(a, h));
+    if (lane == 0) ra[i] = (signed char)(a > 0.0 && a < 1e300 ? max(-100, min(100, 14 - ilogb(a))) : 0);
+}
+
+// A operands.  Function group g holds nu = 16 g .. 16 g + 15; lane (row = lane %
+// 16, kk = lane / 16) carries nu_j = 16 g + 4 kk + j, j < 4, as fft_halves words
+// in Ap[((s groups + group0(rb) + g - rb) 64 + lane], g >= rb.  f16 halves: W is
+// the same at every point, so what the halves drop (up to 2^-23 W) would stay in
+// the transform; a third half per weight, two words per lane in Ar, takes it.
+template <bool BF>
+__global__ void fft_pack_kernel(const double* __restrict__ T, const double* __restrict__ cnorm, int nbf, int ns, int RB,
+                                double spin, const signed char* __restrict__ ra, uint4* __restrict__ Ap,
+                                uint2* __restrict__ Ar) {
+    const int per = RB * (RB + 1) / 2;
+    const long long total = (long long)ns * per * 64;
     for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
          i += (long long)gridDim.x * blockDim.x) {
         const int lane = (int)(i & 63);
-        long long r = i >> 6;
-        const int g = (int)(r % RB);
-        r /= RB;
-        const int rb = (int)(r % RB);
-        const int s = (int)(r / RB);
+        const long long r = i >> 6;
+        const int s = (int)(r / per), k = (int)(r - (long long)s * per);
+        int rb = 0;
+        while (fft_group0(rb + 1, RB) <= k) ++rb;
+        const int g = rb + k - fft_group0(rb, RB);
         const int mu = 16 * rb + (lane & 15);
         const double* Ts = T + (size_t)s * nbf * nbf;
-        uint32_t w[4];
+        uint32_t w[4], t[4];
         for (int j = 0; j < 4; ++j) {
             const int nu = 16 * g + 4 * (lane >> 4) + j;
             double v = 0.0;
-            if (mu < nbf && nu < nbf && mu <= nu) {
-                const double tt =
-                    mu == nu ? Ts[(size_t)mu * nbf + mu] : Ts[(size_t)mu * nbf + nu] + Ts[(size_t)nu * nbf + mu];
-                v = spin * cnorm[mu] * cnorm[nu] * tt;
+            if (mu < nbf && nu < nbf && mu <= nu) v = fft_weight(Ts, cnorm, nbf, spin, mu, nu);
+            if (BF) {
+                w[j] = fft_split((float)v);
+            } else {
+                v = ldexp(v, ra[s * 16 * RB + mu]);
+                const _Float16 h = (_Float16)(float)v, l = (_Float16)(float)(v - (double)h);
+                w[j] = __builtin_bit_cast(uint32_t, fft_halfx2{h, l});
+                t[j] = __builtin_bit_cast(unsigned short, (_Float16)(float)(v - (double)h - (double)l));
             }
-            w[j] = fft_split((float)v);
         }
-        Ap[i] = make_uint4((w[0] & 0xffffu) | (w[1] << 16), (w[2] & 0xffffu) | (w[3] << 16),
-                           (w[0] >> 16) | (w[1] & 0xffff0000u), (w[2] >> 16) | (w[3] & 0xffff0000u));
+        Ap[i] = fft_halves(w);
+        if (!BF) Ar[i] = make_uint2(t[0] | (t[1] << 16), t[2] | (t[3] << 16));
     }
 }
 
@@ -202,20 +226,27 @@ __host__ __device__ constexpr size_t fft_lds_bytes(int nbf_pad, int cb) {
 //
 // AO phase: a lane evaluates one shell at one point (64 / NP shells per wave
 // step; with NP = 64 every lane of a wave takes the same shell, so its data
-// are scalar loads), FP64, rounded into the LDS block:
-//   FP32  phi(r, c) at float index r NP + col CB + cb, so that a lane reads the
-//         CB values of its column in one ds_read (b32 / b64 / b128) and a
-//         quarter wave reads one contiguous run (no bank conflicts);
-//   BF    split halves as the B operands of v_mfma_f32_16x16x32_bf16: the
-//         uint4 entry ((g 4 + kk) CB + cb) 16 + col holds rows r_j = 16 g +
-//         4 kk + j (j < 4) of column c as (hi(r_0) | hi(r_1) << 16, hi(r_2) |
-//         hi(r_3) << 16, lo(r_0) | lo(r_1) << 16, lo(r_2) | lo(r_3) << 16).
-//         A lane (kk, col) takes it as the 8 k-items of one MFMA (no operand
-//         copies), and the same entry holds the rows 16 rb + 4 kk + i that
-//         the lane folds after row block rb.
-// Split-BF16 products per function group and column block: MFMA 1 with
-// A = (W hi, W hi) gives hi*hi + hi*lo over the items, MFMA 2 with
-// A = (W lo, 0) gives lo*hi.
+// are scalar loads).  The values end in LDS as split halves, the B operands of a
+// 16x16x32 matrix instruction: the uint4 entry ((g 4 + kk) CB + cb) 16 + col holds
+// rows r_j = 16 g + 4 kk + j (j < 4) of column c as (hi(r_0) | hi(r_1) << 16,
+// hi(r_2) | hi(r_3) << 16, lo(r_0) | lo(r_1) << 16, lo(r_2) | lo(r_3) << 16).  A lane
+// (kk, col) takes it as the 8 k-items of one instruction (no operand copies), and
+// the same entry holds the rows 16 rb + 4 kk + i that the lane folds after row
+// block rb.  BF: BF16 halves of the FP32 value, written at once.  FP32
+// precision: FP64 values rounded to FP32 into the entry's four words; then, with
+// every point's largest value known, f16 halves of value 2^e(point) with |value|
+// 2^e < 2^15, in place (far from the molecule all values are small: the scale
+// keeps their bits).
+// Products per function group and column block: instruction 1 with A = (W hi,
+// W hi) gives hi*hi + hi*lo over the items, instruction 2 with A = (W lo, W lo)
+// lo*hi + lo*lo (BF: (W lo, 0), lo*hi only); FP32 precision has a third with A =
+// (W's third half, 0).
+//
+// FP32 precision used FP32 matrix instructions, 2.7x the cycles of the split
+// products: 8.75 ms for 190 functions, 12 states on 128^3 points, 74 % of it in the
+// matrix cores; 4.94 ms now, bound by the vector unit (AO values and fold, FP64) and
+// the matrix cores in equal parts, which overlap little at three waves per SIMD
+// (172 registers, two waves: 5.04 ms without the third instruction).
 //
 // Contraction: wave w takes row blocks rb of 16 functions in a snake order
 // (0 1 2 3 3 2 1 0 ...), which evens out the triangle's rows; per row block
@@ -225,8 +256,9 @@ __host__ __device__ constexpr size_t fft_lds_bytes(int nbf_pad, int cb) {
 // partial densities of a group of states are summed through LDS and wave 0
 // writes the tile.
 template <bool BF, int CB>
-__global__ __launch_bounds__(256) void fft_density_kernel(FftMol m, const void* __restrict__ Av, int nbf_pad, int ns,
-                                                          int RB, int KS, int3 n, double3 x0, double3 h,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void fft_density_kernel(FftMol m, const uint4* __restrict__ Av,
+                                                          const uint2* __restrict__ Ar, const signed char* __restrict__ ra, int nbf_pad, int ns, int RB,
+                                                          int3 n, double3 x0, double3 h,
                                                           long long npts, float* __restrict__ Z,
                                                           float* __restrict__ phi_out, double* __restrict__ psum) {
     extern __shared__ __align__(16) float fft_lds[];
@@ -236,14 +268,16 @@ __global__ __launch_bounds__(256) void fft_density_kernel(FftMol m, const void* 
     // wave-uniform: the row-block loop and the A-operand addresses stay scalar
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const long long p0 = (long long)blockIdx.x * NP;
-    float* ph = fft_lds;
     uint32_t* pu = reinterpret_cast<uint32_t*>(fft_lds);
     unsigned short* ps16 = reinterpret_cast<unsigned short*>(fft_lds);
     double* red = reinterpret_cast<double*>(fft_lds + (size_t)nbf_pad * NP);
 
+    uint32_t* const cmax = reinterpret_cast<uint32_t*>(red);   // [NP], until the exponents are known
     for (int i = tid; i < nbf_pad * NP; i += 256) pu[i] = 0u;
+    if (tid < NP) cmax[tid] = 0u;
     __syncthreads();
     {
+        float vmax = 0.f;   // of the lane's point
         constexpr int SPI = 64 / NP;   // shells per wave step
         const int p = lane % NP;
         const long long g = p0 + p;
@@ -253,138 +287,150 @@ __global__ __launch_bounds__(256) void fft_density_kernel(FftMol m, const void* 
         const double x = x0.x + ix * h.x, y = x0.y + iy * h.y, z = x0.z + iz * h.z;
         const int col = p & 15, cb = p >> 4;
         auto put = [&](int r, auto v) {
+            const int i = r & 3;
+            const int e0 = ((((r >> 4) * 4 + ((r >> 2) & 3)) * CB + cb) * 16 + col) * 4;   // dword of the entry
             if constexpr (BF) {
                 uint32_t hi, lo;
                 fft_split((float)v, hi, lo);
-                const int i = r & 3;
-                // dword of the hi half; the lo half is two dwords on
-                const int wd = ((((r >> 4) * 4 + ((r >> 2) & 3)) * CB + cb) * 16 + col) * 4 + (i >> 1);
+                // the lo half is two dwords after the hi half
+                const int wd = e0 + (i >> 1);
                 ps16[2 * wd + (i & 1)] = (unsigned short)hi;
                 ps16[2 * wd + 4 + (i & 1)] = (unsigned short)lo;
             } else {
-                ph[r * NP + col * CB + cb] = (float)v;
+                const float w = (float)v;
+                vmax = fmaxf(vmax, fabsf(w));
+                pu[e0 + i] = __float_as_uint(w);
             }
         };
         for (int sh0 = wave * SPI; sh0 < m.n_shells; sh0 += 4 * SPI) {
             const int sh = sh0 + lane / NP;
             if (sh < m.n_shells && g < npts) shell_values<std::conditional_t<BF, float, double>>(m, sh, x, y, z, put);
         }
+        if constexpr (!BF) atomicMax(&cmax[p], __float_as_uint(vmax));
+    }
+    // exponent of column c: |phi| 2^e < 2^15 (values that overflow FP32 stay as they are)
+    auto col_exp = [&](int c) {
+        const int b = (int)(cmax[c] >> 23);
+        return b == 0 || b == 255 ? (b ? 0 : 120) : min(120, 14 + 127 - b);
+    };
+    int pe = 0;   // exponent of column `lane` (the store's)
+    if constexpr (!BF) {
+        __syncthreads();
+        if (lane < NP) pe = col_exp(lane);
+        for (int i = tid; i < nbf_pad * NP / 4; i += 256) {
+            const int e = col_exp((i / 16 % CB) * 16 + i % 16);
+            uint4* const o = reinterpret_cast<uint4*>(pu) + i;
+            const uint4 u = *o;
+            const uint32_t w[4] = {fft_split_f16(__builtin_ldexpf(__uint_as_float(u.x), e)),
+                                   fft_split_f16(__builtin_ldexpf(__uint_as_float(u.y), e)),
+                                   fft_split_f16(__builtin_ldexpf(__uint_as_float(u.z), e)),
+                                   fft_split_f16(__builtin_ldexpf(__uint_as_float(u.w), e))};
+            *o = fft_halves(w);
+        }
     }
 
     const int kk = lane >> 4, col = lane & 15;
     // the AO values of rows 16 rb + 4 kk + i (i < 4) at this lane's CB columns,
-    // v[i][cb] (in the split form hi + lo, summed in FP32: within 2^-24 of the
-    // split value, far below the split's own 2^-16)
+    // v[i][cb]: hi + lo, summed in FP32 (exact for the f16 halves; for the BF16
+    // halves within 2^-24 of the split value, far below the split's own 2^-16)
     using FV = std::conditional_t<BF, float, double>;
     auto phi_rows = [&](int rb, FV (&v)[4][CB]) {
-        if constexpr (BF) {
 #pragma unroll
-            for (int q = 0; q < CB; ++q) {
-                const uint4 e = reinterpret_cast<const uint4*>(pu)[((rb * 4 + kk) * CB + q) * 16 + col];
+        for (int q = 0; q < CB; ++q) {
+            const uint4 e = reinterpret_cast<const uint4*>(pu)[((rb * 4 + kk) * CB + q) * 16 + col];
+            if constexpr (BF) {
                 v[0][q] = __uint_as_float(e.x << 16) + __uint_as_float(e.z << 16);
                 v[1][q] = __uint_as_float(e.x & 0xffff0000u) + __uint_as_float(e.z & 0xffff0000u);
                 v[2][q] = __uint_as_float(e.y << 16) + __uint_as_float(e.w << 16);
                 v[3][q] = __uint_as_float(e.y & 0xffff0000u) + __uint_as_float(e.w & 0xffff0000u);
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float* q = ph + (16 * rb + 4 * kk + i) * NP + col * CB;
-                if constexpr (CB == 1) {
-                    v[i][0] = q[0];
-                } else if constexpr (CB == 2) {
-                    const float2 e = *reinterpret_cast<const float2*>(q);
-                    v[i][0] = e.x;
-                    v[i][1] = e.y;
-                } else {
-                    const float4 e = *reinterpret_cast<const float4*>(q);
-                    v[i][0] = e.x;
-                    v[i][1] = e.y;
-                    v[i][2] = e.z;
-                    v[i][3] = e.w;
-                }
+            } else {
+                const fft_halfx2 h0 = __builtin_bit_cast(fft_halfx2, e.x), h1 = __builtin_bit_cast(fft_halfx2, e.y);
+                const fft_halfx2 l0 = __builtin_bit_cast(fft_halfx2, e.z), l1 = __builtin_bit_cast(fft_halfx2, e.w);
+                v[0][q] = (float)h0[0] + (float)l0[0];
+                v[1][q] = (float)h0[1] + (float)l0[1];
+                v[2][q] = (float)h1[0] + (float)l1[0];
+                v[3][q] = (float)h1[1] + (float)l1[1];
             }
         }
     };
     __syncthreads();
 
-    // one k-step (FP32: functions 4k .. 4k+3) or k-group (BF: 8t .. 8t+7) of
-    // row block rb for all CB column blocks
-    auto kstep = [&](auto a, int k, int par, fft_floatx4 (&c)[NCH]) {
-        if constexpr (BF) {
-            const fft_bf16x8 A1 = __builtin_bit_cast(fft_bf16x8, fft_uintx4{a.x, a.y, a.x, a.y});
-            const fft_bf16x8 A2 = __builtin_bit_cast(fft_bf16x8, fft_uintx4{a.z, a.w, 0u, 0u});
-            fft_bf16x8 B[CB];
+    // function group k (functions 16 k .. 16 k + 15) of row block rb for all CB
+    // column blocks; the two products of a column block go to different chains
+    // (CB = 1) or are CB instructions apart
+    struct AOp {
+        uint4 a;
+        uint2 r;   // third halves (not BF)
+    };
+    auto kstep = [&](const AOp& o, int k, fft_floatx4 (&c)[NCH]) {
+        const uint4 a = o.a;
+        fft_uintx4 B[CB];
 #pragma unroll
-            for (int q = 0; q < CB; ++q) {
-                const uint4 e = reinterpret_cast<const uint4*>(pu)[((k * 4 + kk) * CB + q) * 16 + col];
-                B[q] = __builtin_bit_cast(fft_bf16x8, fft_uintx4{e.x, e.y, e.z, e.w});
-            }
-            // the two products of a column block go to different chains (CB = 1)
-            // or are CB instructions apart
-#pragma unroll
-            for (int q = 0; q < CB; ++q) c[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A1, B[q], c[q], 0, 0, 0);
-#pragma unroll
-            for (int q = 0; q < CB; ++q)
-                c[CB == 1 ? 1 : q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A2, B[q], c[CB == 1 ? 1 : q], 0, 0, 0);
-        } else {
-            const float* q = ph + (4 * k + kk) * NP + col * CB;
-            if constexpr (CB == 1) {
-                c[par] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, q[0], c[par], 0, 0, 0);
-            } else if constexpr (CB == 2) {
-                const float2 e = *reinterpret_cast<const float2*>(q);
-                c[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, e.x, c[0], 0, 0, 0);
-                c[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, e.y, c[1], 0, 0, 0);
-            } else {
-                const float4 e = *reinterpret_cast<const float4*>(q);
-                c[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, e.x, c[0], 0, 0, 0);
-                c[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, e.y, c[1], 0, 0, 0);
-                c[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, e.z, c[2], 0, 0, 0);
-                c[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, e.w, c[3], 0, 0, 0);
-            }
+        for (int q = 0; q < CB; ++q) {
+            const uint4 e = reinterpret_cast<const uint4*>(pu)[((k * 4 + kk) * CB + q) * 16 + col];
+            B[q] = fft_uintx4{e.x, e.y, e.z, e.w};
         }
+        auto mma = [](fft_uintx4 x, fft_uintx4 y, fft_floatx4 z) {
+            if constexpr (BF)
+                return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(fft_bf16x8, x),
+                                                               __builtin_bit_cast(fft_bf16x8, y), z, 0, 0, 0);
+            else
+                return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(fft_halfx8, x),
+                                                              __builtin_bit_cast(fft_halfx8, y), z, 0, 0, 0);
+        };
+        const fft_uintx4 A1{a.x, a.y, a.x, a.y}, A2{a.z, a.w, BF ? 0u : a.z, BF ? 0u : a.w};
+        if constexpr (!BF) {
+            const fft_uintx4 A3{o.r.x, o.r.y, 0u, 0u};
+#pragma unroll
+            for (int q = 0; q < CB; ++q) c[q] = mma(A3, B[q], c[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < CB; ++q) c[CB == 1 ? 1 : q] = mma(A2, B[q], c[CB == 1 ? 1 : q]);
+#pragma unroll
+        for (int q = 0; q < CB; ++q) c[q] = mma(A1, B[q], c[q]);
     };
 
-    // the k-steps k0 .. k0 + nk - 1 of one row block (nk a multiple of GS, at
-    // least GS).  The main loop runs whole blocks of 2 PD k-steps with no exit
+    // the k-steps k0 .. k0 + nk - 1 of one row block (nk >= 1).  The main loop runs whole blocks of 2 PD k-steps with no exit
     // inside, the A operands of the next PD k-steps loaded while the current
     // PD run (an exit between a load and its use lets the compiler sink the
-    // load to the use, which then waits for it); the last 0 .. 2 PD - GS
+    // load to the use, which then waits for it); the last 0 .. 2 PD - 1
     // k-steps run in a guarded tail.  Loads past the row block read the next
     // block or the array's slack and are not used.
-    constexpr int GS = BF ? 1 : 4;
-    constexpr int PD = BF ? 4 : 8;   // k-steps per register set (prefetch depth)
-    auto run_row = [&](const auto* ap, auto (&A0)[PD], auto (&A1)[PD], int k0, int nk, fft_floatx4 (&c)[NCH]) {
+    constexpr int PD = BF ? 4 : 2;   // k-steps per register set (prefetch depth)
+    auto run_row = [&](size_t a0, int k0, int nk, fft_floatx4 (&c)[NCH]) {
+        AOp A0[PD], A1[PD];
+        auto load = [&](int k) {
+            AOp o;
+            o.a = Av[a0 + (size_t)k * 64 + lane];
+            o.r = BF ? make_uint2(0, 0) : Ar[a0 + (size_t)k * 64 + lane];
+            return o;
+        };
 #pragma unroll
-        for (int j = 0; j < PD; ++j) A0[j] = ap[j * 64];
+        for (int j = 0; j < PD; ++j) A0[j] = load(j);
         int t = 0;
         for (; t + 2 * PD <= nk; t += 2 * PD) {
-            const auto* q = ap + (size_t)t * 64;
 #pragma unroll
-            for (int j = 0; j < PD; ++j) A1[j] = q[(PD + j) * 64];
+            for (int j = 0; j < PD; ++j) A1[j] = load(t + PD + j);
 #pragma unroll
-            for (int j = 0; j < PD; ++j) kstep(A0[j], k0 + t + j, j & 1, c);
+            for (int j = 0; j < PD; ++j) kstep(A0[j], k0 + t + j, c);
 #pragma unroll
-            for (int j = 0; j < PD; ++j) A0[j] = q[(2 * PD + j) * 64];
+            for (int j = 0; j < PD; ++j) A0[j] = load(t + 2 * PD + j);
 #pragma unroll
-            for (int j = 0; j < PD; ++j) kstep(A1[j], k0 + t + PD + j, j & 1, c);
+            for (int j = 0; j < PD; ++j) kstep(A1[j], k0 + t + PD + j, c);
         }
         const int r = nk - t;   // wave-uniform
         if (r > 0) {
-            const auto* q = ap + (size_t)t * 64;
 #pragma unroll
-            for (int j = 0; j < PD; ++j) A1[j] = q[(PD + j) * 64];
+            for (int j = 0; j < PD; ++j) A1[j] = load(t + PD + j);
 #pragma unroll
-            for (int j = 0; j < PD; j += GS) {
+            for (int j = 0; j < PD; ++j) {
                 if (j >= r) return;
-#pragma unroll
-                for (int i = 0; i < GS; ++i) kstep(A0[j + i], k0 + t + j + i, (j + i) & 1, c);
+                kstep(A0[j], k0 + t + j, c);
             }
 #pragma unroll
-            for (int j = 0; j < PD; j += GS) {
+            for (int j = 0; j < PD; ++j) {
                 if (PD + j >= r) return;
-#pragma unroll
-                for (int i = 0; i < GS; ++i) kstep(A1[j + i], k0 + t + PD + j + i, (j + i) & 1, c);
+                kstep(A1[j], k0 + t + PD + j, c);
             }
         }
     };
@@ -417,24 +463,15 @@ __global__ __launch_bounds__(256) void fft_density_kernel(FftMol m, const void* 
                 fft_floatx4 c[NCH];
 #pragma unroll
                 for (int q = 0; q < NCH; ++q) c[q] = fft_floatx4{0.f, 0.f, 0.f, 0.f};
-                if constexpr (BF) {
-                    const int k0 = rb, nk = RB - k0;
-                    const uint4* ap =
-                        reinterpret_cast<const uint4*>(Av) + ((size_t)(s * RB + rb) * RB + k0) * 64 + lane;
-                    uint4 A0[PD], A1[PD];
-                    run_row(ap, A0, A1, k0, nk, c);
-                } else {
-                    const int k0 = 4 * rb, nk = KS - k0;
-                    const float* ap =
-                        reinterpret_cast<const float*>(Av) + ((size_t)(s * RB + rb) * KS + k0) * 64 + lane;
-                    float A0[PD], A1[PD];
-                    run_row(ap, A0, A1, k0, nk, c);
-                }
+                run_row(((size_t)s * (RB * (RB + 1) / 2) + fft_group0(rb, RB)) * 64, rb, RB - rb, c);
+                uint32_t a4 = 0;   // exponents of the lane's rows
+                if constexpr (!BF) a4 = *reinterpret_cast<const uint32_t*>(ra + s * 16 * RB + 16 * rb + 4 * kk);
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
                     for (int q = 0; q < CB; ++q) {
-                        const float y = CB == 1 ? c[0][i] + c[1][i] : c[q][i];
+                        float y = CB == 1 ? c[0][i] + c[1][i] : c[q][i];
+                        if constexpr (!BF) y = __builtin_ldexpf(y, -(int)(signed char)(a4 >> (8 * i)));
                         acc[si][q] += v[i][q] * (FV)y;
                     }
             }
@@ -459,6 +496,7 @@ __global__ __launch_bounds__(256) void fft_density_kernel(FftMol m, const void* 
                 const FV* r4 = rd + si * 4 * NP;
                 double d = 0.0;
                 if (lane < NP) d = (double)r4[lane] + (double)r4[NP + lane] + (double)r4[2 * NP + lane] + (double)r4[3 * NP + lane];
+                if constexpr (!BF) d = __builtin_ldexp(d, -2 * pe);
                 if (valid) {
                     const float v = (float)d;
                     float* zp = Z + ((size_t)(s >> 1) * npts + g) * 2;
@@ -633,16 +671,47 @@ __global__ __launch_bounds__(256) void fft_sum_kernel(const double* __restrict__
 
 }  // namespace
 
-hipError_t launch_fft_pack(int precision, const double* T, const double* cnorm, int nbf, int ns, int RB, int KS,
+// Bytes of the A operands: the upper triangle of function groups per state and
+// what the density kernel loads past a row block (up to 7 groups, unused); FP32
+// precision: the same of the third halves, then the rows' exponents.
+static size_t fft_groups(int nbf_pad, int ns) {
+    const size_t RB = nbf_pad / 16;
+    return (size_t)ns * (RB * (RB + 1) / 2);
+}
+struct FftPack {
+    size_t ar, ra, total;   // offsets of the third halves and the exponents
+};
+static FftPack fft_pack_layout(int precision, int nbf_pad, int ns) {
+    const size_t g = fft_groups(nbf_pad, ns);
+    FftPack p;
+    if (precision == SCFF_BF16X3) {
+        p.ar = p.ra = p.total = (g + 7) * 64 * sizeof(uint4);
+    } else {
+        p.ar = (g + 3) * 64 * sizeof(uint4);
+        p.ra = p.ar + (g + 3) * 64 * sizeof(uint2);
+        p.total = p.ra + (size_t)ns * nbf_pad;
+    }
+    return p;
+}
+size_t fft_pack_bytes(int precision, int nbf_pad, int ns) { return fft_pack_layout(precision, nbf_pad, ns).total; }
+
+hipError_t launch_fft_pack(int precision, const double* T, const double* cnorm, int nbf, int nbf_pad, int ns,
                            double spin, void* Ap, hipStream_t st) {
-    const long long total = (long long)ns * RB * (precision == SCFF_BF16X3 ? RB : KS) * 64;
+    const int RB = nbf_pad / 16;
+    const FftPack p = fft_pack_layout(precision, nbf_pad, ns);
+    signed char* ra = (signed char*)Ap + p.ra;
+    uint2* ar = (uint2*)((char*)Ap + p.ar);
+    const long long total = (long long)fft_groups(nbf_pad, ns) * 64;
     const int blocks = (int)std::min<long long>((total + 255) / 256, 65536);
-    if (precision == SCFF_BF16X3)
-        hipLaunchKernelGGL(fft_pack_bf_kernel, dim3(blocks), dim3(256), 0, st, T, cnorm, nbf, ns, RB, spin,
-                           (uint4*)Ap);
-    else
-        hipLaunchKernelGGL(fft_pack_kernel, dim3(blocks), dim3(256), 0, st, T, cnorm, nbf, ns, RB, KS, spin,
-                           (float*)Ap);
+    if (precision == SCFF_BF16X3) {
+        hipLaunchKernelGGL(fft_pack_kernel<true>, dim3(blocks), dim3(256), 0, st, T, cnorm, nbf, ns, RB, spin, ra,
+                           (uint4*)Ap, ar);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(fft_rowmax_kernel, dim3((ns * nbf_pad + 3) / 4), dim3(256), 0, st, T, cnorm, nbf, nbf_pad, ns,
+                       spin, ra);
+    hipLaunchKernelGGL(fft_pack_kernel<false>, dim3(blocks), dim3(256), 0, st, T, cnorm, nbf, ns, RB, spin, ra,
+                       (uint4*)Ap, ar);
     return hipGetLastError();
 }
 
@@ -654,12 +723,15 @@ int fft_density_cb(int nbf_pad, size_t lds_limit) {
     return fft_lds_bytes(nbf_pad, 1) <= lds_limit ? 1 : 0;
 }
 
-hipError_t launch_fft_density(int precision, const FftMol& m, const void* Ap, int nbf_pad, int ns, int RB, int KS,
-                              const int n[3], const double x0[3], const double h[3], float* Z, float* phi, double* psum,
+hipError_t launch_fft_density(int precision, const FftMol& m, const void* Ap, int nbf_pad, int ns, const int n[3],
+                              const double x0[3], const double h[3], float* Z, float* phi, double* psum,
                               size_t lds_limit, long long* n_part, hipStream_t st) {
     const long long npts = (long long)n[0] * n[1] * n[2];
     const int cb = fft_density_cb(nbf_pad, lds_limit);
-    if (cb == 0 || nbf_pad % 16 || KS * 4 != nbf_pad || RB * 16 != nbf_pad) return hipErrorInvalidValue;
+    if (cb == 0 || nbf_pad % 16) return hipErrorInvalidValue;
+    const FftPack p = fft_pack_layout(precision, nbf_pad, ns);
+    const signed char* ra = (const signed char*)Ap + p.ra;
+    const uint2* ar = (const uint2*)((const char*)Ap + p.ar);
     const size_t lds = fft_lds_bytes(nbf_pad, cb);
     const long long tiles = (npts + 16 * cb - 1) / (16 * cb);
     if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
@@ -679,8 +751,8 @@ hipError_t launch_fft_density(int precision, const FftMol& m, const void* Ap, in
     const double3 xx = make_double3(x0[0], x0[1], x0[2]), hh = make_double3(h[0], h[1], h[2]);
     const dim3 grid((unsigned)tiles), block(256);
 #define SCFF_FFT_DENSITY(B, C)                                                                                  \
-    hipLaunchKernelGGL((fft_density_kernel<B, C>), grid, block, lds, st, m, Ap, nbf_pad, ns, RB, KS, nn, xx, hh, \
-                       npts, Z, phi, psum)
+    hipLaunchKernelGGL((fft_density_kernel<B, C>), grid, block, lds, st, m, (const uint4*)Ap, ar, ra, nbf_pad, ns, \
+                       nbf_pad / 16, nn, xx, hh, npts, Z, phi, psum)
     if (bf) {
         if (cb == 4) SCFF_FFT_DENSITY(true, 4);
         else if (cb == 2) SCFF_FFT_DENSITY(true, 2);

@@ -1166,13 +1166,11 @@ int scff_eval_fft(scff_ctx* c, const scff_fft_grid* g, int precision, float* f, 
     if ((rc = set_device(c))) return rc;
     hipStream_t st = (hipStream_t)hip_stream;
     if ((rc = order_after(c, st))) return rc;
-    const int RB = nbf_pad / 16, KS = nbf_pad / 4, nb = (ns + 1) / 2;
+    const int nb = (ns + 1) / 2;
     const long long npts = (long long)g->n[0] * g->n[1] * g->n[2];
     const size_t nout = (size_t)npts * ns;
     const long long part_d = (npts + 15) / 16, part_f = (npts + 63) / 64;
-    // the density kernel loads A operands up to 15 k-steps of 4 bytes (FP32) or 7 function groups
-    // of 16 bytes (split BF16) per lane past a row block (unused): slack of 32 x 64 floats covers both
-    if ((rc = dev_reserve(c, c->d_fft_A, ((size_t)ns * RB * KS + 32) * 64 * sizeof(float))) ||
+    if ((rc = dev_reserve(c, c->d_fft_A, fft_pack_bytes(precision, nbf_pad, ns))) ||
         (rc = dev_reserve(c, c->d_fft_Z, (size_t)nb * npts * sizeof(float2))))
         return rc;
     if (parseval &&
@@ -1212,11 +1210,10 @@ int scff_eval_fft(scff_ctx* c, const scff_fft_grid* g, int precision, float* f, 
     long long np_d = 0, np_f = 0;
     c->fft_recorded = false;
     if ((rc = record(c, EV_FFT0, st))) return rc;
-    if ((rc = hip_check(launch_fft_pack(precision, (const double*)c->d_T.p, m.cnorm, nbf, ns, RB, KS, c->spin,
-                                       c->d_fft_A.p, st),
+    if ((rc = hip_check(launch_fft_pack(precision, (const double*)c->d_T.p, m.cnorm, nbf, nbf_pad, ns, c->spin, c->d_fft_A.p, st),
                         "FFT weight packing")) ||
         (rc = record(c, EV_FFT1, st)) ||
-        (rc = hip_check(launch_fft_density(precision, m, c->d_fft_A.p, nbf_pad, ns, RB, KS, g->n, g->xmin, h,
+        (rc = hip_check(launch_fft_density(precision, m, c->d_fft_A.p, nbf_pad, ns, g->n, g->xmin, h,
                                            (float*)c->d_fft_Z.p, dphi, part, lds_limit, &np_d, st),
                         "transition density kernel")) ||
         (rc = record(c, EV_FFT2, st)))
