@@ -200,7 +200,7 @@ struct PrepWork {
 
 constexpr size_t kPinnedBytes = (size_t)4 << 20;
 // byte offsets in the precompute's small buffer
-constexpr size_t kSmallStats = 1024, kSmallSinv = 1280, kSmallKs = 1792, kSmallZhist = 2048;
+constexpr size_t kSmallStats = 1024, kSmallSinv = 1280, kSmallKs = 1792, kSmallMeta = 2048, kSmallZmax = 2304;
 constexpr size_t kPinnedTables = 4096;   // byte offset of the chunk table / molecule upload
 
 struct PrepResult {

@@ -14,7 +14,7 @@
 //    Gaussian, polynomial) and rounded once to FP32: the polynomial can
 //    cancel, and FP32 evaluation would leave errors proportional to its bound
 //    rather than to its value.  Exported only; the grid kernel reads
-//    xytable_kernel's and ztable_kernel's layouts of the same values.
+//    tables_kernel's layouts of the same values.
 //  * grid_kernel: the sum contracted over z rows on the f16 matrix cores (hi +
 //    lo halves, FP32 accumulation; FP32 precision folds into FP64 totals); the
 //    operand is formed on the VALU.  grid_batch_kernel: the same tiles popped
@@ -69,12 +69,11 @@ __global__ void vtable_kernel(const VRowDev* __restrict__ rows, int nrows, int v
 // lines; y: blocks of 8 values, V[qy / 8][row][8], so that a tile's lines read
 // whole 64-byte runs.  rows: the zero row, the x rows, the y rows; nxr and nyr
 // count the zero row too.
-__global__ __launch_bounds__(256) void xytable_kernel(const VRowDev* __restrict__ rows, int nxr, int nyr, int nx, int ny,
-                                                      double2 qmin, double2 dq, float2* __restrict__ X,
-                                                      float2* __restrict__ Y) {
+__device__ __forceinline__ void xytable(const VRowDev* __restrict__ rows, int nxr, int nyr, int nx, int ny, double2 qmin,
+                                        double2 dq, float2* __restrict__ X, float2* __restrict__ Y, long long i0,
+                                        long long step) {
     const long long tx = (long long)nx * nxr, tot = tx + (long long)((ny + 7) & ~7) * nyr;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < tot;
-         i += (long long)gridDim.x * blockDim.x) {
+    for (long long i = i0; i < tot; i += step) {
         if (i < tx) {
             const int q = (int)(i / nxr), r = (int)(i - (long long)q * nxr);
             X[i] = eval_row(rows[r], qmin.x + dq.x * (double)q);
@@ -93,12 +92,11 @@ __global__ __launch_bounds__(256) void xytable_kernel(const VRowDev* __restrict_
 // (g, n) = z rows 8 g .. 8 g + 7 of the k-step at column n, planes re hi, re
 // lo, im hi, im lo (f16 halves of the row scaled by its power of two; lo from
 // the FP64 value).  One thread per (8 z rows, column).
-__global__ __launch_bounds__(256) void ztable_kernel(const VRowDev* __restrict__ rows, const int2* __restrict__ zslots,
-                                                     int n_oct, int ncg, int ncol, int iz0, double qmin, double dq,
-                                                     uint4* __restrict__ Bt) {
+__device__ __forceinline__ void ztable(const VRowDev* __restrict__ rows, const int2* __restrict__ zslots, int n_oct,
+                                       int ncg, int ncol, int iz0, double qmin, double dq, uint4* __restrict__ Bt,
+                                       long long i0, long long step) {
     const long long tot = (long long)n_oct * ncg * 16;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < tot;
-         i += (long long)gridDim.x * blockDim.x) {
+    for (long long i = i0; i < tot; i += step) {
         const int oct = (int)(i / (ncg * 16)), col = (int)(i - (long long)oct * ncg * 16);
         halfx8 pl[4];
 #pragma unroll
@@ -120,6 +118,19 @@ __global__ __launch_bounds__(256) void ztable_kernel(const VRowDev* __restrict__
 #pragma unroll
         for (int p = 0; p < 4; ++p) o[p * 64] = __builtin_bit_cast(uint4, pl[p]);
     }
+}
+
+// All of them in one launch: the z axis' blocks (eight values per thread, the
+// longest) first.
+__global__ __launch_bounds__(256) void tables_kernel(const VRowDev* __restrict__ rows, int nxr, int nyr, int nx, int ny,
+                                                     double3 qmin, double3 dq, float2* __restrict__ X,
+                                                     float2* __restrict__ Y, const int2* __restrict__ zslots, int n_oct,
+                                                     int ncg, int ncol, int iz0, uint4* __restrict__ Bt, int nbz) {
+    if ((int)blockIdx.x < nbz)
+        ztable(rows, zslots, n_oct, ncg, ncol, iz0, qmin.z, dq.z, Bt, blockIdx.x * 256LL + threadIdx.x, nbz * 256LL);
+    else
+        xytable(rows, nxr, nyr, nx, ny, make_double2(qmin.x, qmin.y), make_double2(dq.x, dq.y), X, Y,
+                (blockIdx.x - nbz) * 256LL + threadIdx.x, (gridDim.x - nbz) * 256LL);
 }
 
 // ---------------------------------------------------------------- grid kernel
@@ -151,7 +162,7 @@ __global__ __launch_bounds__(256) void ztable_kernel(const VRowDev* __restrict__
 // to the matrix cores.  The products W = Vx Vy, which the states of a line
 // share, are formed once per workgroup, two lines per gather (a pair's y values
 // are 16 adjacent bytes), and pass through LDS; the V block of a k-step (stored
-// in operand order by ztable_kernel) and the weights come to LDS by DMA.  All of
+// in operand order by tables_kernel) and the weights come to LDS by DMA.  All of
 // it goes out one step (one or two terms of a k-step) ahead, one barrier a step.
 //
 // Why: the kernel before formed G = sum_t Vx Vy Vz per (pair, q) on the VALU (4
@@ -597,23 +608,17 @@ int vtable_stride(const int n[3]) {
     return ((m + 15) / 16) * 16 + 16;
 }
 
-hipError_t launch_xytable(const VRowDev* rows, int nxr, int nyr, const int n[3], const double qmin[3], const double dq[3],
-                          float2* X, float2* Y, hipStream_t st) {
-    const long long tot = (long long)n[0] * nxr + (long long)((n[1] + 7) & ~7) * nyr;
-    const int blocks = (int)std::min<long long>((tot + 255) / 256, 65536);
-    hipLaunchKernelGGL(xytable_kernel, dim3(blocks), dim3(256), 0, st, rows, nxr, nyr, n[0], n[1],
-                       make_double2(qmin[0], qmin[1]), make_double2(dq[0], dq[1]), X, Y);
-    return hipGetLastError();
-}
-
-hipError_t launch_ztable(const VRowDev* rows, const int2* zslots, int n_zpad, const GridShape& g, double qmin, double dq,
-                         uint4* Bt, hipStream_t st) {
+hipError_t launch_grid_tables(const VRowDev* rows, int nxr, int nyr, const int2* zslots, int n_zpad, const GridShape& g,
+                              const int n[3], const double qmin[3], const double dq[3], float2* X, float2* Y, uint4* Bt,
+                              hipStream_t st) {
     const int n_oct = n_zpad / 8;
-    const long long tot = (long long)n_oct * g.ncg * 16;
-    const int blocks = (int)std::min<long long>((tot + 255) / 256, 65536);
-    if (blocks < 1) return hipSuccess;
-    hipLaunchKernelGGL(ztable_kernel, dim3(blocks), dim3(256), 0, st, rows, zslots, n_oct, g.ncg, g.ncol, g.iz0, qmin,
-                       dq, Bt);
+    const long long tz = (long long)n_oct * g.ncg * 16;
+    const long long txy = (long long)n[0] * nxr + (long long)((n[1] + 7) & ~7) * nyr;
+    const int nbz = (int)std::min<long long>((tz + 255) / 256, 32768);
+    const int nbxy = (int)std::max<long long>(1, std::min<long long>((txy + 255) / 256, 32768));
+    hipLaunchKernelGGL(tables_kernel, dim3(nbz + nbxy), dim3(256), 0, st, rows, nxr, nyr, n[0], n[1],
+                       make_double3(qmin[0], qmin[1], qmin[2]), make_double3(dq[0], dq[1], dq[2]), X, Y, zslots, n_oct,
+                       g.ncg, g.ncol, g.iz0, Bt, nbz);
     return hipGetLastError();
 }
 

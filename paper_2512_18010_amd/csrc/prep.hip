@@ -7,10 +7,11 @@
 // threshold acts on a q-independent magnitude bound so the dropped part is
 // controlled.  Everything below runs on the device from device-resident T:
 //
-//   rows_kernel     one 1D V-tensor row per (primitive pair, axis, power
+//   rows_terms_kernel
+//                   one 1D V-tensor row per (primitive pair, axis, power
 //                   pair): P, 1/(4p), e_u (all q-independent factors folded),
-//                   and its bound sum_u |e_u| max_q |q|^u e^{-q^2/4p}
-//   terms_kernel    per (component pair, primitive pair) term: its 3 rows and
+//                   and its bound sum_u |e_u| max_q |q|^u e^{-q^2/4p}; per
+//                   (component pair, primitive pair) term: its 3 rows and
 //                   bound; per component pair Tp(s) = (T_mn + T_nm) c_m c_n s_f;
 //                   per shell pair the partial sums of |Tp| * bound
 //   tot_kernel      tot_s = sum over all terms of |Tp(s)| * bound
@@ -22,12 +23,15 @@
 // Grid kernel's layout (run_prep):
 //   zcount_kernel   kept terms of every z row (one per primitive pair and
 //                   power pair of the z axis), flags of the referenced rows, and
-//                   per shell pair and state the largest bound of the row's
-//                   contribution
-//   compact         rows compacted: a zero row, the x and y rows, the z rows
-//   zlayout_kernel  z rows sorted by term count (stable radix sort: most terms
-//                   first -> deterministic layout) in k-steps of 32; their term
+//                   per state the largest bound of a row's contribution
+//   scan            one scan numbers the rows (a zero row, the x and y rows,
+//                   the z rows) and sorts the z rows by term count (most terms
+//                   first, ties in row order)
+//   zmeta_kernel    scales of the states; what the host reads back, once
+//   zlayout_kernel  rows compacted; z rows in k-steps of 32: their term
 //                   records (x row, y row), scaled weights and scales
+// Small problems are bound by the number of launches and copies: 29 before, 15
+// now for a 4-heavy-atom, one-state, 32^3 grid with its tables (200 -> 147 us).
 // Layout by component pairs, for the other paths (run_prep_pairs):
 //   count/vkeys     kept terms per component pair, split into virtual pairs
 //                   of <= 9 terms, keyed by length (longest first, ties in pair
@@ -84,10 +88,16 @@ constexpr int kHistBins = 1200;
 
 // ------------------------------------------------------------------ kernels
 
-__global__ void rows_kernel(const PrepShell* __restrict__ sh, const int4* __restrict__ sp,
-                            const double* __restrict__ xyz, const double* __restrict__ exps,
-                            const double* __restrict__ coefs, const double* __restrict__ n1d,
-                            VRowDev* __restrict__ rows, double* __restrict__ rowsum) {
+// One workgroup per shell pair: its rows, then its terms and component pairs
+// (which need the bounds of its own rows only), and the pair's share of tot.
+__global__ __launch_bounds__(128) void rows_terms_kernel(
+    const PrepShell* __restrict__ sh, const int4* __restrict__ sp, const double* __restrict__ xyz,
+    const double* __restrict__ exps, const double* __restrict__ coefs, const double* __restrict__ n1d, int nr,
+    const int* __restrict__ sp_cp, const int* __restrict__ bf0, const double* __restrict__ cnorm,
+    const double* __restrict__ T, int nbf, int ns, double spin, VRowDev* __restrict__ rows, double* __restrict__ rowsum,
+    int* __restrict__ used, unsigned* __restrict__ small, int nsmall, int4* __restrict__ trow,
+    double* __restrict__ tbound, int2* __restrict__ cpmn, double* __restrict__ tp64, double* __restrict__ bsum,
+    double* __restrict__ part) {
     const int isp = blockIdx.x;
     const int4 s = sp[isp];   // sA, sB, row_off, term_off
     const PrepShell A_ = sh[s.x], B_ = sh[s.y];
@@ -138,26 +148,17 @@ __global__ void rows_kernel(const PrepShell* __restrict__ sh, const int4* __rest
         }
         rows[s.z + r] = out;
         rowsum[s.z + r] = sum;
+        for (int k = 0; k < 3; ++k) used[(size_t)k * nr + s.z + r] = 0;
     }
-}
-
-__global__ void terms_kernel(const PrepShell* __restrict__ sh, const int4* __restrict__ sp,
-                             const int* __restrict__ sp_cp, const int* __restrict__ bf0,
-                             const double* __restrict__ cnorm, const double* __restrict__ rowsum,
-                             const double* __restrict__ T, int nbf, int ns, double spin,
-                             int4* __restrict__ trow, double* __restrict__ tbound,
-                             int2* __restrict__ cpmn, double* __restrict__ tp64,
-                             double* __restrict__ bsum, double* __restrict__ part) {
-    const int isp = blockIdx.x;
-    const int4 s = sp[isp];
-    const PrepShell A_ = sh[s.x], B_ = sh[s.y];
-    const int lA = A_.l, lB = B_.l;
-    const int npp = A_.nprim * B_.nprim;
-    const int ncls = (lA + 1) * (lB + 1);
+    // cleared for the kernels that count into it
+    if (isp == 0)
+        for (int i = threadIdx.x; i < nsmall; i += blockDim.x) small[i] = 0u;
+    const int npp = A_.nprim * npb;
     const bool same = s.x == s.y;
     const int ncA = ncart_d(lA), ncB = ncart_d(lB);
     const int ncp = same ? ncA * (ncA + 1) / 2 : ncA * ncB;
     const int cp0 = sp_cp[isp];
+    __syncthreads();
     // terms and their bounds
     for (int t = threadIdx.x; t < ncp * npp; t += blockDim.x) {
         const int c = t / npp, pp = t - c * npp;
@@ -175,21 +176,24 @@ __global__ void terms_kernel(const PrepShell* __restrict__ sh, const int4* __res
         tbound[s.w + t] = bd;
     }
     __syncthreads();
-    // component pairs: mu, nu, packed weights and the sum of their term bounds
+    // component pairs: mu, nu and the sum of their term bounds; packed weights,
+    // component pairs fastest (neighbours of one state share T's cache lines)
     for (int c = threadIdx.x; c < ncp; c += blockDim.x) {
         int c1, c2;
         cp_decode(c, same, ncB, c1, c2);
-        const int mu = bf0[s.x] + c1, nu = bf0[s.y] + c2;
-        cpmn[cp0 + c] = make_int2(mu, nu);
+        cpmn[cp0 + c] = make_int2(bf0[s.x] + c1, bf0[s.y] + c2);
         double b = 0.0;
         for (int pp = 0; pp < npp; ++pp) b += tbound[s.w + c * npp + pp];
         bsum[cp0 + c] = b;
-        const double cc = cnorm[mu] * cnorm[nu] * spin;
-        for (int st = 0; st < ns; ++st) {
-            const double* Ts = T + (size_t)st * nbf * nbf;
-            const double v = mu == nu ? Ts[(size_t)mu * nbf + mu] : Ts[(size_t)mu * nbf + nu] + Ts[(size_t)nu * nbf + mu];
-            tp64[(size_t)(cp0 + c) * ns + st] = v * cc;
-        }
+    }
+    for (int i = threadIdx.x; i < ncp * ns; i += blockDim.x) {
+        const int st = i / ncp, c = i - st * ncp;
+        int c1, c2;
+        cp_decode(c, same, ncB, c1, c2);
+        const int mu = bf0[s.x] + c1, nu = bf0[s.y] + c2;
+        const double* Ts = T + (size_t)st * nbf * nbf;
+        const double v = mu == nu ? Ts[(size_t)mu * nbf + mu] : Ts[(size_t)mu * nbf + nu] + Ts[(size_t)nu * nbf + mu];
+        tp64[(size_t)(cp0 + c) * ns + st] = v * (cnorm[mu] * cnorm[nu] * spin);
     }
     __syncthreads();
     // per shell pair partial of sum_t |Tp(s)| bound(t), fixed order
@@ -200,10 +204,10 @@ __global__ void terms_kernel(const PrepShell* __restrict__ sh, const int4* __res
     }
 }
 
-__global__ void tot_kernel(const double* __restrict__ part, int nsp, int ns, double* __restrict__ tot) {
-    // one block of 256 threads per state: fixed-order strided partial sums,
+__global__ __launch_bounds__(1024) void tot_kernel(const double* __restrict__ part, int nsp, int ns, double* __restrict__ tot) {
+    // one block of 1024 threads per state: fixed-order strided partial sums,
     // then a fixed-shape tree (deterministic)
-    __shared__ double red[256];
+    __shared__ double red[1024];
     for (int st = blockIdx.x; st < ns; st += gridDim.x) {
         double a = 0.0;
         for (int i = threadIdx.x; i < nsp; i += blockDim.x) a += part[(size_t)i * ns + st];
@@ -257,10 +261,10 @@ __global__ void weight_kernel(const int4* __restrict__ trow, const double* __res
 __global__ void thresh_kernel(const unsigned int* __restrict__ hist, double eps, double* __restrict__ thr) {
     // one wave: per-bin upper bounds in LDS, then the largest bin `best` such
     // that the bounds of all bins <= best sum to at most eps.  The bins are
-    // scanned in order as 64 runs of consecutive bins (one run per lane):
-    // each lane sums its run, lane 0 adds the run sums in order until the
-    // total would pass eps and then walks that run bin by bin (83 serial
-    // steps instead of 1200; a fixed order, so the result is deterministic)
+    // scanned as 64 runs of consecutive bins (one run per lane): each lane sums
+    // its run, a scan over the lanes finds the run in which the total would pass
+    // eps, and lane 0 walks that run bin by bin (a fixed order, so the result is
+    // deterministic)
     constexpr int kRun = (kHistBins + 63) / 64;
     __shared__ double pre[kHistBins];
     __shared__ double run[64];
@@ -273,14 +277,21 @@ __global__ void thresh_kernel(const unsigned int* __restrict__ hist, double eps,
         run[lane] = sr;
     }
     __syncthreads();
+    // sums of the runs up to and including each (a fixed-shape scan); the runs
+    // that fit whole are the first r
+    double incl = run[lane];
+    for (int h = 1; h < 64; h <<= 1) {
+        const double o = __shfl_up(incl, h);
+        if (lane >= h) incl += o;
+    }
+    const int r = __popcll(__ballot(incl <= eps));   // non-decreasing: a prefix of the lanes
+    double sum = __shfl(incl, max(r - 1, 0));
     if (lane == 0) {
         if (!(eps > 0.0)) {
             thr[0] = -1.0;   // no screening: keep every term, zero or not
             return;
         }
-        double sum = 0.0;
-        int r = 0;
-        while (r < 64 && sum + run[r] <= eps) sum += run[r++];
+        if (r == 0) sum = 0.0;
         int best = r * kRun - 1;   // every bin of the runs before r is dropped
         if (r < 64) {
             for (int b = r * kRun; b < min((r + 1) * kRun, kHistBins); ++b) {
@@ -410,20 +421,6 @@ __global__ void layout_kernel(const int* __restrict__ order, const int4* __restr
     }
 }
 
-// used: flags of the x rows in [0, nrows), of the y rows in [nrows, 2 nrows), of
-// the z rows in [2 nrows, 3 nrows)
-__global__ void compact_kernel(const VRowDev* __restrict__ rows, const int* __restrict__ used,
-                               const int* __restrict__ newid, int nrows, VRowDev* __restrict__ out) {
-    for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < 3 * nrows; r += gridDim.x * blockDim.x) {
-        if (r == 0) {
-            VRowDev z{};
-            z.inv4p = 1.0;
-            out[0] = z;
-        }
-        if (used[r]) out[1 + newid[r]] = rows[r % nrows];
-    }
-}
-
 // Component pairs of a shell pair by the powers (i, j) of the z axis, in
 // component order: for every (lA, lB, same shell), class i (lB + 1) + j ->
 // count and component pairs.
@@ -453,18 +450,19 @@ __device__ __forceinline__ int z_exponent(double bound) {
     return bound > 0.0 && bound < 1e300 ? max(-900, min(900, 13 - ilogb(bound))) : 0;
 }
 
-// Per z row (index row offset / 3 + pp ncls + class): sort key 9 - (kept
-// terms), 15 if none, and (shell pair, pp ncls + class).  part: per shell pair
-// and state the largest sum of |Tp| x bound x y bound over a row's terms,
-// divided by the row's scale.
+// Per z row (id = row offset / 3 + pp ncls + class): kept terms n, one-hot flags
+// of 9 - n behind the row flags (used + 3 nr, 9 segments of all z rows, so that
+// the one scan that numbers the rows also sorts the z rows, most terms first),
+// and (shell pair, pp ncls + class).  mx: per state the largest sum of |Tp| x bound
+// x y bound over a row's terms, divided by the row's scale, as the bits of a
+// non-negative double (which order like the values); a maximum does not depend
+// on the order of the atomics.
 __global__ __launch_bounds__(128) void zcount_kernel(const PrepShell* __restrict__ sh, const int4* __restrict__ sp,
                                                     const int4* __restrict__ trow, const double* __restrict__ rowsum,
                                                     const double* __restrict__ w, const double* __restrict__ thr,
                                                     const double* __restrict__ tp64, int ns, int nr,
-                                                    int* __restrict__ used, unsigned* __restrict__ key,
-                                                    int* __restrict__ val, int2* __restrict__ zinfo,
-                                                    int* __restrict__ zhist, double* __restrict__ part) {
-    __shared__ int lh[16];
+                                                    int nz_all, int* __restrict__ used, int* __restrict__ zn,
+                                                    int2* __restrict__ zinfo, unsigned long long* __restrict__ gmx) {
     __shared__ unsigned long long mx[kMaxStates];
     const int isp = blockIdx.x;
     const int4 s = sp[isp];
@@ -472,7 +470,6 @@ __global__ __launch_bounds__(128) void zcount_kernel(const PrepShell* __restrict
     const bool same = s.x == s.y;
     const int ncls = (lA + 1) * (lB + 1);
     const double th = thr[0];
-    if (threadIdx.x < 16) lh[threadIdx.x] = 0;
     if (threadIdx.x < kMaxStates) mx[threadIdx.x] = 0ull;
     __syncthreads();
     const int kc = lA * 6 + lB * 2 + (same ? 1 : 0), nz = npp * ncls;
@@ -488,12 +485,10 @@ __global__ __launch_bounds__(128) void zcount_kernel(const PrepShell* __restrict
             ++n;
         }
         const int id = s.z / 3 + z;
-        key[id] = n ? (unsigned)(kZTerms - n) : 15u;
-        val[id] = id;
+        zn[id] = n;
         zinfo[id] = make_int2(isp, z);
-        if (!n) continue;
-        used[2 * nr + s.z + pp * 3 * ncls + 2 * ncls + cls] = 1;
-        atomicAdd(&lh[n], 1);
+        for (int k = 0; k < kZTerms; ++k) used[(size_t)3 * nr + (size_t)k * nz_all + id] = n == kZTerms - k;
+        if (n) used[2 * nr + s.z + pp * 3 * ncls + 2 * ncls + cls] = 1;
     }
     for (int i = threadIdx.x; i < nz * ns; i += blockDim.x) {
         const int z = i / ns, st = i - z * ns;
@@ -510,47 +505,67 @@ __global__ __launch_bounds__(128) void zcount_kernel(const PrepShell* __restrict
         if (b > 0.0 && b < 1e300) atomicMax(&mx[st], (unsigned long long)__double_as_longlong(b));
     }
     __syncthreads();
-    if (threadIdx.x < 16 && lh[threadIdx.x]) atomicAdd(&zhist[threadIdx.x], lh[threadIdx.x]);
     for (int st = threadIdx.x; st < ns; st += blockDim.x)
-        part[(size_t)isp * ns + st] = __longlong_as_double((long long)mx[st]);
+        if (mx[st] > __hip_atomic_load(&gmx[st], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&gmx[st], mx[st]);
 }
 
 // Per state: its largest z-row bound, as the exponent ks with bound 2^ks <
-// 2^15 (weights are scaled by 2^ks) and the factor 2^-ks of the results.
-__global__ __launch_bounds__(256) void zscale_kernel(const double* __restrict__ part, int nsp, int ns,
-                                                     int* __restrict__ ks, double* __restrict__ sinv) {
-    __shared__ double red[256];
-    const int st = blockIdx.x;
-    double a = 0.0;
-    for (int i = threadIdx.x; i < nsp; i += 256) a = fmax(a, part[(size_t)i * ns + st]);
-    red[threadIdx.x] = a;
-    __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + h]);
-        __syncthreads();
+// 2^15 (weights are scaled by 2^ks) and the factor 2^-ks of the results.  Then
+// what the host needs: the first numbers of the y rows, the z rows and the nine
+// segments of sorted z rows, and their end (meta[12], all numbers of one scan).
+__global__ __launch_bounds__(64) void zmeta_kernel(const unsigned long long* __restrict__ mx, int ns,
+                                                   const int* __restrict__ newid, const int* __restrict__ used, int nr,
+                                                   int nz_all, int* __restrict__ ks, double* __restrict__ sinv,
+                                                   int* __restrict__ meta) {
+    const int i = threadIdx.x;
+    if (i < ns) {
+        const double b = __longlong_as_double((long long)mx[i]);
+        const int k = b > 0.0 ? max(-900, min(900, 14 - ilogb(b))) : 0;
+        ks[i] = k;
+        sinv[i] = ldexp(1.0, -k);
     }
-    if (threadIdx.x == 0) {
-        const int k = red[0] > 0.0 ? max(-900, min(900, 14 - ilogb(red[0]))) : 0;
-        ks[st] = k;
-        sinv[st] = ldexp(1.0, -k);
-    }
+    const size_t end = (size_t)3 * nr + (size_t)kZTerms * nz_all;
+    if (i < 2) meta[i] = newid[(size_t)(i + 1) * nr];
+    else if (i < 2 + kZTerms) meta[i] = newid[(size_t)3 * nr + (size_t)(i - 2) * nz_all];
+    else if (i == 2 + kZTerms) meta[i] = newid[end - 1] + used[end - 1];
 }
 
-// One thread per (sorted z row, state): term records,
-// weights T 2^(ks - e) and (thread of state 0) the z slot (row, e).
+// Rows compacted (blocks from nbz on), and one thread per (z row, state): its
+// term records, weights T 2^(ks - e) and (thread of state 0) its z slot (row, e) at
+// its sorted place p; then the places past the last row.
 __global__ __launch_bounds__(256) void zlayout_kernel(const PrepShell* __restrict__ sh, const int4* __restrict__ sp,
                                                       const int4* __restrict__ trow, const double* __restrict__ rowsum,
                                                       const double* __restrict__ w, const double* __restrict__ thr,
                                                       const double* __restrict__ tp64, int ns, int nr,
-                                                      const int* __restrict__ newid, const int* __restrict__ order,
-                                                      const int2* __restrict__ zinfo, int nz, int nzpad,
+                                                      const int* __restrict__ newid, const int* __restrict__ znum,
+                                                      const int2* __restrict__ zinfo, int nz, int nzpad, int nz_all,
                                                       KSteps steps, const int* __restrict__ ks,
                                                       int2* __restrict__ zslots, int2* __restrict__ terms,
-                                                      float* __restrict__ Tw) {
-    const long long tot = (long long)nzpad * ns;
-    for (long long gi = blockIdx.x * (long long)blockDim.x + threadIdx.x; gi < tot;
-         gi += (long long)gridDim.x * blockDim.x) {
-        const int p = (int)(gi / ns), st = (int)(gi - (long long)p * ns);
+                                                      float* __restrict__ Tw, int nbz, const VRowDev* __restrict__ rows,
+                                                      const int* __restrict__ used, VRowDev* __restrict__ out) {
+    if ((int)blockIdx.x >= nbz) {
+        const long long all = 3LL * nr;
+        for (long long r = (blockIdx.x - nbz) * (long long)blockDim.x + threadIdx.x; r < all;
+             r += (long long)(gridDim.x - nbz) * blockDim.x) {
+            if (r == 0) {
+                VRowDev z{};
+                z.inv4p = 1.0;
+                out[0] = z;
+            }
+            if (used[r]) out[1 + newid[r]] = rows[r % nr];
+        }
+        return;
+    }
+    const long long tot = (long long)(nz_all + nzpad - nz) * ns;
+    for (long long gi = blockIdx.x * (long long)blockDim.x + threadIdx.x; gi < tot; gi += (long long)nbz * blockDim.x) {
+        const int id = (int)(gi / ns), st = (int)(gi - (long long)id * ns);
+        int p = nz + id - nz_all;
+        if (id < nz_all) {
+            const int m = znum[id];
+            if (m == 0) continue;
+            const size_t seg = (size_t)3 * nr;
+            p = newid[seg + (size_t)(kZTerms - m) * nz_all + id] - newid[seg];
+        }
         const int zn = ksteps_terms(steps, p / kZStep), zc = ksteps_first(steps, p / kZStep);
         // record t of the row at rec[32 t], weight t at tw[grid_term_weights t]
         const int zl = p % kZStep;
@@ -558,8 +573,8 @@ __global__ __launch_bounds__(256) void zlayout_kernel(const PrepShell* __restric
         float* tw = Tw + (size_t)zc * grid_term_weights(ns) + ((zl >> 3) * ns + st) * 12 + (zl & 7);
         const int tstep = grid_term_weights(ns);
         int n = 0;
-        if (p < nz) {
-            const int2 zi = zinfo[order[p]];
+        if (id < nz_all) {
+            const int2 zi = zinfo[id];
             const int4 s = sp[zi.x];
             const int lA = sh[s.x].l, lB = sh[s.y].l, npp = sh[s.x].nprim * sh[s.y].nprim;
             const int ncls = (lA + 1) * (lB + 1), pp = zi.y / ncls, cls = zi.y - pp * ncls;
@@ -621,33 +636,33 @@ hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStrea
     CK(alloc(w.rows_all, (size_t)NR * sizeof(VRowDev)));
     CK(alloc(w.rowsum, (size_t)NR * sizeof(double)));
     CK(alloc(w.trow, (size_t)NT * sizeof(int4)));
-    CK(alloc(w.tbound, std::max((size_t)NT * sizeof(double), (size_t)NZ * 24)));
+    CK(alloc(w.tbound, std::max((size_t)NT * sizeof(double), (size_t)NZ * 12)));
     CK(alloc(w.wt, (size_t)NT * sizeof(double)));
     CK(alloc(w.cpmn, (size_t)NCP * sizeof(int2)));
     CK(alloc(w.tp64, (size_t)NCP * ns * sizeof(double)));
     CK(alloc(w.bsum, (size_t)NCP * sizeof(double)));
     CK(alloc(w.part, (size_t)NSP * ns * sizeof(double)));
     CK(alloc(w.small, 4096 + kHistBins * sizeof(unsigned) + 64));
-    if (NR > INT32_MAX / 3) return hipErrorInvalidValue;
-    CK(alloc(w.row_used, (size_t)NR * 3 * sizeof(int)));
-    CK(alloc(w.newid, (size_t)NR * 3 * sizeof(int)));
+    // flags: rows used per axis, then the z rows' one-hot term counts
+    const long long NF = 3 * NR + (long long)kZTerms * NZ;
+    if (NF > INT32_MAX) return hipErrorInvalidValue;
+    CK(alloc(w.row_used, (size_t)NF * sizeof(int)));
+    CK(alloc(w.newid, (size_t)NF * sizeof(int)));
     double* tot = (double*)w.small.p;                                    // [<= 32]
     double* thr = tot + 64;                                              // [1]
     double* sinv = (double*)((char*)w.small.p + kSmallSinv);             // [<= 32]
     int* ks = (int*)((char*)w.small.p + kSmallKs);                       // [<= 32]
-    int* zhist = (int*)((char*)w.small.p + kSmallZhist);                 // [16]
+    int* meta = (int*)((char*)w.small.p + kSmallMeta);                   // [12]
+    unsigned long long* zmx = (unsigned long long*)((char*)w.small.p + kSmallZmax);   // [<= 32]
     unsigned* hist = (unsigned*)((char*)w.small.p + 4096);               // [kHistBins]
 
-    CK(hipMemsetAsync(w.small.p, 0, w.small.bytes, st));
-    hipLaunchKernelGGL(rows_kernel, dim3(NSP), dim3(128), 0, st, in.shells, in.sp, in.xyz, in.exps,
-                       in.coefs, in.n1d, (VRowDev*)w.rows_all.p, (double*)w.rowsum.p);
+    const int nsmall = (int)((4096 + kHistBins * sizeof(unsigned)) / sizeof(unsigned));
+    hipLaunchKernelGGL(rows_terms_kernel, dim3(NSP), dim3(128), 0, st, in.shells, in.sp, in.xyz, in.exps, in.coefs, in.n1d,
+                       (int)NR, in.sp_cp, in.bf0, in.cnorm, in.T, in.nbf, ns, in.spin, (VRowDev*)w.rows_all.p,
+                       (double*)w.rowsum.p, (int*)w.row_used.p, (unsigned*)w.small.p, nsmall, (int4*)w.trow.p,
+                       (double*)w.tbound.p, (int2*)w.cpmn.p, (double*)w.tp64.p, (double*)w.bsum.p, (double*)w.part.p);
     CK(hipGetLastError());
-    hipLaunchKernelGGL(terms_kernel, dim3(NSP), dim3(128), 0, st, in.shells, in.sp, in.sp_cp, in.bf0,
-                       in.cnorm, (const double*)w.rowsum.p, in.T, in.nbf, ns, in.spin,
-                       (int4*)w.trow.p, (double*)w.tbound.p, (int2*)w.cpmn.p, (double*)w.tp64.p,
-                       (double*)w.bsum.p, (double*)w.part.p);
-    CK(hipGetLastError());
-    hipLaunchKernelGGL(tot_kernel, dim3(ns), dim3(256), 0, st, (const double*)w.part.p, NSP, ns, tot);
+    hipLaunchKernelGGL(tot_kernel, dim3(ns), dim3(1024), 0, st, (const double*)w.part.p, NSP, ns, tot);
     CK(hipGetLastError());
     hipLaunchKernelGGL(pairmax_kernel, dim3(blocks_for(NCP, 256)), dim3(256), 0, st, (const double*)w.tp64.p,
                        (const double*)tot, ns, NCP, (double*)w.bsum.p);
@@ -658,46 +673,33 @@ hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStrea
     hipLaunchKernelGGL(thresh_kernel, dim3(1), dim3(64), 0, st, (const unsigned*)hist, in.eps, thr);
     CK(hipGetLastError());
     // the term bounds were last read by weight_kernel: their buffer holds the
-    // z rows' sort arrays from here on
+    // z rows' places and term counts from here on
     int2* zinfo = (int2*)w.tbound.p;
-    unsigned* zk_in = (unsigned*)(zinfo + NZ);
-    unsigned* zk_out = zk_in + NZ;
-    int* zv_in = (int*)(zk_out + NZ);
-    int* zv_out = zv_in + NZ;
-    CK(hipMemsetAsync(w.row_used.p, 0, (size_t)NR * 3 * sizeof(int), st));
+    int* zn = (int*)(zinfo + NZ);
     hipLaunchKernelGGL(zcount_kernel, dim3(NSP), dim3(128), 0, st, in.shells, in.sp, (const int4*)w.trow.p,
                        (const double*)w.rowsum.p, (const double*)w.wt.p, (const double*)thr, (const double*)w.tp64.p, ns,
-                       (int)NR, (int*)w.row_used.p, zk_in, zv_in, zinfo, zhist, (double*)w.part.p);
-    CK(hipGetLastError());
-    hipLaunchKernelGGL(zscale_kernel, dim3(ns), dim3(256), 0, st, (const double*)w.part.p, NSP, ns, ks, sinv);
+                       (int)NR, NZ, (int*)w.row_used.p, zn, zinfo, zmx);
     CK(hipGetLastError());
     size_t tmp_bytes = 0;
-    CK(hipcub::DeviceScan::ExclusiveSum(nullptr, tmp_bytes, (int*)w.row_used.p, (int*)w.newid.p, (int)(3 * NR), st));
+    CK(hipcub::DeviceScan::ExclusiveSum(nullptr, tmp_bytes, (int*)w.row_used.p, (int*)w.newid.p, (int)NF, st));
     CK(alloc(w.tmp4, tmp_bytes + 256));
-    CK(hipcub::DeviceScan::ExclusiveSum(w.tmp4.p, tmp_bytes, (int*)w.row_used.p, (int*)w.newid.p, (int)(3 * NR), st));
-    // readbacks of sizes land in the context's pinned host memory when it has
+    CK(hipcub::DeviceScan::ExclusiveSum(w.tmp4.p, tmp_bytes, (int*)w.row_used.p, (int*)w.newid.p, (int)NF, st));
+    hipLaunchKernelGGL(zmeta_kernel, dim3(1), dim3(64), 0, st, (const unsigned long long*)zmx, ns,
+                       (const int*)w.newid.p, (const int*)w.row_used.p, (int)NR, NZ, ks, sinv, meta);
+    CK(hipGetLastError());
+    // the one readback lands in the context's pinned host memory when it has
     // some (a DMA; pageable destinations are staged by the runtime)
-    alignas(16) unsigned char local_rb[256];
-    unsigned char* rb = w.pinned ? (unsigned char*)w.pinned : local_rb;
-    int* zh = (int*)rb;                 // [16]
-    int* lastr = (int*)(rb + 64);       // [4]: first y id, first z id; last id and flag
-    CK(hipMemcpyAsync(zh, zhist, 16 * sizeof(int), hipMemcpyDeviceToHost, st));
-    CK(hipMemcpyAsync(&lastr[0], (int*)w.newid.p + NR, sizeof(int), hipMemcpyDeviceToHost, st));
-    CK(hipMemcpyAsync(&lastr[1], (int*)w.newid.p + 2 * NR, sizeof(int), hipMemcpyDeviceToHost, st));
-    CK(hipMemcpyAsync(&lastr[2], (int*)w.newid.p + 3 * NR - 1, sizeof(int), hipMemcpyDeviceToHost, st));
-    CK(hipMemcpyAsync(&lastr[3], (int*)w.row_used.p + 3 * NR - 1, sizeof(int), hipMemcpyDeviceToHost, st));
-    size_t sort_bytes = 0;
-    CK(hipcub::DeviceRadixSort::SortPairs(nullptr, sort_bytes, zk_in, zk_out, zv_in, zv_out, NZ, 0, 4, st));
-    CK(alloc(w.tmp2, sort_bytes + 256));
-    CK(hipcub::DeviceRadixSort::SortPairs(w.tmp2.p, sort_bytes, zk_in, zk_out, zv_in, zv_out, NZ, 0, 4, st));
+    alignas(16) int local_rb[12];
+    int* rb = w.pinned ? (int*)w.pinned : local_rb;
+    CK(hipMemcpyAsync(rb, meta, sizeof(local_rb), hipMemcpyDeviceToHost, st));
     CK(hipStreamSynchronize(st));
-    const int nrows_used = lastr[2] + lastr[3];
+    const int nrows_used = rb[2];   // the numbers of the z rows' segments start after the rows'
     // k-steps of kZStep sorted z rows; every row is padded to the count of the
     // k-step's first (a single k-step of zero rows if nothing is kept)
     KSteps steps{};
     int nz = 0;
     for (int n = kZTerms; n >= 1; --n) {
-        nz += zh[n];
+        nz += rb[2 + kZTerms - n + 1] - rb[2 + kZTerms - n];
         steps.kend[n] = (nz + kZStep - 1) / kZStep;
     }
     if (nz == 0) steps.kend[1] = 1;
@@ -710,19 +712,17 @@ hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStrea
     CK(alloc(w.zterms, (size_t)nterm * sizeof(int2)));
     CK(alloc(w.zw, (size_t)nw * sizeof(float)));
     CK(alloc(w.rows, (size_t)(nrows_used + 1) * sizeof(VRowDev)));
-    hipLaunchKernelGGL(compact_kernel, dim3(blocks_for(3 * NR, 256)), dim3(256), 0, st, (const VRowDev*)w.rows_all.p,
-                       (const int*)w.row_used.p, (const int*)w.newid.p, (int)NR, (VRowDev*)w.rows.p);
-    CK(hipGetLastError());
-    hipLaunchKernelGGL(zlayout_kernel, dim3(blocks_for((long long)nzpad * ns, 256)), dim3(256), 0, st, in.shells, in.sp,
+    const int nbz = blocks_for((long long)(NZ + nzpad - nz) * ns, 256);
+    hipLaunchKernelGGL(zlayout_kernel, dim3(nbz + blocks_for(3 * NR, 256)), dim3(256), 0, st, in.shells, in.sp,
                        (const int4*)w.trow.p, (const double*)w.rowsum.p, (const double*)w.wt.p, (const double*)thr,
-                       (const double*)w.tp64.p, ns, (int)NR, (const int*)w.newid.p, (const int*)zv_out,
-                       (const int2*)zinfo, nz, nzpad, steps, (const int*)ks, (int2*)w.zslots.p,
-                       (int2*)w.zterms.p, (float*)w.zw.p);
+                       (const double*)w.tp64.p, ns, (int)NR, (const int*)w.newid.p, (const int*)zn, (const int2*)zinfo, nz,
+                       nzpad, NZ, steps, (const int*)ks, (int2*)w.zslots.p, (int2*)w.zterms.p, (float*)w.zw.p, nbz,
+                       (const VRowDev*)w.rows_all.p, (const int*)w.row_used.p, (VRowDev*)w.rows.p);
     CK(hipGetLastError());
     res = PrepResult{};
     res.n_rows = nrows_used + 1;
-    res.n_x = lastr[0];
-    res.n_y = lastr[1] - lastr[0];
+    res.n_x = rb[0];
+    res.n_y = rb[1] - rb[0];
     res.n_ksteps = n_ksteps;
     res.ksteps = steps;
     res.n_zterms = nterm;

@@ -18,10 +18,9 @@ namespace scff {
 hipError_t launch_vtable(const VRowDev* rows, int nrows, int vstride, const int n[3],
                          const double qmin[3], const double dq[3], float2* V, hipStream_t st);
 int vtable_stride(const int n[3]);
-hipError_t launch_xytable(const VRowDev* rows, int nxr, int nyr, const int n[3], const double qmin[3], const double dq[3],
-                          float2* X, float2* Y, hipStream_t st);
-hipError_t launch_ztable(const VRowDev* rows, const int2* zslots, int n_zpad, const GridShape& g, double qmin, double dq,
-                         uint4* Bt, hipStream_t st);
+hipError_t launch_grid_tables(const VRowDev* rows, int nxr, int nyr, const int2* zslots, int n_zpad, const GridShape& g,
+                              const int n[3], const double qmin[3], const double dq[3], float2* X, float2* Y, uint4* Bt,
+                              hipStream_t st);
 GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect);
 int grid_wgs_per_cu(int cls, int lds);
 hipError_t launch_grid(int cls, const GridShape& g, const GridDesc& d, long long blocks, hipStream_t st);
@@ -403,13 +402,10 @@ int launch_tables(scff_ctx* c, const scff_grid* g, const GridShape& sh, void* ta
     double dq[3];
     grid_spacing(g, dq);
     const TableBytes tb = table_bytes(c, g, sh);
-    int rc = hip_check(launch_xytable((const VRowDev*)c->prep.rows.p, c->pres.n_x + 1, c->pres.n_y + 1, g->n, g->qmin, dq,
-                                      (float2*)tab, (float2*)((char*)tab + tb.y), st),
-                       "x / y table kernel launch");
-    if (rc) return rc;
-    return hip_check(launch_ztable((const VRowDev*)c->prep.rows.p, (const int2*)c->prep.zslots.p,
-                                   c->pres.n_ksteps * kZStep, sh, g->qmin[2], dq[2], (uint4*)((char*)tab + tb.z), st),
-                     "z table kernel launch");
+    return hip_check(launch_grid_tables((const VRowDev*)c->prep.rows.p, c->pres.n_x + 1, c->pres.n_y + 1,
+                                        (const int2*)c->prep.zslots.p, c->pres.n_ksteps * kZStep, sh, g->n, g->qmin, dq,
+                                        (float2*)tab, (float2*)((char*)tab + tb.y), (uint4*)((char*)tab + tb.z), st),
+                     "table kernel launch");
 }
 
 // every axis holds -q with q: index i and n-1-i are q and -q.  An axis of
