@@ -57,10 +57,6 @@ __host__ __device__ constexpr int grid_term_weights(int ns) { return 48 * ns; }
 // (one workgroup per tile and range, FP64 partial sums reduced afterwards)
 // when the grid has too few tiles to fill the device.
 constexpr int kMaxSplit = 32;
-// The pair-sum buffer G of the separable-integral and dipole paths holds
-// nv x ncomp pair sums followed by ns x ncomp x kSepParts slices of their
-// transition-weighted reduction.
-constexpr int kSepParts = 64;
 struct ChunkSplit {
     int n;                   // number of ranges (1 = no split)
     int lo[kMaxSplit + 1];   // range j is k-steps [lo[j], lo[j+1]); lo[0] = 0, lo[n] = n_ksteps
@@ -167,6 +163,17 @@ struct PrepInputs {
     double eps, spin;
 };
 
+// What the separable-integral and dipole kernels (lowq.hip) read of the
+// precompute; newid numbers the used rows from 0, at [axis nr + row].
+struct LowqPrep {
+    const int *cp_first, *cp_nterms;
+    const VRowDev* rows;   // all rows, by shell pair
+    const int4* trow;
+    const double *wt, *thr, *tp64;
+    const int* newid;
+    int nr;
+};
+
 // Point evaluation (points.hip): the precompute's arrays, the points and what is
 // written (f, |f|^2, |f|^2 in FP64; each may be null).  part: FP64 sums per
 // share of the shell pairs, [n_split][state][point], null for one share.
@@ -185,13 +192,12 @@ struct PointArgs {
 
 // Device buffers of the precompute.  What the grid kernel reads: rows, zslots,
 // zterms, zw and the state factors in small; the layout by component
-// pairs (made when another path first needs it): slots, tp32, vcp and, per
+// pairs (made when the export first needs it): slots, tp32 and, per
 // unit, cnpp (terms per pair) and coff (first slot).
 struct PrepWork {
     DeviceBuffer rows_all, rowsum, trow, tbound, wt, cpmn, tp64, bsum, part, small, nk, nv, vbase,
         tmp, key, val, vinfo, tmp2, cnpp, csize, coff, tmp3, slots, tp32, row_used, newid, tmp4,
-        rows, zslots, zterms, zw,
-        vcp;   // per packed pair: its component pair (index of tp64), -1 for padding
+        rows, zslots, zterms, zw;
     // pinned host memory of the context (kPinnedBytes, or NULL if it could
     // not be allocated): small readbacks and the chunk table travel through
     // it by DMA; every use is complete before run_prep returns

@@ -5,19 +5,22 @@
 //  * separable integral  I_s = sum_{ix,iy,iz} wx[ix] wy[iy] wz[iz] f_s(q)
 //      = sum_t Tp_s(t) (sum_ix wx V^x_t) (sum_iy wy V^y_t) (sum_iz wz V^z_t):
 //    one weighted row sum per 1D row, then one complex triple product per
-//    term, then the transition-weighted sum over packed pairs;
+//    kept term, then the transition-weighted sum over component pairs;
 //  * transition dipole  mu_s = grad_q Im f_s at q = 0: each row's value and
 //    first derivative at q = 0 are V(0) = e_0 and V'(0) = i (P e_0 + e_1), so
-//    d f_s / d q_x (0) = i sum_t Tp_s(t) (P e_0 + e_1)^x e_0^y e_0^z;
-//  * |f_s(q)|^2 at arbitrary points entirely in FP64 (rows evaluated on the
-//    fly, FP64 transition weights), for the angular-average fit of Sec. 6.
+//    d f_s / d q_x (0) = i sum_t Tp_s(t) (P e_0 + e_1)^x e_0^y e_0^z.
 //
-// All sums run in FP64 with the FP64 packed weights tp64[component pair][s];
-// the reductions over packed pairs use a fixed order (deterministic).
+// All sums run in FP64 with the FP64 weights tp64[component pair][s], straight
+// from the precompute's rows and terms; the reductions use a fixed order
+// (deterministic).  The layout by packed pairs that these sums read before cost a
+// context's first call 200 us and is not needed any more; the pair sums and
+// their reduction are one kernel (dipole 41 us, separable 24 us, for 30 heavy
+// atoms and 24 states; 10 + 29 us each before, from that layout).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "engine.h"
-#include "vrow.h"
 
 namespace scff {
 
@@ -27,9 +30,15 @@ __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
-// S[r] = sum_i w_a[i] V_r(q_a[i]) for the axis a of row r (w: x, y, z
-// weights concatenated).  Eight lanes per row: lane l of a row's group takes
-// the values i = l, l + 8, ..., then a fixed butterfly sums the eight.
+// S[r] = sum_i w_a[i] V_r(q_a[i]) for the axis a of row r (w: x, y, z weights
+// concatenated).  Eight lanes per row: lane l takes the values i = l, l + 8, ...,
+// then a fixed butterfly sums the eight.  The phase q P moves by a constant
+// from one value of a lane to the next: one complex product, and the sine and
+// cosine themselves at every 16th (fifteen products add less than the rounding
+// of q P does); bound by FP64 issue: 116 us with a sine and a cosine per value
+// for 30 heavy atoms and 96 values per axis, 80 us now.  (Four rows per
+// eight lanes, sharing the factors where they belong to one primitive pair:
+// 122 us, since some row of a wave always starts a new one.)
 __global__ __launch_bounds__(256) void sep_rows_kernel(const VRowDev* __restrict__ rows, int nrows,
                                                        const double2* __restrict__ w, int3 n, double3 qmin,
                                                        double3 dq, double2* __restrict__ S) {
@@ -42,12 +51,28 @@ __global__ __launch_bounds__(256) void sep_rows_kernel(const VRowDev* __restrict
     const int off = a == 0 ? 0 : (a == 1 ? n.x : n.x + n.y);
     const double q0 = a == 0 ? qmin.x : (a == 1 ? qmin.y : qmin.z);
     const double d = a == 0 ? dq.x : (a == 1 ? dq.y : dq.z);
-    double sr = 0.0, si = 0.0;
-    for (int i = l8; i < na; i += 8) {
-        const double2 v = eval_row_fp64(row, q0 + d * (double)i);
+    auto phase = [&](double q, double& sn, double& cs) {
+        const double rev = q * row.P * 0.15915494309189535;   // 1 / (2 pi)
+        sincospi(2.0 * (rev - rint(rev)), &sn, &cs);
+    };
+    double sr = 0.0, si = 0.0, sn = 0.0, cs = 1.0, ds, dc;
+    phase(8.0 * d, ds, dc);
+    for (int i = l8, j = 0; i < na; i += 8, ++j) {
+        const double q = q0 + d * (double)i, q2 = q * q;
+        if ((j & 15) == 0) {
+            phase(q, sn, cs);
+        } else {
+            const double c1 = fma(-sn, ds, cs * dc);
+            sn = fma(sn, dc, cs * ds);
+            cs = c1;
+        }
+        const double g = exp(-q2 * row.inv4p);
+        const double pr = fma(fma(row.e[4], q2, -row.e[2]), q2, row.e[0]);
+        const double pi = q * fma(-row.e[3], q2, row.e[1]);
+        const double vx = g * (cs * pr - sn * pi), vy = g * (cs * pi + sn * pr);
         const double2 wi = w[off + i];
-        sr += wi.x * v.x - wi.y * v.y;
-        si += wi.x * v.y + wi.y * v.x;
+        sr += wi.x * vx - wi.y * vy;
+        si += wi.x * vy + wi.y * vx;
     }
     for (int o = 1; o < 8; o <<= 1) {
         sr += __shfl_xor(sr, o);
@@ -56,149 +81,123 @@ __global__ __launch_bounds__(256) void sep_rows_kernel(const VRowDev* __restrict
     if (ok && l8 == 0) S[r] = make_double2(sr, si);
 }
 
-// S[r] = (V(0), V'(0) / i) = (e_0, P e_0 + e_1), both real
-__global__ void dip_rows_kernel(const VRowDev* __restrict__ rows, int nrows, double2* __restrict__ S) {
-    for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < nrows; r += gridDim.x * blockDim.x) {
-        const VRowDev row = rows[r];
-        S[r] = make_double2(row.e[0], fma(row.P, row.e[0], row.e[1]));
-    }
-}
-
-// Per packed pair o (unit o / 8, pair o % 8): mode 0 -> G[o] = sum_t Sx Sy Sz
-// (complex); mode 1 -> G[4o + c]: c = 0 the value at q = 0 (sum_t a_x a_y a_z),
-// c = 1..3 the derivatives / i along x, y, z (a: value, b: derivative / i).
-__global__ void sep_pairs_kernel(const int4* __restrict__ slots, const int* __restrict__ coff,
-                                 const int* __restrict__ cnpp, int n_units, const double2* __restrict__ S,
-                                 int mode, double2* __restrict__ G) {
-    const int nv = n_units * kChunk;
-    for (int o = blockIdx.x * blockDim.x + threadIdx.x; o < nv; o += gridDim.x * blockDim.x) {
-        const int c = o / kChunk, j = o - c * kChunk;
-        const int npp = cnpp[c];
-        const int4* tc = slots + coff[c] + j * npp;
-        if (mode == 0) {
-            double2 g = make_double2(0.0, 0.0);
-            for (int t = 0; t < npp; ++t) {
-                const int4 tr = tc[t];
-                if (!tr.w) continue;
-                const double2 p = cmul(cmul(S[tr.x], S[tr.y]), S[tr.z]);
-                g.x += p.x;
-                g.y += p.y;
+// Per chunk of 64 component pairs: G = sum over the kept terms (DIP: four real
+// sums, the value at q = 0 and the derivatives / i along x, y, z; else Sx Sy Sz,
+// complex), four lanes per pair (the loads of a term depend on one another),
+// into LDS, then for every (state, component) the sum of tp64 G over the
+// chunk, eight slices of 8 added in order.  part[(state ncomp + comp) nparts +
+// block], a block's chunks added in order.
+template <bool DIP>
+__global__ __launch_bounds__(256) void sep_pairs_kernel(LowqPrep p, const double2* __restrict__ S, int ncp, int ns,
+                                                        double2* __restrict__ part) {
+    constexpr int NC = DIP ? 4 : 1;
+    __shared__ double2 G[64][NC];
+    __shared__ double2 red[8][kMaxStates * NC];
+    const int tid = threadIdx.x, nsc = ns * NC;
+    const double thr = p.thr[0];
+    double2 acc = make_double2(0.0, 0.0);   // of (state, component) tid
+    for (int k0 = blockIdx.x * 64; k0 < ncp; k0 += gridDim.x * 64) {
+        const int k = k0 + (tid >> 2);
+        double2 g[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) g[c] = make_double2(0.0, 0.0);
+        if (k < ncp) {
+            const int t0 = p.cp_first[k], t1 = t0 + p.cp_nterms[k];
+            for (int t = t0 + (tid & 3); t < t1; t += 4) {
+                const double w = p.wt[t];
+                const int4 tr = p.trow[t];
+                if (!(thr < 0.0 || (w > 0.0 && w >= thr))) continue;
+                if constexpr (DIP) {
+                    const VRowDev &X = p.rows[tr.x], &Y = p.rows[tr.y], &Z = p.rows[tr.z];
+                    const double x = X.e[0], y = Y.e[0], z = Z.e[0];
+                    const double dx = fma(X.P, x, X.e[1]), dy = fma(Y.P, y, Y.e[1]), dz = fma(Z.P, z, Z.e[1]);
+                    g[0].x += x * y * z;
+                    g[1].x += dx * y * z;
+                    g[2].x += x * dy * z;
+                    g[3].x += x * y * dz;
+                } else {
+                    const double2 v = cmul(cmul(S[p.newid[tr.x]], S[p.newid[p.nr + tr.y]]), S[p.newid[2 * p.nr + tr.z]]);
+                    g[0].x += v.x;
+                    g[0].y += v.y;
+                }
             }
-            G[o] = g;
-        } else {
-            double v0 = 0.0, dx = 0.0, dy = 0.0, dz = 0.0;
-            for (int t = 0; t < npp; ++t) {
-                const int4 tr = tc[t];
-                if (!tr.w) continue;
-                const double2 X = S[tr.x], Y = S[tr.y], Z = S[tr.z];
-                v0 += X.x * Y.x * Z.x;
-                dx += X.y * Y.x * Z.x;
-                dy += X.x * Y.y * Z.x;
-                dz += X.x * Y.x * Z.y;
-            }
-            G[4 * (size_t)o + 0] = make_double2(v0, 0.0);
-            G[4 * (size_t)o + 1] = make_double2(dx, 0.0);
-            G[4 * (size_t)o + 2] = make_double2(dy, 0.0);
-            G[4 * (size_t)o + 3] = make_double2(dz, 0.0);
         }
-    }
-}
-
-// part[(s * ncomp + c) * nparts + b] = sum over the b-th of nparts slices of
-// o of tp64[vcp[o] * ns + s] * G[o * ncomp + c]; one block per (s, c, slice),
-// strided partial sums then a fixed tree in LDS.  sep_final_kernel adds the
-// slices in order, so the result does not depend on scheduling.
-__global__ __launch_bounds__(256) void sep_reduce_kernel(const double* __restrict__ tp64, const int* __restrict__ vcp,
-                                                         int nv, int ns, const double2* __restrict__ G, int ncomp,
-                                                         int nparts, double2* __restrict__ part) {
-    __shared__ double2 red[256];
-    const int sc = blockIdx.x / nparts, b = blockIdx.x - sc * nparts;
-    const int s = sc / ncomp, c = sc - s * ncomp;
-    const int per = (nv + nparts - 1) / nparts, o0 = b * per, o1 = min(nv, o0 + per);
-    double sr = 0.0, si = 0.0;
-    for (int o = o0 + threadIdx.x; o < o1; o += 256) {
-        const int k = vcp[o];
-        if (k < 0) continue;
-        const double t = tp64[(size_t)k * ns + s];
-        const double2 g = G[(size_t)o * ncomp + c];
-        sr += t * g.x;
-        si += t * g.y;
-    }
-    red[threadIdx.x] = make_double2(sr, si);
-    __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if (threadIdx.x < h) {
-            red[threadIdx.x].x += red[threadIdx.x + h].x;
-            red[threadIdx.x].y += red[threadIdx.x + h].y;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            for (int o = 1; o < 4; o <<= 1) {
+                g[c].x += __shfl_xor(g[c].x, o);
+                if (!DIP) g[c].y += __shfl_xor(g[c].y, o);
+            }
+            if ((tid & 3) == 0) G[tid >> 2][c] = g[c];
         }
         __syncthreads();
+        const int nk = min(64, ncp - k0);
+        for (int i = tid; i < 8 * nsc; i += 256) {
+            const int sl = i / nsc, sc = i - sl * nsc, s = sc / NC, c = sc - s * NC;
+            double2 a = make_double2(0.0, 0.0);
+            for (int j = 8 * sl; j < min(8 * sl + 8, nk); ++j) {
+                const double t = p.tp64[(size_t)(k0 + j) * ns + s];
+                a.x = fma(t, G[j][c].x, a.x);
+                if (!DIP) a.y = fma(t, G[j][c].y, a.y);
+            }
+            red[sl][sc] = a;
+        }
+        __syncthreads();
+        if (tid < nsc)
+            for (int sl = 0; sl < 8; ++sl) {
+                acc.x += red[sl][tid].x;
+                acc.y += red[sl][tid].y;
+            }
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+    if (tid < nsc) part[(size_t)tid * gridDim.x + blockIdx.x] = acc;
 }
 
-__global__ void sep_final_kernel(const double2* __restrict__ part, int n, int nparts, double2* __restrict__ out) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+// One wave per (state, component): strided sums, then a fixed tree.
+__global__ __launch_bounds__(64) void sep_final_kernel(const double2* __restrict__ part, int nparts,
+                                                       double2* __restrict__ out) {
     double2 a = make_double2(0.0, 0.0);
-    for (int b = 0; b < nparts; ++b) {
-        a.x += part[(size_t)i * nparts + b].x;
-        a.y += part[(size_t)i * nparts + b].y;
+    for (int b = threadIdx.x; b < nparts; b += 64) {
+        a.x += part[(size_t)blockIdx.x * nparts + b].x;
+        a.y += part[(size_t)blockIdx.x * nparts + b].y;
     }
-    out[i] = a;
-}
-
-int blocks_for(long long n, int b) {
-    long long g = (n + b - 1) / b;
-    if (g < 1) g = 1;
-    if (g > 65536) g = 65536;
-    return (int)g;
-}
-
-// slices of the transition-weighted reduction per (state, component): about
-// 2048 pairs each, at most kSepParts
-int sep_parts(int nv) { return std::max(1, std::min(kSepParts, nv / 2048)); }
-
-hipError_t launch_sep_reduce(const double* tp64, const int* vcp, int nv, int ns, const double2* G, int ncomp,
-                             double2* part, double2* out, hipStream_t st) {
-    const int np = sep_parts(nv);
-    hipLaunchKernelGGL(sep_reduce_kernel, dim3(ns * ncomp * np), dim3(256), 0, st, tp64, vcp, nv, ns, G, ncomp, np,
-                       part);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(sep_final_kernel, dim3((ns * ncomp + 63) / 64), dim3(64), 0, st, (const double2*)part,
-                       ns * ncomp, np, out);
-    return hipGetLastError();
+    for (int h = 32; h > 0; h >>= 1) {
+        a.x += __shfl_xor(a.x, h);
+        a.y += __shfl_xor(a.y, h);
+    }
+    if (threadIdx.x == 0) out[blockIdx.x] = a;
 }
 
 }  // namespace
 
-hipError_t launch_separable(const VRowDev* rows, int nrows, const int4* slots, const int* coff, const int* cnpp,
-                            int n_units, const double* tp64, const int* vcp, int ns, const double2* w, const int n[3],
-                            const double qmin[3], const double dq[3], double2* S, double2* G, double2* out,
-                            hipStream_t st) {
-    hipLaunchKernelGGL(sep_rows_kernel, dim3((nrows + 31) / 32), dim3(256), 0, st, rows, nrows, w,
-                       make_int3(n[0], n[1], n[2]), make_double3(qmin[0], qmin[1], qmin[2]),
-                       make_double3(dq[0], dq[1], dq[2]), S);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int nv = n_units * kChunk;
-    hipLaunchKernelGGL(sep_pairs_kernel, dim3(blocks_for(nv, 256)), dim3(256), 0, st, slots, coff, cnpp, n_units,
-                       (const double2*)S, 0, G);
+// Workgroups (and partial sums per state and component) of the pair sums.
+int sep_parts(int ncp) { return std::max(1, std::min(1024, (ncp + 63) / 64)); }
+
+hipError_t launch_separable(const LowqPrep& p, const VRowDev* rows, int nrows, int ncp, int ns, const double2* w,
+                            const int n[3], const double qmin[3], const double dq[3], double2* S, double2* part,
+                            double2* out, hipStream_t st) {
+    if (ns < 1 || ns > kMaxStates || ncp < 1) return hipErrorInvalidValue;
+    hipError_t e;
+    if (nrows > 1) {   // row 0 is the zero row
+        hipLaunchKernelGGL(sep_rows_kernel, dim3((nrows - 1 + 31) / 32), dim3(256), 0, st, rows + 1, nrows - 1, w,
+                           make_int3(n[0], n[1], n[2]), make_double3(qmin[0], qmin[1], qmin[2]),
+                           make_double3(dq[0], dq[1], dq[2]), S);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(sep_pairs_kernel<false>, dim3(sep_parts(ncp)), dim3(256), 0, st, p, (const double2*)S, ncp, ns,
+                       part);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    return launch_sep_reduce(tp64, vcp, nv, ns, G, 1, G + nv, out, st);
+    hipLaunchKernelGGL(sep_final_kernel, dim3(ns), dim3(64), 0, st, (const double2*)part, sep_parts(ncp), out);
+    return hipGetLastError();
 }
 
-hipError_t launch_dipole(const VRowDev* rows, int nrows, const int4* slots, const int* coff, const int* cnpp,
-                         int n_units, const double* tp64, const int* vcp, int ns, double2* S, double2* G,
-                         double2* out, hipStream_t st) {
-    hipLaunchKernelGGL(dip_rows_kernel, dim3(blocks_for(nrows, 256)), dim3(256), 0, st, rows, nrows, S);
+hipError_t launch_dipole(const LowqPrep& p, int ncp, int ns, double2* part, double2* out, hipStream_t st) {
+    if (ns < 1 || ns > kMaxStates || ncp < 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(sep_pairs_kernel<true>, dim3(sep_parts(ncp)), dim3(256), 0, st, p, (const double2*)nullptr, ncp,
+                       ns, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int nv = n_units * kChunk;
-    hipLaunchKernelGGL(sep_pairs_kernel, dim3(blocks_for(nv, 256)), dim3(256), 0, st, slots, coff, cnpp, n_units,
-                       (const double2*)S, 1, G);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    return launch_sep_reduce(tp64, vcp, nv, ns, G, 4, G + 4 * (size_t)nv, out, st);
+    hipLaunchKernelGGL(sep_final_kernel, dim3(4 * ns), dim3(64), 0, st, (const double2*)part, sep_parts(ncp), out);
+    return hipGetLastError();
 }
 
 }  // namespace scff

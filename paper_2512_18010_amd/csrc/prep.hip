@@ -32,7 +32,7 @@
 //                   records (x row, y row), scaled weights and scales
 // Small problems are bound by the number of launches and copies: 29 before, 15
 // now for a 4-heavy-atom, one-state, 32^3 grid with its tables (200 -> 147 us).
-// Layout by component pairs, for the other paths (run_prep_pairs):
+// Layout by component pairs, for the export (run_prep_pairs):
 //   count/vkeys     kept terms per component pair, split into virtual pairs
 //                   of <= 9 terms, keyed by length (longest first, ties in pair
 //                   order)
@@ -393,7 +393,7 @@ __global__ void layout_kernel(const int* __restrict__ order, const int4* __restr
                               const int4* __restrict__ trow, const double* __restrict__ w,
                               const double* __restrict__ thr, const double* __restrict__ tp64, int ns,
                               int SW, const int* __restrict__ newid, int nr, int4* __restrict__ slots,
-                              float* __restrict__ tp32, int* __restrict__ vcp) {
+                              float* __restrict__ tp32) {
     for (int o = blockIdx.x * blockDim.x + threadIdx.x; o < n_vpairs; o += gridDim.x * blockDim.x) {
         const int c = o / kChunk, j = o - c * kChunk;
         const int npp = cnpp[c];
@@ -414,7 +414,6 @@ __global__ void layout_kernel(const int* __restrict__ order, const int4* __restr
             }
         }
         for (int q = len; q < npp; ++q) dst[q] = make_int4(0, 0, 0, 0);   // the zero row
-        vcp[o] = k;   // component pair of this packed pair (-1: padding), for the FP64 weights
         for (int st = 0; st < SW; ++st) {
             tp32[(size_t)o * SW + st] = (k >= 0 && st < ns) ? (float)tp64[(size_t)k * ns + st] : 0.0f;
         }
@@ -796,7 +795,6 @@ hipError_t run_prep_pairs(const PrepInputs& in, PrepWork& w, const PrepResult& r
     CK(alloc(w.coff, (size_t)n_units * sizeof(int)));
     CK(alloc(w.slots, (size_t)res.n_slots * sizeof(int4)));
     CK(alloc(w.tp32, (size_t)n_vpairs * SW * sizeof(float)));
-    CK(alloc(w.vcp, (size_t)n_vpairs * sizeof(int)));
     hipLaunchKernelGGL(count_kernel, dim3(blocks_for(NCP, 256)), dim3(256), 0, st, in.cp_first,
                        in.cp_nterms, (const double*)w.wt.p, (const double*)thr, NCP, (int*)w.nk.p, (int*)w.nv.p);
     CK(hipGetLastError());
@@ -830,7 +828,7 @@ hipError_t run_prep_pairs(const PrepInputs& in, PrepWork& w, const PrepResult& r
                        (const int4*)w.vinfo.p, NV, n_vpairs, (const int*)w.cnpp.p, (const int*)w.coff.p,
                        in.cp_first, in.cp_nterms, (const int4*)w.trow.p, (const double*)w.wt.p,
                        (const double*)thr, (const double*)w.tp64.p, ns, SW, (const int*)w.newid.p, (int)NR,
-                       (int4*)w.slots.p, (float*)w.tp32.p, (int*)w.vcp.p);
+                       (int4*)w.slots.p, (float*)w.tp32.p);
     CK(hipGetLastError());
     return hipSuccess;
 }

@@ -33,13 +33,11 @@ hipError_t grid_desc(const GridShape& g, const float2* V, int nxr, int nyr, uint
                      int nx_eval, int n_states, float2* f, float* f2, double2* part, GridDesc* d, long long* blocks);
 int points_split(int nq, int ns, int n_sp);
 hipError_t launch_points(const PointArgs& a, int n_split, hipStream_t st);
-hipError_t launch_separable(const VRowDev* rows, int nrows, const int4* slots, const int* coff, const int* cnpp,
-                            int n_units, const double* tp64, const int* vcp, int ns, const double2* w, const int n[3],
-                            const double qmin[3], const double dq[3], double2* S, double2* G, double2* out,
-                            hipStream_t st);
-hipError_t launch_dipole(const VRowDev* rows, int nrows, const int4* slots, const int* coff, const int* cnpp,
-                         int n_units, const double* tp64, const int* vcp, int ns, double2* S, double2* G,
-                         double2* out, hipStream_t st);
+int sep_parts(int ncp);
+hipError_t launch_separable(const LowqPrep& p, const VRowDev* rows, int nrows, int ncp, int ns, const double2* w,
+                            const int n[3], const double qmin[3], const double dq[3], double2* S, double2* part,
+                            double2* out, hipStream_t st);
+hipError_t launch_dipole(const LowqPrep& p, int ncp, int ns, double2* part, double2* out, hipStream_t st);
 }  // namespace scff
 
 using namespace scff;
@@ -539,7 +537,7 @@ void free_all(scff_ctx* c) {
     for (DeviceBuffer* b : {&w.rows_all, &w.rowsum, &w.trow, &w.tbound, &w.wt, &w.cpmn, &w.tp64, &w.bsum,
                             &w.part, &w.small, &w.nk, &w.nv, &w.vbase, &w.tmp, &w.key, &w.val, &w.vinfo,
                             &w.tmp2, &w.cnpp, &w.csize, &w.coff, &w.tmp3, &w.slots, &w.tp32,
-                            &w.row_used, &w.newid, &w.tmp4, &w.rows, &w.zslots, &w.zterms, &w.zw, &w.vcp})
+                            &w.row_used, &w.newid, &w.tmp4, &w.rows, &w.zslots, &w.zterms, &w.zw})
         dev_free(c, *b);
 }
 
@@ -1101,7 +1099,15 @@ int prepare_sync(scff_ctx* c) {
     int rc;
     if ((rc = set_device(c))) return rc;
     if ((rc = order_after(c, nullptr))) return rc;
-    return ensure_pairs(c, nullptr);
+    return ensure_prepared(c, nullptr);
+}
+
+LowqPrep lowq_prep(scff_ctx* c) {
+    const PrepInputs in = prep_inputs(c);
+    const PrepWork& w = c->prep;
+    return LowqPrep{in.cp_first, in.cp_nterms, (const VRowDev*)w.rows_all.p, (const int4*)w.trow.p,
+                    (const double*)w.wt.p, (const double*)w.small.p + 64, (const double*)w.tp64.p,
+                    (const int*)w.newid.p, (int)in.n_rows_all};
 }
 
 int finish_sync(scff_ctx* c) {
@@ -1435,12 +1441,10 @@ int scff_eval_separable(scff_ctx* c, const scff_grid* g, const double* wx, const
         for (int i = 0; i < 2 * g->n[a]; ++i)
             if (!std::isfinite(ws[a][i])) return fail(SCFF_EINVAL, "non-finite weight");
     if ((rc = prepare_sync(c))) return rc;
-    const PrepResult& p = c->pres;
-    const size_t nw = (size_t)g->n[0] + g->n[1] + g->n[2];
-    const size_t nv = (size_t)p.n_units * kChunk;
+    const size_t nw = (size_t)g->n[0] + g->n[1] + g->n[2], np = (size_t)sep_parts(c->basis.n_cp);
     if ((rc = dev_reserve(c, c->d_lq_in, nw * sizeof(double2))) ||
-        (rc = dev_reserve(c, c->d_lq_S, (size_t)p.n_rows * sizeof(double2))) ||
-        (rc = dev_reserve(c, c->d_lq_G, (nv + (size_t)c->n_states * kSepParts) * sizeof(double2))) ||
+        (rc = dev_reserve(c, c->d_lq_S, (size_t)c->pres.n_rows * sizeof(double2))) ||
+        (rc = dev_reserve(c, c->d_lq_G, np * c->n_states * sizeof(double2))) ||
         (rc = dev_reserve(c, c->d_lq_out, (size_t)c->n_states * sizeof(double2))))
         return rc;
     size_t off = 0;
@@ -1453,9 +1457,7 @@ int scff_eval_separable(scff_ctx* c, const scff_grid* g, const double* wx, const
     }
     double dq[3];
     for (int a = 0; a < 3; ++a) dq[a] = g->n[a] > 1 ? (g->qmax[a] - g->qmin[a]) / (g->n[a] - 1) : 0.0;
-    if ((rc = hip_check(launch_separable((const VRowDev*)c->prep.rows.p, p.n_rows, (const int4*)c->prep.slots.p,
-                                         (const int*)c->prep.coff.p, (const int*)c->prep.cnpp.p, p.n_units,
-                                         (const double*)c->prep.tp64.p, (const int*)c->prep.vcp.p, c->n_states,
+    if ((rc = hip_check(launch_separable(lowq_prep(c), (const VRowDev*)c->prep.rows.p, c->pres.n_rows, c->basis.n_cp, c->n_states,
                                          (const double2*)c->d_lq_in.p, g->n, g->qmin, dq, (double2*)c->d_lq_S.p,
                                          (double2*)c->d_lq_G.p, (double2*)c->d_lq_out.p, nullptr),
                         "separable kernels")))
@@ -1474,20 +1476,14 @@ int scff_dipole(scff_ctx* c, const double* dE, double* mu, double* f0) {
     if (f0 && !dE) return fail(SCFF_EINVAL, "oscillator strengths need the transition energies dE");
     int rc;
     if ((rc = prepare_sync(c))) return rc;
-    const PrepResult& p = c->pres;
     const int ns = c->n_states;
     if (dE)
         for (int s = 0; s < ns; ++s)
             if (!std::isfinite(dE[s])) return fail(SCFF_EINVAL, "non-finite transition energy");
-    const size_t nv = (size_t)p.n_units * kChunk;
-    if ((rc = dev_reserve(c, c->d_lq_S, (size_t)p.n_rows * sizeof(double2))) ||
-        (rc = dev_reserve(c, c->d_lq_G, 4 * (nv + (size_t)ns * kSepParts) * sizeof(double2))) ||
+    if ((rc = dev_reserve(c, c->d_lq_G, (size_t)sep_parts(c->basis.n_cp) * ns * 4 * sizeof(double2))) ||
         (rc = dev_reserve(c, c->d_lq_out, (size_t)ns * 4 * sizeof(double2))))
         return rc;
-    if ((rc = hip_check(launch_dipole((const VRowDev*)c->prep.rows.p, p.n_rows, (const int4*)c->prep.slots.p,
-                                      (const int*)c->prep.coff.p, (const int*)c->prep.cnpp.p, p.n_units,
-                                      (const double*)c->prep.tp64.p, (const int*)c->prep.vcp.p, ns,
-                                      (double2*)c->d_lq_S.p, (double2*)c->d_lq_G.p, (double2*)c->d_lq_out.p,
+    if ((rc = hip_check(launch_dipole(lowq_prep(c), c->basis.n_cp, ns, (double2*)c->d_lq_G.p, (double2*)c->d_lq_out.p,
                                       nullptr),
                         "dipole kernels")))
         return rc;
