@@ -316,13 +316,13 @@ def fft_benchmark(ctx, stream, n_axis, steps, warmup, log, precision="fp32"):
     passes = sum(1 for a in range(3) if n[a] > 1)
     tr_bytes = passes * 2 * nb * npts * 8 + 2 * nb * npts * 8 + ns * npts * 12
     bf = precision == "bf16x3"
-    peak = PEAK_BF16_MFMA if bf else PEAK_FP32_MFMA
-    # matrix-core instructions as issued: per 16-point tile, state and row block rb
-    # of 16 functions, the k-steps from the block's diagonal to the end
-    nbf_pad = (nbf + 15) // 16 * 16
-    RB, kstep = nbf_pad // 16, (8 if bf else 4)
-    n_mfma = ns * ((npts + 15) // 16) * sum(nbf_pad // kstep - 16 * rb // kstep for rb in range(RB))
-    issued = n_mfma * 2.0 * 16 * 16 * (32 if bf else 4)
+    peak = PEAK_BF16_MFMA   # split BF16 or split f16 operands: the same rate
+    # matrix-core instructions (16x16x32) as issued: per 16-point tile, state and
+    # row block of 16 functions, three (split f16) or two (split BF16) per group
+    # of 16 functions from the block's diagonal to the end
+    RB = (nbf + 15) // 16
+    n_mfma = ns * ((npts + 15) // 16) * (RB * (RB + 1) // 2) * (2 if bf else 3)
+    issued = n_mfma * 2.0 * 16 * 16 * 32
     log(f"fft method {n} {precision}: {ms:.2f} ms/step, density {dens_ms:.2f} ms ({flops / dens_ms / 1e9:.1f} TFLOP/s), "
         f"transforms {tr_ms:.2f} ms, density error {e_phi.max():.2e}, Parseval {e_par.max():.2e}")
     return {
@@ -386,7 +386,7 @@ def lowq_benchmark(ctx, case, log, calls=20):
             "ms_per_call": sep_ms, "calls": calls,
             "value": ns * nq / (sep_ms * 1e-3), "unit": "equivalent q-points*transitions/s",
             "note": "host-timed synchronous calls (weights in, I_s out): three small FP64 kernels "
-                    "(row sums, triple products per term, transition-weighted reduction), latency-bound",
+                    "(row sums, triple products per term with their transition-weighted sums, final sums)",
             "relative_difference_vs_fp32_grid": e_sep},
         "dipole": {"ms_per_call": dip_ms, "calls": calls,
                    "mu_norm": [float(x) for x in np.linalg.norm(mu, axis=1)],
@@ -441,7 +441,12 @@ def sph_benchmark(ctx, stream, lmax, n, steps, warmup, log):
     n_geo = int(sum(int(W.mol.shell_nprim[a]) * int(W.mol.shell_nprim[b])
                     for a in range(W.mol.n_shells) for b in range(a, W.mol.n_shells)))
     ncols = (lmax + 5) ** 2
-    flops = 8.0 * ns * 25 * ncols * n_geo * n
+    # one real multiply-add per (transition, lam mu, L M, geometry with l_A + l_B >=
+    # lam, radius): a pair's polynomial has harmonics lam <= l_A + l_B only
+    rows = sum((2 * lam + 1) * int(W.mol.shell_nprim[a]) * int(W.mol.shell_nprim[b])
+               for a in range(W.mol.n_shells) for b in range(a, W.mol.n_shells)
+               for lam in range(int(W.mol.shell_l[a]) + int(W.mol.shell_l[b]) + 1))
+    flops = 2.0 * ns * rows * ncols * n
     del T_dev, f, f2, R, avg
     log(f"spherical method lmax {lmax}, {n}^3: {ms:.2f} ms/step, contraction {con_ms:.2f} ms "
         f"({flops / con_ms / 1e9:.1f} TFLOP/s FP64), geometry {geom_ms:.2f} ms, rest {rest_ms:.2f} ms, "
@@ -454,8 +459,9 @@ def sph_benchmark(ctx, stream, lmax, n, steps, warmup, log):
         "stages_ms": {"geometry": geom_ms, "contraction": con_ms, "coupling_and_grid": rest_ms},
         "roofline": {"bound": "fp64", "kernel": "sph_q_kernel", "achieved": flops / (con_ms * 1e-3) / 1e12,
                      "peak": 78.6, "unit": "TFLOP/s", "frac": flops / (con_ms * 1e-3) / 78.6e12,
-                     "per_unit": "8 flops per (transition, harmonic lam mu <= 4, harmonic L M <= lmax + 4, "
-                                 "geometry, radius): one complex multiply-add of the contraction over geometries"},
+                     "per_unit": "2 flops per (transition, harmonic lam mu <= 4, harmonic L M <= lmax + 4, "
+                                 "geometry with l_A + l_B >= lam, radius): one real multiply-add of the "
+                                 "contraction over geometries"},
         "errors_vs_oracle": {"R_relative_max": float(e_R.max()), "R_per_transition": [float(x) for x in e_R],
                              "radius": float(qs[k])},
     }
