@@ -633,8 +633,13 @@ hipError_t launch_grid_tables(const VRowDev* rows, int nxr, int nyr, const int2*
 // and, in FP32, their fold) and forming U, which every column tile repeats: about
 // 16 CG + 30 (in units of one matrix instruction).  Two terms per step where
 // the LDS allows (one barrier for both), else one (one or two states: W has up to
-// 64 lines).
-GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect) {
+// 64 lines).  FP32 precision stops at three column groups: the totals of a fourth
+// spill 34 registers of 256 (10 heavy atoms, 12 states, 128^3, whose 64 columns are
+// then two tiles of two: 27.4 -> 21.6 ms; 48x48x256, 128 columns, three tiles of three:
+// 8.9 -> 6.2 ms).
+int max_cg(int precision) { return precision == 0 ? 3 : 4; }
+
+GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect, int precision) {
     GridShape g{};
     g.reflect = reflect ? 1 : 0;
     g.ncol = reflect ? (n[2] + 1) / 2 : n[2];
@@ -650,7 +655,7 @@ GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect) {
         g.np = std::max(g.np, p);
     }
     long long best = 0;
-    for (int cg = 1; cg <= 4; ++cg) {
+    for (int cg = 1; cg <= max_cg(precision); ++cg) {
         int tcm = 2;
         auto bytes = [&] { return 4 * (2 * cg * 1024 + 2 * tcm * (48 * n_states + 2 * g.np * kWLine)); };
         if (bytes() > kGridLds) tcm = 1;
@@ -670,12 +675,13 @@ GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect) {
 }
 
 // Workgroups resident per CU: what the registers allow (FP64 totals of two and
-// more quads: two waves per SIMD, else three), and the 160 KB of LDS.
+// three column groups: two waves per SIMD, else three), and the 160 KB of LDS.
 int grid_wgs_per_cu(int cls, int lds) {
-    const int by_regs = cls >= 1 && cls <= 3 ? 2 : 3;
+    const int by_regs = cls == 1 || cls == 2 ? 2 : 3;
     return std::min(by_regs, 160 * 1024 / (lds + 1024));
 }
 
+// The kernel's variant; class 3 (four column groups with totals) does not exist.
 int grid_class(const GridShape& g, int precision) { return (g.cg - 1) + 4 * precision; }
 
 hipError_t grid_desc(const GridShape& g, const float2* V, int nxr, int nyr, uint32_t ybase, const uint4* Bt, const KSteps& steps,
@@ -725,7 +731,6 @@ hipError_t grid_desc(const GridShape& g, const float2* V, int nxr, int nyr, uint
         case 0: hipLaunchKernelGGL((KERNEL<1, true>), __VA_ARGS__); break;        \
         case 1: hipLaunchKernelGGL((KERNEL<2, true>), __VA_ARGS__); break;        \
         case 2: hipLaunchKernelGGL((KERNEL<3, true>), __VA_ARGS__); break;        \
-        case 3: hipLaunchKernelGGL((KERNEL<4, true>), __VA_ARGS__); break;        \
         case 4: hipLaunchKernelGGL((KERNEL<1, false>), __VA_ARGS__); break;       \
         case 5: hipLaunchKernelGGL((KERNEL<2, false>), __VA_ARGS__); break;       \
         case 6: hipLaunchKernelGGL((KERNEL<3, false>), __VA_ARGS__); break;       \

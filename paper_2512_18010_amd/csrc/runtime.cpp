@@ -21,7 +21,7 @@ int vtable_stride(const int n[3]);
 hipError_t launch_grid_tables(const VRowDev* rows, int nxr, int nyr, const int2* zslots, int n_zpad, const GridShape& g,
                               const int n[3], const double qmin[3], const double dq[3], float2* X, float2* Y, uint4* Bt,
                               hipStream_t st);
-GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect);
+GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect, int precision);
 int grid_wgs_per_cu(int cls, int lds);
 hipError_t launch_grid(int cls, const GridShape& g, const GridDesc& d, long long blocks, hipStream_t st);
 hipError_t launch_reduce(const double2* part, int n_split, const int n[3], int nx_eval, int n_states, float2* f,
@@ -448,7 +448,7 @@ struct EvalPlan {
 EvalPlan plan_eval(const scff_ctx* c, const scff_grid* g, int precision, bool allow_split = true) {
     EvalPlan e{};
     e.nx_eval = (c->symmetry && grid_symmetric(g)) ? (g->n[0] + 1) / 2 : g->n[0];
-    e.shape = grid_shape(g->n, e.nx_eval, c->n_states, z_reflects(g));
+    e.shape = grid_shape(g->n, e.nx_eval, c->n_states, z_reflects(g), precision);
     const int nst = c->pres.n_ksteps;
     const long long tiles = (long long)e.shape.ntl * e.shape.ntc, 
                     slots = (long long)grid_wgs_per_cu(grid_class(e.shape, precision), e.shape.lds) * c->n_cu;
