@@ -636,7 +636,8 @@ hipError_t launch_grid_tables(const VRowDev* rows, int nxr, int nyr, const int2*
 // 64 lines).  FP32 precision stops at three column groups: the totals of a fourth
 // spill 34 registers of 256 (10 heavy atoms, 12 states, 128^3, whose 64 columns are
 // then two tiles of two: 27.4 -> 21.6 ms; 48x48x256, 128 columns, three tiles of three:
-// 8.9 -> 6.2 ms).
+// 8.9 -> 6.2 ms).  At most one group of padding: the z blocks then stay within
+// rows x vtable_stride, by which a grid is accepted.
 int max_cg(int precision) { return precision == 0 ? 3 : 4; }
 
 GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect, int precision) {
@@ -661,6 +662,7 @@ GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect, in
         if (bytes() > kGridLds) tcm = 1;
         if (bytes() > kGridLds) break;
         const int nt = (ng + cg - 1) / cg;
+        if (nt * cg > ng + 1) continue;
         const long long cost = (long long)nt * (16 * cg + 30);
         if (!g.cg || cost < best) {
             best = cost;
