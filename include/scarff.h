@@ -181,10 +181,10 @@ int scff_eval_grid(scff_ctx* ctx, const scff_grid* grid, int precision, float* f
  * loops, harnesses that forbid hipMalloc).  It computes exactly what
  * scff_eval_grid computes into device outputs, with the same kernels, but
  * calls no hipMalloc, hipFree or allocating library routine: the 1D tables
- * of the grid, and the FP64 partial sums of a split chunk list when they
+ * of the grid, and the FP64 partial sums of a split evaluation when they
  * fit after the tables, live in a static per-device scratch array of
- * 256 MiB (held by every device the library runs on until the process ends;
- * the 190-function, 64^3 problem's tables take 81 MB).
+ * 256 MiB (held by every device the library runs on until the process
+ * ends).
  *   f, f2          device pointers as for scff_eval_grid with
  *                  out_on_device = 1 (either may be NULL); asynchronous on
  *                  hip_stream (NULL = default stream).

@@ -199,7 +199,7 @@ struct PrepWork {
         tmp, key, val, vinfo, tmp2, cnpp, csize, coff, tmp3, slots, tp32, row_used, newid, tmp4,
         rows, zslots, zterms, zw;
     // pinned host memory of the context (kPinnedBytes, or NULL if it could
-    // not be allocated): small readbacks and the chunk table travel through
+    // not be allocated): small readbacks and the molecule upload travel through
     // it by DMA; every use is complete before run_prep returns
     void* pinned = nullptr;
 };
@@ -207,7 +207,7 @@ struct PrepWork {
 constexpr size_t kPinnedBytes = (size_t)4 << 20;
 // byte offsets in the precompute's small buffer
 constexpr size_t kSmallStats = 1024, kSmallSinv = 1280, kSmallKs = 1792, kSmallMeta = 2048, kSmallZmax = 2304;
-constexpr size_t kPinnedTables = 4096;   // byte offset of the chunk table / molecule upload
+constexpr size_t kPinnedTables = 4096;   // byte offset of the molecule upload
 
 struct PrepResult {
     int n_rows = 0, n_x = 0, n_y = 0;   // compacted rows: the zero row, n_x x rows, n_y y rows, the z rows
@@ -258,9 +258,8 @@ constexpr size_t kFftLdsBytes = (size_t)78 << 10;
 // Column blocks of 16 points per density workgroup for nbf_pad basis rows
 // (4, 2 or 1), 0 if the AO block does not fit lds_limit bytes of LDS.
 int fft_density_cb(int nbf_pad, size_t lds_limit);
-// precision: SCFF_FP32 (FP32 weights, Ap holds ns RB KS 64 floats) or
-// SCFF_BF16X3 (split-BF16 weights of 4 functions per lane, ns RB RB 64 uint4:
-// the same bytes).
+// precision: SCFF_FP32 (weights in three f16 parts) or SCFF_BF16X3 (split-BF16
+// weights), as operands of 16x16x32 products.
 size_t fft_pack_bytes(int precision, int nbf_pad, int ns);   // of the array that launch_fft_pack fills
 hipError_t launch_fft_pack(int precision, const double* T, const double* cnorm, int nbf, int nbf_pad, int ns,
                            double spin, void* Ap, hipStream_t st);

@@ -98,7 +98,7 @@ struct scff_ctx {
     // (environment SCFF_VALIDATE set and not "0" when the context is created)
     bool validate = false;
     int n_cu = 256;     // compute units of the device
-    DeviceBuffer d_part;   // FP64 partial results of a split chunk list
+    DeviceBuffer d_part;   // FP64 partial results of split k-steps
     // FP64 low-momentum and separable work: weights / points, per-row and
     // per-pair values, per-state results
     DeviceBuffer d_lq_in, d_lq_S, d_lq_G, d_lq_out;
