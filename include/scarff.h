@@ -54,7 +54,8 @@ extern "C" {
 
 /* ---- precision of the pair contraction (paper Sec. 5.3 step "final grid
  *      contraction"; precision is this engine's choice) -------------------- */
-#define SCFF_FP32    0   /* FP32 generator + FP32 MFMA contraction              */
+#define SCFF_FP32    0   /* FP32 values; matrix products of BF16 triples (24 bits,
+                            FP32's exponent range), FP64 totals                 */
 #define SCFF_BF16X3  1   /* FP32 generator + split-BF16 (hi*hi+hi*lo+lo*hi) MFMA */
 
 typedef struct scff_ctx scff_ctx;

@@ -33,7 +33,8 @@ constexpr int kMaxChunkTerms = kChunk * kMaxTermsPerPair;   // 72
 constexpr int kZStep = 32;
 constexpr int kZTerms = 9;
 constexpr int kWPasses = 2;       // W items per lane whose loads go out a step ahead
-constexpr int kGridLds = 65536 - 16;   // LDS bytes of a workgroup (the batch kernel adds 16)
+constexpr int kGridLds = 81920 - 16;   // LDS bytes of a workgroup, at most: half a CU's (the batch kernel adds 16)
+constexpr int kLdsGranule = 1280;      // a CU's 160 KB in 128 blocks
 constexpr int kWLine = 84;        // floats of W per line: 4 groups of 8 z rows, padded apart in the banks
 constexpr int kGridClasses = 8;   // kernel variants: column groups per tile x precision
 // Term counts of the k-steps, longest rows first: k-step k has the largest n
@@ -65,9 +66,9 @@ struct ChunkSplit {
 // axis symmetric about 0), column groups of 16 per tile (cg) and in all (ncg,
 // padded to whole tiles), row and column tiles, lines per qx (padded to pairs),
 // terms of a k-step handled between two barriers, most line pairs a tile
-// touches, LDS bytes of a workgroup.
+// touches, planes of a V block, LDS bytes of a workgroup.
 struct GridShape {
-    int reflect, ncol, iz0, cg, ntc, ncg, ntl, nyp, tcm, np, lds;
+    int reflect, ncol, iz0, cg, ntc, ncg, ntl, nyp, tcm, np, planes, lds;
 };
 // Everything the fused grid kernel needs for one evaluation (one request of
 // a batch): the x / y tables, the z axis' operand blocks, the k-steps with
@@ -233,10 +234,12 @@ hipError_t run_prep_pairs(const PrepInputs& in, PrepWork& w, const PrepResult& r
 
 // ---- static scratch (scratch.hip) ----
 // Bytes of the per-device scratch array of scff_eval_grid_noalloc.
-// kScratchBytes is the limit on a grid's tables; kScratchSlack covers z rows
-// padded to whole k-steps and column tiles when there are few of them.
+// kScratchBytes is the limit on a grid's tables of 8 bytes per (row, value);
+// kScratchSlack covers the z axis' 12 bytes in FP32 precision (at most 9 of 19
+// rows of a primitive pair are z rows, so 0.24 of the limit) and z rows padded
+// to whole k-steps and column tiles when there are few of them.
 constexpr size_t kScratchBytes = (size_t)256 << 20;
-constexpr size_t kScratchSlack = (size_t)8 << 20;
+constexpr size_t kScratchSlack = (size_t)72 << 20;
 // Device address of this device's array (device current; resolved once).
 hipError_t scratch_address(int device, void** ptr);
 
@@ -374,6 +377,7 @@ int ctx_batch_finish(scff_ctx* c, const scff_grid* g, const BatchEval& be, float
 // asynchronous work pending.
 void ctx_batch_done(scff_ctx* c);
 // Grid kernel launchers (kernels.hip)
+hipError_t grid_allow_lds();   // once per device, before the first launch on it
 int grid_wgs_per_cu(int cls, int lds);
 hipError_t launch_grid_batch(int cls, int lds, const GridDesc* descs, const int2* items, int n_items, int* counter, int wgs,
                              hipStream_t st);

@@ -15,9 +15,10 @@
 //    cancel, and FP32 evaluation would leave errors proportional to its bound
 //    rather than to its value.  Exported only; the grid kernel reads
 //    tables_kernel's layouts of the same values.
-//  * grid_kernel: the sum contracted over z rows on the f16 matrix cores (hi +
-//    lo halves, FP32 accumulation; FP32 precision folds into FP64 totals); the
-//    operand is formed on the VALU.  grid_batch_kernel: the same tiles popped
+//  * grid_kernel: the sum contracted over z rows on the matrix cores (FP32
+//    accumulation; FP32 precision: three BF16 parts per operand, folded into
+//    FP64 totals; split precision: two f16 halves); the operand is formed on the
+//    VALU.  grid_batch_kernel: the same tiles popped
 //    from a queue of several requests.
 #include <hip/hip_runtime.h>
 
@@ -35,7 +36,8 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
 typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
-
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // ---------------------------------------------------------------- 1D tables
 
@@ -88,17 +90,20 @@ __device__ __forceinline__ void xytable(const VRowDev* __restrict__ rows, int nx
 }
 
 // V block of the z axis in the grid kernel's operand order: fragment
-// ((k-step * ncg + column group) * 4 + plane) of 64 lanes x 16 bytes, lane
-// (g, n) = z rows 8 g .. 8 g + 7 of the k-step at column n, planes re hi, re
-// lo, im hi, im lo (f16 halves of the row scaled by its power of two; lo from
-// the FP64 value).  One thread per (8 z rows, column).
+// ((k-step * ncg + column group) * planes + plane) of 64 lanes x 16 bytes, lane
+// (g, n) = z rows 8 g .. 8 g + 7 of the k-step at column n, planes re then im,
+// each part of the row (scaled by its power of two) in turn: three BF16 parts
+// (FP32 precision) or two f16 halves, every part the FP64 value's rest rounded
+// to nearest.  One thread per (8 z rows, column).
+template <typename H, int PARTS>
 __device__ __forceinline__ void ztable(const VRowDev* __restrict__ rows, const int2* __restrict__ zslots, int n_oct,
                                        int ncg, int ncol, int iz0, double qmin, double dq, uint4* __restrict__ Bt,
                                        long long i0, long long step) {
+    typedef H hx8 __attribute__((ext_vector_type(8)));
     const long long tot = (long long)n_oct * ncg * 16;
     for (long long i = i0; i < tot; i += step) {
         const int oct = (int)(i / (ncg * 16)), col = (int)(i - (long long)oct * ncg * 16);
-        halfx8 pl[4];
+        hx8 pl[2 * PARTS];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             double2 v = make_double2(0.0, 0.0);
@@ -108,26 +113,31 @@ __device__ __forceinline__ void ztable(const VRowDev* __restrict__ rows, const i
                 v.x = ldexp(v.x, zs.y);
                 v.y = ldexp(v.y, zs.y);
             }
-            const _Float16 hr = (_Float16)(float)v.x, hi = (_Float16)(float)v.y;
-            pl[0][j] = hr;
-            pl[1][j] = (_Float16)(float)(v.x - (double)hr);
-            pl[2][j] = hi;
-            pl[3][j] = (_Float16)(float)(v.y - (double)hi);
-        }
-        uint4* o = Bt + (((size_t)(oct >> 2) * ncg + (col >> 4)) * 4) * 64 + (oct & 3) * 16 + (col & 15);
 #pragma unroll
-        for (int p = 0; p < 4; ++p) o[p * 64] = __builtin_bit_cast(uint4, pl[p]);
+            for (int p = 0; p < PARTS; ++p) {
+                const H re = (H)(float)v.x, im = (H)(float)v.y;
+                pl[p][j] = re;
+                pl[PARTS + p][j] = im;
+                v.x -= (double)(float)re;
+                v.y -= (double)(float)im;
+            }
+        }
+        uint4* o = Bt + (((size_t)(oct >> 2) * ncg + (col >> 4)) * (2 * PARTS)) * 64 + (oct & 3) * 16 + (col & 15);
+#pragma unroll
+        for (int p = 0; p < 2 * PARTS; ++p) o[p * 64] = __builtin_bit_cast(uint4, pl[p]);
     }
 }
 
 // All of them in one launch: the z axis' blocks (eight values per thread, the
 // longest) first.
+template <typename H, int PARTS>
 __global__ __launch_bounds__(256) void tables_kernel(const VRowDev* __restrict__ rows, int nxr, int nyr, int nx, int ny,
                                                      double3 qmin, double3 dq, float2* __restrict__ X,
                                                      float2* __restrict__ Y, const int2* __restrict__ zslots, int n_oct,
                                                      int ncg, int ncol, int iz0, uint4* __restrict__ Bt, int nbz) {
     if ((int)blockIdx.x < nbz)
-        ztable(rows, zslots, n_oct, ncg, ncol, iz0, qmin.z, dq.z, Bt, blockIdx.x * 256LL + threadIdx.x, nbz * 256LL);
+        ztable<H, PARTS>(rows, zslots, n_oct, ncg, ncol, iz0, qmin.z, dq.z, Bt, blockIdx.x * 256LL + threadIdx.x,
+                         nbz * 256LL);
     else
         xytable(rows, nxr, nyr, nx, ny, make_double2(qmin.x, qmin.y), make_double2(dq.x, dq.y), X, Y,
                 (blockIdx.x - nbz) * 256LL + threadIdx.x, (gridDim.x - nbz) * 256LL);
@@ -147,13 +157,19 @@ __global__ __launch_bounds__(256) void tables_kernel(const VRowDev* __restrict__
 // with qmin_z = -qmax_z the columns are the upper half of the axis only and
 // the mirror value is (P + Q) + i (S - R): the same products serve both.
 //
-// Products run on the f16 matrix cores with U and V split into hi + lo halves
-// (22 significant bits and more), hi hi + hi lo + lo hi per pair of values,
-// FP32 accumulation.  Exact powers of two bring V's rows to |V| < 2^14 and
-// U to |U| < 2^15 (prep.hip, from q-independent bounds), so the halves keep
-// their bits and nothing overflows; the epilogue removes them.  FOLD (FP32
-// precision): the FP32 sums of two k-steps go to FP64 totals (the sum over z
-// cancels); without it (split-BF16's bounds) they run through.
+// FOLD (FP32 precision): U and V as three BF16 parts each, which hold FP32's 24
+// bits over FP32's whole exponent range, and the six products above 2^-24 of the
+// whole; the FP32 sums of two k-steps go to FP64 totals (the sum over z cancels).
+// Split precision: f16 halves hi + lo (22 significant bits and more), hi hi + hi
+// lo + lo hi, FP32 sums throughout.  Exact powers of two bring V's rows to |V| <
+// 2^14 and U to |U| < 2^15 (prep.hip, from q-independent bounds), so the f16
+// halves keep their bits and nothing overflows; the epilogue removes them.
+//
+// FP32 precision on f16 halves as well took 37.6 ms where the BF16 parts take 54.3
+// (30 heavy atoms, 24 states, 96^3; 10 heavy atoms, 12 states, 64^3: 1.63 and
+// 2.10), but an f16 half ends at 2^-24: in the tail of a diffuse basis, where
+// every value of U and V lies far below its bound, nothing was left (relative
+// error 4e-4 where |f| is 3e-15 of the peak; 2e-7 down to 1e-33 now).
 //
 // A workgroup is 4 waves; its tile 64 rows (row = line * states + state, lines
 // padded to pairs per qx) by 16 CG columns.  Each wave forms its own 16 rows'
@@ -230,13 +246,52 @@ __device__ __forceinline__ void split_f16(float v0, float v1, uint32_t& hi, uint
     lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{r0, r1}, halfx2));
 }
 
+// Split of two FP32 values into three BF16 parts, each the rest rounded to
+// nearest: 24 bits, so the sum of the parts is the value (parts below the BF16
+// subnormals aside).  A BF16 dot product with (-1, -0) or (-0, -1) forms a rest
+// in one instruction without unpacking the part (-0, not +0: (-1, +0) would be
+// sent as the inline constant -1.0, which the instruction reads as (+0, -1)).
+__device__ __forceinline__ void split_bf16(float v0, float v1, uint32_t (&part)[3]) {
+    const bf16x2 first{(__bf16)-1.0f, (__bf16)-0.0f}, second{(__bf16)-0.0f, (__bf16)-1.0f};
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        const bf16x2 h = __builtin_convertvector(floatx2{v0, v1}, bf16x2);
+        part[p] = __builtin_bit_cast(uint32_t, h);
+        if (p < 2) {
+            v0 = __builtin_amdgcn_fdot2_f32_bf16(h, first, v0, false);
+            v1 = __builtin_amdgcn_fdot2_f32_bf16(h, second, v1, false);
+        }
+    }
+}
+
+// Operand parts, planes of a V block (re and im of every part) and, smallest
+// products first, the parts of U and V that are multiplied.
+template <bool FOLD>
+struct Operands {   // three BF16 parts; left out: products below 2^-24 of the whole
+    typedef bf16x8 frag;
+    static constexpr int parts = 3, planes = 6, products = 6;
+    static constexpr int u[products] = {1, 0, 2, 0, 1, 0}, v[products] = {1, 2, 0, 1, 0, 0};
+};
+template <>
+struct Operands<false> {   // f16 halves
+    typedef halfx8 frag;
+    static constexpr int parts = 2, planes = 4, products = 3;
+    static constexpr int u[products] = {1, 0, 0}, v[products] = {0, 1, 0};
+};
+__device__ __forceinline__ floatx4 mma(bf16x8 a, bf16x8 b, floatx4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ floatx4 mma(halfx8 a, halfx8 b, floatx4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+}
+
 // One tile of one evaluation (blk = (split * row tiles + row tile) * column
 // tiles + column tile).  Shared by the single-request kernel (one tile per
 // workgroup) and the persistent batch kernel (tiles of several requests popped
 // from a queue), so a tile's values do not depend on which of the two computed
 // it; nor do they depend on the tile a row falls into.
 //
-// LDS (floats): V blocks [2][CG 4 256 x 4], weights [2][tcm 48 ns],
+// LDS (floats): V blocks [2][CG planes 256], weights [2][tcm 48 ns],
 // W [2][tcm][2 np lines][kWLine].
 template <int CG, bool FOLD>
 __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds) {
@@ -244,7 +299,9 @@ __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, m = lane & 15;
     const int ns = d.n_states, tcm = d.tcm;           // tcm: 1 or 2
-    constexpr int BW = CG * 4 * 256;                  // floats of a V block
+    using Op = Operands<FOLD>;
+    using frag = typename Op::frag;
+    constexpr int PL = Op::planes, BW = CG * PL * 256;   // floats of a V block
     const int TW = tcm * 48 * ns;                     // floats of a weight buffer
     const int WT = 2 * d.np * kWLine;                 // floats of W, one term
     float* const Tl = lds + 2 * BW;
@@ -307,11 +364,12 @@ __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds
             if (u + lane < units) dma_b128(16u * (u + lane), src, dst + 16u * u);
     };
     auto dma_v = [&](int k) {
-        const uint4* src = d.Bt + ((size_t)k * d.ncg + ct * CG) * 256;
+        const uint4* src = d.Bt + ((size_t)k * d.ncg + ct * CG) * (64 * PL);
         const uint32_t dst = lds_addr(lds + (k & 1) * BW);
 #pragma unroll
-        for (int i = 0; i < CG; ++i)
-            dma_b128(16u * (64 * (4 * i + wave) + lane), src, dst + 1024u * (4 * i + wave));
+        for (int i = 0; i < CG * PL; i += kGridWaves)   // a wave copies a plane of 1 KB at a time
+            if (CG * PL % kGridWaves == 0 || i + wave < CG * PL)
+                dma_b128(16u * (64 * (i + wave) + lane), src, dst + 1024u * (i + wave));
     };
     // term record (x row, y row) of the lane's item
     auto load_rec = [&](const Pos& p) { return d.terms[(p.c + p.t0 + min(wt, terms_of(p) - 1)) * 32 + wz]; };
@@ -410,37 +468,37 @@ __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds
             else add(0, false);
             if (tc > 1) add(1, false);
             if (last_term) {
-                halfx8 A[2][2];   // [re/im][hi/lo]
+                frag A[2][Op::parts];   // [re/im][part]
 #pragma unroll
                 for (int a = 0; a < 2; ++a) {
                     const float(&u)[8] = a ? ui : ur;
-                    uintx4 hi, lo;
+                    uintx4 w[Op::parts];
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
-                        uint32_t h, l;
-                        split_f16(u[2 * j], u[2 * j + 1], h, l);
-                        hi[j] = h;
-                        lo[j] = l;
+                        uint32_t t[Op::parts];
+                        if constexpr (FOLD) split_bf16(u[2 * j], u[2 * j + 1], t);
+                        else split_f16(u[2 * j], u[2 * j + 1], t[0], t[1]);
+#pragma unroll
+                        for (int p = 0; p < Op::parts; ++p) w[p][j] = t[p];
                     }
-                    A[a][0] = __builtin_bit_cast(halfx8, hi);
-                    A[a][1] = __builtin_bit_cast(halfx8, lo);
+#pragma unroll
+                    for (int p = 0; p < Op::parts; ++p) A[a][p] = __builtin_bit_cast(frag, w[p]);
                 }
                 const uint4* B = reinterpret_cast<const uint4*>(lds + (p0.k & 1) * BW) + lane;
                 __builtin_amdgcn_s_setprio(0);
 #pragma unroll
                 for (int q = 0; q < CG; ++q) {
-                    halfx8 V[2][2];
+                    frag V[2][Op::parts];
 #pragma unroll
-                    for (int b = 0; b < 4; ++b) V[b >> 1][b & 1] = __builtin_bit_cast(halfx8, B[(q * 4 + b) * 64]);
-                    // lo hi, hi lo, hi hi
+                    for (int b = 0; b < PL; ++b)
+                        V[b / Op::parts][b % Op::parts] = __builtin_bit_cast(frag, B[(q * PL + b) * 64]);
 #pragma unroll
-                    for (int pr = 0; pr < 3; ++pr)
+                    for (int pr = 0; pr < Op::products; ++pr)
 #pragma unroll
                         for (int a = 0; a < 2; ++a)
 #pragma unroll
                             for (int b = 0; b < 2; ++b)
-                                acc[q][a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[a][pr == 0], V[b][pr == 1],
-                                                                                     acc[q][a][b], 0, 0, 0);
+                                acc[q][a][b] = mma(A[a][Op::u[pr]], V[b][Op::v[pr]], acc[q][a][b]);
                 }
                 if (FOLD && ((p0.k - k_lo) % kFoldSteps == kFoldSteps - 1 || last)) {
 #pragma unroll
@@ -622,9 +680,13 @@ hipError_t launch_grid_tables(const VRowDev* rows, int nxr, int nyr, const int2*
     const long long txy = (long long)n[0] * nxr + (long long)((n[1] + 7) & ~7) * nyr;
     const int nbz = (int)std::min<long long>((tz + 255) / 256, 32768);
     const int nbxy = (int)std::max<long long>(1, std::min<long long>((txy + 255) / 256, 32768));
-    hipLaunchKernelGGL(tables_kernel, dim3(nbz + nbxy), dim3(256), 0, st, rows, nxr, nyr, n[0], n[1],
-                       make_double3(qmin[0], qmin[1], qmin[2]), make_double3(dq[0], dq[1], dq[2]), X, Y, zslots, n_oct,
-                       g.ncg, g.ncol, g.iz0, Bt, nbz);
+    const double3 q0 = make_double3(qmin[0], qmin[1], qmin[2]), d = make_double3(dq[0], dq[1], dq[2]);
+    if (g.planes == Operands<true>::planes)
+        hipLaunchKernelGGL((tables_kernel<__bf16, Operands<true>::parts>), dim3(nbz + nbxy), dim3(256), 0, st, rows, nxr,
+                           nyr, n[0], n[1], q0, d, X, Y, zslots, n_oct, g.ncg, g.ncol, g.iz0, Bt, nbz);
+    else
+        hipLaunchKernelGGL((tables_kernel<_Float16, Operands<false>::parts>), dim3(nbz + nbxy), dim3(256), 0, st, rows, nxr,
+                           nyr, n[0], n[1], q0, d, X, Y, zslots, n_oct, g.ncg, g.ncol, g.iz0, Bt, nbz);
     return hipGetLastError();
 }
 
@@ -643,6 +705,7 @@ int max_cg(int precision) { return precision == 0 ? 3 : 4; }
 GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect, int precision) {
     GridShape g{};
     g.reflect = reflect ? 1 : 0;
+    g.planes = precision == SCFF_FP32 ? Operands<true>::planes : Operands<false>::planes;
     g.ncol = reflect ? (n[2] + 1) / 2 : n[2];
     g.iz0 = reflect ? n[2] - g.ncol : 0;
     g.nyp = (n[1] + 1) & ~1;   // lines in pairs of one qx
@@ -658,7 +721,7 @@ GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect, in
     long long best = 0;
     for (int cg = 1; cg <= max_cg(precision); ++cg) {
         int tcm = 2;
-        auto bytes = [&] { return 4 * (2 * cg * 1024 + 2 * tcm * (48 * n_states + 2 * g.np * kWLine)); };
+        auto bytes = [&] { return 4 * (2 * cg * g.planes * 256 + 2 * tcm * (48 * n_states + 2 * g.np * kWLine)); };
         if (bytes() > kGridLds) tcm = 1;
         if (bytes() > kGridLds) break;
         const int nt = (ng + cg - 1) / cg;
@@ -680,7 +743,7 @@ GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect, in
 // three column groups: two waves per SIMD, else three), and the 160 KB of LDS.
 int grid_wgs_per_cu(int cls, int lds) {
     const int by_regs = cls == 1 || cls == 2 ? 2 : 3;
-    return std::min(by_regs, 160 * 1024 / (lds + 1024));
+    return std::min(by_regs, 160 * 1024 / ((lds + 16 + kLdsGranule - 1) / kLdsGranule * kLdsGranule));
 }
 
 // The kernel's variant; class 3 (four column groups with totals) does not exist.
@@ -739,6 +802,22 @@ hipError_t grid_desc(const GridShape& g, const float2* V, int nxr, int nyr, uint
         case 7: hipLaunchKernelGGL((KERNEL<4, false>), __VA_ARGS__); break;       \
         default: return hipErrorInvalidValue;                                     \
     }
+
+// Dynamic LDS beyond 64 KB must be allowed per kernel (on the current device).
+hipError_t grid_allow_lds() {
+    const void* fns[] = {(const void*)grid_kernel<1, true>,        (const void*)grid_kernel<2, true>,
+                         (const void*)grid_kernel<3, true>,        (const void*)grid_kernel<1, false>,
+                         (const void*)grid_kernel<2, false>,       (const void*)grid_kernel<3, false>,
+                         (const void*)grid_kernel<4, false>,       (const void*)grid_batch_kernel<1, true>,
+                         (const void*)grid_batch_kernel<2, true>,  (const void*)grid_batch_kernel<3, true>,
+                         (const void*)grid_batch_kernel<1, false>, (const void*)grid_batch_kernel<2, false>,
+                         (const void*)grid_batch_kernel<3, false>, (const void*)grid_batch_kernel<4, false>};
+    for (const void* f : fns) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kGridLds + 16);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 
 hipError_t launch_grid(int cls, const GridShape& g, const GridDesc& d, long long blocks, hipStream_t st) {
     if (blocks < 1 || blocks > 0x7fffffffLL || g.lds > kGridLds) return hipErrorInvalidValue;

@@ -385,7 +385,7 @@ TableBytes table_bytes(const scff_ctx* c, const scff_grid* g, const GridShape& s
     TableBytes t;
     t.y = up((size_t)(c->pres.n_x + 1) * g->n[0] * sizeof(float2));
     t.z = t.y + up((size_t)(c->pres.n_y + 1) * ((g->n[1] + 7) & ~7) * sizeof(float2));
-    t.total = t.z + (size_t)c->pres.n_ksteps * sh.ncg * 4 * 1024;
+    t.total = t.z + (size_t)c->pres.n_ksteps * sh.ncg * sh.planes * 1024;
     return t;
 }
 
@@ -650,6 +650,7 @@ int scff_create(int device, size_t hbm_budget_bytes, scff_ctx** out) {
     if (e != hipSuccess || n <= 0) return fail(SCFF_EDEVICE, "no HIP device available");
     if (device < 0 || device >= n) return fail(SCFF_EINVAL, "device index out of range");
     if (hipSetDevice(device) != hipSuccess) return fail(SCFF_EDEVICE, "hipSetDevice failed");
+    if ((e = grid_allow_lds()) != hipSuccess) return fail(SCFF_EDEVICE, std::string("grid kernels: ") + hipGetErrorString(e));
     scff_ctx* c = new scff_ctx();
     c->device = device;
     int ncu = 0;
