@@ -56,7 +56,10 @@ extern "C" {
  *      contraction"; precision is this engine's choice) -------------------- */
 #define SCFF_FP32    0   /* FP32 values; matrix products of BF16 triples (24 bits,
                             FP32's exponent range), FP64 totals                 */
-#define SCFF_BF16X3  1   /* FP32 generator + split-BF16 (hi*hi+hi*lo+lo*hi) MFMA */
+#define SCFF_BF16X3  1   /* FP32 values, split products, FP32 sums.  Grid: pairs of
+                            f16 halves (hi*hi+hi*lo+lo*hi), or BF16 triples where f
+                            falls too far below its bound for their range; FFT
+                            method: BF16 pairs                                  */
 
 typedef struct scff_ctx scff_ctx;
 

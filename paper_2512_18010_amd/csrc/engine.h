@@ -36,7 +36,13 @@ constexpr int kWPasses = 2;       // W items per lane whose loads go out a step 
 constexpr int kGridLds = 81920 - 16;   // LDS bytes of a workgroup, at most: half a CU's (the batch kernel adds 16)
 constexpr int kLdsGranule = 1280;      // a CU's 160 KB in 128 blocks
 constexpr int kWLine = 84;        // floats of W per line: 4 groups of 8 z rows, padded apart in the banks
-constexpr int kGridClasses = 8;   // kernel variants: column groups per tile x precision
+// Arithmetic of the grid kernel's products: FP32 precision; split precision on
+// f16 halves, or on BF16 parts where the values fall out of the halves' range.
+enum GridKind { kGridFp32, kGridSplitF16, kGridSplitBf16 };
+constexpr int kGridClasses = 12;   // kernel variants: column groups per tile x kind
+// Bins of the s-s terms by binary exponent of p (PrepResult::tail): the first
+// holds p < 2^(kTailMin + 1)
+constexpr int kTailBins = 32, kTailMin = -12;
 // Term counts of the k-steps, longest rows first: k-step k has the largest n
 // with k < kend[n], so a k-step's position in the term arrays is closed form.
 struct KSteps {
@@ -68,6 +74,7 @@ struct ChunkSplit {
 // terms of a k-step handled between two barriers, most line pairs a tile
 // touches, planes of a V block, LDS bytes of a workgroup.
 struct GridShape {
+    GridKind kind;
     int reflect, ncol, iz0, cg, ntc, ncg, ntl, nyp, tcm, np, planes, lds;
 };
 // Everything the fused grid kernel needs for one evaluation (one request of
@@ -207,7 +214,10 @@ struct PrepWork {
 
 constexpr size_t kPinnedBytes = (size_t)4 << 20;
 // byte offsets in the precompute's small buffer
-constexpr size_t kSmallStats = 1024, kSmallSinv = 1280, kSmallKs = 1792, kSmallMeta = 2048, kSmallZmax = 2304;
+constexpr size_t kSmallStats = 1024, kSmallSinv = 1280, kSmallKs = 1792, kSmallHist = 2048;   // kHistBins unsigned
+// what the host reads back, together
+constexpr size_t kSmallMeta = 7168, kSmallZmax = kSmallMeta + 64, kSmallTail = kSmallZmax + 8 * kMaxStates;
+constexpr size_t kSmallBytes = kSmallTail + 8 * kMaxStates * kTailBins;
 constexpr size_t kPinnedTables = 4096;   // byte offset of the molecule upload
 
 struct PrepResult {
@@ -215,6 +225,10 @@ struct PrepResult {
     int n_ksteps = 0, state_blocks = 1;
     KSteps ksteps{};
     long long n_zterms = 0, n_zweights = 0;
+    // per state: bound of its largest z row, and the largest |weight| x bound of its
+    // s-s terms by exponent of p (a term of bin b falls off as e^{-q^2/4p}, p >=
+    // 2^(kTailMin + b)); the range of f over a grid
+    double zmax[kMaxStates] = {}, tail[kMaxStates][kTailBins] = {};
     // layout by component pairs (run_prep_stats)
     int n_virtual = 0, n_vpairs = 0, n_units = 0, n_chunks = 0;
     long long n_slots = 0, pairs_kept = 0, terms_kept = 0;

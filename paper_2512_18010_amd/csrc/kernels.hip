@@ -17,8 +17,8 @@
 //    tables_kernel's layouts of the same values.
 //  * grid_kernel: the sum contracted over z rows on the matrix cores (FP32
 //    accumulation; FP32 precision: three BF16 parts per operand, folded into
-//    FP64 totals; split precision: two f16 halves); the operand is formed on the
-//    VALU.  grid_batch_kernel: the same tiles popped
+//    FP64 totals; split precision: two f16 halves, or BF16 parts); the operand is
+//    formed on the VALU.  grid_batch_kernel: the same tiles popped
 //    from a queue of several requests.
 #include <hip/hip_runtime.h>
 
@@ -161,7 +161,8 @@ __global__ __launch_bounds__(256) void tables_kernel(const VRowDev* __restrict__
 // bits over FP32's whole exponent range, and the six products above 2^-24 of the
 // whole; the FP32 sums of two k-steps go to FP64 totals (the sum over z cancels).
 // Split precision: f16 halves hi + lo (22 significant bits and more), hi hi + hi
-// lo + lo hi, FP32 sums throughout.  Exact powers of two bring V's rows to |V| <
+// lo + lo hi, FP32 sums throughout; where a half's range is too short for the
+// grid (grid_kind, runtime.cpp), the BF16 parts without totals.  Exact powers of two bring V's rows to |V| <
 // 2^14 and U to |U| < 2^15 (prep.hip, from q-independent bounds), so the f16
 // halves keep their bits and nothing overflows; the epilogue removes them.
 //
@@ -266,7 +267,7 @@ __device__ __forceinline__ void split_bf16(float v0, float v1, uint32_t (&part)[
 
 // Operand parts, planes of a V block (re and im of every part) and, smallest
 // products first, the parts of U and V that are multiplied.
-template <bool FOLD>
+template <bool BF>
 struct Operands {   // three BF16 parts; left out: products below 2^-24 of the whole
     typedef bf16x8 frag;
     static constexpr int parts = 3, planes = 6, products = 6;
@@ -293,13 +294,13 @@ __device__ __forceinline__ floatx4 mma(halfx8 a, halfx8 b, floatx4 c) {
 //
 // LDS (floats): V blocks [2][CG planes 256], weights [2][tcm 48 ns],
 // W [2][tcm][2 np lines][kWLine].
-template <int CG, bool FOLD>
+template <int CG, bool FOLD, bool BF>
 __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, m = lane & 15;
     const int ns = d.n_states, tcm = d.tcm;           // tcm: 1 or 2
-    using Op = Operands<FOLD>;
+    using Op = Operands<BF>;
     using frag = typename Op::frag;
     constexpr int PL = Op::planes, BW = CG * PL * 256;   // floats of a V block
     const int TW = tcm * 48 * ns;                     // floats of a weight buffer
@@ -476,7 +477,7 @@ __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         uint32_t t[Op::parts];
-                        if constexpr (FOLD) split_bf16(u[2 * j], u[2 * j + 1], t);
+                        if constexpr (BF) split_bf16(u[2 * j], u[2 * j + 1], t);
                         else split_f16(u[2 * j], u[2 * j + 1], t[0], t[1]);
 #pragma unroll
                         for (int p = 0; p < Op::parts; ++p) w[p][j] = t[p];
@@ -557,10 +558,12 @@ __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds
     }
 }
 
-template <int CG, bool FOLD>
-__global__ __launch_bounds__(kGridWaves * 64) __attribute__((amdgpu_waves_per_eu(FOLD && CG > 1 ? 2 : 3, FOLD && CG > 1 ? 2 : 3))) void grid_kernel(GridDesc d) {
+constexpr int grid_waves(int cg, bool fold) { return fold && cg > 1 ? 2 : 3; }   // per SIMD
+template <int CG, bool FOLD, bool BF>
+__global__ __launch_bounds__(kGridWaves * 64) __attribute__((amdgpu_waves_per_eu(grid_waves(CG, FOLD), grid_waves(CG, FOLD)))) void grid_kernel(
+    GridDesc d) {
     extern __shared__ __align__(16) float grid_lds[];
-    grid_tile<CG, FOLD>(d, blockIdx.x, grid_lds);
+    grid_tile<CG, FOLD, BF>(d, blockIdx.x, grid_lds);
 }
 
 // Persistent batch kernel: every workgroup pops (request, tile) items from a
@@ -569,8 +572,8 @@ __global__ __launch_bounds__(kGridWaves * 64) __attribute__((amdgpu_waves_per_eu
 // several requests share one launch.  Every workgroup leaves the loop once
 // the counter passes n_items; the counter must be 0 at launch.  The launch's
 // LDS holds the largest of its requests' needs after the 16 bytes of the queue.
-template <int CG, bool FOLD>
-__global__ __launch_bounds__(kGridWaves * 64) __attribute__((amdgpu_waves_per_eu(FOLD && CG > 1 ? 2 : 3, FOLD && CG > 1 ? 2 : 3))) void grid_batch_kernel(
+template <int CG, bool FOLD, bool BF>
+__global__ __launch_bounds__(kGridWaves * 64) __attribute__((amdgpu_waves_per_eu(grid_waves(CG, FOLD), grid_waves(CG, FOLD)))) void grid_batch_kernel(
     const GridDesc* __restrict__ descs, const int2* __restrict__ items, int n_items, int* __restrict__ counter) {
     extern __shared__ __align__(16) float grid_lds[];
     int* s_item = reinterpret_cast<int*>(grid_lds);
@@ -581,7 +584,7 @@ __global__ __launch_bounds__(kGridWaves * 64) __attribute__((amdgpu_waves_per_eu
         const int it = __builtin_amdgcn_readfirstlane(s_item[0]);
         if (it >= n_items) break;
         const int2 w = items[it];
-        grid_tile<CG, FOLD>(descs[w.x], w.y, grid_lds + 4);
+        grid_tile<CG, FOLD, BF>(descs[w.x], w.y, grid_lds + 4);
     }
 }
 
@@ -700,12 +703,13 @@ hipError_t launch_grid_tables(const VRowDev* rows, int nxr, int nyr, const int2*
 // then two tiles of two: 27.4 -> 21.6 ms; 48x48x256, 128 columns, three tiles of three:
 // 8.9 -> 6.2 ms).  At most one group of padding: the z blocks then stay within
 // rows x vtable_stride, by which a grid is accepted.
-int max_cg(int precision) { return precision == 0 ? 3 : 4; }
+int max_cg(GridKind kind) { return kind == kGridFp32 ? 3 : 4; }
 
-GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect, int precision) {
+GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect, GridKind kind) {
     GridShape g{};
     g.reflect = reflect ? 1 : 0;
-    g.planes = precision == SCFF_FP32 ? Operands<true>::planes : Operands<false>::planes;
+    g.kind = kind;
+    g.planes = kind == kGridSplitF16 ? Operands<false>::planes : Operands<true>::planes;
     g.ncol = reflect ? (n[2] + 1) / 2 : n[2];
     g.iz0 = reflect ? n[2] - g.ncol : 0;
     g.nyp = (n[1] + 1) & ~1;   // lines in pairs of one qx
@@ -719,7 +723,7 @@ GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect, in
         g.np = std::max(g.np, p);
     }
     long long best = 0;
-    for (int cg = 1; cg <= max_cg(precision); ++cg) {
+    for (int cg = 1; cg <= max_cg(kind); ++cg) {
         int tcm = 2;
         auto bytes = [&] { return 4 * (2 * cg * g.planes * 256 + 2 * tcm * (48 * n_states + 2 * g.np * kWLine)); };
         if (bytes() > kGridLds) tcm = 1;
@@ -747,7 +751,7 @@ int grid_wgs_per_cu(int cls, int lds) {
 }
 
 // The kernel's variant; class 3 (four column groups with totals) does not exist.
-int grid_class(const GridShape& g, int precision) { return (g.cg - 1) + 4 * precision; }
+int grid_class(const GridShape& g) { return (g.cg - 1) + 4 * g.kind; }
 
 hipError_t grid_desc(const GridShape& g, const float2* V, int nxr, int nyr, uint32_t ybase, const uint4* Bt, const KSteps& steps,
                      const int2* terms, const float* Tw, const double* sinv, const ChunkSplit& sp, const int n[3],
@@ -793,32 +797,44 @@ hipError_t grid_desc(const GridShape& g, const float2* V, int nxr, int nyr, uint
 
 #define SCFF_GRID_CASES(KERNEL, ...)                                              \
     switch (cls) {                                                                \
-        case 0: hipLaunchKernelGGL((KERNEL<1, true>), __VA_ARGS__); break;        \
-        case 1: hipLaunchKernelGGL((KERNEL<2, true>), __VA_ARGS__); break;        \
-        case 2: hipLaunchKernelGGL((KERNEL<3, true>), __VA_ARGS__); break;        \
-        case 4: hipLaunchKernelGGL((KERNEL<1, false>), __VA_ARGS__); break;       \
-        case 5: hipLaunchKernelGGL((KERNEL<2, false>), __VA_ARGS__); break;       \
-        case 6: hipLaunchKernelGGL((KERNEL<3, false>), __VA_ARGS__); break;       \
-        case 7: hipLaunchKernelGGL((KERNEL<4, false>), __VA_ARGS__); break;       \
+        case 0: SCFF_GRID_VARIANT((KERNEL<1, true, true>), __VA_ARGS__); break;   \
+        case 1: SCFF_GRID_VARIANT((KERNEL<2, true, true>), __VA_ARGS__); break;   \
+        case 2: SCFF_GRID_VARIANT((KERNEL<3, true, true>), __VA_ARGS__); break;   \
+        case 4: SCFF_GRID_VARIANT((KERNEL<1, false, false>), __VA_ARGS__); break; \
+        case 5: SCFF_GRID_VARIANT((KERNEL<2, false, false>), __VA_ARGS__); break; \
+        case 6: SCFF_GRID_VARIANT((KERNEL<3, false, false>), __VA_ARGS__); break; \
+        case 7: SCFF_GRID_VARIANT((KERNEL<4, false, false>), __VA_ARGS__); break; \
+        case 8: SCFF_GRID_VARIANT((KERNEL<1, false, true>), __VA_ARGS__); break;  \
+        case 9: SCFF_GRID_VARIANT((KERNEL<2, false, true>), __VA_ARGS__); break;  \
+        case 10: SCFF_GRID_VARIANT((KERNEL<3, false, true>), __VA_ARGS__); break; \
+        case 11: SCFF_GRID_VARIANT((KERNEL<4, false, true>), __VA_ARGS__); break; \
         default: return hipErrorInvalidValue;                                     \
     }
 
 // Dynamic LDS beyond 64 KB must be allowed per kernel (on the current device).
 hipError_t grid_allow_lds() {
-    const void* fns[] = {(const void*)grid_kernel<1, true>,        (const void*)grid_kernel<2, true>,
-                         (const void*)grid_kernel<3, true>,        (const void*)grid_kernel<1, false>,
-                         (const void*)grid_kernel<2, false>,       (const void*)grid_kernel<3, false>,
-                         (const void*)grid_kernel<4, false>,       (const void*)grid_batch_kernel<1, true>,
-                         (const void*)grid_batch_kernel<2, true>,  (const void*)grid_batch_kernel<3, true>,
-                         (const void*)grid_batch_kernel<1, false>, (const void*)grid_batch_kernel<2, false>,
-                         (const void*)grid_batch_kernel<3, false>, (const void*)grid_batch_kernel<4, false>};
-    for (const void* f : fns) {
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kGridLds + 16);
-        if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
+    auto allow = [&](const void* f) {
+        if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kGridLds + 16);
+    };
+#define SCFF_GRID_VARIANT(K, ...) allow((const void*)(K))
+    auto one = [&](int cls) {
+        SCFF_GRID_CASES(grid_kernel)
+        return hipSuccess;
+    };
+    auto batch = [&](int cls) {
+        SCFF_GRID_CASES(grid_batch_kernel)
+        return hipSuccess;
+    };
+#undef SCFF_GRID_VARIANT
+    for (int cls = 0; cls < kGridClasses; ++cls) {
+        (void)one(cls);   // (a class that does not exist allows nothing)
+        (void)batch(cls);
     }
-    return hipSuccess;
+    return e;
 }
 
+#define SCFF_GRID_VARIANT(K, ...) hipLaunchKernelGGL(K, __VA_ARGS__)
 hipError_t launch_grid(int cls, const GridShape& g, const GridDesc& d, long long blocks, hipStream_t st) {
     if (blocks < 1 || blocks > 0x7fffffffLL || g.lds > kGridLds) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks), block(kGridWaves * 64);

@@ -455,21 +455,27 @@ __device__ __forceinline__ int z_exponent(double bound) {
 // and (shell pair, pp ncls + class).  mx: per state the largest sum of |Tp| x bound
 // x y bound over a row's terms, divided by the row's scale, as the bits of a
 // non-negative double (which order like the values); a maximum does not depend
-// on the order of the atomics.
+// on the order of the atomics.  tail: per state and exponent of p the largest
+// |Tp| x bound of an s-s term.
 __global__ __launch_bounds__(128) void zcount_kernel(const PrepShell* __restrict__ sh, const int4* __restrict__ sp,
                                                     const int4* __restrict__ trow, const double* __restrict__ rowsum,
                                                     const double* __restrict__ w, const double* __restrict__ thr,
                                                     const double* __restrict__ tp64, int ns, int nr,
                                                     int nz_all, int* __restrict__ used, int* __restrict__ zn,
-                                                    int2* __restrict__ zinfo, unsigned long long* __restrict__ gmx) {
-    __shared__ unsigned long long mx[kMaxStates];
+                                                    int2* __restrict__ zinfo, unsigned long long* __restrict__ gmx,
+                                                    unsigned long long* __restrict__ gtail,
+                                                    const VRowDev* __restrict__ rows) {
+    __shared__ unsigned long long mx[kMaxStates], tail[kMaxStates * kTailBins];
     const int isp = blockIdx.x;
     const int4 s = sp[isp];
     const int lA = sh[s.x].l, lB = sh[s.y].l, npp = sh[s.x].nprim * sh[s.y].nprim;
     const bool same = s.x == s.y;
     const int ncls = (lA + 1) * (lB + 1);
     const double th = thr[0];
+    const bool ss = lA + lB == 0;
     if (threadIdx.x < kMaxStates) mx[threadIdx.x] = 0ull;
+    if (ss)
+        for (int i = threadIdx.x; i < ns * kTailBins; i += blockDim.x) tail[i] = 0ull;
     __syncthreads();
     const int kc = lA * 6 + lB * 2 + (same ? 1 : 0), nz = npp * ncls;
     for (int z = threadIdx.x; z < nz; z += blockDim.x) {
@@ -499,13 +505,24 @@ __global__ __launch_bounds__(128) void zcount_kernel(const PrepShell* __restrict
             const int4 tr = trow[t];
             b += fabs(tp64[(size_t)tr.w * ns + st]) * rowsum[tr.x] * rowsum[tr.y];
         }
-        b *= ldexp(1.0, -z_exponent(rowsum[s.z + pp * 3 * ncls + 2 * ncls + cls]));
+        const int rz = s.z + pp * 3 * ncls + 2 * ncls + cls;
+        if (ss) {   // one term, of magnitude b times its Gaussian
+            const double t = b * rowsum[rz];
+            const int e = ilogb(0.25 / rows[rz].inv4p) - kTailMin;
+            if (t > 0.0 && t < 1e300)
+                atomicMax(&tail[st * kTailBins + max(0, min(e, kTailBins - 1))], (unsigned long long)__double_as_longlong(t));
+        }
+        b *= ldexp(1.0, -z_exponent(rowsum[rz]));
         // non-negative doubles order like their bit patterns; NaN and infinity are left out
         if (b > 0.0 && b < 1e300) atomicMax(&mx[st], (unsigned long long)__double_as_longlong(b));
     }
     __syncthreads();
     for (int st = threadIdx.x; st < ns; st += blockDim.x)
         if (mx[st] > __hip_atomic_load(&gmx[st], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&gmx[st], mx[st]);
+    if (ss)
+        for (int i = threadIdx.x; i < ns * kTailBins; i += blockDim.x)
+            if (tail[i] && tail[i] > __hip_atomic_load(&gtail[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                atomicMax(&gtail[i], tail[i]);
 }
 
 // Per state: its largest z-row bound, as the exponent ks with bound 2^ks <
@@ -641,7 +658,8 @@ hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStrea
     CK(alloc(w.tp64, (size_t)NCP * ns * sizeof(double)));
     CK(alloc(w.bsum, (size_t)NCP * sizeof(double)));
     CK(alloc(w.part, (size_t)NSP * ns * sizeof(double)));
-    CK(alloc(w.small, 4096 + kHistBins * sizeof(unsigned) + 64));
+    static_assert(kSmallHist + kHistBins * sizeof(unsigned) <= kSmallMeta, "histogram overlaps what the host reads");
+    CK(alloc(w.small, kSmallBytes));
     // flags: rows used per axis, then the z rows' one-hot term counts
     const long long NF = 3 * NR + (long long)kZTerms * NZ;
     if (NF > INT32_MAX) return hipErrorInvalidValue;
@@ -653,9 +671,10 @@ hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStrea
     int* ks = (int*)((char*)w.small.p + kSmallKs);                       // [<= 32]
     int* meta = (int*)((char*)w.small.p + kSmallMeta);                   // [12]
     unsigned long long* zmx = (unsigned long long*)((char*)w.small.p + kSmallZmax);   // [<= 32]
-    unsigned* hist = (unsigned*)((char*)w.small.p + 4096);               // [kHistBins]
+    unsigned long long* tail = (unsigned long long*)((char*)w.small.p + kSmallTail);  // [ns][kTailBins]
+    unsigned* hist = (unsigned*)((char*)w.small.p + kSmallHist);         // [kHistBins]
 
-    const int nsmall = (int)((4096 + kHistBins * sizeof(unsigned)) / sizeof(unsigned));
+    const int nsmall = (int)(kSmallBytes / sizeof(unsigned));
     hipLaunchKernelGGL(rows_terms_kernel, dim3(NSP), dim3(128), 0, st, in.shells, in.sp, in.xyz, in.exps, in.coefs, in.n1d,
                        (int)NR, in.sp_cp, in.bf0, in.cnorm, in.T, in.nbf, ns, in.spin, (VRowDev*)w.rows_all.p,
                        (double*)w.rowsum.p, (int*)w.row_used.p, (unsigned*)w.small.p, nsmall, (int4*)w.trow.p,
@@ -677,7 +696,7 @@ hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStrea
     int* zn = (int*)(zinfo + NZ);
     hipLaunchKernelGGL(zcount_kernel, dim3(NSP), dim3(128), 0, st, in.shells, in.sp, (const int4*)w.trow.p,
                        (const double*)w.rowsum.p, (const double*)w.wt.p, (const double*)thr, (const double*)w.tp64.p, ns,
-                       (int)NR, NZ, (int*)w.row_used.p, zn, zinfo, zmx);
+                       (int)NR, NZ, (int*)w.row_used.p, zn, zinfo, zmx, tail, (const VRowDev*)w.rows_all.p);
     CK(hipGetLastError());
     size_t tmp_bytes = 0;
     CK(hipcub::DeviceScan::ExclusiveSum(nullptr, tmp_bytes, (int*)w.row_used.p, (int*)w.newid.p, (int)NF, st));
@@ -688,9 +707,11 @@ hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStrea
     CK(hipGetLastError());
     // the one readback lands in the context's pinned host memory when it has
     // some (a DMA; pageable destinations are staged by the runtime)
-    alignas(16) int local_rb[12];
-    int* rb = w.pinned ? (int*)w.pinned : local_rb;
-    CK(hipMemcpyAsync(rb, meta, sizeof(local_rb), hipMemcpyDeviceToHost, st));
+    const size_t rbytes = kSmallTail - kSmallMeta + (size_t)ns * kTailBins * sizeof(double);
+    alignas(16) unsigned char local_rb[kSmallBytes - kSmallMeta];
+    unsigned char* rbuf = w.pinned ? (unsigned char*)w.pinned : local_rb;
+    const int* rb = (const int*)rbuf;
+    CK(hipMemcpyAsync(rbuf, meta, rbytes, hipMemcpyDeviceToHost, st));
     CK(hipStreamSynchronize(st));
     const int nrows_used = rb[2];   // the numbers of the z rows' segments start after the rows'
     // k-steps of kZStep sorted z rows; every row is padded to the count of the
@@ -722,6 +743,8 @@ hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStrea
     res.n_rows = nrows_used + 1;
     res.n_x = rb[0];
     res.n_y = rb[1] - rb[0];
+    std::memcpy(res.zmax, rbuf + kSmallZmax - kSmallMeta, ns * sizeof(double));
+    std::memcpy(res.tail, rbuf + kSmallTail - kSmallMeta, ns * sizeof(res.tail[0]));
     res.n_ksteps = n_ksteps;
     res.ksteps = steps;
     res.n_zterms = nterm;

@@ -21,13 +21,13 @@ int vtable_stride(const int n[3]);
 hipError_t launch_grid_tables(const VRowDev* rows, int nxr, int nyr, const int2* zslots, int n_zpad, const GridShape& g,
                               const int n[3], const double qmin[3], const double dq[3], float2* X, float2* Y, uint4* Bt,
                               hipStream_t st);
-GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect, int precision);
+GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect, GridKind kind);
 int grid_wgs_per_cu(int cls, int lds);
 hipError_t launch_grid(int cls, const GridShape& g, const GridDesc& d, long long blocks, hipStream_t st);
 hipError_t launch_reduce(const double2* part, int n_split, const int n[3], int nx_eval, int n_states, float2* f,
                          float* f2, hipStream_t st);
 hipError_t launch_mirror(const int n[3], int nx_eval, int n_states, float2* f, float* f2, hipStream_t st);
-int grid_class(const GridShape& g, int precision);
+int grid_class(const GridShape& g);
 hipError_t grid_desc(const GridShape& g, const float2* V, int nxr, int nyr, uint32_t ybase, const uint4* Bt, const KSteps& steps,
                      const int2* terms, const float* Tw, const double* sinv, const ChunkSplit& sp, const int n[3],
                      int nx_eval, int n_states, float2* f, float* f2, double2* part, GridDesc* d, long long* blocks);
@@ -424,6 +424,31 @@ bool grid_symmetric(const scff_grid* g) {
 // for every 1D row).
 bool z_reflects(const scff_grid* g) { return g->n[2] > 1 && g->qmin[2] == -g->qmax[2]; }
 
+// Arithmetic of the products.  f16 halves end at 2^-24 of what they are scaled
+// to: per product about 2^-39 of the largest z row's bound, sqrt(n) of that over n
+// rows.  Split precision takes them where that stays below 2^-16 (what BF16 halves
+// hold) of the largest term at every q of the grid, for up to 2^16 rows: where some
+// s-s term, whose magnitude is a plain Gaussian, is at least 2^-15 of that bound
+// at the grid's farthest corner, for every state.  Else BF16 parts (30 heavy
+// atoms, 24 states, 96^3: 48 ms instead of 30).
+GridKind grid_kind(const scff_ctx* c, const scff_grid* g, int precision) {
+    if (precision == SCFF_FP32) return kGridFp32;
+    double q2 = 0.0;
+    for (int a = 0; a < 3; ++a) {
+        const double q = g->n[a] > 1 ? std::max(std::fabs(g->qmin[a]), std::fabs(g->qmax[a])) : std::fabs(g->qmin[a]);
+        q2 += q * q;
+    }
+    for (int s = 0; s < c->n_states; ++s) {
+        // zmax is divided by the row's scale, 2^-14 of its bound
+        const double need = std::ldexp(c->pres.zmax[s], 14 - 15);
+        double t = 0.0;
+        for (int b = 1; b < kTailBins; ++b)
+            t = std::max(t, c->pres.tail[s][b] * std::exp(-q2 / std::ldexp(4.0, kTailMin + b)));
+        if (!(t >= need)) return kGridSplitBf16;   // (a state of zero weights: 0 >= 0)
+    }
+    return kGridSplitF16;
+}
+
 // How scff_eval_grid evaluates grid g: the planes it computes (ix < nx_eval;
 // the rest are mirrored in the symmetric mode), the tiling, and the split of
 // the k-steps.  Every tile costs the same (it runs all k-steps) and the device
@@ -448,10 +473,10 @@ struct EvalPlan {
 EvalPlan plan_eval(const scff_ctx* c, const scff_grid* g, int precision, bool allow_split = true) {
     EvalPlan e{};
     e.nx_eval = (c->symmetry && grid_symmetric(g)) ? (g->n[0] + 1) / 2 : g->n[0];
-    e.shape = grid_shape(g->n, e.nx_eval, c->n_states, z_reflects(g), precision);
+    e.shape = grid_shape(g->n, e.nx_eval, c->n_states, z_reflects(g), grid_kind(c, g, precision));
     const int nst = c->pres.n_ksteps;
     const long long tiles = (long long)e.shape.ntl * e.shape.ntc, 
-                    slots = (long long)grid_wgs_per_cu(grid_class(e.shape, precision), e.shape.lds) * c->n_cu;
+                    slots = (long long)grid_wgs_per_cu(grid_class(e.shape), e.shape.lds) * c->n_cu;
     const size_t part1 = (size_t)g->n[0] * g->n[1] * g->n[2] * (size_t)c->n_states * sizeof(double2);
     long long smax = std::min<long long>(kMaxSplit, nst);
     smax = std::min<long long>(smax, part1 ? (long long)(kMaxPartBytes / part1) : kMaxSplit);
@@ -509,7 +534,7 @@ int run_grid(scff_ctx* c, const scff_grid* g, int precision, const void* tab, co
     if ((rc = make_desc(c, g, pl, tab, part, df, df2, &d, &blocks))) return rc;
     // f(-q) = f(q)* for real T: on a grid symmetric about q = 0 the planes
     // ix >= ceil(nx/2) are the conjugates of computed ones (symmetric mode)
-    if ((rc = hip_check(launch_grid(grid_class(pl.shape, precision), pl.shape, d, blocks, st), "grid kernel launch"))) return rc;
+    if ((rc = hip_check(launch_grid(grid_class(pl.shape), pl.shape, d, blocks, st), "grid kernel launch"))) return rc;
     if (pl.sp.n > 1 &&
         (rc = hip_check(launch_reduce(part, pl.sp.n, g->n, pl.nx_eval, c->n_states, df, df2, st), "reduce launch")))
         return rc;
@@ -566,7 +591,6 @@ int scff::ctx_prepare(scff_ctx* c, const scff_grid* g, int precision, hipStream_
     if ((rc = hip_check(hipStreamSynchronize(st), "precompute sync"))) return rc;
     order_done(c);
     const size_t npts = (size_t)g->n[0] * g->n[1] * g->n[2];
-    (void)precision;
     // the 1D tables and output staging reuse buffers the context already
     // holds when those are large enough (a reused context)
     const EvalPlan pl = plan_eval(c, g, precision);
@@ -606,7 +630,7 @@ int scff::ctx_batch_reserve(scff_ctx* c, const scff_grid* g, int precision, bool
     if ((rc = make_desc(c, g, pl, c->d_vtab.p, part, want_f ? (float2*)c->d_f.p : nullptr,
                         want_f2 ? (float*)c->d_f2.p : nullptr, &be->desc, &be->blocks)))
         return rc;
-    be->cls = grid_class(pl.shape, precision);
+    be->cls = grid_class(pl.shape);
     be->shape = pl.shape;
     be->n_split = pl.sp.n;
     be->nx_eval = pl.nx_eval;
