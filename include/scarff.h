@@ -169,7 +169,10 @@ int scff_set_options(scff_ctx* ctx, double screen_eps, double spin_factor);
  *                  call returns when they are filled.
  *   hip_stream     a hipStream_t of the context's device, or NULL.
  * Requires a loaded molecule and transitions (else SCFF_ESTATE).
- * Grid sizes: 1 <= n[a] <= 4096.
+ * Grid sizes: 1 <= n[a] <= 4096.  The sum over terms is contracted along one
+ * axis, chosen for the grid; the first evaluation that needs another axis than
+ * the context's last one lays the terms out again and waits for their number
+ * (not in a stream that is being captured, where the present layout is kept).
  * Device memory: the context keeps its 1D tables, host-output staging and,
  * for grids whose tile count would leave launch rounds partly idle, an FP64
  * buffer of split pair sums (at most 1 GiB) between calls.  A split that the
@@ -198,8 +201,10 @@ int scff_eval_grid(scff_ctx* ctx, const scff_grid* grid, int precision, float* f
  * whose 1D tables exceed the scratch (rows x (roundup16(max n) + 16) x 8
  * bytes > 256 MiB) is rejected with SCFF_EINVAL before any device work; a
  * split whose partial sums do not fit is not taken (the grid is evaluated
- * unsplit, equal up to the order of the FP64 sums).  Every call on one GPU
- * shares that GPU's scratch, which keeps the last call's contents (every
+ * unsplit, equal up to the order of the FP64 sums).  The layout of the last
+ * evaluation on the context is used (scff_query's is by q_z): for a grid that
+ * scff_eval_grid would contract along another axis, evaluate it once so first.
+ * Every call on one GPU shares that GPU's scratch, which keeps the last call's contents (every
  * value a call reads is written by that call first): calls that overlap on
  * one GPU (other streams, other contexts, other threads) race and must be
  * serialised by the caller.

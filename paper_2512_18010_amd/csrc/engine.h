@@ -27,8 +27,8 @@ constexpr int kChunk = 8;
 // kMaxUnitsPerChunk units and kMaxChunkTerms terms (reported by scff_query).
 constexpr int kMaxUnitsPerChunk = 4;
 constexpr int kMaxChunkTerms = kChunk * kMaxTermsPerPair;   // 72
-// Grid kernel: z rows (distinct 1D rows of the z axis) come in k-steps of
-// kZStep, sorted by their number of terms (at most kZTerms: the component
+// Grid kernel: z rows (distinct 1D rows of the contracted axis, "z" in all that
+// follows; x or y of the grid where that is cheaper) come in k-steps of kZStep, sorted by their number of terms (at most kZTerms: the component
 // pairs of one primitive pair that share its z powers).
 constexpr int kZStep = 32;
 constexpr int kZTerms = 9;
@@ -68,13 +68,17 @@ struct ChunkSplit {
     int n;                   // number of ranges (1 = no split)
     int lo[kMaxSplit + 1];   // range j is k-steps [lo[j], lo[j+1]); lo[0] = 0, lo[n] = n_ksteps
 };
-// Tiling of an evaluation: columns (q_z values computed: the upper half of an
-// axis symmetric about 0), column groups of 16 per tile (cg) and in all (ncg,
-// padded to whole tiles), row and column tiles, lines per qx (padded to pairs),
-// terms of a k-step handled between two barriers, most line pairs a tile
-// touches, planes of a V block, LDS bytes of a workgroup.
+// Tiling of an evaluation: the contracted axis, whose values are the columns, and
+// the line axes l[0], l[1] (the others, in order; lines are numbered with l[1]
+// fastest); columns computed (the upper half of an axis symmetric about 0),
+// column groups of 16 per tile (cg) and in all (ncg, padded to whole tiles), row
+// and column tiles, lines per value of l[0] (padded to pairs), terms of a k-step
+// handled between two barriers, most line pairs a tile touches, planes of a V
+// block, LDS bytes of a workgroup; estimated cost (relative).
 struct GridShape {
     GridKind kind;
+    int axis, l[2], n1;   // n1: values of l[0] computed
+    long long cost;
     int reflect, ncol, iz0, cg, ntc, ncg, ntl, nyp, tcm, np, planes, lds;
 };
 // Everything the fused grid kernel needs for one evaluation (one request of
@@ -83,17 +87,19 @@ struct GridShape {
 // and the outputs.  Filled on the host; the batch kernel reads it from device
 // memory.
 struct GridDesc {
-    const float2* V;          // x table, then (from byte ybase) the y table
+    const float2* V;          // table of line axis 0 ("x"), then (from byte ybase) of line axis 1 ("y")
     int nxr, nyr;             // their rows, the zero row included
     uint32_t ybase;
-    const uint4* Bt;          // z axis, operand order
+    const uint4* Bt;          // contracted axis ("z"), operand order
     const int2* terms;        // (x row, y row)
     const float* Tw;          // weights (grid_term_weights)
     const double* sinv;       // per state: the power of two that undoes the scaling
     ChunkSplit sp;
-    int3 n;                   // grid points per axis
+    int nl, nc;               // grid points of line axis 1 and of the contracted axis
+    int sx, sy, sz;           // output strides of the line axes and the contracted one
+    long long npts;           // grid points
     KSteps steps;
-    int nx_eval, n_states;
+    int n1, n_states;         // values of line axis 0 computed
     int ntl, ntc, ncg, ncol, iz0, reflect, nyp, tcm, np;
     float2* f;                // outputs (NULL to skip), or
     float* f2;
@@ -221,7 +227,9 @@ constexpr size_t kSmallBytes = kSmallTail + 8 * kMaxStates * kTailBins;
 constexpr size_t kPinnedTables = 4096;   // byte offset of the molecule upload
 
 struct PrepResult {
-    int n_rows = 0, n_x = 0, n_y = 0;   // compacted rows: the zero row, n_x x rows, n_y y rows, the z rows
+    int n_rows = 0, n_axis[3] = {};   // compacted rows: the zero row, then the rows of x, y and z
+    int axis = 2;                     // contracted axis of the grid kernel's layout
+    int seg(int a) const { return (a > 0 ? n_axis[0] : 0) + (a > 1 ? n_axis[1] : 0); }   // rows before axis a's, the zero row aside
     int n_ksteps = 0, state_blocks = 1;
     KSteps ksteps{};
     long long n_zterms = 0, n_zweights = 0;
@@ -240,8 +248,12 @@ std::string build_basis(Basis& b, int n_atoms, const double* xyz, int n_shells,
                         const double* exps, const double* coefs, int normalise);
 
 // ---- device precompute (prep.hip) ----
-hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStream_t st,
+// axis: contracted axis of the grid kernel's layout; run_prep_layout makes the
+// layout of another one.
+hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, int axis, hipStream_t st,
                     const std::function<hipError_t(DeviceBuffer&, size_t)>& alloc);
+hipError_t run_prep_layout(const PrepInputs& in, PrepWork& w, PrepResult& res, int axis, bool first, hipStream_t st,
+                           const std::function<hipError_t(DeviceBuffer&, size_t)>& alloc);
 hipError_t run_prep_stats(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStream_t st);
 hipError_t run_prep_pairs(const PrepInputs& in, PrepWork& w, const PrepResult& res, hipStream_t st,
                           const std::function<hipError_t(DeviceBuffer&, size_t)>& alloc);

@@ -66,30 +66,30 @@ __global__ void vtable_kernel(const VRowDev* __restrict__ rows, int nrows, int v
     }
 }
 
-// The x and y rows' tables of the grid kernel.  x: value-major V[qx][row], so
-// that the rows of neighbouring terms (which neighbour each other) share cache
-// lines; y: blocks of 8 values, V[qy / 8][row][8], so that a tile's lines read
-// whole 64-byte runs.  rows: the zero row, the x rows, the y rows; nxr and nyr
-// count the zero row too.
-__device__ __forceinline__ void xytable(const VRowDev* __restrict__ rows, int nxr, int nyr, int nx, int ny, double2 qmin,
+// The tables of the grid kernel's line axes, "x" and "y".  x: value-major
+// V[qx][row], so that the rows of neighbouring terms (which neighbour each other)
+// share cache lines; y: blocks of 8 values, V[qy / 8][row][8], so that a tile's
+// lines read whole 64-byte runs.  Table row r is the zero row rows[0] or
+// rows[seg + r]; nxr and nyr count the zero row too.
+__device__ __forceinline__ void xytable(const VRowDev* __restrict__ rows, int nxr, int nyr, int2 seg, int nx, int ny, double2 qmin,
                                         double2 dq, float2* __restrict__ X, float2* __restrict__ Y, long long i0,
                                         long long step) {
     const long long tx = (long long)nx * nxr, tot = tx + (long long)((ny + 7) & ~7) * nyr;
     for (long long i = i0; i < tot; i += step) {
         if (i < tx) {
             const int q = (int)(i / nxr), r = (int)(i - (long long)q * nxr);
-            X[i] = eval_row(rows[r], qmin.x + dq.x * (double)q);
+            X[i] = eval_row(rows[r ? seg.x + r : 0], qmin.x + dq.x * (double)q);
         } else {
             const long long o = i - tx;
             const int v = (int)(o & 7);
             const long long br = o >> 3;
             const int b = (int)(br / nyr), r = (int)(br - (long long)b * nyr), q = 8 * b + v;
-            Y[o] = q < ny ? eval_row(rows[r ? nxr - 1 + r : 0], qmin.y + dq.y * (double)q) : make_float2(0.f, 0.f);
+            Y[o] = q < ny ? eval_row(rows[r ? seg.y + r : 0], qmin.y + dq.y * (double)q) : make_float2(0.f, 0.f);
         }
     }
 }
 
-// V block of the z axis in the grid kernel's operand order: fragment
+// V block of the contracted axis in the grid kernel's operand order: fragment
 // ((k-step * ncg + column group) * planes + plane) of 64 lanes x 16 bytes, lane
 // (g, n) = z rows 8 g .. 8 g + 7 of the k-step at column n, planes re then im,
 // each part of the row (scaled by its power of two) in turn: three BF16 parts
@@ -128,18 +128,19 @@ __device__ __forceinline__ void ztable(const VRowDev* __restrict__ rows, const i
     }
 }
 
-// All of them in one launch: the z axis' blocks (eight values per thread, the
-// longest) first.
+// All of them in one launch: the contracted axis' blocks (eight values per
+// thread, the longest) first.  nx, ny and the members of qmin and dq: line axes
+// 0 and 1, contracted axis.
 template <typename H, int PARTS>
-__global__ __launch_bounds__(256) void tables_kernel(const VRowDev* __restrict__ rows, int nxr, int nyr, int nx, int ny,
-                                                     double3 qmin, double3 dq, float2* __restrict__ X,
+__global__ __launch_bounds__(256) void tables_kernel(const VRowDev* __restrict__ rows, int nxr, int nyr, int2 seg, int nx,
+                                                     int ny, double3 qmin, double3 dq, float2* __restrict__ X,
                                                      float2* __restrict__ Y, const int2* __restrict__ zslots, int n_oct,
                                                      int ncg, int ncol, int iz0, uint4* __restrict__ Bt, int nbz) {
     if ((int)blockIdx.x < nbz)
         ztable<H, PARTS>(rows, zslots, n_oct, ncg, ncol, iz0, qmin.z, dq.z, Bt, blockIdx.x * 256LL + threadIdx.x,
                          nbz * 256LL);
     else
-        xytable(rows, nxr, nyr, nx, ny, make_double2(qmin.x, qmin.y), make_double2(dq.x, dq.y), X, Y,
+        xytable(rows, nxr, nyr, seg, nx, ny, make_double2(qmin.x, qmin.y), make_double2(dq.x, dq.y), X, Y,
                 (blockIdx.x - nbz) * 256LL + threadIdx.x, (gridDim.x - nbz) * 256LL);
 }
 
@@ -149,7 +150,9 @@ __global__ __launch_bounds__(256) void tables_kernel(const VRowDev* __restrict__
 //   U_s(z, line) = sum_{t with z row z} T'_s(t) Vx_t(qx) Vy_t(qy)     (VALU)
 //   f_s(line, qz) = sum_z U_s(z, line) Vz(z, qz)                      (matrix cores)
 // z runs over the distinct 1D rows of the z axis (one per primitive pair and
-// power pair; about half as many as terms), line over the (qx, qy) pairs.
+// power pair; about half as many as terms), line over the (qx, qy) pairs.  "z" is
+// the contracted axis, of the three the one of the least cost (choose_axis,
+// runtime.cpp), "x" and "y" the other two.
 // The second sum is a real matrix product of [Re U; Im U] (rows: state, line)
 // with [Re V | Im V] (columns: qz), K = z rows, whose four blocks
 //   P = Ur Vr, Q = Ui Vi, R = Ur Vi, S = Ui Vr
@@ -314,7 +317,7 @@ __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds
     const int k_lo = d.sp.lo[split], k_hi = d.sp.lo[split + 1];
 
     // the tile's line pairs; the lane's row (clamped into the problem)
-    const int nlines = d.nx_eval * d.nyp, nrows = nlines * ns;
+    const int nlines = d.n1 * d.nyp, nrows = nlines * ns;
     const int row0 = lt * kGridWaves * 16;
     const int pair0 = row0 / ns >> 1;
     const int npair = (min(row0 + kGridWaves * 16, nrows) - 1) / ns / 2 - pair0 + 1;
@@ -524,15 +527,14 @@ __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds
     }
 
     // epilogue: lane (g, m) holds rows 4 g + i, column m of its quads
-    const long long plane = (long long)d.n.y * d.n.z;
     const int rw = row0 + 16 * wave + 4 * g;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int ln = (rw + i) / ns, s = rw + i - ln * ns;
         const int qx = ln / d.nyp, qy = ln - qx * d.nyp;
-        if (rw + i >= nrows || qy >= d.n.y) continue;
+        if (rw + i >= nrows || qy >= d.nl) continue;
         const double sc = d.sinv[s];
-        const size_t base = (size_t)s * d.n.x * plane + (size_t)qx * plane + (size_t)qy * d.n.z;
+        const size_t base = (size_t)s * d.npts + (size_t)qx * d.sx + (size_t)qy * d.sy;
 #pragma unroll
         for (int q = 0; q < CG; ++q) {
             const int col = (ct * CG + q) * 16 + m;
@@ -543,7 +545,7 @@ __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds
 #pragma unroll
                 for (int b = 0; b < 2; ++b) v[a][b] = sc * (FOLD ? tot[FOLD ? q : 0][a][b][i] : (double)acc[q][a][b][i]);
             auto put = [&](int iz, double re, double im) {
-                const size_t o = base + iz;
+                const size_t o = base + (size_t)iz * d.sz;
                 if (d.partial) {   // split pair sum: FP64 partial, summed by reduce_kernel
                     d.partial[(size_t)split * d.part_stride + o] = make_double2(re, im);
                 } else {
@@ -551,7 +553,7 @@ __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds
                     if (d.f2) d.f2[o] = (float)(re * re + im * im);
                 }
             };
-            const int iz = d.iz0 + col, im = d.n.z - 1 - iz;
+            const int iz = d.iz0 + col, im = d.nc - 1 - iz;
             put(iz, v[0][0] - v[1][1], v[0][1] + v[1][0]);
             if (d.reflect && im != iz) put(im, v[0][0] + v[1][1], v[1][0] - v[0][1]);
         }
@@ -675,28 +677,33 @@ int vtable_stride(const int n[3]) {
     return ((m + 15) / 16) * 16 + 16;
 }
 
-hipError_t launch_grid_tables(const VRowDev* rows, int nxr, int nyr, const int2* zslots, int n_zpad, const GridShape& g,
+hipError_t launch_grid_tables(const PrepResult& p, const VRowDev* rows, const int2* zslots, const GridShape& g,
                               const int n[3], const double qmin[3], const double dq[3], float2* X, float2* Y, uint4* Bt,
                               hipStream_t st) {
-    const int n_oct = n_zpad / 8;
+    if (p.axis != g.axis) return hipErrorInvalidValue;
+    const int n_oct = p.n_ksteps * (kZStep / 8);
+    const int a = g.l[0], b = g.l[1], c = g.axis, nxr = p.n_axis[a] + 1, nyr = p.n_axis[b] + 1;
+    const int2 seg = make_int2(p.seg(a), p.seg(b));
     const long long tz = (long long)n_oct * g.ncg * 16;
-    const long long txy = (long long)n[0] * nxr + (long long)((n[1] + 7) & ~7) * nyr;
+    const long long txy = (long long)n[a] * nxr + (long long)((n[b] + 7) & ~7) * nyr;
     const int nbz = (int)std::min<long long>((tz + 255) / 256, 32768);
     const int nbxy = (int)std::max<long long>(1, std::min<long long>((txy + 255) / 256, 32768));
-    const double3 q0 = make_double3(qmin[0], qmin[1], qmin[2]), d = make_double3(dq[0], dq[1], dq[2]);
+    const double3 q0 = make_double3(qmin[a], qmin[b], qmin[c]), d = make_double3(dq[a], dq[b], dq[c]);
     if (g.planes == Operands<true>::planes)
         hipLaunchKernelGGL((tables_kernel<__bf16, Operands<true>::parts>), dim3(nbz + nbxy), dim3(256), 0, st, rows, nxr,
-                           nyr, n[0], n[1], q0, d, X, Y, zslots, n_oct, g.ncg, g.ncol, g.iz0, Bt, nbz);
+                           nyr, seg, n[a], n[b], q0, d, X, Y, zslots, n_oct, g.ncg, g.ncol, g.iz0, Bt, nbz);
     else
         hipLaunchKernelGGL((tables_kernel<_Float16, Operands<false>::parts>), dim3(nbz + nbxy), dim3(256), 0, st, rows, nxr,
-                           nyr, n[0], n[1], q0, d, X, Y, zslots, n_oct, g.ncg, g.ncol, g.iz0, Bt, nbz);
+                           nyr, seg, n[a], n[b], q0, d, X, Y, zslots, n_oct, g.ncg, g.ncol, g.iz0, Bt, nbz);
     return hipGetLastError();
 }
 
 // Tiling: column groups per tile (CG), chosen for the least time among those
-// whose LDS fits.  A wave's k-step costs its products (12 CG matrix instructions
-// and, in FP32, their fold) and forming U, which every column tile repeats: about
-// 16 CG + 30 (in units of one matrix instruction).  Two terms per step where
+// whose LDS fits.  A wave's k-step costs its products (and, in FP32, their
+// fold) and forming U, which every column tile repeats: 30 + 31 CG in FP32
+// precision, 30 + 10 CG and 30 + 22 CG in split precision on f16 halves and BF16
+// parts (30 heavy atoms, 24 states, 96x96 lines, one and three column groups: 26.9
+// and 54.3, 20.3 and 30.2, 26.1 and 48.2 ms).  Two terms per step where
 // the LDS allows (one barrier for both), else one (one or two states: W has up to
 // 64 lines).  FP32 precision stops at three column groups: the totals of a fourth
 // spill 34 registers of 256 (10 heavy atoms, 12 states, 128^3, whose 64 columns are
@@ -705,16 +712,21 @@ hipError_t launch_grid_tables(const VRowDev* rows, int nxr, int nyr, const int2*
 // rows x vtable_stride, by which a grid is accepted.
 int max_cg(GridKind kind) { return kind == kGridFp32 ? 3 : 4; }
 
-GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect, GridKind kind) {
+GridShape grid_shape(const int n[3], int axis, int nx_eval, int n_states, bool reflect, GridKind kind) {
     GridShape g{};
+    g.axis = axis;
+    g.l[0] = axis == 0 ? 1 : 0;
+    g.l[1] = axis == 2 ? 1 : 2;
+    g.n1 = g.l[0] == 0 ? nx_eval : n[1];
+    const int nc = n[axis];
     g.reflect = reflect ? 1 : 0;
     g.kind = kind;
     g.planes = kind == kGridSplitF16 ? Operands<false>::planes : Operands<true>::planes;
-    g.ncol = reflect ? (n[2] + 1) / 2 : n[2];
-    g.iz0 = reflect ? n[2] - g.ncol : 0;
-    g.nyp = (n[1] + 1) & ~1;   // lines in pairs of one qx
+    g.ncol = reflect ? (nc + 1) / 2 : nc;
+    g.iz0 = reflect ? nc - g.ncol : 0;
+    g.nyp = (n[g.l[1]] + 1) & ~1;   // lines in pairs of one value of l[0]
     const int ng = (g.ncol + 15) / 16, tr = 16 * kGridWaves;
-    const long long nrows = (long long)nx_eval * g.nyp * n_states;
+    const long long nrows = (long long)g.n1 * g.nyp * n_states;
     g.ntl = (int)((nrows + tr - 1) / tr);
     // most line pairs that a tile's rows touch
     g.np = 1;
@@ -730,7 +742,7 @@ GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect, Gr
         if (bytes() > kGridLds) break;
         const int nt = (ng + cg - 1) / cg;
         if (nt * cg > ng + 1) continue;
-        const long long cost = (long long)nt * (16 * cg + 30);
+        const long long cost = (long long)nt * (30 + (kind == kGridFp32 ? 31 : kind == kGridSplitF16 ? 10 : 22) * cg);
         if (!g.cg || cost < best) {
             best = cost;
             g.cg = cg;
@@ -740,6 +752,7 @@ GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect, Gr
         }
     }
     g.ncg = g.ntc * g.cg;
+    g.cost = best * g.ntl;
     return g;
 }
 
@@ -753,14 +766,15 @@ int grid_wgs_per_cu(int cls, int lds) {
 // The kernel's variant; class 3 (four column groups with totals) does not exist.
 int grid_class(const GridShape& g) { return (g.cg - 1) + 4 * g.kind; }
 
-hipError_t grid_desc(const GridShape& g, const float2* V, int nxr, int nyr, uint32_t ybase, const uint4* Bt, const KSteps& steps,
+hipError_t grid_desc(const GridShape& g, const PrepResult& p, const float2* V, uint32_t ybase, const uint4* Bt,
                      const int2* terms, const float* Tw, const double* sinv, const ChunkSplit& sp, const int n[3],
-                     int nx_eval, int n_states, float2* f, float* f2, double2* part, GridDesc* d, long long* blocks) {
-    if (nxr < 1 || nyr < 1 || (size_t)ybase < (size_t)n[0] * nxr * sizeof(float2)) return hipErrorInvalidValue;
-    if (nx_eval < 1 || nx_eval > n[0] || n_states < 1 || n_states > kMaxStates) return hipErrorInvalidValue;
+                     int n_states, float2* f, float* f2, double2* part, GridDesc* d, long long* blocks) {
+    const int nxr = p.n_axis[g.l[0]] + 1, nyr = p.n_axis[g.l[1]] + 1;
+    if (p.axis != g.axis || (size_t)ybase < (size_t)n[g.l[0]] * nxr * sizeof(float2)) return hipErrorInvalidValue;
+    if (g.n1 < 1 || g.n1 > n[g.l[0]] || n_states < 1 || n_states > kMaxStates) return hipErrorInvalidValue;
     if (g.cg < 1 || g.cg > 4 || g.ncg != g.cg * g.ntc || g.ncg * 16 < g.ncol || g.tcm < 1 || g.tcm > 2)
         return hipErrorInvalidValue;
-    if ((long long)nx_eval * g.nyp * n_states > 0x7fffffff - 64) return hipErrorInvalidValue;
+    if ((long long)g.n1 * g.nyp * n_states > 0x7fffffff - 64) return hipErrorInvalidValue;   // at most 4096 4096 32
     if (sp.n < 1 || sp.n > kMaxSplit || sp.lo[0] != 0) return hipErrorInvalidValue;
     for (int j = 0; j < sp.n; ++j)
         if (sp.lo[j + 1] < sp.lo[j]) return hipErrorInvalidValue;
@@ -770,13 +784,19 @@ hipError_t grid_desc(const GridShape& g, const float2* V, int nxr, int nyr, uint
     d->nyr = nyr;
     d->ybase = ybase;
     d->Bt = Bt;
-    d->steps = steps;
+    d->steps = p.ksteps;
     d->terms = terms;
     d->Tw = Tw;
     d->sinv = sinv;
     d->sp = sp;
-    d->n = make_int3(n[0], n[1], n[2]);
-    d->nx_eval = nx_eval;
+    const int stride[3] = {n[1] * n[2], n[2], 1};
+    d->sx = stride[g.l[0]];
+    d->sy = stride[g.l[1]];
+    d->sz = stride[g.axis];
+    d->npts = (long long)n[0] * n[1] * n[2];
+    d->nl = n[g.l[1]];
+    d->nc = n[g.axis];
+    d->n1 = g.n1;
     d->n_states = n_states;
     d->nyp = g.nyp;
     d->tcm = g.tcm;
@@ -790,7 +810,7 @@ hipError_t grid_desc(const GridShape& g, const float2* V, int nxr, int nyr, uint
     d->f = f;
     d->f2 = f2;
     d->partial = sp.n > 1 ? part : nullptr;
-    d->part_stride = (long long)n_states * n[0] * n[1] * n[2];
+    d->part_stride = n_states * d->npts;
     *blocks = (long long)g.ntl * g.ntc * sp.n;
     return hipSuccess;
 }

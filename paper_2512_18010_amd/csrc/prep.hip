@@ -20,9 +20,10 @@
 //   thresh_kernel   largest 2^b with sum_{e <= b} count_e 2^e <= eps: dropping
 //                   every w < 2^b keeps, for every transition, the dropped
 //                   bounds below eps * tot_s
-// Grid kernel's layout (run_prep):
+// Grid kernel's layout (run_prep, run_prep_layout), by the contracted axis, called z
+// here whichever of the grid's it is:
 //   zcount_kernel   kept terms of every z row (one per primitive pair and
-//                   power pair of the z axis), flags of the referenced rows, and
+//                   power pair of the axis), flags of the referenced rows, and
 //                   per state the largest bound of a row's contribution
 //   scan            one scan numbers the rows (a zero row, the x and y rows,
 //                   the z rows) and sorts the z rows by term count (most terms
@@ -420,16 +421,20 @@ __global__ void layout_kernel(const int* __restrict__ order, const int4* __restr
     }
 }
 
-// Component pairs of a shell pair by the powers (i, j) of the z axis, in
-// component order: for every (lA, lB, same shell), class i (lB + 1) + j ->
+// Component pairs of a shell pair by the powers (i, j) of an axis, in
+// component order: for every axis and (lA, lB, same shell), class i (lB + 1) + j ->
 // count and component pairs.
 struct ZClasses {
-    unsigned char n[18][9], c[18][9][kZTerms];
+    unsigned char n[54][9], c[54][9][kZTerms];
 };
 constexpr ZClasses make_zclasses() {
-    constexpr int cz[3][6] = {{0}, {0, 0, 1}, {0, 0, 1, 0, 1, 2}};
+    constexpr int cart[3][3][6] = {{{0}, {1, 0, 0}, {2, 1, 1, 0, 0, 0}},
+                                   {{0}, {0, 1, 0}, {0, 1, 0, 2, 1, 0}},
+                                   {{0}, {0, 0, 1}, {0, 0, 1, 0, 1, 2}}};
     ZClasses t{};
-    for (int k = 0; k < 18; ++k) {
+    for (int ak = 0; ak < 54; ++ak) {
+        const int(&cz)[3][6] = cart[ak / 18];
+        const int k = ak % 18;
         const int lA = k / 6, lB = k / 2 % 3, same = k & 1;
         const int ncA = (lA + 1) * (lA + 2) / 2, ncB = (lB + 1) * (lB + 2) / 2;
         if (same && lA != lB) continue;
@@ -437,7 +442,7 @@ constexpr ZClasses make_zclasses() {
         for (int c1 = 0; c1 < ncA; ++c1)
             for (int c2 = same ? c1 : 0; c2 < ncB; ++c2, ++c) {
                 const int cls = cz[lA][c1] * (lB + 1) + cz[lB][c2];
-                t.c[k][cls][t.n[k][cls]++] = (unsigned char)c;
+                t.c[ak][cls][t.n[ak][cls]++] = (unsigned char)c;
             }
     }
     return t;
@@ -448,6 +453,8 @@ __device__ __constant__ ZClasses kZClasses = make_zclasses();
 __device__ __forceinline__ int z_exponent(double bound) {
     return bound > 0.0 && bound < 1e300 ? max(-900, min(900, 13 - ilogb(bound))) : 0;
 }
+
+__device__ __forceinline__ int term_row(const int4& t, int axis) { return axis == 0 ? t.x : axis == 1 ? t.y : t.z; }
 
 // Per z row (id = row offset / 3 + pp ncls + class): kept terms n, one-hot flags
 // of 9 - n behind the row flags (used + 3 nr, 9 segments of all z rows, so that
@@ -461,7 +468,7 @@ __global__ __launch_bounds__(128) void zcount_kernel(const PrepShell* __restrict
                                                     const int4* __restrict__ trow, const double* __restrict__ rowsum,
                                                     const double* __restrict__ w, const double* __restrict__ thr,
                                                     const double* __restrict__ tp64, int ns, int nr,
-                                                    int nz_all, int* __restrict__ used, int* __restrict__ zn,
+                                                    int nz_all, int axis, int* __restrict__ used, int* __restrict__ zn,
                                                     int2* __restrict__ zinfo, unsigned long long* __restrict__ gmx,
                                                     unsigned long long* __restrict__ gtail,
                                                     const VRowDev* __restrict__ rows) {
@@ -477,7 +484,8 @@ __global__ __launch_bounds__(128) void zcount_kernel(const PrepShell* __restrict
     if (ss)
         for (int i = threadIdx.x; i < ns * kTailBins; i += blockDim.x) tail[i] = 0ull;
     __syncthreads();
-    const int kc = lA * 6 + lB * 2 + (same ? 1 : 0), nz = npp * ncls;
+    const int kc = 18 * axis + lA * 6 + lB * 2 + (same ? 1 : 0), nz = npp * ncls;
+    const int la = axis == 0 ? 1 : 0, lb = axis == 2 ? 1 : 2;   // the line axes
     for (int z = threadIdx.x; z < nz; z += blockDim.x) {
         const int pp = z / ncls, cls = z - pp * ncls;
         int n = 0;
@@ -485,15 +493,15 @@ __global__ __launch_bounds__(128) void zcount_kernel(const PrepShell* __restrict
             const int t = s.w + kZClasses.c[kc][cls][k] * npp + pp;
             if (!term_kept(w[t], th)) continue;
             const int4 tr = trow[t];
-            used[tr.x] = 1;
-            used[nr + tr.y] = 1;
+            used[la * nr + term_row(tr, la)] = 1;
+            used[lb * nr + term_row(tr, lb)] = 1;
             ++n;
         }
         const int id = s.z / 3 + z;
         zn[id] = n;
         zinfo[id] = make_int2(isp, z);
         for (int k = 0; k < kZTerms; ++k) used[(size_t)3 * nr + (size_t)k * nz_all + id] = n == kZTerms - k;
-        if (n) used[2 * nr + s.z + pp * 3 * ncls + 2 * ncls + cls] = 1;
+        if (n) used[axis * nr + s.z + pp * 3 * ncls + axis * ncls + cls] = 1;
     }
     for (int i = threadIdx.x; i < nz * ns; i += blockDim.x) {
         const int z = i / ns, st = i - z * ns;
@@ -503,9 +511,9 @@ __global__ __launch_bounds__(128) void zcount_kernel(const PrepShell* __restrict
             const int t = s.w + kZClasses.c[kc][cls][k] * npp + pp;
             if (!term_kept(w[t], th)) continue;
             const int4 tr = trow[t];
-            b += fabs(tp64[(size_t)tr.w * ns + st]) * rowsum[tr.x] * rowsum[tr.y];
+            b += fabs(tp64[(size_t)tr.w * ns + st]) * rowsum[term_row(tr, la)] * rowsum[term_row(tr, lb)];
         }
-        const int rz = s.z + pp * 3 * ncls + 2 * ncls + cls;
+        const int rz = s.z + pp * 3 * ncls + axis * ncls + cls;
         if (ss) {   // one term, of magnitude b times its Gaussian
             const double t = b * rowsum[rz];
             const int e = ilogb(0.25 / rows[rz].inv4p) - kTailMin;
@@ -555,7 +563,7 @@ __global__ __launch_bounds__(256) void zlayout_kernel(const PrepShell* __restric
                                                       const double* __restrict__ tp64, int ns, int nr,
                                                       const int* __restrict__ newid, const int* __restrict__ znum,
                                                       const int2* __restrict__ zinfo, int nz, int nzpad, int nz_all,
-                                                      KSteps steps, const int* __restrict__ ks,
+                                                      int axis, KSteps steps, const int* __restrict__ ks,
                                                       int2* __restrict__ zslots, int2* __restrict__ terms,
                                                       float* __restrict__ Tw, int nbz, const VRowDev* __restrict__ rows,
                                                       const int* __restrict__ used, VRowDev* __restrict__ out) {
@@ -572,6 +580,7 @@ __global__ __launch_bounds__(256) void zlayout_kernel(const PrepShell* __restric
         }
         return;
     }
+    const int la = axis == 0 ? 1 : 0, lb = axis == 2 ? 1 : 2;   // the line axes
     const long long tot = (long long)(nz_all + nzpad - nz) * ns;
     for (long long gi = blockIdx.x * (long long)blockDim.x + threadIdx.x; gi < tot; gi += (long long)nbz * blockDim.x) {
         const int id = (int)(gi / ns), st = (int)(gi - (long long)id * ns);
@@ -594,16 +603,18 @@ __global__ __launch_bounds__(256) void zlayout_kernel(const PrepShell* __restric
             const int4 s = sp[zi.x];
             const int lA = sh[s.x].l, lB = sh[s.y].l, npp = sh[s.x].nprim * sh[s.y].nprim;
             const int ncls = (lA + 1) * (lB + 1), pp = zi.y / ncls, cls = zi.y - pp * ncls;
-            const int rz = s.z + pp * 3 * ncls + 2 * ncls + cls;
+            const int rz = s.z + pp * 3 * ncls + axis * ncls + cls;
             const int e = z_exponent(rowsum[rz]);
             const double th = thr[0], sc = ldexp(1.0, ks[st] - e);
-            const int kc = lA * 6 + lB * 2 + (s.x == s.y ? 1 : 0);
+            const int kc = 18 * axis + lA * 6 + lB * 2 + (s.x == s.y ? 1 : 0);
             for (int k = 0; k < kZClasses.n[kc][cls]; ++k) {
                 const int t = s.w + kZClasses.c[kc][cls][k] * npp + pp;
                 if (!term_kept(w[t], th)) continue;
                 const int4 tr = trow[t];
-                // rows of the x and y tables, whose row 0 is the zero row
-                if (st == 0) rec[kZStep * n] = make_int2(1 + newid[tr.x], 1 + newid[nr + tr.y] - newid[nr]);
+                // rows of the line axes' tables, whose row 0 is the zero row
+                if (st == 0)
+                    rec[kZStep * n] = make_int2(1 + newid[la * nr + term_row(tr, la)] - newid[la * nr],
+                                                1 + newid[lb * nr + term_row(tr, lb)] - newid[lb * nr]);
                 const double tp = tp64[(size_t)tr.w * ns + st];
                 float v = (float)(tp * sc);
                 // finite weights stay finite (a row bound that underflows)
@@ -611,7 +622,7 @@ __global__ __launch_bounds__(256) void zlayout_kernel(const PrepShell* __restric
                 tw[n * tstep] = v;
                 ++n;
             }
-            if (st == 0) zslots[p] = make_int2(1 + newid[2 * nr + rz], e);
+            if (st == 0) zslots[p] = make_int2(1 + newid[axis * nr + rz], e);
         } else if (st == 0) {
             zslots[p] = make_int2(0, 0);
         }
@@ -620,6 +631,10 @@ __global__ __launch_bounds__(256) void zlayout_kernel(const PrepShell* __restric
             tw[n * tstep] = 0.f;
         }
     }
+}
+
+__global__ __launch_bounds__(256) void clear_kernel(unsigned* __restrict__ p, int n) {
+    for (int i = threadIdx.x; i < n; i += 256) p[i] = 0u;
 }
 
 // ------------------------------------------------------------------ host driver
@@ -643,12 +658,12 @@ int blocks_for(long long n, int bs) {
 // Runs the precompute and the grid kernel's layout on `st`.  Buffers in `w` are (re)allocated through
 // `alloc`, which enforces the caller's memory budget.  Returns hipSuccess or
 // the first HIP error; sizes and statistics are written to `res`.
-hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStream_t st,
+hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, int axis, hipStream_t st,
                     const std::function<hipError_t(DeviceBuffer&, size_t)>& alloc) {
     hipError_t e;
     const long long NR = in.n_rows_all, NT = in.n_terms_all;
     const int NCP = in.n_cp, NSP = in.n_sp, ns = in.n_states;
-    const int NZ = (int)(NR / 3);   // z rows
+    const int NZ = (int)(NR / 3);   // rows per axis
     CK(alloc(w.rows_all, (size_t)NR * sizeof(VRowDev)));
     CK(alloc(w.rowsum, (size_t)NR * sizeof(double)));
     CK(alloc(w.trow, (size_t)NT * sizeof(int4)));
@@ -667,11 +682,6 @@ hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStrea
     CK(alloc(w.newid, (size_t)NF * sizeof(int)));
     double* tot = (double*)w.small.p;                                    // [<= 32]
     double* thr = tot + 64;                                              // [1]
-    double* sinv = (double*)((char*)w.small.p + kSmallSinv);             // [<= 32]
-    int* ks = (int*)((char*)w.small.p + kSmallKs);                       // [<= 32]
-    int* meta = (int*)((char*)w.small.p + kSmallMeta);                   // [12]
-    unsigned long long* zmx = (unsigned long long*)((char*)w.small.p + kSmallZmax);   // [<= 32]
-    unsigned long long* tail = (unsigned long long*)((char*)w.small.p + kSmallTail);  // [ns][kTailBins]
     unsigned* hist = (unsigned*)((char*)w.small.p + kSmallHist);         // [kHistBins]
 
     const int nsmall = (int)(kSmallBytes / sizeof(unsigned));
@@ -690,13 +700,35 @@ hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStrea
     CK(hipGetLastError());
     hipLaunchKernelGGL(thresh_kernel, dim3(1), dim3(64), 0, st, (const unsigned*)hist, in.eps, thr);
     CK(hipGetLastError());
+    return run_prep_layout(in, w, res, axis, true, st, alloc);
+}
+
+// The grid kernel's layout by one axis, after the rest of the precompute (first),
+// or again by another axis.
+hipError_t run_prep_layout(const PrepInputs& in, PrepWork& w, PrepResult& res, int axis, bool first, hipStream_t st,
+                           const std::function<hipError_t(DeviceBuffer&, size_t)>& alloc) {
+    hipError_t e;
+    const long long NR = in.n_rows_all, NF = 3 * NR + (long long)kZTerms * (NR / 3);
+    const int NZ = (int)(NR / 3), NSP = in.n_sp, ns = in.n_states;
+    const double* thr = (const double*)w.small.p + 64;
+    double* sinv = (double*)((char*)w.small.p + kSmallSinv);             // [<= 32]
+    int* ks = (int*)((char*)w.small.p + kSmallKs);                       // [<= 32]
+    int* meta = (int*)((char*)w.small.p + kSmallMeta);                   // [12]
+    unsigned long long* zmx = (unsigned long long*)((char*)w.small.p + kSmallZmax);   // [<= 32]
+    unsigned long long* tail = (unsigned long long*)((char*)w.small.p + kSmallTail);  // [ns][kTailBins]
+    if (axis < 0 || axis > 2) return hipErrorInvalidValue;
+    if (!first) {
+        hipLaunchKernelGGL(clear_kernel, dim3(1), dim3(256), 0, st, (unsigned*)zmx,
+                           (int)((kSmallBytes - kSmallZmax) / sizeof(unsigned)));
+        CK(hipGetLastError());
+    }
     // the term bounds were last read by weight_kernel: their buffer holds the
     // z rows' places and term counts from here on
     int2* zinfo = (int2*)w.tbound.p;
     int* zn = (int*)(zinfo + NZ);
     hipLaunchKernelGGL(zcount_kernel, dim3(NSP), dim3(128), 0, st, in.shells, in.sp, (const int4*)w.trow.p,
                        (const double*)w.rowsum.p, (const double*)w.wt.p, (const double*)thr, (const double*)w.tp64.p, ns,
-                       (int)NR, NZ, (int*)w.row_used.p, zn, zinfo, zmx, tail, (const VRowDev*)w.rows_all.p);
+                       (int)NR, NZ, axis, (int*)w.row_used.p, zn, zinfo, zmx, tail, (const VRowDev*)w.rows_all.p);
     CK(hipGetLastError());
     size_t tmp_bytes = 0;
     CK(hipcub::DeviceScan::ExclusiveSum(nullptr, tmp_bytes, (int*)w.row_used.p, (int*)w.newid.p, (int)NF, st));
@@ -736,13 +768,14 @@ hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, hipStrea
     hipLaunchKernelGGL(zlayout_kernel, dim3(nbz + blocks_for(3 * NR, 256)), dim3(256), 0, st, in.shells, in.sp,
                        (const int4*)w.trow.p, (const double*)w.rowsum.p, (const double*)w.wt.p, (const double*)thr,
                        (const double*)w.tp64.p, ns, (int)NR, (const int*)w.newid.p, (const int*)zn, (const int2*)zinfo, nz,
-                       nzpad, NZ, steps, (const int*)ks, (int2*)w.zslots.p, (int2*)w.zterms.p, (float*)w.zw.p, nbz,
+                       nzpad, NZ, axis, steps, (const int*)ks, (int2*)w.zslots.p, (int2*)w.zterms.p, (float*)w.zw.p, nbz,
                        (const VRowDev*)w.rows_all.p, (const int*)w.row_used.p, (VRowDev*)w.rows.p);
     CK(hipGetLastError());
-    res = PrepResult{};
+    res.axis = axis;
     res.n_rows = nrows_used + 1;
-    res.n_x = rb[0];
-    res.n_y = rb[1] - rb[0];
+    res.n_axis[0] = rb[0];
+    res.n_axis[1] = rb[1] - rb[0];
+    res.n_axis[2] = rb[2] - rb[1];
     std::memcpy(res.zmax, rbuf + kSmallZmax - kSmallMeta, ns * sizeof(double));
     std::memcpy(res.tail, rbuf + kSmallTail - kSmallMeta, ns * sizeof(res.tail[0]));
     res.n_ksteps = n_ksteps;

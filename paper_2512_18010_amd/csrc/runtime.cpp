@@ -18,19 +18,19 @@ namespace scff {
 hipError_t launch_vtable(const VRowDev* rows, int nrows, int vstride, const int n[3],
                          const double qmin[3], const double dq[3], float2* V, hipStream_t st);
 int vtable_stride(const int n[3]);
-hipError_t launch_grid_tables(const VRowDev* rows, int nxr, int nyr, const int2* zslots, int n_zpad, const GridShape& g,
+hipError_t launch_grid_tables(const PrepResult& p, const VRowDev* rows, const int2* zslots, const GridShape& g,
                               const int n[3], const double qmin[3], const double dq[3], float2* X, float2* Y, uint4* Bt,
                               hipStream_t st);
-GridShape grid_shape(const int n[3], int nx_eval, int n_states, bool reflect, GridKind kind);
+GridShape grid_shape(const int n[3], int axis, int nx_eval, int n_states, bool reflect, GridKind kind);
 int grid_wgs_per_cu(int cls, int lds);
 hipError_t launch_grid(int cls, const GridShape& g, const GridDesc& d, long long blocks, hipStream_t st);
 hipError_t launch_reduce(const double2* part, int n_split, const int n[3], int nx_eval, int n_states, float2* f,
                          float* f2, hipStream_t st);
 hipError_t launch_mirror(const int n[3], int nx_eval, int n_states, float2* f, float* f2, hipStream_t st);
 int grid_class(const GridShape& g);
-hipError_t grid_desc(const GridShape& g, const float2* V, int nxr, int nyr, uint32_t ybase, const uint4* Bt, const KSteps& steps,
+hipError_t grid_desc(const GridShape& g, const PrepResult& p, const float2* V, uint32_t ybase, const uint4* Bt,
                      const int2* terms, const float* Tw, const double* sinv, const ChunkSplit& sp, const int n[3],
-                     int nx_eval, int n_states, float2* f, float* f2, double2* part, GridDesc* d, long long* blocks);
+                     int n_states, float2* f, float* f2, double2* part, GridDesc* d, long long* blocks);
 int points_split(int nq, int ns, int n_sp);
 hipError_t launch_points(const PointArgs& a, int n_split, hipStream_t st);
 int sep_parts(int ncp);
@@ -237,7 +237,7 @@ int record(scff_ctx* c, int which, hipStream_t st) {
 }
 
 // Host check of the tables the grid kernel indexes with (on request): every
-// term record names an x row in [0, n_x] and a y row in [0, n_y], every z slot
+// term record names rows of the two line axes' tables, every z slot
 // a row in [0, n_rows), and the k-steps lie inside the term arrays.  A violation is an
 // engine bug; it is reported as SCFF_EDEVICE before any kernel reads the
 // tables.
@@ -252,7 +252,7 @@ int validate_prep(scff_ctx* c, hipStream_t st) {
         (rc = hip_check(hipStreamSynchronize(st), "validation sync")))
         return rc;
     for (size_t i = 0; i < terms.size(); ++i) {
-        const int top = i % 2 ? p.n_y : p.n_x;
+        const int top = p.n_axis[i % 2 ? (p.axis == 2 ? 1 : 2) : (p.axis == 0 ? 1 : 0)];
         if (terms[i] < 0 || terms[i] > top)
             return fail(SCFF_EDEVICE, "precompute produced a term outside the 1D tables (term " + std::to_string(i / 2) +
                                           ", axis " + std::to_string(i % 2) + ", row " + std::to_string(terms[i]) +
@@ -300,21 +300,39 @@ PrepInputs prep_inputs(scff_ctx* c) {
     return in;
 }
 
-// The precompute and the grid kernel's layout.
-int ensure_prepared(scff_ctx* c, hipStream_t st) {
+// The precompute and the grid kernel's layout; axis: the axis to contract (-1:
+// any).  The layout of an axis other than z is optional: where its buffers do not
+// fit there is one by z.  A stream that is being captured cannot wait for a new
+// layout's sizes and keeps the present one.
+int ensure_prepared(scff_ctx* c, hipStream_t st, int axis = -1) {
     if (!c->have_mol) return fail(SCFF_ESTATE, "no molecule loaded");
     if (!c->have_T) return fail(SCFF_ESTATE, "no transitions loaded");
-    if (c->prepared) return SCFF_OK;
-    PrepResult res;
+    const bool again = c->prepared;
+    if (again) {
+        if (axis < 0 || axis == c->pres.axis) return SCFF_OK;
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            return SCFF_OK;
+        }
+    }
+    PrepResult res = again ? c->pres : PrepResult{};
     int rc;
     if ((rc = record(c, EV_PREP0, st))) return rc;
-    hipError_t e = run_prep(prep_inputs(c), c->prep, res, st,
-                            [c](DeviceBuffer& buf, size_t n) { return dev_reserve_raw(c, buf, n); });
+    const auto alloc = [c](DeviceBuffer& buf, size_t n) { return dev_reserve_raw(c, buf, n); };
+    const PrepInputs in = prep_inputs(c);
+    c->prepared = false;
+    hipError_t e = again ? run_prep_layout(in, c->prep, res, axis, false, st, alloc)
+                         : run_prep(in, c->prep, res, axis < 0 ? 2 : axis, st, alloc);
+    if (e == hipErrorOutOfMemory && axis >= 0 && axis != 2) {
+        (void)hipGetLastError();
+        e = again ? run_prep_layout(in, c->prep, res, 2, false, st, alloc) : run_prep(in, c->prep, res, 2, st, alloc);
+    }
     if (e != hipSuccess) return hip_check(e, "pair precompute");
     if ((rc = record(c, EV_PREP1, st))) return rc;
     c->ev_prep = c->timing;
     c->pres = res;
-    c->stats_ready = c->pairs_ready = false;
+    if (!again) c->stats_ready = c->pairs_ready = false;
     if (c->validate && (rc = validate_prep(c, st))) return rc;
     c->prepared = true;
     return SCFF_OK;
@@ -375,16 +393,16 @@ void grid_spacing(const scff_grid* g, double dq[3]) {
     for (int a = 0; a < 3; ++a) dq[a] = g->n[a] > 1 ? (g->qmax[a] - g->qmin[a]) / (g->n[a] - 1) : 0.0;
 }
 
-// Device bytes of a grid's 1D tables: the x table, the y table, then the z
-// axis' operand blocks.
+// Device bytes of a grid's 1D tables: those of the two line axes, then the
+// contracted axis' operand blocks.
 struct TableBytes {
-    size_t y, z, total;   // offsets of the y table and the blocks; total
+    size_t y, z, total;   // offsets of the second table and the blocks; total
 };
 TableBytes table_bytes(const scff_ctx* c, const scff_grid* g, const GridShape& sh) {
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
     TableBytes t;
-    t.y = up((size_t)(c->pres.n_x + 1) * g->n[0] * sizeof(float2));
-    t.z = t.y + up((size_t)(c->pres.n_y + 1) * ((g->n[1] + 7) & ~7) * sizeof(float2));
+    t.y = up((size_t)(c->pres.n_axis[sh.l[0]] + 1) * g->n[sh.l[0]] * sizeof(float2));
+    t.z = t.y + up((size_t)(c->pres.n_axis[sh.l[1]] + 1) * ((g->n[sh.l[1]] + 7) & ~7) * sizeof(float2));
     t.total = t.z + (size_t)c->pres.n_ksteps * sh.ncg * sh.planes * 1024;
     return t;
 }
@@ -400,8 +418,7 @@ int launch_tables(scff_ctx* c, const scff_grid* g, const GridShape& sh, void* ta
     double dq[3];
     grid_spacing(g, dq);
     const TableBytes tb = table_bytes(c, g, sh);
-    return hip_check(launch_grid_tables((const VRowDev*)c->prep.rows.p, c->pres.n_x + 1, c->pres.n_y + 1,
-                                        (const int2*)c->prep.zslots.p, c->pres.n_ksteps * kZStep, sh, g->n, g->qmin, dq,
+    return hip_check(launch_grid_tables(c->pres, (const VRowDev*)c->prep.rows.p, (const int2*)c->prep.zslots.p, sh, g->n, g->qmin, dq,
                                         (float2*)tab, (float2*)((char*)tab + tb.y), (uint4*)((char*)tab + tb.z), st),
                      "table kernel launch");
 }
@@ -420,9 +437,9 @@ bool grid_symmetric(const scff_grid* g) {
     return true;
 }
 
-// The z axis holds -q with q: only its upper half is computed (V(-q) = V(q)*
-// for every 1D row).
-bool z_reflects(const scff_grid* g) { return g->n[2] > 1 && g->qmin[2] == -g->qmax[2]; }
+// An axis holds -q with q: contracted, only its upper half is computed (V(-q) =
+// V(q)* for every 1D row).
+bool axis_reflects(const scff_grid* g, int a) { return g->n[a] > 1 && g->qmin[a] == -g->qmax[a]; }
 
 // Arithmetic of the products.  f16 halves end at 2^-24 of what they are scaled
 // to: per product about 2^-39 of the largest z row's bound, sqrt(n) of that over n
@@ -470,10 +487,35 @@ struct EvalPlan {
     ChunkSplit sp;
 };
 
+// Planes computed (the rest mirrored) where axis is contracted: contracted along
+// x, a symmetric grid's halves come with the columns.
+int planes_eval(const scff_ctx* c, const scff_grid* g, int axis) {
+    return c->symmetry && axis != 0 && grid_symmetric(g) ? (g->n[0] + 1) / 2 : g->n[0];
+}
+
+// The axis to contract: forming U costs the same for 1 and for 48 columns, so a
+// grid that is short along z, or symmetric along another axis only, is cheaper
+// along that one.  z, whose stores are contiguous and whose layout a query or a
+// point evaluation leaves, unless another saves a tenth (30 heavy atoms, 24 states:
+// 96x96x16 26.9 -> 10.4 ms in FP32 precision and 20.3 -> 5.3 ms in split precision,
+// the kernel by pairs before 17.4 and 8.6; 96^3 symmetric along x and y only 110
+// -> 58 and 61 -> 31 ms, before 100 and 50).
+int choose_axis(const scff_ctx* c, const scff_grid* g, int precision) {
+    const GridKind kind = precision == SCFF_FP32 ? kGridFp32 : kGridSplitF16;
+    int best = 2;
+    long long cost[3];
+    for (int a = 2; a >= 0; --a) {
+        cost[a] = grid_shape(g->n, a, planes_eval(c, g, a), c->n_states, axis_reflects(g, a), kind).cost;
+        if (cost[a] < (best == 2 ? cost[2] / 10 * 9 : cost[best])) best = a;
+    }
+    return best;
+}
+
 EvalPlan plan_eval(const scff_ctx* c, const scff_grid* g, int precision, bool allow_split = true) {
     EvalPlan e{};
-    e.nx_eval = (c->symmetry && grid_symmetric(g)) ? (g->n[0] + 1) / 2 : g->n[0];
-    e.shape = grid_shape(g->n, e.nx_eval, c->n_states, z_reflects(g), grid_kind(c, g, precision));
+    const int axis = c->pres.axis;
+    e.nx_eval = planes_eval(c, g, axis);
+    e.shape = grid_shape(g->n, axis, e.nx_eval, c->n_states, axis_reflects(g, axis), grid_kind(c, g, precision));
     const int nst = c->pres.n_ksteps;
     const long long tiles = (long long)e.shape.ntl * e.shape.ntc, 
                     slots = (long long)grid_wgs_per_cu(grid_class(e.shape), e.shape.lds) * c->n_cu;
@@ -515,10 +557,9 @@ int make_desc(scff_ctx* c, const scff_grid* g, const EvalPlan& pl, const void* t
               GridDesc* d, long long* blocks) {
     const PrepWork& w = c->prep;
     const TableBytes tb = table_bytes(c, g, pl.shape);
-    return hip_check(grid_desc(pl.shape, (const float2*)tab, c->pres.n_x + 1, c->pres.n_y + 1, (uint32_t)tb.y,
-                               (const uint4*)((const char*)tab + tb.z),
-                               c->pres.ksteps, (const int2*)w.zterms.p, (const float*)w.zw.p,
-                               (const double*)((const char*)w.small.p + kSmallSinv), pl.sp, g->n, pl.nx_eval, c->n_states,
+    return hip_check(grid_desc(pl.shape, c->pres, (const float2*)tab, (uint32_t)tb.y,
+                               (const uint4*)((const char*)tab + tb.z), (const int2*)w.zterms.p, (const float*)w.zw.p,
+                               (const double*)((const char*)w.small.p + kSmallSinv), pl.sp, g->n, c->n_states,
                                df, df2, part, d, blocks),
                      "grid descriptor");
 }
@@ -584,7 +625,7 @@ int scff::ctx_prepare(scff_ctx* c, const scff_grid* g, int precision, hipStream_
     if (rc) return rc;
     if ((rc = set_device(c))) return rc;
     if ((rc = order_after(c, st))) return rc;
-    if ((rc = ensure_prepared(c, st))) return rc;
+    if ((rc = ensure_prepared(c, st, choose_axis(c, g, precision)))) return rc;
     // the last precompute kernels (row compaction, slot remap) are still in
     // flight on st: the caller evaluates on another stream, which is not
     // ordered after this one
@@ -861,7 +902,7 @@ int scff_eval_grid(scff_ctx* c, const scff_grid* g, int precision, float* f, flo
     hipStream_t st = (hipStream_t)hip_stream;
     c->ev_prep = false;
     if ((rc = order_after(c, st))) return rc;
-    if ((rc = ensure_prepared(c, st))) return rc;
+    if ((rc = ensure_prepared(c, st, choose_axis(c, g, precision)))) return rc;
     const size_t npts = (size_t)g->n[0] * g->n[1] * g->n[2];
     const size_t nout = npts * (size_t)c->n_states;
     float2* df = (float2*)f;
@@ -875,9 +916,12 @@ int scff_eval_grid(scff_ctx* c, const scff_grid* g, int precision, float* f, flo
     if ((rc = record(c, EV_VT0, st))) return rc;
     if ((rc = check_tables(c, g))) return rc;
     EvalPlan pl = plan_eval(c, g, precision);
-    if ((rc = dev_reserve(c, c->d_vtab, table_bytes(c, g, pl.shape).total)) ||
-        (rc = launch_tables(c, g, pl.shape, c->d_vtab.p, st)))
-        return rc;
+    rc = dev_reserve(c, c->d_vtab, table_bytes(c, g, pl.shape).total);
+    if (rc == SCFF_ENOMEM && c->pres.axis != 2 && (rc = ensure_prepared(c, st, 2)) == SCFF_OK) {   // z may need less
+        pl = plan_eval(c, g, precision);
+        rc = dev_reserve(c, c->d_vtab, table_bytes(c, g, pl.shape).total);
+    }
+    if (rc || (rc = launch_tables(c, g, pl.shape, c->d_vtab.p, st))) return rc;
     // the partial buffer is the last reservation: a split that the context's
     // HBM budget cannot hold falls back to the unsplit evaluation (the same
     // values up to the order of the FP64 sums)
