@@ -39,7 +39,7 @@ constexpr int kWLine = 84;        // floats of W per line: 4 groups of 8 z rows,
 // Arithmetic of the grid kernel's products: FP32 precision; split precision on
 // f16 halves, or on BF16 parts where the values fall out of the halves' range.
 enum GridKind { kGridFp32, kGridSplitF16, kGridSplitBf16 };
-constexpr int kGridClasses = 12;   // kernel variants: column groups per tile x kind
+constexpr int kGridClasses = 30;   // kernel variants: kind, mirror values or not, column groups per tile
 // Bins of the s-s terms by binary exponent of p (PrepResult::tail): the first
 // holds p < 2^(kTailMin + 1)
 constexpr int kTailBins = 32, kTailMin = -12;
@@ -100,7 +100,7 @@ struct GridDesc {
     long long npts;           // grid points
     KSteps steps;
     int n1, n_states;         // values of line axis 0 computed
-    int ntl, ntc, ncg, ncol, iz0, reflect, nyp, tcm, np;
+    int ntl, ntc, ncg, ncol, iz0, nyp, tcm, np;
     float2* f;                // outputs (NULL to skip), or
     float* f2;
     double2* partial;         // FP64 partial sums of a split (NULL: unsplit)

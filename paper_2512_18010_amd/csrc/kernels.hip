@@ -158,7 +158,11 @@ __global__ __launch_bounds__(256) void tables_kernel(const VRowDev* __restrict__
 //   P = Ur Vr, Q = Ui Vi, R = Ur Vi, S = Ui Vr
 // give f = (P - Q) + i (R + S).  V(-q) = V(q)* for every 1D row, so on an axis
 // with qmin_z = -qmax_z the columns are the upper half of the axis only and
-// the mirror value is (P + Q) + i (S - R): the same products serve both.
+// the mirror value is (P + Q) + i (S - R): the same products serve both.  On other
+// axes P - Q and R + S are the sums (half the registers per column, so that a tile
+// may be twice as wide and U is formed once for up to 96 columns): 30 heavy atoms,
+// 24 states, 96^3 off centre on every axis 110 -> 88 ms in FP32 precision, 62 -> 46
+// in split precision, where the kernel by pairs took 100 and 50.
 //
 // FOLD (FP32 precision): U and V as three BF16 parts each, which hold FP32's 24
 // bits over FP32's whole exponent range, and the six products above 2^-24 of the
@@ -187,20 +191,29 @@ __global__ __launch_bounds__(256) void tables_kernel(const VRowDev* __restrict__
 //
 // Why: the kernel before formed G = sum_t Vx Vy Vz per (pair, q) on the VALU (4
 // FMAs per term and q) and contracted with FP32 matrix instructions; here the
-// VALU's part does not depend on the number of columns.  A version whose waves
-// formed W each for itself was bound by its gathers (64 cache lines per
-// instruction): 46.8 ms on a 30-heavy-atom molecule with 24 states on 96^3, FP32;
-// sharing W: 40.2 ms; the kernel before: 96.8 ms (split-BF16 48.9 -> 31.6 ms; 10
-// heavy atoms, 12 states, 64^3: 3.56 -> 1.67 ms).  What bounds it now: instruction issue
-// of two waves per SIMD (48 CG registers of accumulators and FP64 totals; three
-// waves without the totals) - about 190 VALU and 36 matrix instructions per wave
-// and k-step at CG = 3, matrix cores busy 29 %, a third of the cycles in waits.
-// Folding every four k-steps instead of two is 5 % faster but raises the error
-// (1.2 -> 1.4e-7, above the kernel before), three waves per SIMD at CG = 2 with totals
-// spill (2.05 -> 2.47 ms); neither is done.
+// VALU's part does not depend on the number of columns.  It pays where there are
+// more columns than about two thirds of the states: with 24 states and 48 columns
+// off centre it is 0.8 to 0.9 of the kernel before, the worst case.  A version whose
+// waves formed W each for itself was bound by its gathers (64 cache lines per
+// instruction): 46.8 ms on a 30-heavy-atom molecule with 24 states on 96^3; sharing
+// W: 40.2 ms (both with f16 halves).  What bounds it now: the LDS reads of U's
+// operands (six of 16 bytes per lane for 16 FMAs), about 20 of 30 ms of a split
+// precision call on that grid, and in FP32 precision the matrix cores (72
+// instructions per wave and k-step at CG = 3) and the FP64 totals, which two waves
+// per SIMD overlap little.  Three waves per SIMD at CG = 2 with totals and mirror
+// values spill (2.05 -> 2.47 ms).
 
 constexpr int kGridWaves = 4;
-constexpr int kFoldSteps = 2;   // k-steps per FP64 fold
+// Waves per SIMD, by the registers of the sums: 48 per column group with FP64 totals
+// (four sums), 24 without the mirror values (two sums), a third of both without totals.
+constexpr int grid_waves(int cg, bool fold, bool refl) { return fold && cg * (refl ? 2 : 1) > 2 ? 2 : 3; }
+// Buffers of V blocks: tiles of four groups and more have one, so that two or three
+// workgroups fit a CU's LDS (96 columns off centre, 24 states: the other workgroups
+// cover the wait).
+constexpr int grid_vbufs(int cg, bool refl) { return refl || cg < 4 ? 2 : 1; }
+// k-steps per FP64 fold.  Two sums take twice the products each, so they are folded
+// twice as often (at the same cost per product).
+constexpr int fold_steps(bool refl) { return refl ? 2 : 1; }
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 
@@ -295,9 +308,9 @@ __device__ __forceinline__ floatx4 mma(halfx8 a, halfx8 b, floatx4 c) {
 // from a queue), so a tile's values do not depend on which of the two computed
 // it; nor do they depend on the tile a row falls into.
 //
-// LDS (floats): V blocks [2][CG planes 256], weights [2][tcm 48 ns],
+// LDS (floats): V blocks [1 or 2][CG planes 256], weights [2][tcm 48 ns],
 // W [2][tcm][2 np lines][kWLine].
-template <int CG, bool FOLD, bool BF>
+template <int CG, bool FOLD, bool BF, bool REFL>
 __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -308,7 +321,8 @@ __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds
     constexpr int PL = Op::planes, BW = CG * PL * 256;   // floats of a V block
     const int TW = tcm * 48 * ns;                     // floats of a weight buffer
     const int WT = 2 * d.np * kWLine;                 // floats of W, one term
-    float* const Tl = lds + 2 * BW;
+    constexpr int VB = grid_vbufs(CG, REFL);
+    float* const Tl = lds + VB * BW;
     float* const Wl = Tl + 2 * TW;
 
     const int ct = blk % d.ntc;
@@ -369,7 +383,7 @@ __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds
     };
     auto dma_v = [&](int k) {
         const uint4* src = d.Bt + ((size_t)k * d.ncg + ct * CG) * (64 * PL);
-        const uint32_t dst = lds_addr(lds + (k & 1) * BW);
+        const uint32_t dst = lds_addr(lds + (k & (VB - 1)) * BW);
 #pragma unroll
         for (int i = 0; i < CG * PL; i += kGridWaves)   // a wave copies a plane of 1 KB at a time
             if (CG * PL % kGridWaves == 0 || i + wave < CG * PL)
@@ -409,25 +423,26 @@ __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds
         }
     };
 
-    floatx4 acc[CG][2][2];
-    double tot[FOLD ? CG : 1][2][2][4];
+    // sums of a column group: [2 a + b] of part a of U (re, im) and b of V, or
+    // (where no mirror value is wanted) the real and the imaginary part of f
+    constexpr int NS = REFL ? 4 : 2;
+    floatx4 acc[CG][NS];
+    double tot[FOLD ? CG : 1][NS][4];
 #pragma unroll
     for (int q = 0; q < CG; ++q)
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
+        for (int a = 0; a < NS; ++a) {
+            acc[q][a] = floatx4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (FOLD)
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                acc[q][a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-                if constexpr (FOLD)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) tot[q][a][b][i] = 0.0;
-            }
+                for (int i = 0; i < 4; ++i) tot[q][a][i] = 0.0;
+        }
     float ur[8], ui[8];
 
     if (k_hi > k_lo) {
         const int n0 = ksteps_terms(d.steps, k_lo);
         Pos p0{k_lo, 0, n0, ksteps_first(d.steps, k_lo), d.steps.kend[n0]}, p1 = next(p0);
-        dma_v(k_lo);
+        if constexpr (VB == 2) dma_v(k_lo);
         dma_w(p0, 0);
         int2 rec = load_rec(p0);
         gather(terms_of(p0), rec);
@@ -440,11 +455,13 @@ __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds
             const Pos p2 = next(p1);
             int2 rec2 = rec;
             // the next step's loads and copies go out first
+            if constexpr (VB == 1)
+                if (p0.t0 == 0) dma_v(p0.k);
             if (!last) {
                 gather(tc1, rec);
                 rec2 = load_rec(p2);
                 dma_w(p1, i ^ 1);
-                if (last_term) dma_v(p1.k);
+                if (VB == 2 && last_term) dma_v(p1.k);
             }
             // U of the lane's row: eight z rows
             auto add = [&](int t, bool first) {
@@ -488,8 +505,16 @@ __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds
 #pragma unroll
                     for (int p = 0; p < Op::parts; ++p) A[a][p] = __builtin_bit_cast(frag, w[p]);
                 }
-                const uint4* B = reinterpret_cast<const uint4*>(lds + (p0.k & 1) * BW) + lane;
+                frag M[Op::parts];   // -im
+                if constexpr (!REFL)
+#pragma unroll
+                    for (int p = 0; p < Op::parts; ++p)
+                        M[p] = __builtin_bit_cast(frag, __builtin_bit_cast(uintx4, A[1][p]) ^ 0x80008000u);
+                const uint4* B = reinterpret_cast<const uint4*>(lds + (p0.k & (VB - 1)) * BW) + lane;
                 __builtin_amdgcn_s_setprio(0);
+                // one V block: it was asked for in this step where the k-step has no other
+                if constexpr (VB == 1)
+                    if (p0.t0 == 0) barrier_dma();
 #pragma unroll
                 for (int q = 0; q < CG; ++q) {
                     frag V[2][Op::parts];
@@ -497,24 +522,30 @@ __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds
                     for (int b = 0; b < PL; ++b)
                         V[b / Op::parts][b % Op::parts] = __builtin_bit_cast(frag, B[(q * PL + b) * 64]);
 #pragma unroll
-                    for (int pr = 0; pr < Op::products; ++pr)
+                    for (int pr = 0; pr < Op::products; ++pr) {
+                        const int u = Op::u[pr], v = Op::v[pr];
+                        if constexpr (REFL) {
 #pragma unroll
-                        for (int a = 0; a < 2; ++a)
+                            for (int a = 0; a < 2; ++a)
 #pragma unroll
-                            for (int b = 0; b < 2; ++b)
-                                acc[q][a][b] = mma(A[a][Op::u[pr]], V[b][Op::v[pr]], acc[q][a][b]);
+                                for (int b = 0; b < 2; ++b) acc[q][2 * a + b] = mma(A[a][u], V[b][v], acc[q][2 * a + b]);
+                        } else {
+                            acc[q][0] = mma(A[0][u], V[0][v], acc[q][0]);
+                            acc[q][1] = mma(A[0][u], V[1][v], acc[q][1]);
+                            acc[q][0] = mma(M[u], V[1][v], acc[q][0]);
+                            acc[q][1] = mma(A[1][u], V[0][v], acc[q][1]);
+                        }
+                    }
                 }
-                if (FOLD && ((p0.k - k_lo) % kFoldSteps == kFoldSteps - 1 || last)) {
+                if (FOLD && ((p0.k - k_lo) % fold_steps(REFL) == fold_steps(REFL) - 1 || last)) {
 #pragma unroll
                     for (int q = 0; q < (FOLD ? CG : 0); ++q)
 #pragma unroll
-                        for (int a = 0; a < 2; ++a)
+                        for (int a = 0; a < NS; ++a) {
 #pragma unroll
-                            for (int b = 0; b < 2; ++b) {
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) tot[q][a][b][e] += (double)acc[q][a][b][e];
-                                acc[q][a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-                            }
+                            for (int e = 0; e < 4; ++e) tot[q][a][e] += (double)acc[q][a][e];
+                            acc[q][a] = floatx4{0.f, 0.f, 0.f, 0.f};
+                        }
                 }
             }
             if (last) break;
@@ -539,11 +570,9 @@ __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds
         for (int q = 0; q < CG; ++q) {
             const int col = (ct * CG + q) * 16 + m;
             if (col >= d.ncol) continue;
-            double v[2][2];
+            double v[NS];
 #pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b) v[a][b] = sc * (FOLD ? tot[FOLD ? q : 0][a][b][i] : (double)acc[q][a][b][i]);
+            for (int a = 0; a < NS; ++a) v[a] = sc * (FOLD ? tot[FOLD ? q : 0][a][i] : (double)acc[q][a][i]);
             auto put = [&](int iz, double re, double im) {
                 const size_t o = base + (size_t)iz * d.sz;
                 if (d.partial) {   // split pair sum: FP64 partial, summed by reduce_kernel
@@ -553,19 +582,24 @@ __device__ __forceinline__ void grid_tile(const GridDesc& d, int blk, float* lds
                     if (d.f2) d.f2[o] = (float)(re * re + im * im);
                 }
             };
-            const int iz = d.iz0 + col, im = d.nc - 1 - iz;
-            put(iz, v[0][0] - v[1][1], v[0][1] + v[1][0]);
-            if (d.reflect && im != iz) put(im, v[0][0] + v[1][1], v[1][0] - v[0][1]);
+            if constexpr (REFL) {
+                const int iz = d.iz0 + col, im = d.nc - 1 - iz;
+                put(iz, v[0] - v[3], v[1] + v[2]);
+                if (im != iz) put(im, v[0] + v[3], v[2] - v[1]);
+            } else {
+                put(col, v[0], v[1]);
+            }
         }
     }
 }
 
-constexpr int grid_waves(int cg, bool fold) { return fold && cg > 1 ? 2 : 3; }   // per SIMD
-template <int CG, bool FOLD, bool BF>
-__global__ __launch_bounds__(kGridWaves * 64) __attribute__((amdgpu_waves_per_eu(grid_waves(CG, FOLD), grid_waves(CG, FOLD)))) void grid_kernel(
-    GridDesc d) {
+#define SCFF_GRID_BOUNDS                    \
+    __launch_bounds__(kGridWaves * 64)      \
+        __attribute__((amdgpu_waves_per_eu(grid_waves(CG, FOLD, REFL), grid_waves(CG, FOLD, REFL))))
+template <int CG, bool FOLD, bool BF, bool REFL>
+__global__ SCFF_GRID_BOUNDS void grid_kernel(GridDesc d) {
     extern __shared__ __align__(16) float grid_lds[];
-    grid_tile<CG, FOLD, BF>(d, blockIdx.x, grid_lds);
+    grid_tile<CG, FOLD, BF, REFL>(d, blockIdx.x, grid_lds);
 }
 
 // Persistent batch kernel: every workgroup pops (request, tile) items from a
@@ -574,8 +608,8 @@ __global__ __launch_bounds__(kGridWaves * 64) __attribute__((amdgpu_waves_per_eu
 // several requests share one launch.  Every workgroup leaves the loop once
 // the counter passes n_items; the counter must be 0 at launch.  The launch's
 // LDS holds the largest of its requests' needs after the 16 bytes of the queue.
-template <int CG, bool FOLD, bool BF>
-__global__ __launch_bounds__(kGridWaves * 64) __attribute__((amdgpu_waves_per_eu(grid_waves(CG, FOLD), grid_waves(CG, FOLD)))) void grid_batch_kernel(
+template <int CG, bool FOLD, bool BF, bool REFL>
+__global__ SCFF_GRID_BOUNDS void grid_batch_kernel(
     const GridDesc* __restrict__ descs, const int2* __restrict__ items, int n_items, int* __restrict__ counter) {
     extern __shared__ __align__(16) float grid_lds[];
     int* s_item = reinterpret_cast<int*>(grid_lds);
@@ -586,7 +620,7 @@ __global__ __launch_bounds__(kGridWaves * 64) __attribute__((amdgpu_waves_per_eu
         const int it = __builtin_amdgcn_readfirstlane(s_item[0]);
         if (it >= n_items) break;
         const int2 w = items[it];
-        grid_tile<CG, FOLD, BF>(descs[w.x], w.y, grid_lds + 4);
+        grid_tile<CG, FOLD, BF, REFL>(descs[w.x], w.y, grid_lds + 4);
     }
 }
 
@@ -705,12 +739,12 @@ hipError_t launch_grid_tables(const PrepResult& p, const VRowDev* rows, const in
 // parts (30 heavy atoms, 24 states, 96x96 lines, one and three column groups: 26.9
 // and 54.3, 20.3 and 30.2, 26.1 and 48.2 ms).  Two terms per step where
 // the LDS allows (one barrier for both), else one (one or two states: W has up to
-// 64 lines).  FP32 precision stops at three column groups: the totals of a fourth
+// 64 lines).  With mirror values FP32 precision stops at three column groups: the totals of a fourth
 // spill 34 registers of 256 (10 heavy atoms, 12 states, 128^3, whose 64 columns are
 // then two tiles of two: 27.4 -> 21.6 ms; 48x48x256, 128 columns, three tiles of three:
 // 8.9 -> 6.2 ms).  At most one group of padding: the z blocks then stay within
 // rows x vtable_stride, by which a grid is accepted.
-int max_cg(GridKind kind) { return kind == kGridFp32 ? 3 : 4; }
+int max_cg(GridKind kind, bool refl) { return refl ? (kind == kGridFp32 ? 3 : 4) : 6; }
 
 GridShape grid_shape(const int n[3], int axis, int nx_eval, int n_states, bool reflect, GridKind kind) {
     GridShape g{};
@@ -735,9 +769,9 @@ GridShape grid_shape(const int n[3], int axis, int nx_eval, int n_states, bool r
         g.np = std::max(g.np, p);
     }
     long long best = 0;
-    for (int cg = 1; cg <= max_cg(kind); ++cg) {
+    for (int cg = 1; cg <= max_cg(kind, reflect); ++cg) {
         int tcm = 2;
-        auto bytes = [&] { return 4 * (2 * cg * g.planes * 256 + 2 * tcm * (48 * n_states + 2 * g.np * kWLine)); };
+        auto bytes = [&] { return 4 * (grid_vbufs(cg, reflect) * cg * g.planes * 256 + 2 * tcm * (48 * n_states + 2 * g.np * kWLine)); };
         if (bytes() > kGridLds) tcm = 1;
         if (bytes() > kGridLds) break;
         const int nt = (ng + cg - 1) / cg;
@@ -756,15 +790,16 @@ GridShape grid_shape(const int n[3], int axis, int nx_eval, int n_states, bool r
     return g;
 }
 
-// Workgroups resident per CU: what the registers allow (FP64 totals of two and
-// three column groups: two waves per SIMD, else three), and the 160 KB of LDS.
-int grid_wgs_per_cu(int cls, int lds) {
-    const int by_regs = cls == 1 || cls == 2 ? 2 : 3;
-    return std::min(by_regs, 160 * 1024 / ((lds + 16 + kLdsGranule - 1) / kLdsGranule * kLdsGranule));
-}
+// The kernel's variant: kind, with or without mirror values, column groups; some
+// numbers have no kernel (FP32 precision with four groups and mirror values).
+int grid_class(const GridShape& g) { return 10 * g.kind + (g.reflect ? g.cg - 1 : 3 + g.cg); }
 
-// The kernel's variant; class 3 (four column groups with totals) does not exist.
-int grid_class(const GridShape& g) { return (g.cg - 1) + 4 * g.kind; }
+// Workgroups resident per CU: what the registers allow, and the 160 KB of LDS.
+int grid_wgs_per_cu(int cls, int lds) {
+    const bool fold = cls / 10 == kGridFp32, refl = cls % 10 < 4;
+    return std::min(grid_waves(refl ? cls % 10 + 1 : cls % 10 - 3, fold, refl),
+                    160 * 1024 / ((lds + 16 + kLdsGranule - 1) / kLdsGranule * kLdsGranule));
+}
 
 hipError_t grid_desc(const GridShape& g, const PrepResult& p, const float2* V, uint32_t ybase, const uint4* Bt,
                      const int2* terms, const float* Tw, const double* sinv, const ChunkSplit& sp, const int n[3],
@@ -772,7 +807,7 @@ hipError_t grid_desc(const GridShape& g, const PrepResult& p, const float2* V, u
     const int nxr = p.n_axis[g.l[0]] + 1, nyr = p.n_axis[g.l[1]] + 1;
     if (p.axis != g.axis || (size_t)ybase < (size_t)n[g.l[0]] * nxr * sizeof(float2)) return hipErrorInvalidValue;
     if (g.n1 < 1 || g.n1 > n[g.l[0]] || n_states < 1 || n_states > kMaxStates) return hipErrorInvalidValue;
-    if (g.cg < 1 || g.cg > 4 || g.ncg != g.cg * g.ntc || g.ncg * 16 < g.ncol || g.tcm < 1 || g.tcm > 2)
+    if (g.cg < 1 || g.cg > 6 || g.ncg != g.cg * g.ntc || g.ncg * 16 < g.ncol || g.tcm < 1 || g.tcm > 2)
         return hipErrorInvalidValue;
     if ((long long)g.n1 * g.nyp * n_states > 0x7fffffff - 64) return hipErrorInvalidValue;   // at most 4096 4096 32
     if (sp.n < 1 || sp.n > kMaxSplit || sp.lo[0] != 0) return hipErrorInvalidValue;
@@ -806,7 +841,6 @@ hipError_t grid_desc(const GridShape& g, const PrepResult& p, const float2* V, u
     d->ncg = g.ncg;
     d->ncol = g.ncol;
     d->iz0 = g.iz0;
-    d->reflect = g.reflect;
     d->f = f;
     d->f2 = f2;
     d->partial = sp.n > 1 ? part : nullptr;
@@ -815,20 +849,38 @@ hipError_t grid_desc(const GridShape& g, const PrepResult& p, const float2* V, u
     return hipSuccess;
 }
 
-#define SCFF_GRID_CASES(KERNEL, ...)                                              \
-    switch (cls) {                                                                \
-        case 0: SCFF_GRID_VARIANT((KERNEL<1, true, true>), __VA_ARGS__); break;   \
-        case 1: SCFF_GRID_VARIANT((KERNEL<2, true, true>), __VA_ARGS__); break;   \
-        case 2: SCFF_GRID_VARIANT((KERNEL<3, true, true>), __VA_ARGS__); break;   \
-        case 4: SCFF_GRID_VARIANT((KERNEL<1, false, false>), __VA_ARGS__); break; \
-        case 5: SCFF_GRID_VARIANT((KERNEL<2, false, false>), __VA_ARGS__); break; \
-        case 6: SCFF_GRID_VARIANT((KERNEL<3, false, false>), __VA_ARGS__); break; \
-        case 7: SCFF_GRID_VARIANT((KERNEL<4, false, false>), __VA_ARGS__); break; \
-        case 8: SCFF_GRID_VARIANT((KERNEL<1, false, true>), __VA_ARGS__); break;  \
-        case 9: SCFF_GRID_VARIANT((KERNEL<2, false, true>), __VA_ARGS__); break;  \
-        case 10: SCFF_GRID_VARIANT((KERNEL<3, false, true>), __VA_ARGS__); break; \
-        case 11: SCFF_GRID_VARIANT((KERNEL<4, false, true>), __VA_ARGS__); break; \
-        default: return hipErrorInvalidValue;                                     \
+#define SCFF_GRID_CASES(KERNEL, ...)                                                      \
+    switch (cls) {                                                                        \
+        case 0: SCFF_GRID_VARIANT((KERNEL<1, true, true, true>), __VA_ARGS__); break;     \
+        case 1: SCFF_GRID_VARIANT((KERNEL<2, true, true, true>), __VA_ARGS__); break;     \
+        case 2: SCFF_GRID_VARIANT((KERNEL<3, true, true, true>), __VA_ARGS__); break;     \
+        case 4: SCFF_GRID_VARIANT((KERNEL<1, true, true, false>), __VA_ARGS__); break;    \
+        case 5: SCFF_GRID_VARIANT((KERNEL<2, true, true, false>), __VA_ARGS__); break;    \
+        case 6: SCFF_GRID_VARIANT((KERNEL<3, true, true, false>), __VA_ARGS__); break;    \
+        case 7: SCFF_GRID_VARIANT((KERNEL<4, true, true, false>), __VA_ARGS__); break;    \
+        case 8: SCFF_GRID_VARIANT((KERNEL<5, true, true, false>), __VA_ARGS__); break;    \
+        case 9: SCFF_GRID_VARIANT((KERNEL<6, true, true, false>), __VA_ARGS__); break;    \
+        case 10: SCFF_GRID_VARIANT((KERNEL<1, false, false, true>), __VA_ARGS__); break;  \
+        case 11: SCFF_GRID_VARIANT((KERNEL<2, false, false, true>), __VA_ARGS__); break;  \
+        case 12: SCFF_GRID_VARIANT((KERNEL<3, false, false, true>), __VA_ARGS__); break;  \
+        case 13: SCFF_GRID_VARIANT((KERNEL<4, false, false, true>), __VA_ARGS__); break;  \
+        case 14: SCFF_GRID_VARIANT((KERNEL<1, false, false, false>), __VA_ARGS__); break; \
+        case 15: SCFF_GRID_VARIANT((KERNEL<2, false, false, false>), __VA_ARGS__); break; \
+        case 16: SCFF_GRID_VARIANT((KERNEL<3, false, false, false>), __VA_ARGS__); break; \
+        case 17: SCFF_GRID_VARIANT((KERNEL<4, false, false, false>), __VA_ARGS__); break; \
+        case 18: SCFF_GRID_VARIANT((KERNEL<5, false, false, false>), __VA_ARGS__); break; \
+        case 19: SCFF_GRID_VARIANT((KERNEL<6, false, false, false>), __VA_ARGS__); break; \
+        case 20: SCFF_GRID_VARIANT((KERNEL<1, false, true, true>), __VA_ARGS__); break;   \
+        case 21: SCFF_GRID_VARIANT((KERNEL<2, false, true, true>), __VA_ARGS__); break;   \
+        case 22: SCFF_GRID_VARIANT((KERNEL<3, false, true, true>), __VA_ARGS__); break;   \
+        case 23: SCFF_GRID_VARIANT((KERNEL<4, false, true, true>), __VA_ARGS__); break;   \
+        case 24: SCFF_GRID_VARIANT((KERNEL<1, false, true, false>), __VA_ARGS__); break;  \
+        case 25: SCFF_GRID_VARIANT((KERNEL<2, false, true, false>), __VA_ARGS__); break;  \
+        case 26: SCFF_GRID_VARIANT((KERNEL<3, false, true, false>), __VA_ARGS__); break;  \
+        case 27: SCFF_GRID_VARIANT((KERNEL<4, false, true, false>), __VA_ARGS__); break;  \
+        case 28: SCFF_GRID_VARIANT((KERNEL<5, false, true, false>), __VA_ARGS__); break;  \
+        case 29: SCFF_GRID_VARIANT((KERNEL<6, false, true, false>), __VA_ARGS__); break;  \
+        default: return hipErrorInvalidValue;                                             \
     }
 
 // Dynamic LDS beyond 64 KB must be allowed per kernel (on the current device).
