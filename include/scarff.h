@@ -292,10 +292,10 @@ int scff_export_vtensors(scff_ctx* ctx, const scff_grid* grid, long long* n_term
  * they are written) or device buffers (out_on_device = 1, asynchronous on
  * hip_stream unless parseval is requested, which waits for the stream).
  * The density is FP32 (AO values built in FP64 and rounded once, weights
- * contracted on the matrix cores with FP64 sums over each 16 functions;
- * SCFF_BF16X3 splits weights and AO values into BF16 hi + lo halves and
- * keeps hi*hi + hi*lo + lo*hi, about 2^-16 relative per product, in half
- * the matrix-core instructions),
+ * contracted on the matrix cores as BF16 triples, 24 bits, with FP64 sums over
+ * each 16 functions; SCFF_BF16X3 splits weights and AO values into BF16 hi +
+ * lo halves and keeps hi*hi + hi*lo + lo*hi, about 2^-16 relative per product,
+ * in two thirds of the matrix-core instructions),
  * the transform FP32 radix-2, the corner phase FP64.  The context's
  * screening threshold is not applied (primitives below the FP32 range are
  * skipped); the spin factor is.  Basis size: up to 1232 functions.

@@ -281,14 +281,15 @@ struct FftMol {
     const double* cnorm;
     int n_shells;
 };
-// LDS a density workgroup may hold (its AO block grows with the basis: up to
-// 1232 functions; 64-point tiles up to 240 functions, 32-point tiles up to 496).
-constexpr size_t kFftLdsBytes = (size_t)78 << 10;
+// LDS a density workgroup may hold: its AO block grows with the basis, up to
+// 1232 functions of 6 bytes a value in FP32 precision (4 in split-BF16).
+constexpr size_t kFftLdsBytes = (size_t)120 << 10;
+constexpr int kFftMaxPad = 1232;
 // Column blocks of 16 points per density workgroup for nbf_pad basis rows
 // (4, 2 or 1), 0 if the AO block does not fit lds_limit bytes of LDS.
-int fft_density_cb(int nbf_pad, size_t lds_limit);
-// precision: SCFF_FP32 (weights in three f16 parts) or SCFF_BF16X3 (split-BF16
-// weights), as operands of 16x16x32 products.
+int fft_density_cb(int precision, int nbf_pad, size_t lds_limit);
+// precision: SCFF_FP32 (weights in three BF16 parts) or SCFF_BF16X3 (in two), as
+// operands of 16x16x32 products.
 size_t fft_pack_bytes(int precision, int nbf_pad, int ns);   // of the array that launch_fft_pack fills
 hipError_t launch_fft_pack(int precision, const double* T, const double* cnorm, int nbf, int nbf_pad, int ns,
                            double spin, void* Ap, hipStream_t st);

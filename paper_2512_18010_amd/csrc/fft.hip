@@ -1,16 +1,15 @@
 // The FFT method (paper Sec. 3 and Sec. 5.2) on the device:
 //
-//   1. fft_rowmax_kernel,   transition weights as MFMA A operands:
-//      fft_pack_kernel      s_f c_mu c_nu (T_{mu nu} + T_{nu mu}) per unordered
+//   1. fft_pack_kernel      transition weights as MFMA A operands:
+//                           s_f c_mu c_nu (T_{mu nu} + T_{nu mu}) per unordered
 //                           component pair (T_{mu mu} on the diagonal), split
-//                           into f16 halves (FP32 precision, rows scaled by
-//                           powers of two) or BF16 halves;
+//                           into three BF16 parts (FP32 precision) or two;
 //   2. fft_density_kernel   the transition density (eq. PhiTDM, AO form)
 //                             Phi_s(r) = sum_mu phi_mu(r) sum_{nu >= mu} Tp_s(mu,nu) phi_nu(r)
 //                           on a tile of up to 64 real-space points: the AO
 //                           values of the tile are formed in LDS (FP64,
-//                           rounded once, scaled per point and split into f16
-//                           halves; or FP32 and split into BF16 halves), Y_s(mu, r) = sum_nu Tp_s(mu,nu) phi_nu(r)
+//                           rounded once and split into three BF16 parts; or FP32
+//                           and split into two), Y_s(mu, r) = sum_nu Tp_s(mu,nu) phi_nu(r)
 //                           runs on the matrix cores (rows mu of one state,
 //                           k = nu, columns = points), and sum_mu phi_mu Y_s(mu)
 //                           is folded per 16 rows.  Two states share one
@@ -36,8 +35,6 @@ namespace scff {
 typedef float fft_floatx4 __attribute__((ext_vector_type(4)));
 typedef float fft_floatx2 __attribute__((ext_vector_type(2)));
 typedef unsigned int fft_uintx4 __attribute__((ext_vector_type(4)));
-typedef _Float16 fft_halfx2 __attribute__((ext_vector_type(2)));
-typedef _Float16 fft_halfx8 __attribute__((ext_vector_type(8)));
 typedef __bf16 fft_bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 fft_bf16x8 __attribute__((ext_vector_type(8)));
 
@@ -52,30 +49,24 @@ __device__ inline void fft_split(float v, uint32_t& hi, uint32_t& lo) {
     hi = __builtin_bit_cast(uint32_t, h);
     lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(fft_floatx2{r, 0.f}, fft_bf16x2));
 }
-// Split-f16 of one value, |v| < 2^16: hi = RNE(v), lo = RNE(v - hi) in one
-// dword, hi in the low half; 22 significant bits and more down to 2^-25 absolute.
-__device__ inline uint32_t fft_split_f16(float v) {
-    const _Float16 h = (_Float16)v;
-    return __builtin_bit_cast(uint32_t, fft_halfx2{h, (_Float16)(v - (float)h)});
+// The three BF16 parts of two values (the second's in the high halves), each the
+// rest of the one before: FP32's 24 bits over its exponent range.
+__device__ inline void fft_split3(float v0, float v1, uint32_t (&part)[3]) {
+    const fft_bf16x2 first{(__bf16)-1.0f, (__bf16)-0.0f}, second{(__bf16)-0.0f, (__bf16)-1.0f};
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        const fft_bf16x2 h = __builtin_convertvector(fft_floatx2{v0, v1}, fft_bf16x2);
+        part[p] = __builtin_bit_cast(uint32_t, h);
+        if (p < 2) {
+            v0 = __builtin_amdgcn_fdot2_f32_bf16(h, first, v0, false);
+            v1 = __builtin_amdgcn_fdot2_f32_bf16(h, second, v1, false);
+        }
+    }
 }
-// (hi, lo) of four values as the words (hi_0 hi_1, hi_2 hi_3, lo_0 lo_1, lo_2 lo_3)
-__device__ inline uint4 fft_halves(const uint32_t (&w)[4]) {
-    return make_uint4((w[0] & 0xffffu) | (w[1] << 16), (w[2] & 0xffffu) | (w[3] << 16),
-                      (w[0] >> 16) | (w[1] & 0xffff0000u), (w[2] >> 16) | (w[3] & 0xffff0000u));
-}
-// The BF16 split in one dword: hi in the low half, lo in the high half.
-__device__ inline uint32_t fft_split(float v) {
-    uint32_t hi, lo;
-    fft_split(v, hi, lo);
-    return hi | (lo << 16);
-}
-
 // Primitives whose exponent argument alpha r^2 exceeds this are skipped (the
 // paper's thresholding of negligible primitives): e^{-103} is below the
 // smallest FP32 subnormal, so the rounded AO value is unchanged.
 constexpr double kExpCut = 103.0;
-
-// Grid points per density workgroup: one MFMA column block.
 
 namespace {
 
@@ -89,31 +80,13 @@ __device__ __forceinline__ double fft_weight(const double* Ts, const double* cno
 // rb .. RB - 1 of every row block).
 __device__ __forceinline__ int fft_group0(int rb, int RB) { return rb * RB - rb * (rb - 1) / 2; }
 
-// Powers of two of the split-f16 rows: a with max_nu |W(mu, nu)| 2^a < 2^15, so
-// that the halves keep their bits.  One wave per (state, row).
-__global__ __launch_bounds__(256) void fft_rowmax_kernel(const double* __restrict__ T, const double* __restrict__ cnorm,
-                                                         int nbf, int nbf_pad, int ns, double spin,
-                                                         signed char* __restrict__ ra) {
-    const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (i >= ns * nbf_pad) return;
-    const int s = i / nbf_pad, mu = i - s * nbf_pad;
-    double a = 0.0;
-    if (mu < nbf)
-        for (int nu = mu + lane; nu < nbf; nu += 64)
-            a = fmax(a, fabs(fft_weight(T + (size_t)s * nbf * nbf, cnorm, nbf, spin, mu, nu)));
-    for (int h = 32; h > 0; h >>= 1) a = fmax(a, __shfl_xor(a, h));
-    if (lane == 0) ra[i] = (signed char)(a > 0.0 && a < 1e300 ? max(-100, min(100, 14 - ilogb(a))) : 0);
-}
-
 // A operands.  Function group g holds nu = 16 g .. 16 g + 15; lane (row = lane %
-// 16, kk = lane / 16) carries nu_j = 16 g + 4 kk + j, j < 4, as fft_halves words
-// in Ap[((s groups + group0(rb) + g - rb) 64 + lane], g >= rb.  f16 halves: W is
-// the same at every point, so what the halves drop (up to 2^-23 W) would stay in
-// the transform; a third half per weight, two words per lane in Ar, takes it.
+// 16, kk = lane / 16) carries nu_j = 16 g + 4 kk + j, j < 4, as the words of the
+// first and of the second parts in Ap[((s groups + group0(rb) + g - rb) 64 + lane],
+// g >= rb, and (FP32 precision) of the third parts in Ar.
 template <bool BF>
 __global__ void fft_pack_kernel(const double* __restrict__ T, const double* __restrict__ cnorm, int nbf, int ns, int RB,
-                                double spin, const signed char* __restrict__ ra, uint4* __restrict__ Ap,
-                                uint2* __restrict__ Ar) {
+                                double spin, uint4* __restrict__ Ap, uint2* __restrict__ Ar) {
     const int per = RB * (RB + 1) / 2;
     const long long total = (long long)ns * per * 64;
     for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
@@ -126,22 +99,16 @@ __global__ void fft_pack_kernel(const double* __restrict__ T, const double* __re
         const int g = rb + k - fft_group0(rb, RB);
         const int mu = 16 * rb + (lane & 15);
         const double* Ts = T + (size_t)s * nbf * nbf;
-        uint32_t w[4], t[4];
+        float v[4];
         for (int j = 0; j < 4; ++j) {
             const int nu = 16 * g + 4 * (lane >> 4) + j;
-            double v = 0.0;
-            if (mu < nbf && nu < nbf && mu <= nu) v = fft_weight(Ts, cnorm, nbf, spin, mu, nu);
-            if (BF) {
-                w[j] = fft_split((float)v);
-            } else {
-                v = ldexp(v, ra[s * 16 * RB + mu]);
-                const _Float16 h = (_Float16)(float)v, l = (_Float16)(float)(v - (double)h);
-                w[j] = __builtin_bit_cast(uint32_t, fft_halfx2{h, l});
-                t[j] = __builtin_bit_cast(unsigned short, (_Float16)(float)(v - (double)h - (double)l));
-            }
+            v[j] = mu < nbf && nu < nbf && mu <= nu ? (float)fft_weight(Ts, cnorm, nbf, spin, mu, nu) : 0.f;
         }
-        Ap[i] = fft_halves(w);
-        if (!BF) Ar[i] = make_uint2(t[0] | (t[1] << 16), t[2] | (t[3] << 16));
+        uint32_t a[3], b[3];
+        fft_split3(v[0], v[1], a);
+        fft_split3(v[2], v[3], b);
+        Ap[i] = make_uint4(a[0], b[0], a[1], b[1]);
+        if (!BF) Ar[i] = make_uint2(a[2], b[2]);
     }
 }
 
@@ -214,70 +181,75 @@ __device__ __forceinline__ void shell_values(const FftMol& m, int sh, double x, 
     }
 }
 
-// LDS bytes of a density workgroup: the AO block of nbf_pad rows x 16 CB
-// points (4 bytes per value in either layout) and two buffers of 4 x 16 CB
+// LDS bytes of a density workgroup of nw waves: the AO block of nbf_pad rows x 16
+// CB points (two or three parts of 2 bytes per value) and two buffers of nw x 16 CB
 // FP64 partial densities.
-__host__ __device__ constexpr size_t fft_lds_bytes(int nbf_pad, int cb) {
-    return (size_t)cb * (64 * (size_t)nbf_pad + 1024);
+__host__ __device__ constexpr size_t fft_lds_bytes(bool bf, int nbf_pad, int cb, int nw) {
+    return (size_t)cb * ((bf ? 64 : 96) * (size_t)nbf_pad + 256 * nw);
 }
 
-// One workgroup (4 waves) per tile of NP = 16 CB consecutive grid points
+// One workgroup (NW waves) per tile of NP = 16 CB consecutive grid points
 // (flattened [ix][iy][iz], z fastest; column c = 16 cb + col of the tile).
 //
 // AO phase: a lane evaluates one shell at one point (64 / NP shells per wave
 // step; with NP = 64 every lane of a wave takes the same shell, so its data
-// are scalar loads).  The values end in LDS as split halves, the B operands of a
+// are scalar loads).  The values end in LDS as parts, the B operands of a
 // 16x16x32 matrix instruction: the uint4 entry ((g 4 + kk) CB + cb) 16 + col holds
-// rows r_j = 16 g + 4 kk + j (j < 4) of column c as (hi(r_0) | hi(r_1) << 16,
-// hi(r_2) | hi(r_3) << 16, lo(r_0) | lo(r_1) << 16, lo(r_2) | lo(r_3) << 16).  A lane
-// (kk, col) takes it as the 8 k-items of one instruction (no operand copies), and
-// the same entry holds the rows 16 rb + 4 kk + i that the lane folds after row
-// block rb.  BF: BF16 halves of the FP32 value, written at once.  FP32
-// precision: FP64 values rounded to FP32 into the entry's four words; then, with
-// every point's largest value known, f16 halves of value 2^e(point) with |value|
-// 2^e < 2^15, in place (far from the molecule all values are small: the scale
-// keeps their bits).
-// Products per function group and column block: instruction 1 with A = (W hi,
-// W hi) gives hi*hi + hi*lo over the items, instruction 2 with A = (W lo, W lo)
-// lo*hi + lo*lo (BF: (W lo, 0), lo*hi only); FP32 precision has a third with A =
-// (W's third half, 0).
+// the first and second BF16 parts of the rows r_j = 16 g + 4 kk + j (j < 4) of
+// column c, as (h(r_0) | h(r_1) << 16, h(r_2) | h(r_3) << 16, m(r_0) | m(r_1) << 16,
+// m(r_2) | m(r_3) << 16); FP32 precision: the uint2 entry of the same number behind
+// them the third parts.  A lane (kk, col) takes an entry as the 8 k-items of one
+// instruction (no operand copies), and the same entry holds the rows 16 rb + 4 kk +
+// i that the lane folds after row block rb.
+// Products per function group and column block: with W = (h, m, l) and phi = (h,
+// m, l) the instructions (W_h, W_h) (phi_h, phi_m), (W_m, W_m) (phi_h, phi_m) and (W_l,
+// W_h) (phi_h, phi_l): every product above 2^-24 of the whole.  BF (split-BF16): two
+// parts each, the first instruction and (W_m, 0) (phi_h, phi_m).
 //
 // FP32 precision used FP32 matrix instructions, 2.7x the cycles of the split
-// products: 8.75 ms for 190 functions, 12 states on 128^3 points, 74 % of it in the
-// matrix cores; 4.94 ms now, bound by the vector unit (AO values and fold, FP64) and
-// the matrix cores in equal parts, which overlap little at three waves per SIMD
-// (172 registers, two waves: 5.04 ms without the third instruction).
+// products: 8.9 ms a call for 190 functions, 12 states on 128^3 points, 74 % of it in
+// the matrix cores; 6.3 ms now, bound by the vector unit (AO values and fold, FP64)
+// and the matrix cores in equal parts, which overlap little at two waves per SIMD.
+// f16 halves of the AO values, scaled per point, take 4 bytes instead of 6 and let
+// three workgroups stay on a CU (4.75 ms), but a shell whose coefficients are given
+// small (the contracted norm is in the weights) then falls below a point's smallest
+// half: density error 1 for coefficients of 1e-12.  Error over 48 boxes of 80 to
+// 420 functions, rms against the peak: 0.64 to 1.05e-8, FP32 matrix instructions
+// 0.76 to 1.3e-8.
 //
 // Contraction: wave w takes row blocks rb of 16 functions in a snake order
-// (0 1 2 3 3 2 1 0 ...), which evens out the triangle's rows; per row block
+// (0 1 .. NW - 1 NW - 1 .. 1 0 ...), which evens out the triangle's rows; per row block
 // the k-steps from the diagonal block on, with the A operands of the next
 // k-steps loaded while the current ones run and each A operand used by CB
-// MFMAs.  The 16-row block is folded with its AO values, the four waves'
+// MFMAs.  The 16-row block is folded with its AO values, the waves'
 // partial densities of a group of states are summed through LDS and wave 0
 // writes the tile.
-template <bool BF, int CB>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void fft_density_kernel(FftMol m, const uint4* __restrict__ Av,
-                                                          const uint2* __restrict__ Ar, const signed char* __restrict__ ra, int nbf_pad, int ns, int RB,
+template <bool BF, int CB, int NW, int WPS>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPS))) void fft_density_kernel(FftMol m, const uint4* __restrict__ Av,
+                                                          const uint2* __restrict__ Ar, int nbf_pad, int ns, int RB,
                                                           int3 n, double3 x0, double3 h,
                                                           long long npts, float* __restrict__ Z,
                                                           float* __restrict__ phi_out, double* __restrict__ psum) {
     extern __shared__ __align__(16) float fft_lds[];
-    constexpr int NP = 16 * CB;
-    constexpr int NCH = CB == 1 ? 2 : CB;   // independent MFMA accumulator chains
+    constexpr int NP = 16 * CB, NT = 64 * NW;
+    // MFMA accumulator chains: per column block one, or (TWO; where the registers
+    // hold them) one of the first products and one of the small ones, so that these
+    // are not rounded to the whole sum each time
+    constexpr bool TWO = CB == 1 || (!BF && !(CB == 4 && WPS > 2));
+    constexpr int NCH = TWO ? 2 * CB : CB;
     const int tid = threadIdx.x, lane = tid & 63;
     // wave-uniform: the row-block loop and the A-operand addresses stay scalar
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const long long p0 = (long long)blockIdx.x * NP;
     uint32_t* pu = reinterpret_cast<uint32_t*>(fft_lds);
     unsigned short* ps16 = reinterpret_cast<unsigned short*>(fft_lds);
-    double* red = reinterpret_cast<double*>(fft_lds + (size_t)nbf_pad * NP);
+    constexpr int WV = BF ? 2 : 3;   // parts of a value
+    uint2* const p3 = reinterpret_cast<uint2*>(ps16 + (size_t)2 * nbf_pad * NP);   // third parts
+    double* red = reinterpret_cast<double*>(ps16 + (size_t)WV * nbf_pad * NP);
 
-    uint32_t* const cmax = reinterpret_cast<uint32_t*>(red);   // [NP], until the exponents are known
-    for (int i = tid; i < nbf_pad * NP; i += 256) pu[i] = 0u;
-    if (tid < NP) cmax[tid] = 0u;
+    for (int i = tid; i < nbf_pad * NP / 4; i += NT) reinterpret_cast<uint4*>(pu)[i] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
     {
-        float vmax = 0.f;   // of the lane's point
         constexpr int SPI = 64 / NP;   // shells per wave step
         const int p = lane % NP;
         const long long g = p0 + p;
@@ -288,69 +260,57 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
         const int col = p & 15, cb = p >> 4;
         auto put = [&](int r, auto v) {
             const int i = r & 3;
-            const int e0 = ((((r >> 4) * 4 + ((r >> 2) & 3)) * CB + cb) * 16 + col) * 4;   // dword of the entry
+            const int e0 = (((r >> 4) * 4 + ((r >> 2) & 3)) * CB + cb) * 16 + col;   // the entry
             if constexpr (BF) {
                 uint32_t hi, lo;
                 fft_split((float)v, hi, lo);
-                // the lo half is two dwords after the hi half
-                const int wd = e0 + (i >> 1);
-                ps16[2 * wd + (i & 1)] = (unsigned short)hi;
-                ps16[2 * wd + 4 + (i & 1)] = (unsigned short)lo;
+                ps16[8 * e0 + i] = (unsigned short)hi;
+                ps16[8 * e0 + 4 + i] = (unsigned short)lo;
             } else {
-                const float w = (float)v;
-                vmax = fmaxf(vmax, fabsf(w));
-                pu[e0 + i] = __float_as_uint(w);
+                pu[4 * e0 + i] = __float_as_uint((float)v);
             }
         };
-        for (int sh0 = wave * SPI; sh0 < m.n_shells; sh0 += 4 * SPI) {
+        for (int sh0 = wave * SPI; sh0 < m.n_shells; sh0 += NW * SPI) {
             const int sh = sh0 + lane / NP;
             if (sh < m.n_shells && g < npts) shell_values<std::conditional_t<BF, float, double>>(m, sh, x, y, z, put);
         }
-        if constexpr (!BF) atomicMax(&cmax[p], __float_as_uint(vmax));
     }
-    // exponent of column c: |phi| 2^e < 2^15 (values that overflow FP32 stay as they are)
-    auto col_exp = [&](int c) {
-        const int b = (int)(cmax[c] >> 23);
-        return b == 0 || b == 255 ? (b ? 0 : 120) : min(120, 14 + 127 - b);
-    };
-    int pe = 0;   // exponent of column `lane` (the store's)
-    if constexpr (!BF) {
+
+    if constexpr (!BF) {   // values to parts, in place (one LDS write a value before instead of three)
         __syncthreads();
-        if (lane < NP) pe = col_exp(lane);
-        for (int i = tid; i < nbf_pad * NP / 4; i += 256) {
-            const int e = col_exp((i / 16 % CB) * 16 + i % 16);
+        for (int i = tid; i < nbf_pad * NP / 4; i += NT) {
             uint4* const o = reinterpret_cast<uint4*>(pu) + i;
             const uint4 u = *o;
-            const uint32_t w[4] = {fft_split_f16(__builtin_ldexpf(__uint_as_float(u.x), e)),
-                                   fft_split_f16(__builtin_ldexpf(__uint_as_float(u.y), e)),
-                                   fft_split_f16(__builtin_ldexpf(__uint_as_float(u.z), e)),
-                                   fft_split_f16(__builtin_ldexpf(__uint_as_float(u.w), e))};
-            *o = fft_halves(w);
+            uint32_t a[3], b[3];
+            fft_split3(__uint_as_float(u.x), __uint_as_float(u.y), a);
+            fft_split3(__uint_as_float(u.z), __uint_as_float(u.w), b);
+            *o = make_uint4(a[0], b[0], a[1], b[1]);
+            p3[i] = make_uint2(a[2], b[2]);
         }
     }
 
     const int kk = lane >> 4, col = lane & 15;
     // the AO values of rows 16 rb + 4 kk + i (i < 4) at this lane's CB columns,
-    // v[i][cb]: hi + lo, summed in FP32 (exact for the f16 halves; for the BF16
-    // halves within 2^-24 of the split value, far below the split's own 2^-16)
+    // v[i][cb]: the parts, summed in FP32 (exact for three parts; for two within
+    // 2^-24 of the split value, far below the split's own 2^-16)
     using FV = std::conditional_t<BF, float, double>;
     auto phi_rows = [&](int rb, FV (&v)[4][CB]) {
 #pragma unroll
         for (int q = 0; q < CB; ++q) {
             const uint4 e = reinterpret_cast<const uint4*>(pu)[((rb * 4 + kk) * CB + q) * 16 + col];
-            if constexpr (BF) {
-                v[0][q] = __uint_as_float(e.x << 16) + __uint_as_float(e.z << 16);
-                v[1][q] = __uint_as_float(e.x & 0xffff0000u) + __uint_as_float(e.z & 0xffff0000u);
-                v[2][q] = __uint_as_float(e.y << 16) + __uint_as_float(e.w << 16);
-                v[3][q] = __uint_as_float(e.y & 0xffff0000u) + __uint_as_float(e.w & 0xffff0000u);
-            } else {
-                const fft_halfx2 h0 = __builtin_bit_cast(fft_halfx2, e.x), h1 = __builtin_bit_cast(fft_halfx2, e.y);
-                const fft_halfx2 l0 = __builtin_bit_cast(fft_halfx2, e.z), l1 = __builtin_bit_cast(fft_halfx2, e.w);
-                v[0][q] = (float)h0[0] + (float)l0[0];
-                v[1][q] = (float)h0[1] + (float)l0[1];
-                v[2][q] = (float)h1[0] + (float)l1[0];
-                v[3][q] = (float)h1[1] + (float)l1[1];
+            float w[4] = {__uint_as_float(e.z << 16), __uint_as_float(e.z & 0xffff0000u), __uint_as_float(e.w << 16),
+                          __uint_as_float(e.w & 0xffff0000u)};
+            if constexpr (!BF) {
+                const uint2 t = p3[((rb * 4 + kk) * CB + q) * 16 + col];
+                w[0] += __uint_as_float(t.x << 16);
+                w[1] += __uint_as_float(t.x & 0xffff0000u);
+                w[2] += __uint_as_float(t.y << 16);
+                w[3] += __uint_as_float(t.y & 0xffff0000u);
             }
+            v[0][q] = __uint_as_float(e.x << 16) + w[0];
+            v[1][q] = __uint_as_float(e.x & 0xffff0000u) + w[1];
+            v[2][q] = __uint_as_float(e.y << 16) + w[2];
+            v[3][q] = __uint_as_float(e.y & 0xffff0000u) + w[3];
         }
     };
     __syncthreads();
@@ -360,32 +320,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
     // (CB = 1) or are CB instructions apart
     struct AOp {
         uint4 a;
-        uint2 r;   // third halves (not BF)
+        uint2 r;   // third parts (not BF)
     };
     auto kstep = [&](const AOp& o, int k, fft_floatx4 (&c)[NCH]) {
         const uint4 a = o.a;
         fft_uintx4 B[CB];
+        uint2 Bl[CB];
 #pragma unroll
         for (int q = 0; q < CB; ++q) {
-            const uint4 e = reinterpret_cast<const uint4*>(pu)[((k * 4 + kk) * CB + q) * 16 + col];
+            const int i = ((k * 4 + kk) * CB + q) * 16 + col;
+            const uint4 e = reinterpret_cast<const uint4*>(pu)[i];
             B[q] = fft_uintx4{e.x, e.y, e.z, e.w};
+            if constexpr (!BF) Bl[q] = p3[i];
         }
         auto mma = [](fft_uintx4 x, fft_uintx4 y, fft_floatx4 z) {
-            if constexpr (BF)
-                return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(fft_bf16x8, x),
-                                                               __builtin_bit_cast(fft_bf16x8, y), z, 0, 0, 0);
-            else
-                return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(fft_halfx8, x),
-                                                              __builtin_bit_cast(fft_halfx8, y), z, 0, 0, 0);
+            return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(fft_bf16x8, x),
+                                                           __builtin_bit_cast(fft_bf16x8, y), z, 0, 0, 0);
         };
         const fft_uintx4 A1{a.x, a.y, a.x, a.y}, A2{a.z, a.w, BF ? 0u : a.z, BF ? 0u : a.w};
         if constexpr (!BF) {
-            const fft_uintx4 A3{o.r.x, o.r.y, 0u, 0u};
+            const fft_uintx4 A3{o.r.x, o.r.y, a.x, a.y};
 #pragma unroll
-            for (int q = 0; q < CB; ++q) c[q] = mma(A3, B[q], c[q]);
+            for (int q = 0; q < CB; ++q)
+                c[NCH - CB + q] = mma(A3, fft_uintx4{B[q][0], B[q][1], Bl[q].x, Bl[q].y}, c[NCH - CB + q]);
         }
 #pragma unroll
-        for (int q = 0; q < CB; ++q) c[CB == 1 ? 1 : q] = mma(A2, B[q], c[CB == 1 ? 1 : q]);
+        for (int q = 0; q < CB; ++q) c[NCH - CB + q] = mma(A2, B[q], c[NCH - CB + q]);
 #pragma unroll
         for (int q = 0; q < CB; ++q) c[q] = mma(A1, B[q], c[q]);
     };
@@ -436,7 +396,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
     };
 
     // States in groups of SG: the AO values of a row block are formed once per
-    // group, and the four waves' partial densities of the group meet in one
+    // group, and the waves' partial densities of the group meet in one
     // LDS slot (two barriers per group).  The fold over a wave's row blocks is
     // FP64 for the FP32 contraction and FP32 for split-BF16 (whose products
     // carry 16 significant bits); the slot holds SG x 4 x NP of them, within
@@ -449,9 +409,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
         for (int si = 0; si < SG; ++si)
 #pragma unroll
             for (int q = 0; q < CB; ++q) acc[si][q] = 0;
-        for (int i4 = 0; i4 < RB; i4 += 4) {
-            // snake order: blocks i4 .. i4+3 go to waves 0..3, then 3..0
-            const int rb = i4 + (((i4 >> 2) & 1) ? 3 - wave : wave);
+        for (int i0 = 0, odd = 0; i0 < RB; i0 += NW, odd ^= 1) {
+            // snake order: blocks i0 .. i0 + NW - 1 go to waves 0 .. NW - 1, then back
+            const int rb = i0 + (odd ? NW - 1 - wave : wave);
             if (rb >= RB) continue;
             // lane (kk, col) holds rows 16 rb + 4 kk + i of its columns
             FV v[4][CB];
@@ -464,14 +424,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
 #pragma unroll
                 for (int q = 0; q < NCH; ++q) c[q] = fft_floatx4{0.f, 0.f, 0.f, 0.f};
                 run_row(((size_t)s * (RB * (RB + 1) / 2) + fft_group0(rb, RB)) * 64, rb, RB - rb, c);
-                uint32_t a4 = 0;   // exponents of the lane's rows
-                if constexpr (!BF) a4 = *reinterpret_cast<const uint32_t*>(ra + s * 16 * RB + 16 * rb + 4 * kk);
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
                     for (int q = 0; q < CB; ++q) {
-                        float y = CB == 1 ? c[0][i] + c[1][i] : c[q][i];
-                        if constexpr (!BF) y = __builtin_ldexpf(y, -(int)(signed char)(a4 >> (8 * i)));
+                        const float y = TWO ? c[q][i] + c[NCH - CB + q][i] : c[q][i];
                         acc[si][q] += v[i][q] * (FV)y;
                     }
             }
@@ -483,7 +440,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
                 FV a = acc[si][q];
                 a += __shfl_xor(a, 16);
                 a += __shfl_xor(a, 32);
-                if (lane < 16) rd[(si * 4 + wave) * NP + q * 16 + lane] = a;
+                if (lane < 16) rd[(si * NW + wave) * NP + q * 16 + lane] = a;
             }
         __syncthreads();
         if (wave == 0) {
@@ -493,10 +450,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
             for (int si = 0; si < SG; ++si) {
                 const int s = s0 + si;
                 if (s >= ns) break;
-                const FV* r4 = rd + si * 4 * NP;
+                const FV* rw = rd + si * NW * NP;
                 double d = 0.0;
-                if (lane < NP) d = (double)r4[lane] + (double)r4[NP + lane] + (double)r4[2 * NP + lane] + (double)r4[3 * NP + lane];
-                if constexpr (!BF) d = __builtin_ldexp(d, -2 * pe);
+                if (lane < NP)
+#pragma unroll
+                    for (int w = 0; w < NW; ++w) d += (double)rw[w * NP + lane];
                 if (valid) {
                     const float v = (float)d;
                     float* zp = Z + ((size_t)(s >> 1) * npts + g) * 2;
@@ -673,23 +631,22 @@ __global__ __launch_bounds__(256) void fft_sum_kernel(const double* __restrict__
 
 // Bytes of the A operands: the upper triangle of function groups per state and
 // what the density kernel loads past a row block (up to 7 groups, unused); FP32
-// precision: the same of the third halves, then the rows' exponents.
+// precision (up to 3): the same of the third parts.
 static size_t fft_groups(int nbf_pad, int ns) {
     const size_t RB = nbf_pad / 16;
     return (size_t)ns * (RB * (RB + 1) / 2);
 }
 struct FftPack {
-    size_t ar, ra, total;   // offsets of the third halves and the exponents
+    size_t ar, total;   // offset of the third parts
 };
 static FftPack fft_pack_layout(int precision, int nbf_pad, int ns) {
     const size_t g = fft_groups(nbf_pad, ns);
     FftPack p;
     if (precision == SCFF_BF16X3) {
-        p.ar = p.ra = p.total = (g + 7) * 64 * sizeof(uint4);
+        p.ar = p.total = (g + 7) * 64 * sizeof(uint4);
     } else {
         p.ar = (g + 3) * 64 * sizeof(uint4);
-        p.ra = p.ar + (g + 3) * 64 * sizeof(uint2);
-        p.total = p.ra + (size_t)ns * nbf_pad;
+        p.total = p.ar + (g + 3) * 64 * sizeof(uint2);
     }
     return p;
 }
@@ -699,71 +656,68 @@ hipError_t launch_fft_pack(int precision, const double* T, const double* cnorm, 
                            double spin, void* Ap, hipStream_t st) {
     const int RB = nbf_pad / 16;
     const FftPack p = fft_pack_layout(precision, nbf_pad, ns);
-    signed char* ra = (signed char*)Ap + p.ra;
     uint2* ar = (uint2*)((char*)Ap + p.ar);
     const long long total = (long long)fft_groups(nbf_pad, ns) * 64;
     const int blocks = (int)std::min<long long>((total + 255) / 256, 65536);
-    if (precision == SCFF_BF16X3) {
-        hipLaunchKernelGGL(fft_pack_kernel<true>, dim3(blocks), dim3(256), 0, st, T, cnorm, nbf, ns, RB, spin, ra,
+    if (precision == SCFF_BF16X3)
+        hipLaunchKernelGGL(fft_pack_kernel<true>, dim3(blocks), dim3(256), 0, st, T, cnorm, nbf, ns, RB, spin, (uint4*)Ap,
+                           ar);
+    else
+        hipLaunchKernelGGL(fft_pack_kernel<false>, dim3(blocks), dim3(256), 0, st, T, cnorm, nbf, ns, RB, spin,
                            (uint4*)Ap, ar);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(fft_rowmax_kernel, dim3((ns * nbf_pad + 3) / 4), dim3(256), 0, st, T, cnorm, nbf, nbf_pad, ns,
-                       spin, ra);
-    hipLaunchKernelGGL(fft_pack_kernel<false>, dim3(blocks), dim3(256), 0, st, T, cnorm, nbf, ns, RB, spin, ra,
-                       (uint4*)Ap, ar);
     return hipGetLastError();
 }
 
-int fft_density_cb(int nbf_pad, size_t lds_limit) {
-    // the widest tile whose block stays within 64 KiB (several workgroups per
-    // CU); 16-point tiles up to the device limit for the largest bases
+// Waves per workgroup: four; eight in FP32 precision for tiles of 16 and 32 points,
+// whose registers allow four waves per SIMD where the LDS holds two workgroups (380
+// functions, 12 states, 64^3: 3.87 -> 2.74 ms a call; 265 functions 1.85 -> 1.53).
+static int fft_density_nw(bool bf, int cb) { return bf || cb == 4 ? 4 : 8; }
+
+int fft_density_cb(int precision, int nbf_pad, size_t lds_limit) {
+    // the widest tile whose block lets two workgroups stay on a CU (split-BF16: within
+    // 64 KiB); 16-point tiles up to the device limit for the largest bases.  FP32
+    // precision, 190 functions, 12 states, 128^3: 64 points 6.4 ms, 32 points 7.0
+    const bool bf = precision == SCFF_BF16X3;
     for (int cb : {4, 2})
-        if (fft_lds_bytes(nbf_pad, cb) <= std::min<size_t>(lds_limit, 64u << 10)) return cb;
-    return fft_lds_bytes(nbf_pad, 1) <= lds_limit ? 1 : 0;
+        if (fft_lds_bytes(bf, nbf_pad, cb, fft_density_nw(bf, cb)) <= std::min<size_t>(lds_limit, bf ? 64u << 10 : 80u << 10))
+            return cb;
+    return fft_lds_bytes(bf, nbf_pad, 1, fft_density_nw(bf, 1)) <= lds_limit ? 1 : 0;
 }
 
 hipError_t launch_fft_density(int precision, const FftMol& m, const void* Ap, int nbf_pad, int ns, const int n[3],
                               const double x0[3], const double h[3], float* Z, float* phi, double* psum,
                               size_t lds_limit, long long* n_part, hipStream_t st) {
     const long long npts = (long long)n[0] * n[1] * n[2];
-    const int cb = fft_density_cb(nbf_pad, lds_limit);
+    const int cb = fft_density_cb(precision, nbf_pad, lds_limit);
     if (cb == 0 || nbf_pad % 16) return hipErrorInvalidValue;
     const FftPack p = fft_pack_layout(precision, nbf_pad, ns);
-    const signed char* ra = (const signed char*)Ap + p.ra;
     const uint2* ar = (const uint2*)((const char*)Ap + p.ar);
-    const size_t lds = fft_lds_bytes(nbf_pad, cb);
+    const bool bf = precision == SCFF_BF16X3;
+    const int nw = fft_density_nw(bf, cb);
+    const size_t lds = fft_lds_bytes(bf, nbf_pad, cb, nw);
     const long long tiles = (npts + 16 * cb - 1) / (16 * cb);
     if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
     *n_part = tiles;
-    const bool bf = precision == SCFF_BF16X3;
-    const void* fns[2][3] = {{(const void*)fft_density_kernel<false, 1>, (const void*)fft_density_kernel<false, 2>,
-                              (const void*)fft_density_kernel<false, 4>},
-                             {(const void*)fft_density_kernel<true, 1>, (const void*)fft_density_kernel<true, 2>,
-                              (const void*)fft_density_kernel<true, 4>}};
-    const int ci = cb == 4 ? 2 : cb - 1;
-    if (lds > 65536) {
-        // dynamic LDS beyond 64 KiB per workgroup must be allowed explicitly
-        const hipError_t e = hipFuncSetAttribute(fns[bf][ci], hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
     const int3 nn = make_int3(n[0], n[1], n[2]);
     const double3 xx = make_double3(x0[0], x0[1], x0[2]), hh = make_double3(h[0], h[1], h[2]);
-    const dim3 grid((unsigned)tiles), block(256);
-#define SCFF_FFT_DENSITY(B, C)                                                                                  \
-    hipLaunchKernelGGL((fft_density_kernel<B, C>), grid, block, lds, st, m, (const uint4*)Ap, ar, ra, nbf_pad, ns, \
-                       nbf_pad / 16, nn, xx, hh, npts, Z, phi, psum)
-    if (bf) {
-        if (cb == 4) SCFF_FFT_DENSITY(true, 4);
-        else if (cb == 2) SCFF_FFT_DENSITY(true, 2);
-        else SCFF_FFT_DENSITY(true, 1);
-    } else {
-        if (cb == 4) SCFF_FFT_DENSITY(false, 4);
-        else if (cb == 2) SCFF_FFT_DENSITY(false, 2);
-        else SCFF_FFT_DENSITY(false, 1);
-    }
-#undef SCFF_FFT_DENSITY
-    return hipGetLastError();
+    const auto launch = [&](auto kernel) {
+        if (lds > 65536) {   // dynamic LDS beyond 64 KiB per workgroup must be allowed explicitly
+            const hipError_t e =
+                hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(64 * nw), lds, st, m, (const uint4*)Ap, ar, nbf_pad, ns,
+                           nbf_pad / 16, nn, xx, hh, npts, Z, phi, psum);
+        return hipGetLastError();
+    };
+    if (bf)
+        return cb == 4   ? launch(fft_density_kernel<true, 4, 4, 3>)
+               : cb == 2 ? launch(fft_density_kernel<true, 2, 4, 3>)
+                         : launch(fft_density_kernel<true, 1, 4, 3>);
+    if (cb == 4)   // three workgroups per CU, or two
+        return 3 * lds <= (160u << 10) ? launch(fft_density_kernel<false, 4, 4, 3>)
+                                       : launch(fft_density_kernel<false, 4, 4, 2>);
+    return cb == 2 ? launch(fft_density_kernel<false, 2, 8, 4>) : launch(fft_density_kernel<false, 1, 8, 4>);
 }
 
 hipError_t launch_fft_lines(float2* Z, int nb, const int n[3], hipStream_t st) {
