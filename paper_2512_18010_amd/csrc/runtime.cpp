@@ -90,8 +90,8 @@ struct scff_ctx {
     hipEvent_t order_ev = nullptr;
     hipStream_t order_st = nullptr;
     bool order_pending = false;
-    // a call has enqueued device work that is not yet covered by order_ev
-    // or a synchronisation (an error return in the middle of a call)
+    // a call (or batch) has enqueued device work that is not yet covered by
+    // order_ev or a synchronisation
     bool async_open = false;
     int symmetry = 0;   // evaluate half of a grid symmetric about q = 0 (scff_set_symmetry)
     // check the precompute's tables on the host after every precompute
@@ -195,14 +195,24 @@ int set_device(scff_ctx* c) { return hip_check(hipSetDevice(c->device), "hipSetD
 // the context's previous asynchronous work with an event, so a call on stream
 // B never overtakes a call still running on stream A.
 int order_after(scff_ctx* c, hipStream_t st) {
-    if (c->async_open) {   // an earlier call failed half-way: its work is on a stream nobody marked
-        GateShared g(device_gate());
-        const int rc = hip_check(hipDeviceSynchronize(), "device sync");
+    if (c->async_open) {
+        // work of an earlier call is on a stream that could not be marked (or in a
+        // batch that failed); a stream under capture cannot wait for it
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) {
+            GateShared g(device_gate());
+            const int rc = hip_check(hipDeviceSynchronize(), "device sync");
+            if (rc) return rc;
+        } else {
+            (void)hipGetLastError();
+        }
+    }
+    if (c->order_pending && st != c->order_st) {
+        const int rc = hip_check(hipStreamWaitEvent(st, c->order_ev, 0), "stream ordering");
         if (rc) return rc;
     }
     c->async_open = true;
-    if (!c->order_pending || st == c->order_st) return SCFF_OK;
-    return hip_check(hipStreamWaitEvent(st, c->order_ev, 0), "stream ordering");
+    return SCFF_OK;
 }
 int order_mark(scff_ctx* c, hipStream_t st) {
     int rc;
@@ -230,6 +240,20 @@ void order_done(scff_ctx* c) {
     c->order_pending = false;
     c->async_open = false;
 }
+
+// A call's work on the context: where the call returns early with an error, what
+// it has enqueued on st is marked, so that later calls are ordered after it.
+struct CallScope {
+    scff_ctx* c;
+    hipStream_t st;
+    ~CallScope() {
+        if (!c->async_open) return;
+        std::string msg;
+        msg.swap(g_err);   // the error that is being returned
+        (void)order_mark(c, st);
+        g_err.swap(msg);
+    }
+};
 
 int record(scff_ctx* c, int which, hipStream_t st) {
     if (!c->timing) return SCFF_OK;
@@ -625,6 +649,7 @@ int scff::ctx_prepare(scff_ctx* c, const scff_grid* g, int precision, hipStream_
     if (rc) return rc;
     if ((rc = set_device(c))) return rc;
     if ((rc = order_after(c, st))) return rc;
+    CallScope scope{c, st};
     if ((rc = ensure_prepared(c, st, choose_axis(c, g, precision)))) return rc;
     // the last precompute kernels (row compaction, slot remap) are still in
     // flight on st: the caller evaluates on another stream, which is not
@@ -842,6 +867,7 @@ int scff_load_transitions_device(scff_ctx* c, int n_states, const double* T_dev,
     const size_t n = (size_t)n_states * c->basis.nbf * c->basis.nbf;
     hipStream_t st = (hipStream_t)hip_stream;
     if ((rc = order_after(c, st))) return rc;
+    CallScope scope{c, st};
     if ((rc = dev_reserve(c, c->d_T, n * sizeof(double)))) return rc;
     if ((rc = hip_check(hipMemcpyAsync(c->d_T.p, T_dev, n * sizeof(double), hipMemcpyDeviceToDevice, st),
                         "device copy of T")))
@@ -879,6 +905,7 @@ int scff_query(scff_ctx* c, scff_info* info) {
         if ((rc = set_device(c))) return rc;
         if (!c->prepared || !c->stats_ready) {
             if ((rc = order_after(c, nullptr))) return rc;
+            CallScope scope{c, nullptr};
             if ((rc = ensure_stats(c, nullptr))) return rc;
             if ((rc = hip_check(hipStreamSynchronize(nullptr), "precompute sync"))) return rc;
             order_done(c);
@@ -902,6 +929,7 @@ int scff_eval_grid(scff_ctx* c, const scff_grid* g, int precision, float* f, flo
     hipStream_t st = (hipStream_t)hip_stream;
     c->ev_prep = false;
     if ((rc = order_after(c, st))) return rc;
+    CallScope scope{c, st};
     if ((rc = ensure_prepared(c, st, choose_axis(c, g, precision)))) return rc;
     const size_t npts = (size_t)g->n[0] * g->n[1] * g->n[2];
     const size_t nout = npts * (size_t)c->n_states;
@@ -968,6 +996,7 @@ int scff_eval_grid_noalloc(scff_ctx* c, const scff_grid* g, int precision, float
     hipStream_t st = (hipStream_t)hip_stream;
     c->ev_prep = false;
     if ((rc = order_after(c, st))) return rc;
+    CallScope scope{c, st};
     unsigned char* base = (unsigned char*)c->scratch;
     if ((rc = record(c, EV_VT0, st))) return rc;
     if ((rc = launch_tables(c, g, pl.shape, base, st))) return rc;
@@ -1071,6 +1100,7 @@ int scff_eval_points(scff_ctx* c, int n_q, const double* q, int precision, float
     if ((rc = set_device(c))) return rc;
     hipStream_t st = (hipStream_t)hip_stream;
     if ((rc = order_after(c, st))) return rc;
+    CallScope scope{c, st};
     if ((rc = ensure_prepared(c, st))) return rc;
     if ((rc = dev_reserve(c, c->d_q, (size_t)n_q * 3 * sizeof(double)))) return rc;
     if ((rc = hip_check(hipMemcpyAsync(c->d_q.p, q, (size_t)n_q * 3 * sizeof(double), hipMemcpyHostToDevice, st),
@@ -1101,6 +1131,7 @@ int scff_export_vtensors(scff_ctx* c, const scff_grid* g, long long* n_terms_out
     if ((rc = set_device(c))) return rc;
     hipStream_t st = nullptr;
     if ((rc = order_after(c, st))) return rc;
+    CallScope scope{c, st};
     if ((rc = ensure_pairs(c, st))) return rc;
     const PrepResult& p = c->pres;
     *n_terms_out = p.terms_kept;
@@ -1162,14 +1193,6 @@ int scff_export_vtensors(scff_ctx* c, const scff_grid* g, long long* n_terms_out
 }
 
 namespace {
-
-// Precompute on the default stream and wait (host-result calls).
-int prepare_sync(scff_ctx* c) {
-    int rc;
-    if ((rc = set_device(c))) return rc;
-    if ((rc = order_after(c, nullptr))) return rc;
-    return ensure_prepared(c, nullptr);
-}
 
 LowqPrep lowq_prep(scff_ctx* c) {
     const PrepInputs in = prep_inputs(c);
@@ -1237,6 +1260,7 @@ int scff_eval_fft(scff_ctx* c, const scff_fft_grid* g, int precision, float* f, 
     if ((rc = set_device(c))) return rc;
     hipStream_t st = (hipStream_t)hip_stream;
     if ((rc = order_after(c, st))) return rc;
+    CallScope scope{c, st};
     const int nb = (ns + 1) / 2;
     const long long npts = (long long)g->n[0] * g->n[1] * g->n[2];
     const size_t nout = (size_t)npts * ns;
@@ -1337,6 +1361,7 @@ int scff_eval_spherical(scff_ctx* c, int lmax, int n_q, const double* q, int n_t
     if ((rc = set_device(c))) return rc;
     hipStream_t st = (hipStream_t)hip_stream;
     if ((rc = order_after(c, st))) return rc;
+    CallScope scope{c, st};
     if ((rc = ensure_prepared(c, st))) return rc;
     const int ns = c->n_states, Lmax = lmax + kSphMaxN;
     const int nl = (lmax + 1) * (lmax + 1), nL = (Lmax + 1) * (Lmax + 1);
@@ -1509,7 +1534,9 @@ int scff_eval_separable(scff_ctx* c, const scff_grid* g, const double* wx, const
     for (int a = 0; a < 3; ++a)
         for (int i = 0; i < 2 * g->n[a]; ++i)
             if (!std::isfinite(ws[a][i])) return fail(SCFF_EINVAL, "non-finite weight");
-    if ((rc = prepare_sync(c))) return rc;
+    if ((rc = set_device(c)) || (rc = order_after(c, nullptr))) return rc;
+    CallScope scope{c, nullptr};
+    if ((rc = ensure_prepared(c, nullptr))) return rc;
     const size_t nw = (size_t)g->n[0] + g->n[1] + g->n[2], np = (size_t)sep_parts(c->basis.n_cp);
     if ((rc = dev_reserve(c, c->d_lq_in, nw * sizeof(double2))) ||
         (rc = dev_reserve(c, c->d_lq_S, (size_t)c->pres.n_rows * sizeof(double2))) ||
@@ -1544,11 +1571,13 @@ int scff_dipole(scff_ctx* c, const double* dE, double* mu, double* f0) {
     if (!mu) return fail(SCFF_EINVAL, "mu must not be NULL");
     if (f0 && !dE) return fail(SCFF_EINVAL, "oscillator strengths need the transition energies dE");
     int rc;
-    if ((rc = prepare_sync(c))) return rc;
     const int ns = c->n_states;
-    if (dE)
+    if (dE && c->have_mol && c->have_T)
         for (int s = 0; s < ns; ++s)
             if (!std::isfinite(dE[s])) return fail(SCFF_EINVAL, "non-finite transition energy");
+    if ((rc = set_device(c)) || (rc = order_after(c, nullptr))) return rc;
+    CallScope scope{c, nullptr};
+    if ((rc = ensure_prepared(c, nullptr))) return rc;
     if ((rc = dev_reserve(c, c->d_lq_G, (size_t)sep_parts(c->basis.n_cp) * ns * 4 * sizeof(double2))) ||
         (rc = dev_reserve(c, c->d_lq_out, (size_t)ns * 4 * sizeof(double2))))
         return rc;
@@ -1580,7 +1609,9 @@ int scff_dipole_fit(scff_ctx* c, double q_fit, const double* dE, double* coef, d
     if (!(q_fit > 0.0) || !std::isfinite(q_fit)) return fail(SCFF_EINVAL, "q_fit must be positive and finite");
     if (f0_fit && !dE) return fail(SCFF_EINVAL, "oscillator strengths need the transition energies dE");
     int rc;
-    if ((rc = set_device(c)) || (rc = order_after(c, nullptr)) || (rc = ensure_prepared(c, nullptr))) return rc;
+    if ((rc = set_device(c)) || (rc = order_after(c, nullptr))) return rc;
+    CallScope scope{c, nullptr};
+    if ((rc = ensure_prepared(c, nullptr))) return rc;
     const int ns = c->n_states;
     // kFitShells radii q_k = q_fit k / kFitShells; on each, the product rule
     // of kFitTheta Gauss-Legendre nodes in cos(theta) and kFitPhi equally
