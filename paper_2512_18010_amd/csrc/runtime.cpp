@@ -143,18 +143,37 @@ void dev_free(scff_ctx* c, DeviceBuffer& b) {
     b.bytes = 0;
 }
 
-// Ensure `b` holds at least `bytes`; keeps the old buffer if large enough.
-hipError_t dev_reserve_raw(scff_ctx* c, DeviceBuffer& b, size_t bytes) {
+// Gives up the partial sums that earlier calls kept (a call without room for its own
+// does with fewer or none), all but b.  True if there were any.
+bool release_partials(scff_ctx* c, const DeviceBuffer& b) {
+    bool any = false;
+    for (DeviceBuffer* x : {&c->d_part, &c->d_pt_part, &c->d_sph_P})
+        if (x != &b && x->p) {
+            dev_free(c, *x);
+            any = true;
+        }
+    return any;
+}
+
+// Ensure `b` holds at least `bytes`; keeps the old buffer if large enough.  Where
+// the budget or the device has no room, other calls' partial sums make it, unless
+// b is such a buffer itself.
+hipError_t dev_reserve_raw(scff_ctx* c, DeviceBuffer& b, size_t bytes, bool partials = false) {
     if (bytes == 0) bytes = 256;
     if (b.p && b.bytes >= bytes) return hipSuccess;
     const size_t old = b.bytes;
-    if (c->budget && c->used - old + bytes > c->budget) return hipErrorOutOfMemory;
+    const auto fits = [&] { return !c->budget || c->used - old + bytes <= c->budget; };
+    if (!fits() && (partials || !release_partials(c, b) || !fits())) return hipErrorOutOfMemory;
     dev_free(c, b);
     void* p = nullptr;
-    hipError_t e;
-    {
+    const auto get = [&] {
         GateShared g(device_gate());
-        e = hipMalloc(&p, bytes);
+        return hipMalloc(&p, bytes);
+    };
+    hipError_t e = get();
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        if (!partials && release_partials(c, b) && (e = get()) == hipErrorOutOfMemory) (void)hipGetLastError();
     }
     if (e != hipSuccess) return e;
     b.p = p;
@@ -163,8 +182,8 @@ hipError_t dev_reserve_raw(scff_ctx* c, DeviceBuffer& b, size_t bytes) {
     return hipSuccess;
 }
 
-int dev_reserve(scff_ctx* c, DeviceBuffer& b, size_t bytes) {
-    hipError_t e = dev_reserve_raw(c, b, bytes);
+int dev_reserve(scff_ctx* c, DeviceBuffer& b, size_t bytes, bool partials = false) {
+    hipError_t e = dev_reserve_raw(c, b, bytes, partials);
     if (e == hipErrorOutOfMemory)
         return fail(SCFF_ENOMEM, "HBM budget or device memory exceeded (need " + std::to_string(bytes) +
                                      " more bytes, context holds " + std::to_string(c->used) + ")");
@@ -391,10 +410,9 @@ int run_points(scff_ctx* c, const double* q, int nq, float2* f, float* f2, doubl
     int n = points_split(nq, c->n_states, in.n_sp);
     for (; n > 1; n /= 2) {
         const hipError_t e =
-            dev_reserve_raw(c, c->d_pt_part, (size_t)n * c->n_states * (size_t)nq * sizeof(double2));
+            dev_reserve_raw(c, c->d_pt_part, (size_t)n * c->n_states * (size_t)nq * sizeof(double2), true);
         if (e == hipSuccess) break;
         if (e != hipErrorOutOfMemory) return hip_check(e, "points partial sums");
-        (void)hipGetLastError();
     }
     const PointArgs a{in.shells, in.sp, in.sp_cp, (const VRowDev*)w.rows_all.p, (const double*)w.wt.p,
                       (const double*)w.small.p + 64, (const double*)w.tp64.p, q, in.n_sp, c->n_states, nq, f, f2, f2d,
@@ -688,7 +706,7 @@ int scff::ctx_batch_reserve(scff_ctx* c, const scff_grid* g, int precision, bool
     if (want_f2 && (rc = dev_reserve(c, c->d_f2, nout * sizeof(float)))) return rc;
     double2* part = nullptr;
     if (pl.sp.n > 1) {
-        if (dev_reserve(c, c->d_part, (size_t)pl.sp.n * nout * sizeof(double2)) == SCFF_OK)
+        if (dev_reserve(c, c->d_part, (size_t)pl.sp.n * nout * sizeof(double2), true) == SCFF_OK)
             part = (double2*)c->d_part.p;
         else
             pl = plan_eval(c, g, precision, false);
@@ -955,7 +973,7 @@ int scff_eval_grid(scff_ctx* c, const scff_grid* g, int precision, float* f, flo
     // values up to the order of the FP64 sums)
     double2* part = nullptr;
     if (pl.sp.n > 1) {
-        if (dev_reserve(c, c->d_part, (size_t)pl.sp.n * nout * sizeof(double2)) == SCFF_OK)
+        if (dev_reserve(c, c->d_part, (size_t)pl.sp.n * nout * sizeof(double2), true) == SCFF_OK)
             part = (double2*)c->d_part.p;
         else
             pl = plan_eval(c, g, precision, false);
@@ -1457,9 +1475,8 @@ int scff_eval_spherical(scff_ctx* c, int lmax, int n_q, const double* q, int n_t
     if ((rc = dev_reserve(c, c->d_sph_items, items.size() * sizeof(SphItem)))) return rc;
     const size_t pbytes = (size_t)segs.first[segs.n_split] * n_q * 32 * nL * sizeof(double);
     if (segs.n_split) {
-        const hipError_t e = pbytes > kMaxPartBytes ? hipErrorOutOfMemory : dev_reserve_raw(c, c->d_sph_P, pbytes);
+        const hipError_t e = pbytes > kMaxPartBytes ? hipErrorOutOfMemory : dev_reserve_raw(c, c->d_sph_P, pbytes, true);
         if (e == hipErrorOutOfMemory) {
-            (void)hipGetLastError();
             sph_plan(ext, ns, Lmax, n_q, false, items, segs);
         } else if (e != hipSuccess) {
             return hip_check(e, "spherical partial sums");
