@@ -116,7 +116,7 @@ __global__ __launch_bounds__(256) void sep_pairs_kernel(LowqPrep p, const double
                     g[2].x += x * dy * z;
                     g[3].x += x * y * dz;
                 } else {
-                    const double2 v = cmul(cmul(S[p.newid[tr.x]], S[p.newid[p.nr + tr.y]]), S[p.newid[2 * p.nr + tr.z]]);
+                    const double2 v = cmul(cmul(S[p.newid[tr.x]], S[p.newid[(size_t)p.nr + tr.y]]), S[p.newid[(size_t)2 * p.nr + tr.z]]);
                     g[0].x += v.x;
                     g[0].y += v.y;
                 }

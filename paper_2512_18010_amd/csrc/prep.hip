@@ -411,7 +411,7 @@ __global__ void layout_kernel(const int* __restrict__ order, const int4* __restr
                 if (!term_kept(w[ti], th)) continue;
                 if (seen++ < vi.y) continue;
                 const int4 tr = trow[ti];
-                dst[q++] = make_int4(1 + newid[tr.x], 1 + newid[nr + tr.y], 1 + newid[2 * nr + tr.z], 1);
+                dst[q++] = make_int4(1 + newid[tr.x], 1 + newid[(size_t)nr + tr.y], 1 + newid[(size_t)2 * nr + tr.z], 1);
             }
         }
         for (int q = len; q < npp; ++q) dst[q] = make_int4(0, 0, 0, 0);   // the zero row
@@ -493,15 +493,15 @@ __global__ __launch_bounds__(128) void zcount_kernel(const PrepShell* __restrict
             const int t = s.w + kZClasses.c[kc][cls][k] * npp + pp;
             if (!term_kept(w[t], th)) continue;
             const int4 tr = trow[t];
-            used[la * nr + term_row(tr, la)] = 1;
-            used[lb * nr + term_row(tr, lb)] = 1;
+            used[(size_t)la * nr + term_row(tr, la)] = 1;
+            used[(size_t)lb * nr + term_row(tr, lb)] = 1;
             ++n;
         }
         const int id = s.z / 3 + z;
         zn[id] = n;
         zinfo[id] = make_int2(isp, z);
         for (int k = 0; k < kZTerms; ++k) used[(size_t)3 * nr + (size_t)k * nz_all + id] = n == kZTerms - k;
-        if (n) used[axis * nr + s.z + pp * 3 * ncls + axis * ncls + cls] = 1;
+        if (n) used[(size_t)axis * nr + s.z + pp * 3 * ncls + axis * ncls + cls] = 1;
     }
     for (int i = threadIdx.x; i < nz * ns; i += blockDim.x) {
         const int z = i / ns, st = i - z * ns;
@@ -613,8 +613,8 @@ __global__ __launch_bounds__(256) void zlayout_kernel(const PrepShell* __restric
                 const int4 tr = trow[t];
                 // rows of the line axes' tables, whose row 0 is the zero row
                 if (st == 0)
-                    rec[kZStep * n] = make_int2(1 + newid[la * nr + term_row(tr, la)] - newid[la * nr],
-                                                1 + newid[lb * nr + term_row(tr, lb)] - newid[lb * nr]);
+                    rec[kZStep * n] = make_int2(1 + newid[(size_t)la * nr + term_row(tr, la)] - newid[(size_t)la * nr],
+                                                1 + newid[(size_t)lb * nr + term_row(tr, lb)] - newid[(size_t)lb * nr]);
                 const double tp = tp64[(size_t)tr.w * ns + st];
                 float v = (float)(tp * sc);
                 // finite weights stay finite (a row bound that underflows)
@@ -622,7 +622,7 @@ __global__ __launch_bounds__(256) void zlayout_kernel(const PrepShell* __restric
                 tw[n * tstep] = v;
                 ++n;
             }
-            if (st == 0) zslots[p] = make_int2(1 + newid[axis * nr + rz], e);
+            if (st == 0) zslots[p] = make_int2(1 + newid[(size_t)axis * nr + rz], e);
         } else if (st == 0) {
             zslots[p] = make_int2(0, 0);
         }
@@ -677,7 +677,6 @@ hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, int axis
     CK(alloc(w.small, kSmallBytes));
     // flags: rows used per axis, then the z rows' one-hot term counts
     const long long NF = 3 * NR + (long long)kZTerms * NZ;
-    if (NF > INT32_MAX) return hipErrorInvalidValue;
     CK(alloc(w.row_used, (size_t)NF * sizeof(int)));
     CK(alloc(w.newid, (size_t)NF * sizeof(int)));
     double* tot = (double*)w.small.p;                                    // [<= 32]
@@ -731,9 +730,9 @@ hipError_t run_prep_layout(const PrepInputs& in, PrepWork& w, PrepResult& res, i
                        (int)NR, NZ, axis, (int*)w.row_used.p, zn, zinfo, zmx, tail, (const VRowDev*)w.rows_all.p);
     CK(hipGetLastError());
     size_t tmp_bytes = 0;
-    CK(hipcub::DeviceScan::ExclusiveSum(nullptr, tmp_bytes, (int*)w.row_used.p, (int*)w.newid.p, (int)NF, st));
+    CK(hipcub::DeviceScan::ExclusiveSum(nullptr, tmp_bytes, (int*)w.row_used.p, (int*)w.newid.p, (size_t)NF, st));
     CK(alloc(w.tmp4, tmp_bytes + 256));
-    CK(hipcub::DeviceScan::ExclusiveSum(w.tmp4.p, tmp_bytes, (int*)w.row_used.p, (int*)w.newid.p, (int)NF, st));
+    CK(hipcub::DeviceScan::ExclusiveSum(w.tmp4.p, tmp_bytes, (int*)w.row_used.p, (int*)w.newid.p, (size_t)NF, st));
     hipLaunchKernelGGL(zmeta_kernel, dim3(1), dim3(64), 0, st, (const unsigned long long*)zmx, ns,
                        (const int*)w.newid.p, (const int*)w.row_used.p, (int)NR, NZ, ks, sinv, meta);
     CK(hipGetLastError());
@@ -759,7 +758,7 @@ hipError_t run_prep_layout(const PrepInputs& in, PrepWork& w, PrepResult& res, i
     long long nc = 0;
     for (int n = 1; n <= kZTerms; ++n) nc += steps.kend[n];
     const long long nterm = nc * kZStep, nw = nc * grid_term_weights(ns);
-    if (nz > nrows_used || nterm > INT32_MAX || nw > INT32_MAX) return hipErrorUnknown;
+    if (nz > nrows_used || nterm > INT32_MAX) return hipErrorUnknown;
     CK(alloc(w.zslots, (size_t)nzpad * sizeof(int2)));
     CK(alloc(w.zterms, (size_t)nterm * sizeof(int2)));
     CK(alloc(w.zw, (size_t)nw * sizeof(float)));
