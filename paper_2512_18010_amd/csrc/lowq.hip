@@ -21,6 +21,7 @@
 #include <algorithm>
 
 #include "engine.h"
+#include "vrow.h"
 
 namespace scff {
 
@@ -32,15 +33,17 @@ __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
 
 // S[r] = sum_i w_a[i] V_r(q_a[i]) for the axis a of row r (w: x, y, z weights
 // concatenated).  Eight lanes per row: lane l takes the values i = l, l + 8, ...,
-// then a fixed butterfly sums the eight.  The phase q P moves by a constant
-// from one value of a lane to the next: one complex product, and the sine and
-// cosine themselves at every 16th (fifteen products add less than the rounding
-// of q P does); bound by FP64 issue: 116 us with a sine and a cosine per value
-// for 30 heavy atoms and 96 values per axis, 80 us now.  (Four rows per
-// eight lanes, sharing the factors where they belong to one primitive pair:
-// 122 us, since some row of a wave always starts a new one.)
+// then a fixed butterfly sums the eight.  On an axis symmetric about 0 (bit a of
+// sym) V(-q) = V(q)* gives the value n - 1 - i with i.  Bound by FP64 issue, an
+// exponential, a sine and a cosine per value: 30 heavy atoms and 96 values per axis
+// 69 us on symmetric axes, 116 on others.  (Moving the
+// phase from one value of a lane to the next by a complex product took 80 us, but
+// carries the rounding of the first value's phase to all that follow, up to four
+// times the error where q is small.  Four rows per eight lanes, sharing the factors where they
+// belong to one primitive pair: 122 us, since some row of a wave always starts a new
+// one.)
 __global__ __launch_bounds__(256) void sep_rows_kernel(const VRowDev* __restrict__ rows, int nrows,
-                                                       const double2* __restrict__ w, int3 n, double3 qmin,
+                                                       const double2* __restrict__ w, int3 n, int sym, double3 qmin,
                                                        double3 dq, double2* __restrict__ S) {
     const int l8 = threadIdx.x & 7;
     const int r = blockIdx.x * 32 + (threadIdx.x >> 3);
@@ -51,28 +54,18 @@ __global__ __launch_bounds__(256) void sep_rows_kernel(const VRowDev* __restrict
     const int off = a == 0 ? 0 : (a == 1 ? n.x : n.x + n.y);
     const double q0 = a == 0 ? qmin.x : (a == 1 ? qmin.y : qmin.z);
     const double d = a == 0 ? dq.x : (a == 1 ? dq.y : dq.z);
-    auto phase = [&](double q, double& sn, double& cs) {
-        const double rev = q * row.P * 0.15915494309189535;   // 1 / (2 pi)
-        sincospi(2.0 * (rev - rint(rev)), &sn, &cs);
-    };
-    double sr = 0.0, si = 0.0, sn = 0.0, cs = 1.0, ds, dc;
-    phase(8.0 * d, ds, dc);
-    for (int i = l8, j = 0; i < na; i += 8, ++j) {
-        const double q = q0 + d * (double)i, q2 = q * q;
-        if ((j & 15) == 0) {
-            phase(q, sn, cs);
-        } else {
-            const double c1 = fma(-sn, ds, cs * dc);
-            sn = fma(sn, dc, cs * ds);
-            cs = c1;
+    const bool half = sym >> a & 1;
+    double sr = 0.0, si = 0.0;
+    for (int i = l8; i < (half ? (na + 1) / 2 : na); i += 8) {
+        const double2 v = eval_row_fp64(row, q0 + d * (double)i);
+        double2 wi = w[off + i];
+        sr += wi.x * v.x - wi.y * v.y;
+        si += wi.x * v.y + wi.y * v.x;
+        if (half && na - 1 - i > i) {
+            wi = w[off + na - 1 - i];
+            sr += wi.x * v.x + wi.y * v.y;
+            si += wi.y * v.x - wi.x * v.y;
         }
-        const double g = exp(-q2 * row.inv4p);
-        const double pr = fma(fma(row.e[4], q2, -row.e[2]), q2, row.e[0]);
-        const double pi = q * fma(-row.e[3], q2, row.e[1]);
-        const double vx = g * (cs * pr - sn * pi), vy = g * (cs * pi + sn * pr);
-        const double2 wi = w[off + i];
-        sr += wi.x * vx - wi.y * vy;
-        si += wi.x * vy + wi.y * vx;
     }
     for (int o = 1; o < 8; o <<= 1) {
         sr += __shfl_xor(sr, o);
@@ -173,13 +166,13 @@ __global__ __launch_bounds__(64) void sep_final_kernel(const double2* __restrict
 int sep_parts(int ncp) { return std::max(1, std::min(1024, (ncp + 63) / 64)); }
 
 hipError_t launch_separable(const LowqPrep& p, const VRowDev* rows, int nrows, int ncp, int ns, const double2* w,
-                            const int n[3], const double qmin[3], const double dq[3], double2* S, double2* part,
+                            const int n[3], int sym, const double qmin[3], const double dq[3], double2* S, double2* part,
                             double2* out, hipStream_t st) {
     if (ns < 1 || ns > kMaxStates || ncp < 1) return hipErrorInvalidValue;
     hipError_t e;
     if (nrows > 1) {   // row 0 is the zero row
         hipLaunchKernelGGL(sep_rows_kernel, dim3((nrows - 1 + 31) / 32), dim3(256), 0, st, rows + 1, nrows - 1, w,
-                           make_int3(n[0], n[1], n[2]), make_double3(qmin[0], qmin[1], qmin[2]),
+                           make_int3(n[0], n[1], n[2]), sym, make_double3(qmin[0], qmin[1], qmin[2]),
                            make_double3(dq[0], dq[1], dq[2]), S);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

@@ -35,7 +35,7 @@ int points_split(int nq, int ns, int n_sp);
 hipError_t launch_points(const PointArgs& a, int n_split, hipStream_t st);
 int sep_parts(int ncp);
 hipError_t launch_separable(const LowqPrep& p, const VRowDev* rows, int nrows, int ncp, int ns, const double2* w,
-                            const int n[3], const double qmin[3], const double dq[3], double2* S, double2* part,
+                            const int n[3], int sym, const double qmin[3], const double dq[3], double2* S, double2* part,
                             double2* out, hipStream_t st);
 hipError_t launch_dipole(const LowqPrep& p, int ncp, int ns, double2* part, double2* out, hipStream_t st);
 }  // namespace scff
@@ -1569,9 +1569,11 @@ int scff_eval_separable(scff_ctx* c, const scff_grid* g, const double* wx, const
         off += g->n[a];
     }
     double dq[3];
-    for (int a = 0; a < 3; ++a) dq[a] = g->n[a] > 1 ? (g->qmax[a] - g->qmin[a]) / (g->n[a] - 1) : 0.0;
+    grid_spacing(g, dq);
+    int sym = 0;
+    for (int a = 0; a < 3; ++a) sym |= axis_reflects(g, a) ? 1 << a : 0;
     if ((rc = hip_check(launch_separable(lowq_prep(c), (const VRowDev*)c->prep.rows.p, c->pres.n_rows, c->basis.n_cp, c->n_states,
-                                         (const double2*)c->d_lq_in.p, g->n, g->qmin, dq, (double2*)c->d_lq_S.p,
+                                         (const double2*)c->d_lq_in.p, g->n, sym, g->qmin, dq, (double2*)c->d_lq_S.p,
                                          (double2*)c->d_lq_G.p, (double2*)c->d_lq_out.p, nullptr),
                         "separable kernels")))
         return rc;
