@@ -190,7 +190,7 @@ int scff_eval_grid(scff_ctx* ctx, const scff_grid* grid, int precision, float* f
  * calls no hipMalloc, hipFree or allocating library routine: the 1D tables
  * of the grid, and the FP64 partial sums of a split evaluation when they
  * fit after the tables, live in a static per-device scratch array of
- * 256 MiB (held by every device the library runs on until the process
+ * 328 MiB (held by every device the library runs on until the process
  * ends).
  *   f, f2          device pointers as for scff_eval_grid with
  *                  out_on_device = 1 (either may be NULL); asynchronous on
@@ -229,8 +229,7 @@ int scff_set_symmetry(scff_ctx* ctx, int enable);
  * individual points from the V-tensors).  Same outputs as scff_eval_grid
  * with the grid axes replaced by the point index: f [n_states][n_q][2],
  * f2 [n_states][n_q].  1 <= n_q <= 2^24.  precision must be SCFF_FP32 (the
- * points kernel runs on the FP32 vector units, with the same FP32 block
- * sums folded into FP64 every 32 pairs as the grid kernel's FP32 path);
+ * points kernel runs in FP64 on the vector units; its outputs are FP32);
  * SCFF_BF16X3 is rejected with SCFF_EINVAL.  The call waits for its
  * stream: it returns with the outputs written (host or device pointers).
  */

@@ -209,7 +209,7 @@ struct PointArgs {
 // pairs (made when the export first needs it): slots, tp32 and, per
 // unit, cnpp (terms per pair) and coff (first slot).
 struct PrepWork {
-    DeviceBuffer rows_all, rowsum, trow, tbound, wt, cpmn, tp64, bsum, part, small, nk, nv, vbase,
+    DeviceBuffer rows_all, rowsum, trow, tbound, wt, tp64, bsum, part, small, nk, nv, vbase,
         tmp, key, val, vinfo, tmp2, cnpp, csize, coff, tmp3, slots, tp32, row_used, newid, tmp4,
         rows, zslots, zterms, zw;
     // pinned host memory of the context (kPinnedBytes, or NULL if it could
@@ -343,7 +343,7 @@ struct SphSegs {
     int first[kMaxStates * (kSphMaxN + 1) * (kSphMaxN + 1) / 32 + 2];
 };
 inline int sph_geo_stride(int n_geo) { return (n_geo + 15) & ~15; }
-void sph_plan(const SphExt& ext, int ns, int Lmax, int n_q, bool split, std::vector<SphItem>& items,
+void sph_plan(const SphExt& ext, int ns, int Lmax, int n_q, int n_cu, bool split, std::vector<SphItem>& items,
               SphSegs& segs);
 hipError_t launch_sph_geom(const SphGeom* geo, int n_geo, const VRowDev* rows, const int4* trow, const double* tp64,
                            int ns, const double* theta, const int* uvw_idx, const int* nfirst, int n_nlm, int Lmax,

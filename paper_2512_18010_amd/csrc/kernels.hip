@@ -632,7 +632,7 @@ __global__ void zero_counters_kernel(int* __restrict__ c, int n) {
 
 // ---------------------------------------------------------------- split reduction
 //
-// Sum of the FP64 partial results of the chunk-list splits (fixed order) for
+// Sum of the FP64 partial results of the k-step ranges (fixed order) for
 // the evaluated planes ix < nx_eval, then f and |f|^2 as from the grid kernel.
 
 __global__ void reduce_kernel(const double2* __restrict__ part, int n_split, long long stride, int3 n,

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(128) void rows_terms_kernel(
     const int* __restrict__ sp_cp, const int* __restrict__ bf0, const double* __restrict__ cnorm,
     const double* __restrict__ T, int nbf, int ns, double spin, VRowDev* __restrict__ rows, double* __restrict__ rowsum,
     int* __restrict__ used, unsigned* __restrict__ small, int nsmall, int4* __restrict__ trow,
-    double* __restrict__ tbound, int2* __restrict__ cpmn, double* __restrict__ tp64, double* __restrict__ bsum,
+    double* __restrict__ tbound, double* __restrict__ tp64, double* __restrict__ bsum,
     double* __restrict__ part) {
     const int isp = blockIdx.x;
     const int4 s = sp[isp];   // sA, sB, row_off, term_off
@@ -177,12 +177,9 @@ __global__ __launch_bounds__(128) void rows_terms_kernel(
         tbound[s.w + t] = bd;
     }
     __syncthreads();
-    // component pairs: mu, nu and the sum of their term bounds; packed weights,
-    // component pairs fastest (neighbours of one state share T's cache lines)
+    // component pairs: the sum of their term bounds; packed weights, component
+    // pairs fastest (neighbours of one state share T's cache lines)
     for (int c = threadIdx.x; c < ncp; c += blockDim.x) {
-        int c1, c2;
-        cp_decode(c, same, ncB, c1, c2);
-        cpmn[cp0 + c] = make_int2(bf0[s.x] + c1, bf0[s.y] + c2);
         double b = 0.0;
         for (int pp = 0; pp < npp; ++pp) b += tbound[s.w + c * npp + pp];
         bsum[cp0 + c] = b;
@@ -669,7 +666,6 @@ hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, int axis
     CK(alloc(w.trow, (size_t)NT * sizeof(int4)));
     CK(alloc(w.tbound, std::max((size_t)NT * sizeof(double), (size_t)NZ * 12)));
     CK(alloc(w.wt, (size_t)NT * sizeof(double)));
-    CK(alloc(w.cpmn, (size_t)NCP * sizeof(int2)));
     CK(alloc(w.tp64, (size_t)NCP * ns * sizeof(double)));
     CK(alloc(w.bsum, (size_t)NCP * sizeof(double)));
     CK(alloc(w.part, (size_t)NSP * ns * sizeof(double)));
@@ -687,7 +683,7 @@ hipError_t run_prep(const PrepInputs& in, PrepWork& w, PrepResult& res, int axis
     hipLaunchKernelGGL(rows_terms_kernel, dim3(NSP), dim3(128), 0, st, in.shells, in.sp, in.xyz, in.exps, in.coefs, in.n1d,
                        (int)NR, in.sp_cp, in.bf0, in.cnorm, in.T, in.nbf, ns, in.spin, (VRowDev*)w.rows_all.p,
                        (double*)w.rowsum.p, (int*)w.row_used.p, (unsigned*)w.small.p, nsmall, (int4*)w.trow.p,
-                       (double*)w.tbound.p, (int2*)w.cpmn.p, (double*)w.tp64.p, (double*)w.bsum.p, (double*)w.part.p);
+                       (double*)w.tbound.p, (double*)w.tp64.p, (double*)w.bsum.p, (double*)w.part.p);
     CK(hipGetLastError());
     hipLaunchKernelGGL(tot_kernel, dim3(ns), dim3(1024), 0, st, (const double*)w.part.p, NSP, ns, tot);
     CK(hipGetLastError());

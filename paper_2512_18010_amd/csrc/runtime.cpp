@@ -642,7 +642,7 @@ void free_all(scff_ctx* c) {
                             &c->d_sph_F, &c->d_sph_avg, &c->d_sph_J, &c->d_sph_P, &c->d_sph_items})
         dev_free(c, *b);
     PrepWork& w = c->prep;
-    for (DeviceBuffer* b : {&w.rows_all, &w.rowsum, &w.trow, &w.tbound, &w.wt, &w.cpmn, &w.tp64, &w.bsum,
+    for (DeviceBuffer* b : {&w.rows_all, &w.rowsum, &w.trow, &w.tbound, &w.wt, &w.tp64, &w.bsum,
                             &w.part, &w.small, &w.nk, &w.nv, &w.vbase, &w.tmp, &w.key, &w.val, &w.vinfo,
                             &w.tmp2, &w.cnpp, &w.csize, &w.coff, &w.tmp3, &w.slots, &w.tp32,
                             &w.row_used, &w.newid, &w.tmp4, &w.rows, &w.zslots, &w.zterms, &w.zw})
@@ -1109,7 +1109,7 @@ int scff_eval_points(scff_ctx* c, int n_q, const double* q, int precision, float
     if (!q) return fail(SCFF_EINVAL, "q is NULL");
     int rc;
     if ((rc = check_precision(precision))) return rc;
-    // points run on the FP32 vector units only (no matrix-core contraction)
+    // points run in FP64 on the vector units only (no matrix-core contraction)
     if (precision != SCFF_FP32)
         return fail(SCFF_EINVAL, "scff_eval_points supports SCFF_FP32 only (the split-BF16 contraction is a "
                                  "grid-kernel path)");
@@ -1471,13 +1471,13 @@ int scff_eval_spherical(scff_ctx* c, int lmax, int n_q, const double* q, int n_t
     // (at most as large as Q; last, so that they never take what the others need)
     std::vector<SphItem> items;
     SphSegs segs;
-    sph_plan(ext, ns, Lmax, n_q, true, items, segs);
+    sph_plan(ext, ns, Lmax, n_q, c->n_cu, true, items, segs);
     if ((rc = dev_reserve(c, c->d_sph_items, items.size() * sizeof(SphItem)))) return rc;
     const size_t pbytes = (size_t)segs.first[segs.n_split] * n_q * 32 * nL * sizeof(double);
     if (segs.n_split) {
         const hipError_t e = pbytes > kMaxPartBytes ? hipErrorOutOfMemory : dev_reserve_raw(c, c->d_sph_P, pbytes, true);
         if (e == hipErrorOutOfMemory) {
-            sph_plan(ext, ns, Lmax, n_q, false, items, segs);
+            sph_plan(ext, ns, Lmax, n_q, c->n_cu, false, items, segs);
         } else if (e != hipSuccess) {
             return hip_check(e, "spherical partial sums");
         }

@@ -1,6 +1,6 @@
 // Static device scratch of the allocation-free evaluation entry point
 // (scff_eval_grid_noalloc): the 1D tables of the grid and, when they fit
-// after them, the FP64 partial sums of a split chunk list live in this
+// after them, the FP64 partial sums of a split evaluation live in this
 // file-scope array instead of context buffers, so that call allocates no
 // device memory.  Each device the library runs on holds its own copy of the
 // array (kScratchBytes + kScratchSlack) until the process ends.

@@ -506,7 +506,7 @@ int enqueue_batch(Runner& R, std::vector<Member*>& live, const int off[], size_t
     for (int v = 0; v < kVariants; ++v) {
         const int n = off[v + 1] - off[v];
         if (n == 0) continue;
-                int lds = 0;
+        int lds = 0;
         for (const Member* m : live)
             if (m->be.cls == v) lds = std::max(lds, m->be.shape.lds);
         const int wgs = std::min(n, ncu * scff::grid_wgs_per_cu(v, lds));

@@ -161,7 +161,7 @@ __global__ __launch_bounds__(256) void sph_ylm_kernel(const double4* __restrict_
 // J[(iq (Lmax + 2) + L) gs + g] = j_L(q |P_g|) for L <= Lmax and, at
 // L = Lmax + 1, e^{-q^2 / 4p_g}; geometries padded to gs (copies of the last
 // one: finite factors of zero rows).  One thread per (radius, geometry); the
-// recurrence of bessel_range, written straight to the strided table.
+// recurrence is written straight to the strided table.
 __global__ void sph_bessel_kernel(const double4* __restrict__ gdat, int n_geo, int gs, int Lmax, const double* __restrict__ qs,
                                   int n_q, double* __restrict__ J) {
     const long long idx = blockIdx.x * (long long)blockDim.x + threadIdx.x;
@@ -508,10 +508,10 @@ hipError_t launch_sph_geom(const SphGeom* geo, int n_geo, const VRowDev* rows, c
 }
 
 // Row tiles and their segments: items of about equal work (products of 16 rows and
-// 16 geometries), enough for six workgroups per CU of a 256-CU device over the
+// 16 geometries), enough for six workgroups per CU over the
 // column tiles and radii, of at least 32 products each; split = false: one segment
 // per tile.
-void sph_plan(const SphExt& ext, int ns, int Lmax, int n_q, bool split, std::vector<SphItem>& items, SphSegs& segs) {
+void sph_plan(const SphExt& ext, int ns, int Lmax, int n_q, int n_cu, bool split, std::vector<SphItem>& items, SphSegs& segs) {
     const int nrows = ns * kLam, ncols = (Lmax + 1) * (Lmax + 1), tiles = (nrows + kQRows - 1) / kQRows;
     auto chunks = [&](int row) {   // extent of 16 rows from `row`
         if (row >= nrows) return 0;
@@ -522,7 +522,7 @@ void sph_plan(const SphExt& ext, int ns, int Lmax, int n_q, bool split, std::vec
     long long total = 0;
     for (int r = 0; r < nrows; r += 16) total += chunks(r);
     const long long wgs = (long long)((ncols + kQCols - 1) / kQCols) * ((n_q + kQRadii - 1) / kQRadii);
-    const long long want = std::max<long long>(1, 1536 / wgs), len = std::max<long long>(32, (total + want - 1) / want);
+    const long long want = std::max<long long>(1, 6LL * n_cu / wgs), len = std::max<long long>(32, (total + want - 1) / want);
     items.clear();
     segs.n_split = 0;
     int parts = 0;

@@ -3,7 +3,7 @@
 //   V(q) = exp(-q^2 / (4p)) * exp(i q P) * sum_u e_u (i q)^u ,
 // with every q-independent factor of the primitive pair folded into e_u.
 // The phase q P is reduced to revolutions in [-1/2, 1/2] before the sine
-// and cosine.  Shared by the 1D-table, points and separable kernels.
+// and cosine.  Shared by the 1D-table and separable kernels.
 #pragma once
 
 #include <hip/hip_runtime.h>
