@@ -404,7 +404,7 @@ int ctx_batch_finish(scff_ctx* c, const scff_grid* g, const BatchEval& be, float
 // asynchronous work pending.
 void ctx_batch_done(scff_ctx* c);
 // Grid kernel launchers (kernels.hip)
-hipError_t grid_allow_lds();   // once per device, before the first launch on it
+hipError_t grid_allow_lds(int device);   // the current device, before the first launch on it
 int grid_wgs_per_cu(int cls, int lds);
 hipError_t launch_grid_batch(int cls, int lds, const GridDesc* descs, const int2* items, int n_items, int* counter, int wgs,
                              hipStream_t st);

@@ -23,6 +23,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdint>
 #include <type_traits>
 
@@ -883,8 +884,12 @@ hipError_t grid_desc(const GridShape& g, const PrepResult& p, const float2* V, u
         default: return hipErrorInvalidValue;                                             \
     }
 
-// Dynamic LDS beyond 64 KB must be allowed per kernel (on the current device).
-hipError_t grid_allow_lds() {
+// Dynamic LDS beyond 64 KB must be allowed per kernel (on the current device; the
+// same each time, so once is enough).
+hipError_t grid_allow_lds(int device) {
+    static std::atomic<uint64_t> allowed{0};   // devices
+    const uint64_t bit = device < 64 ? 1ull << device : 0;
+    if (allowed.load() & bit) return hipSuccess;
     hipError_t e = hipSuccess;
     auto allow = [&](const void* f) {
         if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kGridLds + 16);
@@ -903,6 +908,7 @@ hipError_t grid_allow_lds() {
         (void)one(cls);   // (a class that does not exist allows nothing)
         (void)batch(cls);
     }
+    if (e == hipSuccess) allowed |= bit;
     return e;
 }
 

@@ -213,17 +213,15 @@ int set_device(scff_ctx* c) { return hip_check(hipSetDevice(c->device), "hipSetD
 // the context's device state (precompute results, tables, T) is ordered after
 // the context's previous asynchronous work with an event, so a call on stream
 // B never overtakes a call still running on stream A.
+bool capturing(hipStream_t st);
 int order_after(scff_ctx* c, hipStream_t st) {
     if (c->async_open) {
         // work of an earlier call is on a stream that could not be marked (or in a
         // batch that failed); a stream under capture cannot wait for it
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) {
+        if (!capturing(st)) {
             GateShared g(device_gate());
             const int rc = hip_check(hipDeviceSynchronize(), "device sync");
             if (rc) return rc;
-        } else {
-            (void)hipGetLastError();
         }
     }
     if (c->order_pending && st != c->order_st) {
@@ -258,6 +256,13 @@ int order_drain(scff_ctx* c) {
 void order_done(scff_ctx* c) {
     c->order_pending = false;
     c->async_open = false;
+}
+
+bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();   // the default stream while another one is captured
+    return true;
 }
 
 // A call's work on the context: where the call returns early with an error, what
@@ -353,11 +358,7 @@ int ensure_prepared(scff_ctx* c, hipStream_t st, int axis = -1) {
     const bool again = c->prepared;
     if (again) {
         if (axis < 0 || axis == c->pres.axis) return SCFF_OK;
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
-            (void)hipGetLastError();
-            return SCFF_OK;
-        }
+        if (capturing(st)) return SCFF_OK;
     }
     PrepResult res = again ? c->pres : PrepResult{};
     int rc;
@@ -454,6 +455,19 @@ int check_tables(const scff_ctx* c, const scff_grid* g) {
     if ((size_t)c->pres.n_rows * vtable_stride(g->n) * sizeof(float2) > 0xffffffffull)
         return fail(SCFF_EINVAL, "1D tables of this grid exceed 4 GiB: evaluate it in slabs");
     return SCFF_OK;
+}
+
+// The buffer of a grid's tables: what the layout by any axis needs where there is
+// room, so that a grid that has been evaluated needs no memory when it comes again
+// on the layout of another axis (under capture, for one).
+int reserve_tables(scff_ctx* c, const scff_grid* g, const GridShape& sh) {
+    const size_t need = table_bytes(c, g, sh).total;
+    if (c->d_vtab.bytes >= need) return SCFF_OK;
+    const PrepResult& p = c->pres;
+    const size_t m = (size_t)std::max(p.n_axis[0], std::max(p.n_axis[1], p.n_axis[2])) + 64;
+    const size_t any = ((size_t)p.n_rows * 8 + m * 4 + 64 * 8) * vtable_stride(g->n);
+    if (any > need && dev_reserve_raw(c, c->d_vtab, any, true) == hipSuccess) return SCFF_OK;
+    return dev_reserve(c, c->d_vtab, need);
 }
 
 int launch_tables(scff_ctx* c, const scff_grid* g, const GridShape& sh, void* tab, hipStream_t st) {
@@ -758,7 +772,7 @@ int scff_create(int device, size_t hbm_budget_bytes, scff_ctx** out) {
     if (e != hipSuccess || n <= 0) return fail(SCFF_EDEVICE, "no HIP device available");
     if (device < 0 || device >= n) return fail(SCFF_EINVAL, "device index out of range");
     if (hipSetDevice(device) != hipSuccess) return fail(SCFF_EDEVICE, "hipSetDevice failed");
-    if ((e = grid_allow_lds()) != hipSuccess) return fail(SCFF_EDEVICE, std::string("grid kernels: ") + hipGetErrorString(e));
+    if ((e = grid_allow_lds(device)) != hipSuccess) return fail(SCFF_EDEVICE, std::string("grid kernels: ") + hipGetErrorString(e));
     scff_ctx* c = new scff_ctx();
     c->device = device;
     int ncu = 0;
@@ -962,18 +976,20 @@ int scff_eval_grid(scff_ctx* c, const scff_grid* g, int precision, float* f, flo
     if ((rc = record(c, EV_VT0, st))) return rc;
     if ((rc = check_tables(c, g))) return rc;
     EvalPlan pl = plan_eval(c, g, precision);
-    rc = dev_reserve(c, c->d_vtab, table_bytes(c, g, pl.shape).total);
+    rc = reserve_tables(c, g, pl.shape);
     if (rc == SCFF_ENOMEM && c->pres.axis != 2 && (rc = ensure_prepared(c, st, 2)) == SCFF_OK) {   // z may need less
         pl = plan_eval(c, g, precision);
-        rc = dev_reserve(c, c->d_vtab, table_bytes(c, g, pl.shape).total);
+        rc = reserve_tables(c, g, pl.shape);
     }
     if (rc || (rc = launch_tables(c, g, pl.shape, c->d_vtab.p, st))) return rc;
     // the partial buffer is the last reservation: a split that the context's
     // HBM budget cannot hold falls back to the unsplit evaluation (the same
-    // values up to the order of the FP64 sums)
+    // values up to the order of the FP64 sums), as does one that would have to
+    // allocate under capture
     double2* part = nullptr;
     if (pl.sp.n > 1) {
-        if (dev_reserve(c, c->d_part, (size_t)pl.sp.n * nout * sizeof(double2), true) == SCFF_OK)
+        const size_t pb = (size_t)pl.sp.n * nout * sizeof(double2);
+        if (!(c->d_part.bytes < pb && capturing(st)) && dev_reserve(c, c->d_part, pb, true) == SCFF_OK)
             part = (double2*)c->d_part.p;
         else
             pl = plan_eval(c, g, precision, false);

@@ -91,3 +91,39 @@ def test_axes_in_turn(oracle_mod):
                 assert errors(a[..., 0] + 1j * a[..., 1], refs[j])["f2_peak_norm"].max() <= TOL_F2["fp32"]
                 if j == i:
                     np.testing.assert_array_equal(a[..., 0] + 1j * a[..., 1], f)
+
+
+def test_capture_after_other_axes(oracle_mod):
+    """Grids evaluated before, of different axes, in one captured graph: the graph takes the layout at
+    hand and no memory."""
+    import torch
+    from paper_2512_18010_amd import binding
+    mol, T, gx = workload_of("y_symmetric")
+    ns = T.shape[0]
+    grids = [wl.Grid(n=(40, 5, 3), qmin=gx.qmin, qmax=gx.qmax), wl.Grid(n=(3, 40, 5), qmin=gx.qmin, qmax=gx.qmax),
+             wl.Grid(n=(5, 3, 40), qmin=gx.qmin, qmax=gx.qmax)]
+    refs = [oracle_mod.eval_grid(mol, T, g, n_threads=NTH) for g in grids]
+    outs = [torch.empty((ns,) + g.n + (2,), dtype=torch.float32, device="cuda") for g in grids]
+    print("case capture_after_other_axes", flush=True)
+    with binding.Context(0) as ctx:
+        ctx.load_molecule(mol)
+        ctx.load_transitions(T)
+        ctx.set_options(0.0, 1.0)
+        for g, o in zip(grids, outs):
+            ctx.eval_grid_device(g, o, None)
+        torch.cuda.synchronize()
+        held = ctx.query()["device_bytes"]
+        graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            for g, o in zip(grids, outs):
+                ctx.eval_grid_device(g, o, None, stream=stream)
+        assert ctx.query()["device_bytes"] == held
+        for _ in range(3):
+            for o in outs:
+                o.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            for o, ref in zip(outs, refs):
+                a = o.cpu().numpy()
+                assert errors(a[..., 0] + 1j * a[..., 1], ref)["f2_peak_norm"].max() <= TOL_F2["fp32"]
