@@ -197,11 +197,12 @@ __global__ __launch_bounds__(256) void tables_kernel(const VRowDev* __restrict__
 // off centre it is 0.8 to 0.9 of the kernel before, the worst case.  A version whose
 // waves formed W each for itself was bound by its gathers (64 cache lines per
 // instruction): 46.8 ms on a 30-heavy-atom molecule with 24 states on 96^3; sharing
-// W: 40.2 ms (both with f16 halves).  What bounds it now: the LDS reads of U's
-// operands (six of 16 bytes per lane for 16 FMAs), about 20 of 30 ms of a split
-// precision call on that grid, and in FP32 precision the matrix cores (72
-// instructions per wave and k-step at CG = 3) and the FP64 totals, which two waves
-// per SIMD overlap little.  Three waves per SIMD at CG = 2 with totals and mirror
+// W: 40.2 ms (both with f16 halves).  What bounds it now: the products.  96^3 with 24
+// states issues 3.6e9 matrix instructions in FP32 precision and half of that in split
+// precision, 52 and 26 ms at the rate that a large BF16 product reaches on this card
+// (1130 TFLOP/s), of 57 to 61 and 31 to 32 ms.  The operand's LDS reads do not:
+// broadcasting W between lanes by DPP instead of reading it per lane was 3 to 15 %
+// slower (FP32 55.9 -> 59.9 ms).  Three waves per SIMD at CG = 2 with totals and mirror
 // values spill (2.05 -> 2.47 ms).
 
 constexpr int kGridWaves = 4;
