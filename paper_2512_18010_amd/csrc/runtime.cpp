@@ -573,7 +573,7 @@ EvalPlan plan_eval(const scff_ctx* c, const scff_grid* g, int precision, bool al
     e.nx_eval = planes_eval(c, g, axis);
     e.shape = grid_shape(g->n, axis, e.nx_eval, c->n_states, axis_reflects(g, axis), grid_kind(c, g, precision));
     const int nst = c->pres.n_ksteps;
-    const long long tiles = (long long)e.shape.ntl * e.shape.ntc, 
+    const long long tiles = (long long)e.shape.ntl * e.shape.ntc,
                     slots = (long long)grid_wgs_per_cu(grid_class(e.shape), e.shape.lds) * c->n_cu;
     const size_t part1 = (size_t)g->n[0] * g->n[1] * g->n[2] * (size_t)c->n_states * sizeof(double2);
     long long smax = std::min<long long>(kMaxSplit, nst);
