@@ -667,7 +667,7 @@ __global__ void reduce_kernel(const double2* __restrict__ part, int n_split, lon
 // integrand's phase e^{iq.r} is conjugated by q -> -q, everything else is
 // real).  On a grid symmetric about q = 0 (q_min = -q_max on every axis) the
 // point with indices (nx-1-ix, ny-1-iy, nz-1-iz) is -q of (ix, iy, iz), so
-// the grid kernel evaluates the planes ix < nx_eval = ceil(nx/2) and this
+// the grid kernel need only evaluate the planes ix < nx_eval = ceil(nx/2) and this
 // kernel writes the others as conjugates: f[s][ix][iy][iz] =
 // conj(f[s][nx-1-ix][ny-1-iy][nz-1-iz]), |f|^2 copied.
 

@@ -543,10 +543,15 @@ struct EvalPlan {
     ChunkSplit sp;
 };
 
-// Planes computed (the rest mirrored) where axis is contracted: contracted along
-// x, a symmetric grid's halves come with the columns.
+// The first plane that is written as the conjugate of its mirror plane (none: nx).
+int planes_kept(const scff_ctx* c, const scff_grid* g) {
+    return c->symmetry && grid_symmetric(g) ? (g->n[0] + 1) / 2 : g->n[0];
+}
+
+// Planes computed where axis is contracted: contracted along x, a symmetric grid's
+// halves come with the columns (and the mirrored planes are written over).
 int planes_eval(const scff_ctx* c, const scff_grid* g, int axis) {
-    return c->symmetry && axis != 0 && grid_symmetric(g) ? (g->n[0] + 1) / 2 : g->n[0];
+    return axis != 0 ? planes_kept(c, g) : g->n[0];
 }
 
 // The axis to contract: forming U costs the same for 1 and for 48 columns, so a
@@ -635,9 +640,7 @@ int run_grid(scff_ctx* c, const scff_grid* g, int precision, const void* tab, co
     if (pl.sp.n > 1 &&
         (rc = hip_check(launch_reduce(part, pl.sp.n, g->n, pl.nx_eval, c->n_states, df, df2, st), "reduce launch")))
         return rc;
-    if (pl.nx_eval < g->n[0] &&
-        (rc = hip_check(launch_mirror(g->n, pl.nx_eval, c->n_states, df, df2, st), "mirror kernel launch")))
-        return rc;
+    if ((rc = hip_check(launch_mirror(g->n, planes_kept(c, g), c->n_states, df, df2, st), "mirror kernel launch"))) return rc;
     if ((rc = record(c, EV_GRID1, st))) return rc;
     c->ev_recorded = c->timing;
     return SCFF_OK;
@@ -750,9 +753,7 @@ int scff::ctx_batch_finish(scff_ctx* c, const scff_grid* g, const BatchEval& be,
         (rc = hip_check(launch_reduce(be.desc.partial, be.n_split, g->n, be.nx_eval, c->n_states, df, df2, st),
                         "reduce launch")))
         return rc;
-    if (be.nx_eval < g->n[0] &&
-        (rc = hip_check(launch_mirror(g->n, be.nx_eval, c->n_states, df, df2, st), "mirror kernel launch")))
-        return rc;
+    if ((rc = hip_check(launch_mirror(g->n, planes_kept(c, g), c->n_states, df, df2, st), "mirror kernel launch"))) return rc;
     return copy_out(df, host_f, df2, host_f2, be.nout, st);
 }
 

@@ -57,6 +57,27 @@ def test_axes(oracle_mod, case, precision):
     assert e <= TOL_F2[precision]
 
 
+@pytest.mark.parametrize("precision", ["fp32", "bf16x3"])
+@pytest.mark.parametrize("n", [(40, 5, 3), (41, 4, 1), (5, 40, 3), (6, 3, 40)], ids=str)
+def test_symmetric_mode_conjugates(n, precision):
+    """In the symmetric mode the planes ix >= ceil(nx / 2) are the conjugates of their mirror points bit
+    for bit, whichever axis is contracted."""
+    from paper_2512_18010_amd import binding
+    mol, T, _ = workload_of("mode_x")
+    a = [q if m > 1 else 0.0 for q, m in zip(S[1], n)]
+    grid = wl.Grid(n=n, qmin=tuple(-x for x in a), qmax=tuple(a))
+    print("case symmetric_mode_conjugates", n, precision, flush=True)
+    with binding.Context(0) as ctx:
+        ctx.load_molecule(mol)
+        ctx.load_transitions(T)
+        ctx.set_options(0.0, 1.0)
+        ctx.set_symmetry(True)
+        f, f2 = ctx.eval_grid_host(grid, precision)
+    h = (n[0] + 1) // 2
+    np.testing.assert_array_equal(f[:, h:], np.conj(f[:, ::-1, ::-1, ::-1][:, h:]))
+    np.testing.assert_array_equal(f2[:, h:], f2[:, ::-1, ::-1, ::-1][:, h:])
+
+
 def test_axes_in_turn(oracle_mod):
     """One context, grids of different axes in turn, points and the allocation-free call between them."""
     import ctypes
