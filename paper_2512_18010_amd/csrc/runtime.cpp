@@ -560,7 +560,15 @@ int planes_eval(const scff_ctx* c, const scff_grid* g, int axis) {
 // point evaluation leaves, unless another saves a tenth (30 heavy atoms, 24 states:
 // 96x96x16 26.9 -> 10.4 ms in FP32 precision and 20.3 -> 5.3 ms in split precision,
 // the kernel by pairs before 17.4 and 8.6; 96^3 symmetric along x and y only 110
-// -> 58 and 61 -> 31 ms, before 100 and 50).
+// -> 58 and 61 -> 31 ms, before 100 and 50), and at least twice the time of a layout,
+// which grids of several axes in turn pay on each call (lines of 128 values along x,
+// y and z, 10 heavy atoms, 12 states: 553 us of layouts by their own axes, 267 by z).
+// Both times are fits: per 10^6 of cost x rows 0.8 us and, where few states share a
+// line's products, more (lines, planes and slabs: 0.8 to 0.95 us with 24 and 12 states,
+// 1.2 to 1.6 with three, 2.2 to 3.8 with one); 54, 103 and 400 us for 44 thousand, 239
+// thousand and 2.1 million 1D rows before screening.  The kept rows of an axis are the same in every
+// layout, so the axis is the molecule's, the weights' and the grid's alone; before the
+// precompute a quarter of all rows stands for them.
 int choose_axis(const scff_ctx* c, const scff_grid* g, int precision) {
     const GridKind kind = precision == SCFF_FP32 ? kGridFp32 : kGridSplitF16;
     int best = 2;
@@ -569,7 +577,19 @@ int choose_axis(const scff_ctx* c, const scff_grid* g, int precision) {
         cost[a] = grid_shape(g->n, a, planes_eval(c, g, a), c->n_states, axis_reflects(g, a), kind).cost;
         if (cost[a] < (best == 2 ? cost[2] / 10 * 9 : cost[best])) best = a;
     }
-    return best;
+    const double rows = c->prepared ? c->pres.n_axis[2] : (double)c->basis.n_rows / 12.0;
+    const double layout_us = 60.0 + (double)c->basis.n_rows / 6000.0;
+    const double saved_us = (double)(cost[2] - cost[best]) * rows * (0.8 + 2.5 / std::max(c->n_states, 1)) * 1e-6;
+    return saved_us < 2.0 * layout_us ? 2 : best;
+}
+
+// The precompute and the layout that grid g is evaluated by.
+int prepare_grid(scff_ctx* c, const scff_grid* g, int precision, hipStream_t st) {
+    const int guess = choose_axis(c, g, precision);
+    const int rc = ensure_prepared(c, st, guess);
+    if (rc) return rc;
+    const int axis = choose_axis(c, g, precision);
+    return axis == guess ? SCFF_OK : ensure_prepared(c, st, axis);
 }
 
 EvalPlan plan_eval(const scff_ctx* c, const scff_grid* g, int precision, bool allow_split = true) {
@@ -685,7 +705,7 @@ int scff::ctx_prepare(scff_ctx* c, const scff_grid* g, int precision, hipStream_
     if ((rc = set_device(c))) return rc;
     if ((rc = order_after(c, st))) return rc;
     CallScope scope{c, st};
-    if ((rc = ensure_prepared(c, st, choose_axis(c, g, precision)))) return rc;
+    if ((rc = prepare_grid(c, g, precision, st))) return rc;
     // the last precompute kernels (row compaction, slot remap) are still in
     // flight on st: the caller evaluates on another stream, which is not
     // ordered after this one
@@ -963,7 +983,7 @@ int scff_eval_grid(scff_ctx* c, const scff_grid* g, int precision, float* f, flo
     c->ev_prep = false;
     if ((rc = order_after(c, st))) return rc;
     CallScope scope{c, st};
-    if ((rc = ensure_prepared(c, st, choose_axis(c, g, precision)))) return rc;
+    if ((rc = prepare_grid(c, g, precision, st))) return rc;
     const size_t npts = (size_t)g->n[0] * g->n[1] * g->n[2];
     const size_t nout = npts * (size_t)c->n_states;
     float2* df = (float2*)f;

@@ -1,8 +1,9 @@
 """Grid kernel contracted along each axis, against the FP64 oracle.
 
 A grid that is short along z, or symmetric about 0 along another axis only, is
-contracted along that one: columns then lie apart in the output, lines run over
-the other two axes, and the term layout changes with the axis.
+contracted along that one where this saves more than the layout takes: columns then
+lie apart in the output, lines run over the other two axes, and the term layout
+changes with the axis.
 """
 import os
 
@@ -27,6 +28,14 @@ CASES = {
     "mode_x": (5, (34, 6, 3), *S, True),
     "mode_y": (24, (6, 47, 4), *S, True),
     "mode_z": (5, (9, 6, 33), *S, True),
+    # long enough that another axis than z pays
+    "x_contracted": (3, (300, 70, 1), (-4.0, -3.0, 0.5), (4.0, 3.5, 1.0), False),
+    "x_contracted_off_centre": (24, (150, 23, 1), (-4.0, -3.0, 0.5), (3.0, 3.5, 1.0), False),
+    "y_contracted": (12, (75, 95, 1), (-4.0, -3.0, 0.5), (3.0, 3.0, 1.0), False),
+    "y_contracted_off_centre": (13, (39, 70, 3), (-4.0, -3.0, -1.0), (3.0, 3.5, 2.0), False),
+    "x_contracted_line": (32, (4000, 1, 1), (-4.0, 1.0, 0.5), (4.0, 1.0, 0.5), False),
+    "mode_x_contracted": (12, (600, 21, 1), (-4.0, -4.5, 0.0), (4.0, 4.5, 0.0), True),
+    "mode_y_contracted": (24, (61, 95, 2), *S, True),
 }
 
 
@@ -58,12 +67,12 @@ def test_axes(oracle_mod, case, precision):
 
 
 @pytest.mark.parametrize("precision", ["fp32", "bf16x3"])
-@pytest.mark.parametrize("n", [(40, 5, 3), (41, 4, 1), (5, 40, 3), (6, 3, 40)], ids=str)
+@pytest.mark.parametrize("n", [(600, 21, 1), (601, 20, 1), (21, 600, 1), (6, 3, 40)], ids=str)
 def test_symmetric_mode_conjugates(n, precision):
     """In the symmetric mode the planes ix >= ceil(nx / 2) are the conjugates of their mirror points bit
     for bit, whichever axis is contracted."""
     from paper_2512_18010_amd import binding
-    mol, T, _ = workload_of("mode_x")
+    mol, T, _ = workload_of("mode_x_contracted")
     a = [q if m > 1 else 0.0 for q, m in zip(S[1], n)]
     grid = wl.Grid(n=n, qmin=tuple(-x for x in a), qmax=tuple(a))
     print("case symmetric_mode_conjugates", n, precision, flush=True)
@@ -84,10 +93,10 @@ def test_axes_in_turn(oracle_mod):
 
     import torch
     from paper_2512_18010_amd import binding
-    mol, T, gx = workload_of("y_symmetric")
+    mol, T, gx = workload_of("mode_y_contracted")
     ns = T.shape[0]
-    grids = [wl.Grid(n=(40, 5, 3), qmin=gx.qmin, qmax=gx.qmax), wl.Grid(n=(5, 3, 40), qmin=gx.qmin, qmax=gx.qmax),
-             wl.Grid(n=(3, 40, 5), qmin=gx.qmin, qmax=gx.qmax)]
+    grids = [wl.Grid(n=(90, 31, 1), qmin=gx.qmin, qmax=gx.qmax), wl.Grid(n=(5, 3, 40), qmin=gx.qmin, qmax=gx.qmax),
+             wl.Grid(n=(31, 90, 1), qmin=gx.qmin, qmax=gx.qmax)]
     refs = [oracle_mod.eval_grid(mol, T, g, n_threads=NTH) for g in grids]
     stream = torch.cuda.current_stream()
     with binding.Context(0) as ctx:
@@ -119,9 +128,9 @@ def test_capture_after_other_axes(oracle_mod):
     hand and no memory."""
     import torch
     from paper_2512_18010_amd import binding
-    mol, T, gx = workload_of("y_symmetric")
+    mol, T, gx = workload_of("mode_y_contracted")
     ns = T.shape[0]
-    grids = [wl.Grid(n=(40, 5, 3), qmin=gx.qmin, qmax=gx.qmax), wl.Grid(n=(3, 40, 5), qmin=gx.qmin, qmax=gx.qmax),
+    grids = [wl.Grid(n=(90, 31, 1), qmin=gx.qmin, qmax=gx.qmax), wl.Grid(n=(31, 90, 1), qmin=gx.qmin, qmax=gx.qmax),
              wl.Grid(n=(5, 3, 40), qmin=gx.qmin, qmax=gx.qmax)]
     refs = [oracle_mod.eval_grid(mol, T, g, n_threads=NTH) for g in grids]
     outs = [torch.empty((ns,) + g.n + (2,), dtype=torch.float32, device="cuda") for g in grids]
