@@ -5,6 +5,7 @@ contracted along that one where this saves more than the layout takes: columns t
 lie apart in the output, lines run over the other two axes, and the term layout
 changes with the axis.
 """
+import functools
 import os
 
 import numpy as np
@@ -46,6 +47,12 @@ def workload_of(case):
     return mol, wl.make_transitions(rng, mol.nbf, wl.n_occupied(mol.Z), ns), wl.Grid(n=n, qmin=qmin, qmax=qmax)
 
 
+@functools.lru_cache(maxsize=1)
+def reference(case):
+    import oracle
+    return oracle.eval_grid(*workload_of(case), n_threads=NTH)
+
+
 @pytest.mark.parametrize("precision", ["fp32", "bf16x3"])
 @pytest.mark.parametrize("case", list(CASES))
 def test_axes(oracle_mod, case, precision):
@@ -59,7 +66,7 @@ def test_axes(oracle_mod, case, precision):
         ctx.set_options(0.0, 1.0)
         ctx.set_symmetry(CASES[case][4])
         f, f2 = ctx.eval_grid_host(grid, precision)
-    ref = oracle_mod.eval_grid(mol, T, grid, n_threads=NTH)
+    ref = reference(case)
     np.testing.assert_allclose(f2, np.abs(f) ** 2, rtol=2e-6, atol=1e-12 * np.abs(f).max() ** 2)
     e = errors(f, ref)["f2_peak_norm"].max()
     print(f"  max peak-normalised |f|^2 err {e:.2e}", flush=True)
